@@ -53,7 +53,7 @@ typedef enum {
 } pskv_status;
 
 typedef enum {
-    PSKV_DTYPE_F32 = 0, /* q/k/v/out are float; fp64 arithmetic on the vector ALU, results rounded to fp32 once */
+    PSKV_DTYPE_F32 = 0, /* q/k/v/out are float; fp64 arithmetic, results rounded to fp32 once */
     PSKV_DTYPE_BF16 = 1 /* q/k/v/out are bfloat16; bf16 MFMA with fp32 accumulation and fp32 softmax */
 } pskv_dtype;
 
@@ -61,7 +61,7 @@ typedef enum {
  * exist so that tests and benchmarks can run one problem through both implementations. */
 typedef enum {
     PSKV_IMPL_AUTO = 0,
-    PSKV_IMPL_SIMPLE = 1, /* one wavefront per query row, fp32 vector arithmetic; any D <= 256, any dtype */
+    PSKV_IMPL_SIMPLE = 1, /* one wavefront per query row, vector arithmetic (fp32, or fp64 for f32 tensors); any D <= 256, any dtype */
     PSKV_IMPL_MFMA = 2    /* stacked-M bf16 MFMA path; bf16, D == 128 */
 } pskv_impl;
 

@@ -56,6 +56,7 @@ pskv_status resolve(const pskv_attn_params *p, int np, long long kp_stride_n, ps
     if (rows > 0x7fffffffLL)
         return fail(PSKV_ERR_UNSUPPORTED, "B*S*Hq=%lld exceeds 2^31-1", rows);
 
+    a.plain = p->impl == PSKV_IMPL_SIMPLE;
     a.B = p->B; a.S = p->S; a.P = p->P; a.Hq = p->Hq; a.Hkv = p->Hkv; a.D = p->D;
     a.G = p->Hq / p->Hkv;
     a.Np = np;

@@ -29,6 +29,7 @@ inline FastDiv make_fastdiv(unsigned d)
 
 struct Args {
     int B, S, P, Hq, Hkv, D, G;
+    bool plain; // the caller asked for the vector kernels (PSKV_IMPL_SIMPLE)
     // Batched multi-instruction form (Sec. 4.3): Np instructions with C = B / Np consecutive
     // candidates each; the prefix tensors are [Np, P, Hkv, D], every prefix LEFT-padded to P rows
     // with plen[n] real rows at the end.  Np == 1, plen == nullptr is the single shared prefix.
@@ -82,11 +83,18 @@ hipError_t noalloc_scratch(void **ptr);
 hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream);
 hipError_t launch_bwd_dkv_mfma(const BwdArgs &g, hipStream_t stream);
 
-// Simple path: one wavefront per query row. dtype 0 = f32 storage (fp64 arithmetic),
-// 1 = bf16 storage (fp32 arithmetic). Returns the HIP launch status.
+// Everything outside the bf16, D == 128 kernels: dtype 0 = f32 storage (fp64 arithmetic), 1 = bf16
+// storage (fp32 arithmetic). Returns the HIP launch status.
 hipError_t launch_simple(const Args &a, int dtype, hipStream_t stream);
-// Largest dynamic LDS the simple path needs for this problem, in bytes.
+// Dynamic LDS that the vector kernel needs for this problem, in bytes (0 where it is not the one used).
 size_t simple_lds_bytes(const Args &a, int dtype);
+
+// Double-precision matrix-core kernels for f32 tensors (D == 64 or 128, unless the vector kernels are
+// asked for): they serve such problems behind launch_simple and launch_bwd_*_simple and need no
+// dynamic LDS that grows with the problem.
+bool f32_mfma_supported(const Args &a, int dtype);
+hipError_t launch_f32_fwd(const Args &a, hipStream_t stream);
+hipError_t launch_f32_bwd(const BwdArgs &g, hipStream_t stream); // all three gradients: launch_bwd_dkv_simple adds nothing
 
 // MFMA path: bf16, D == 128.  Prefixes of up to 256 rows take the kernel that keeps the whole
 // prefix K/V of one head resident in LDS; longer ones are streamed through LDS in tiles.
