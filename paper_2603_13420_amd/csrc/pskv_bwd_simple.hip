@@ -218,7 +218,7 @@ __global__ __launch_bounds__(64) void bwd_dkv_kernel(BwdArgs g)
 
 size_t bwd_simple_lds_bytes(const Args &a, int dtype)
 {
-    if (f32_mfma_supported(a, dtype))
+    if (f32_mfma_supported(a, dtype) || hd64_supported(a, dtype))
         return 0;
     const size_t c = dtype == 0 ? sizeof(double) : sizeof(float);
     return c * (2 * (size_t)a.D + (size_t)a.P + (size_t)a.S);
@@ -226,7 +226,7 @@ size_t bwd_simple_lds_bytes(const Args &a, int dtype)
 
 size_t bwd_dkv_lds_bytes(const Args &a, int dtype)
 {
-    if (f32_mfma_supported(a, dtype))
+    if (f32_mfma_supported(a, dtype) || hd64_supported(a, dtype))
         return 0;
     const size_t c = dtype == 0 ? sizeof(double) : sizeof(float);
     return c * (2 * (size_t)a.D + 2 * (size_t)a.G * a.S);
@@ -237,6 +237,8 @@ hipError_t launch_bwd_dq_simple(const BwdArgs &g, int dtype, hipStream_t stream)
     const Args &a = g.f;
     if (f32_mfma_supported(a, dtype))
         return launch_f32_bwd(g, stream); // dk and dv as well
+    if (hd64_supported(a, dtype))
+        return launch_hd64_bwd_dq(g, stream);
     const long long rows = (long long)a.B * a.S * a.Hq;
     const size_t lds = bwd_simple_lds_bytes(a, dtype);
     if (dtype == 0)
@@ -250,6 +252,8 @@ hipError_t launch_bwd_dkv_simple(const BwdArgs &g, int dtype, hipStream_t stream
     const Args &a = g.f;
     if (f32_mfma_supported(a, dtype))
         return hipSuccess; // launched with dq
+    if (hd64_supported(a, dtype))
+        return launch_hd64_bwd_dkv(g, stream);
     const long long rows = (long long)a.B * a.S * a.Hkv;
     const size_t lds = bwd_dkv_lds_bytes(a, dtype);
     if (dtype == 0)

@@ -96,6 +96,13 @@ bool f32_mfma_supported(const Args &a, int dtype);
 hipError_t launch_f32_fwd(const Args &a, hipStream_t stream);
 hipError_t launch_f32_bwd(const BwdArgs &g, hipStream_t stream); // all three gradients: launch_bwd_dkv_simple adds nothing
 
+// Matrix-core kernels for bf16 tensors with D == 64 (unless the vector kernels are asked for), reached in
+// the same way.
+bool hd64_supported(const Args &a, int dtype);
+hipError_t launch_hd64_fwd(const Args &a, hipStream_t stream);
+hipError_t launch_hd64_bwd_dq(const BwdArgs &g, hipStream_t stream);
+hipError_t launch_hd64_bwd_dkv(const BwdArgs &g, hipStream_t stream);
+
 // MFMA path: bf16, D == 128.  Prefixes of up to 256 rows take the kernel that keeps the whole
 // prefix K/V of one head resident in LDS; longer ones are streamed through LDS in tiles.
 bool mfma_supported(const Args &a, int dtype);

@@ -7,9 +7,8 @@
 //
 // Arithmetic type: fp64 when the tensors are f32 (this is the verification-grade path, whose
 // results are the correctly rounded fp32 values up to a final rounding), fp32 when they are
-// bf16.  It covers any head dimension up to 256 and any GQA group size; bf16 problems with D == 128
-// and f32 ones with D == 64 or 128 take the matrix-core kernels instead, unless the caller asks for
-// this one.
+// bf16.  It covers any head dimension up to 256 and any GQA group size; problems with
+// D == 64 or 128 take the matrix-core kernels instead, unless the caller asks for this one.
 #include "pskv_internal.h"
 #include <hip/hip_bf16.h>
 
@@ -138,7 +137,7 @@ __global__ __launch_bounds__(64) void simple_kernel(Args a)
 
 size_t simple_lds_bytes(const Args &a, int dtype)
 {
-    if (f32_mfma_supported(a, dtype))
+    if (f32_mfma_supported(a, dtype) || hd64_supported(a, dtype))
         return 0;
     const size_t c = dtype == 0 ? sizeof(double) : sizeof(float);
     return c * ((size_t)a.D + (size_t)a.P + (size_t)a.S);
@@ -148,6 +147,8 @@ hipError_t launch_simple(const Args &a, int dtype, hipStream_t stream)
 {
     if (f32_mfma_supported(a, dtype))
         return launch_f32_fwd(a, stream);
+    if (hd64_supported(a, dtype))
+        return launch_hd64_fwd(a, stream);
     const long long rows = (long long)a.B * a.S * a.Hq;
     const dim3 grid((unsigned)rows), block(64);
     const size_t lds = simple_lds_bytes(a, dtype);

@@ -1,0 +1,88 @@
+"""GPU parity of the matrix-core kernels for bf16 tensors with heads of 64 columns against the CPU
+oracle, forward and backward, at the edges of their tiles, blocks and prefix chunks.  The bars are those
+of every bf16 comparison (oracle/parity.py)."""
+import numpy as np
+import pytest
+
+from paper_2603_13420_amd import inputs as gen
+import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+BF16_ONE, BF16_TWELVE = 0x3F80, 0x4140
+
+
+@pytest.fixture(scope="module")
+def pk():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2603_13420_amd import binding
+    binding.load()
+    return binding
+
+
+def check(pk, inp, what, backward=True):
+    import torch
+    w, d = inp.w, pu.to_device(inp)
+    print(f"[case] {what} B={w.B} P={w.P} S={w.S} len={w.len_lo}..{w.len_hi} Hq={w.Hq} Hkv={w.Hkv} seed={w.seed}", flush=True)
+    lse = torch.full((w.B, w.Hq, w.S), 123.0, device="cuda:0")
+    out = torch.full_like(d["q"], float("nan"))
+    pk.pskv_attn_fwd(d["q"], d["k_suf"], d["v_suf"], d["k_pre"], d["v_pre"], d["suf_len"], out=out, lse=lse, scale=inp.scale)
+    torch.cuda.synchronize()
+    ref, ref_lse = pu.oracle_out(inp, want_lse=True)
+    pu.compare_lse(lse.cpu().numpy().astype(np.float64), ref_lse, inp.suf_len, "bf16", what)
+    pu.compare(pu.out_to_f64(out), ref, inp.suf_len, "bf16", what)
+    if not backward:
+        return
+    dout_host, dout64 = pu.make_dout(inp, w.seed + 7)
+    dout = torch.from_numpy(dout_host).view(torch.bfloat16).to("cuda:0")
+    nan = float("nan")
+    dq, dk, dv = torch.full_like(d["q"], nan), torch.full_like(d["k_suf"], nan), torch.full_like(d["k_suf"], nan)
+    pk.pskv_attn_bwd(d["q"], d["k_suf"], d["v_suf"], d["k_pre"], d["v_pre"], d["suf_len"], out, lse, dout, dq=dq,
+                     dk_suf=dk, dv_suf=dv, scale=inp.scale)
+    torch.cuda.synchronize()
+    rq, rk, rv = pu.oracle_bwd(inp, dout64)
+    valid = np.arange(w.S)[None, :] < inp.suf_len[:, None]
+    for name, got, r in (("dq", dq, rq), ("dk_suf", dk, rk), ("dv_suf", dv, rv)):
+        pu.compare_grad(pu.out_to_f64(got), r, valid, "bf16", f"{what} {name}")
+
+
+@pytest.mark.parametrize("B,P,S,lo,hi,Hq,Hkv", [
+    (1, 0, 1, 1, 1, 1, 1),          # one row, one key
+    (3, 32, 32, 0, 32, 4, 2),       # whole tiles; candidates may be empty
+    (5, 33, 33, 1, 33, 14, 2),      # one past a tile everywhere, group 7
+    (40, 20, 3, 0, 3, 2, 2),        # ten short candidates in a block: their keys share a step
+    (9, 192, 10, 1, 10, 4, 4),      # the longest prefix that leaves room for two workgroups
+    (4, 193, 70, 30, 70, 4, 1),     # ... one row more; three steps of own keys
+    (3, 513, 20, 4, 20, 6, 2),      # prefix in chunks, forward and backward
+    (300, 40, 24, 12, 24, 16, 16),  # more blocks than wavefronts
+])
+def test_hd64(pk, B, P, S, lo, hi, Hq, Hkv):
+    w = gen.custom_workload(f"hd64_{B}_{P}_{S}", B, P, S, lo, hi, Hq, Hkv, 64, "bf16", index=1800 + B + P)
+    check(pk, gen.make_inputs(w, pad="nan"), w.name)
+
+
+def test_hd64_scores_far_above_the_first_tile(pk):
+    """A late prefix key and a late own key 90 and more above everything before them: rescaling.  Forward
+    only: every other weight of such a row is exp(-90) = 2^-130 and less, under fp32's smallest normal number
+    2^-126, and the gradients' bounds are relative ones (|err| <= const * p_j ...), which hold down to there."""
+    w = gen.custom_workload("hd64_spike", 4, 200, 40, 33, 40, 4, 2, 64, "bf16", index=1850)
+    inp = gen.make_inputs(w, pad="nan")
+    inp.q[1, :inp.suf_len[1]] = BF16_ONE
+    inp.k_pre[197] = BF16_TWELVE
+    inp.q[2, :inp.suf_len[2]] = BF16_ONE
+    inp.k_suf[2, inp.suf_len[2] - 1] = BF16_TWELVE
+    check(pk, inp, w.name, backward=False)
+
+
+def test_hd64_multi_instruction(pk):
+    """Left-padded prefixes of their own lengths (one empty), NaN in the padding."""
+    import torch
+    w = gen.custom_multi_workload("hd64_multi", 4, 5, 70, 0, 70, 11, 0, 11, 6, 2, 64, "bf16", index=1860)
+    inp = gen.make_multi_inputs(w, pad="nan")
+    inp.pre_len[1] = 0
+    inp.k_pre[1] = inp.v_pre[1] = 0x7FC0
+    d = pu.to_device_multi(inp)
+    out = pk.pskv_attn_fwd_multi(d["q"], d["k_suf"], d["v_suf"], d["k_pre"], d["v_pre"], d["pre_len"], d["suf_len"],
+                                 scale=inp.scale)
+    torch.cuda.synchronize()
+    pu.compare(pu.out_to_f64(out), pu.oracle_out_multi(inp), inp.suf_len, "bf16", w.name)
