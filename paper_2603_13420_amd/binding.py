@@ -1,7 +1,10 @@
-"""ctypes binding of libpskv.so: same names as include/pskv.h, argument marshalling only.
+"""Binding of libpskv.so: same names as include/pskv.h, argument marshalling only.
 
 Every step of the attention path runs inside the HIP library.  There is no fallback: if the
-library has not been built, loading raises.
+library has not been built, loading raises.  The calls that take torch tensors go through the
+native marshalling of csrc/pskv_torch.cpp, which makes the call when every argument is of the
+plain form and hands back None otherwise; the checks below define what is allowed, and say what
+is wrong with what is not.
 """
 from __future__ import annotations
 
@@ -86,6 +89,34 @@ def load():
     lib.pskv_attn_bwd_noalloc.argtypes = [P] + [vp] * 13
     _lib = lib
     return lib
+
+
+_native_module = None
+
+
+def _native():
+    """The native marshalling of torch tensors, bound to the loaded library; raises if it is missing."""
+    global _native_module
+    if _native_module is None:
+        import torch                      # brings the libraries that the module is linked against
+        lib = load()
+        try:
+            from . import _pskv_torch as m
+        except ImportError as e:
+            raise ImportError(f"the native part of the binding is missing or unusable ({e}): build it with "
+                              "__graft_entry__.build() or `python -m paper_2603_13420_amd.build`") from e
+        m.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            lib.pskv_attn_fwd, lib.pskv_attn_fwd_multi, lib.pskv_attn_bwd, lib.pskv_attn_bwd_multi,
+            lib.pskv_attn_bwd_noalloc, lib.pskv_attn_bwd_workspace_bytes)), torch._C._cuda_getCurrentRawStream)
+        _native_module = m
+    return _native_module
+
+
+def _done(r):
+    """What a native call returned: its result, or the error that a status number stands for."""
+    if type(r) is int:
+        _raise(r)
+    return r
 
 
 def pskv_version() -> int:
@@ -198,6 +229,9 @@ def pskv_attn_fwd(q, k_suf, v_suf, k_pre, v_pre, suf_len=None, out=None, lse=Non
                   impl: str = "auto", scale: float = 0.0, stream: Optional[int] = None):
     """Enqueue one forward call on torch's current stream (or `stream`, a raw hipStream_t).
     `out` (and `lse`) are allocated by torch when not given; returns `out`."""
+    r = (_native_module or _native()).fwd(q, k_suf, v_suf, k_pre, v_pre, suf_len, out, lse, impl, scale, stream)
+    if r is not None:
+        return _done(r)
     import torch
     if out is None:
         out = torch.empty_like(q)
@@ -267,6 +301,10 @@ def pskv_attn_fwd_multi(q, k_suf, v_suf, k_pre, v_pre, pre_len=None, suf_len=Non
                         impl: str = "auto", scale: float = 0.0, stream: Optional[int] = None):
     """Batched multi-instruction forward call: k_pre, v_pre are [Np,P,Hkv,D] (left-padded,
     pre_len [Np] real rows each), candidate b belongs to instruction b // (B // Np)."""
+    r = (_native_module or _native()).fwd_multi(q, k_suf, v_suf, k_pre, v_pre, pre_len, suf_len, out, lse, impl, scale,
+                                                stream)
+    if r is not None:
+        return _done(r)
     import torch
     if out is None:
         out = torch.empty_like(q)
@@ -326,6 +364,10 @@ def pskv_attn_bwd(q, k_suf, v_suf, k_pre, v_pre, suf_len, out, lse, dout, dq=Non
     tensors are allocated by torch when not given (dq like q, dk_suf/dv_suf like k_suf), and so is
     the scratch tensor (workspace: a tensor to use instead, or False for a call without scratch).
     Returns (dq, dk_suf, dv_suf)."""
+    r = (_native_module or _native()).bwd(q, k_suf, v_suf, k_pre, v_pre, suf_len, out, lse, dout, dq, dk_suf, dv_suf,
+                                          impl, scale, stream, workspace)
+    if r is not None:
+        return _done(r)
     import torch
     if lse is None:
         raise ValueError("the backward pass needs the forward pass's lse")
@@ -358,6 +400,10 @@ def pskv_attn_bwd_multi(q, k_suf, v_suf, k_pre, v_pre, pre_len, suf_len, out, ls
                         workspace=None):
     """Backward pass of the batched multi-instruction form (arguments as for pskv_attn_fwd_multi
     and pskv_attn_bwd).  Returns (dq, dk_suf, dv_suf)."""
+    r = (_native_module or _native()).bwd_multi(q, k_suf, v_suf, k_pre, v_pre, pre_len, suf_len, out, lse, dout, dq,
+                                                dk_suf, dv_suf, impl, scale, stream, workspace)
+    if r is not None:
+        return _done(r)
     import torch
     if lse is None:
         raise ValueError("the backward pass needs the forward pass's lse")
@@ -389,6 +435,10 @@ def pskv_attn_bwd_noalloc(q, k_suf, v_suf, k_pre, v_pre, suf_len, out, lse, dout
     """pskv_attn_bwd through the entry point that allocates nothing: the gradient tensors are the
     caller's, the scratch is the library's built-in array (refused with PSKV_ERR_WORKSPACE when
     B*Hq*S*4 exceeds PSKV_NOALLOC_SCRATCH_BYTES), and this wrapper creates no tensor either."""
+    r = (_native_module or _native()).bwd_noalloc(q, k_suf, v_suf, k_pre, v_pre, suf_len, out, lse, dout, dq, dk_suf,
+                                                  dv_suf, impl, scale, stream)
+    if r is not None:
+        return _done(r)
     import torch
     if lse is None:
         raise ValueError("the backward pass needs the forward pass's lse")

@@ -22,6 +22,18 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-x",
 PROBE_LIB = os.path.join(HERE, "libpskv_probe.so")
 PROBE_SOURCES = ["bench_probe.hip"]
 
+# The marshalling of torch tensors (host code only): linked against the libraries torch has in the process anyway.
+TORCH_LIB = os.path.join(HERE, "_pskv_torch.so")
+TORCH_SOURCE = "pskv_torch.cpp"
+
+
+def torch_command():
+    import sysconfig
+    from torch.utils import cpp_extension
+    inc = [f"-I{p}" for p in (*cpp_extension.include_paths(), sysconfig.get_paths()["include"])]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", *inc, "-o", TORCH_LIB, os.path.join(CSRC, TORCH_SOURCE),
+            f"-L{cpp_extension.TORCH_LIB_PATH}", "-lc10", "-ltorch_cpu", "-ltorch_python"]
+
 
 def _compile(cmd, verbose):
     if verbose:
@@ -30,7 +42,7 @@ def _compile(cmd, verbose):
     out = "\n".join(l for l in res.stdout.splitlines()
                     if "packed-fp32-ops" not in l or "error" in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + res.stdout)
+        raise RuntimeError(f"{cmd[0]} failed:\n" + res.stdout)
     if verbose and out.strip():
         print(out)
 
@@ -38,13 +50,14 @@ def _compile(cmd, verbose):
 def build_library(verbose: bool = False, extra=()) -> str:
     _compile([HIPCC, *FLAGS, *extra, "-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES], verbose)
     _compile([HIPCC, *FLAGS, *extra, "-o", PROBE_LIB] + [os.path.join(CSRC, s) for s in PROBE_SOURCES], verbose)
+    _compile(torch_command(), verbose)
     return LIB
 
 
 def needs_build() -> bool:
-    if not os.path.exists(LIB):
+    if not (os.path.exists(LIB) and os.path.exists(TORCH_LIB)):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(TORCH_LIB))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)]
     deps.append(os.path.join(os.path.dirname(HERE), "include", "pskv.h"))
     return any(os.path.getmtime(d) > t for d in deps)
