@@ -137,12 +137,6 @@ __device__ inline long long own_row(const Args &a, const Ctx &X, const Rows &x, 
     });
     return off;
 }
-__device__ inline long long shfl64(long long v, int lane)
-{
-    const int lo = __shfl((int)v, lane, 64), hi = __shfl((int)(v >> 32), lane, 64);
-    return ((long long)hi << 32) | (unsigned)lo;
-}
-
 __device__ inline void load_row(const void *base, long long off, int h, uintx4 (&f)[kKS])
 {
     const unsigned short *p = reinterpret_cast<const unsigned short *>(base) + off + 8 * h;

@@ -624,6 +624,88 @@ __device__ inline void suffix_step_fixed(const Ctx &X, int ri, int k0, const flo
 }
 
 // ------------------------------------------------------------------------------------------
+// Half images: 32 rows x 64 columns in LDS (4 KB), for rows that are fetched in whole cache lines.
+//
+// What a vector memory request costs is the lines it touches: with all compute units reading from
+// L2, a 1 KB request of 8 rows x 128 bytes takes 17 cycles of a compute unit, 16 rows x 64 bytes
+// 30, and 32 rows x 32 bytes - a row-major fragment fetched the way the matrix cores want it - 58.
+// So rows are requested 8 x 128 bytes at a time (register g of lane l: 16 bytes of row 8g + l/8,
+// chunk l%8) and change places in LDS, from where they are read both ways: as row-major fragments
+// (16 columns of 32 rows, 16 bytes per lane) and, through the transposing read, as columns.
+//
+// The image is four 1 KB pieces, piece g holding rows 8g .. 8g+7.  Within a piece, row k (k = row % 8)
+// sits in 128-byte slot k or, in odd pieces, k ^ 1, and its 16-byte chunk c at c ^ half_swz(k).
+// Rows k and k + 8 thereby fall into different halves of the banks, eight rows read at one chunk into
+// eight different chunks, and rows k and k + 2 read at four consecutive chunks into different halves
+// of the eight: neither kind of read has bank conflicts (measured: 255 and 211 bytes per cycle and
+// compute unit).
+// ------------------------------------------------------------------------------------------
+constexpr int kHalfBytes = kTileBytes / 2;
+
+struct HalfPlaces {
+    unsigned row, col, put; // the lane's places for half_row_frag, half_col_frag, half_put
+};
+
+__device__ inline unsigned half_swz(unsigned k) { return ((k & 2u) << 1) | ((k & 4u) >> 1) | (k & 1u); }
+
+__device__ inline HalfPlaces half_places(int lane)
+{
+    HalfPlaces x;
+    const unsigned h = lane >> 5, k7 = lane & 7, kg = (lane & 31) >> 3;
+    x.row = kg * 1024 + (k7 ^ (kg & 1)) * 128 + ((h ^ half_swz(k7)) << 4);
+    // the transposing read: lane 32h + 16w + t reads 8 bytes of row 4h + t/4 at column 16w + 4*(t%4)
+    const unsigned w = (lane >> 4) & 1, t = lane & 15, r7 = 4 * h + (t >> 2);
+    x.col = r7 * 128 + (((2 * w + ((t & 3) >> 1)) ^ half_swz(r7)) << 4) + (t & 1) * 8;
+    const unsigned s = lane >> 3;
+    x.put = s * 128 + ((k7 ^ half_swz(s)) << 4);
+    return x;
+}
+
+__device__ inline unsigned lds_addr(lds_u8 *p) { return (unsigned)(unsigned long long)p; }
+__device__ inline lds_u8 *lds_at(unsigned addr) { return (lds_u8 *)(unsigned long long)addr; }
+
+// (Images begin at multiples of 256 bytes, so that an exclusive or steps from one of the lane's places to another.)
+__device__ inline void half_put(const HalfPlaces &x, lds_u8 *img, const uintx4 (&raw)[4])
+{
+    const unsigned at = lds_addr(img) + x.put;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        *(lds_u128 *)(lds_at(g & 1 ? at ^ 128 : at) + g * 1024) = raw[g];
+}
+
+// Row-major fragment i (columns 16*i ..): lane (row c32, half h) holds columns 16*i + 8*h ..+7.
+__device__ inline uintx4 half_row_frag(const HalfPlaces &x, lds_u8 *img, int i)
+{
+    return *(lds_u128 *)lds_at((lds_addr(img) + x.row) ^ (i << 5));
+}
+
+// Transposed fragment (32-column group d, contraction step j): lane l holds the rows 16*j + 8*(e/4) + 4*h + e%4 at
+// column 32*d + l%32.
+__device__ inline bf16x8 half_col_frag(const HalfPlaces &x, lds_u8 *img, int d, int j)
+{
+    const unsigned at = (lds_addr(img) + x.col) ^ (d << 6);
+    short4v lo = lds_read_tr(lds_at(at) + j * 2048);
+    short4v hi = lds_read_tr(lds_at(at ^ 128) + j * 2048 + 1024);
+    short8v v8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    bf16x8 f;
+    __builtin_memcpy(&f, &v8, 16);
+    return f;
+}
+
+// Orders a wavefront's own accesses to its scratch.
+__device__ inline void scratch_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+__device__ inline long long shfl64(long long v, int lane)
+{
+    const int lo = __shfl((int)v, lane, 64), hi = __shfl((int)(v >> 32), lane, 64);
+    return ((long long)hi << 32) | (unsigned)lo;
+}
+
+// ------------------------------------------------------------------------------------------
 // Passes of the streamed forward kernels.
 // ------------------------------------------------------------------------------------------
 // A pass is one (virtual head, group of 256 stacked rows) pair; a virtual head is one
