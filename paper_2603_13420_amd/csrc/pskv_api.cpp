@@ -21,6 +21,8 @@ pskv_status fail(pskv_status s, const char *fmt, ...)
     return s;
 }
 
+// The vector kernels' limit, and that of every problem they can be asked for: what is accepted does not depend on
+// which of a problem's kernels the caller selects.
 constexpr size_t kSimpleMaxLds = 64 * 1024;
 
 // Fills `a` (without pointers) and `use_mfma` from p, applying every host-side rule.

@@ -218,16 +218,12 @@ __global__ __launch_bounds__(64) void bwd_dkv_kernel(BwdArgs g)
 
 size_t bwd_simple_lds_bytes(const Args &a, int dtype)
 {
-    if (f32_mfma_supported(a, dtype) || hd64_supported(a, dtype))
-        return 0;
     const size_t c = dtype == 0 ? sizeof(double) : sizeof(float);
     return c * (2 * (size_t)a.D + (size_t)a.P + (size_t)a.S);
 }
 
 size_t bwd_dkv_lds_bytes(const Args &a, int dtype)
 {
-    if (f32_mfma_supported(a, dtype) || hd64_supported(a, dtype))
-        return 0;
     const size_t c = dtype == 0 ? sizeof(double) : sizeof(float);
     return c * (2 * (size_t)a.D + 2 * (size_t)a.G * a.S);
 }

@@ -137,8 +137,6 @@ __global__ __launch_bounds__(64) void simple_kernel(Args a)
 
 size_t simple_lds_bytes(const Args &a, int dtype)
 {
-    if (f32_mfma_supported(a, dtype) || hd64_supported(a, dtype))
-        return 0;
     const size_t c = dtype == 0 ? sizeof(double) : sizeof(float);
     return c * ((size_t)a.D + (size_t)a.P + (size_t)a.S);
 }
