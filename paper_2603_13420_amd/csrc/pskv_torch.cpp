@@ -39,7 +39,7 @@ struct Arg {
     {
         if (o == Py_None)
             return true;
-        if (!THPVariable_Check(o))
+        if (!THPVariable_CheckExact(o)) // (a subclass may have its own empty_like)
             return false;
         t = &THPVariable_Unpack(o);
         return true;

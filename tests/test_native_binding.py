@@ -45,6 +45,10 @@ def test_native_calls_and_what_they_refuse():
     assert all(torch.equal(x, y) for x, y in zip(grads, given))
     assert m.fwd(*a, None, out, lse, "nonsense", 0.0, None) is None
     assert m.fwd(d["q"].float(), *a[1:], None, None, None, "auto", 0.0, None) is None       # types differ
+    class Own(torch.Tensor):                                                                   # may have its own empty_like
+        pass
+    assert m.fwd(d["q"].as_subclass(Own), *a[1:], None, None, None, "auto", 0.0, None) is None
+    assert type(pk.pskv_attn_fwd(d["q"].as_subclass(Own), *a[1:])) is Own
     wide = d["k_pre"][:1].expand(7, 2, 128)                                                    # stride 0
     assert m.fwd(*a[:3], wide, wide, None, None, None, "auto", 0.0, None) is None
     with pytest.raises(ValueError, match="stride 0"):
