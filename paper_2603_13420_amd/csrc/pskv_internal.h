@@ -86,7 +86,7 @@ hipError_t launch_bwd_dkv_mfma(const BwdArgs &g, hipStream_t stream);
 // Everything outside the bf16, D == 128 kernels: dtype 0 = f32 storage (fp64 arithmetic), 1 = bf16
 // storage (fp32 arithmetic). Returns the HIP launch status.
 hipError_t launch_simple(const Args &a, int dtype, hipStream_t stream);
-// Dynamic LDS that the vector kernel needs for this problem, in bytes (0 where it is not the one used).
+// Dynamic LDS that the vector kernel needs for this problem, in bytes.
 size_t simple_lds_bytes(const Args &a, int dtype);
 
 // Double-precision matrix-core kernels for f32 tensors (D == 64 or 128, unless the vector kernels are

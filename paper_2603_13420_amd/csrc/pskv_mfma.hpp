@@ -399,6 +399,21 @@ struct BlockRows {
     unsigned o_off; // ... from the candidate's first out row
 };
 
+// What decode_block works out for row r (lane's own) of the stacked rows of its candidate b.
+__device__ inline BlockRows decode_candidate_row(const Args &a, int b, unsigned r, int head)
+{
+    BlockRows x;
+    x.b = b;
+    x.len = len_uniform(a, b);
+    const unsigned tok = fdiv(r, a.div_g), gq = r - tok * a.G;
+    x.ri = (int)tok;
+    x.rh = head * a.G + (int)gq;
+    const int rq = x.ri < x.len ? x.ri : (x.len > 0 ? x.len - 1 : 0); // (see decode_block)
+    x.q_off = ((unsigned)rq * (unsigned)a.q_ss + (unsigned)x.rh * (unsigned)a.q_sh) * 2u;
+    x.o_off = ((unsigned)x.ri * (unsigned)a.o_ss + (unsigned)x.rh * (unsigned)a.o_sh) * 2u;
+    return x;
+}
+
 __device__ inline BlockRows decode_block(const Args &a, const Ctx &X, int blk, int head, int cand0)
 {
     BlockRows x;
@@ -458,8 +473,9 @@ __device__ inline void load_suffix_v_block(const Args &a, const Ctx &X, int b, i
 
 // Normalise and store the block (as store_block).  Lane l stores rows 8*u + l/8 of the block,
 // whose offsets it takes from the lanes that own those rows.
+// `rows`: the block's rows that exist (the last block of a candidate whose rows fill no whole number of blocks).
 __device__ inline void store_block_rows(const Args &a, const Ctx &X, const BlockRows &x, float m, float l,
-                                        const floatx16 (&o)[4])
+                                        const floatx16 (&o)[4], int rows = kBlockRows)
 {
     const float ltot = l + __shfl_xor(l, 32, 64);
     const float inv = 1.0f / ltot;
@@ -471,25 +487,27 @@ __device__ inline void store_block_rows(const Args &a, const Ctx &X, const Block
     for (int u = 0; u < 4; ++u) {
         const unsigned off = (unsigned)__shfl((int)x.o_off, 8 * u + (X.lane >> 3), 64);
         dst[u] = reinterpret_cast<unsigned short *>(base + (off + 16u * (X.lane & 7)));
-        dst_ok[u] = true;
+        dst_ok[u] = 8 * u + (X.lane >> 3) < rows;
     }
     store_rows(X, dst, dst_ok, rvalid, inv, o);
-    if (a.lse && X.h == 0)
+    if (a.lse && X.h == 0 && X.c32 < rows)
         a.lse[((long long)x.b * a.Hq + x.rh) * a.S + x.ri] = rvalid ? (m + __builtin_log2f(ltot)) * kLn2 : -INFINITY;
 }
 
 // Zeros for a block that holds nothing but padding (stored like a computed block: whole cache lines).
-__device__ inline void store_zero_block_rows(const Args &a, const Ctx &X, const BlockRows &x)
+__device__ inline void store_zero_block_rows(const Args &a, const Ctx &X, const BlockRows &x, int rows = kBlockRows)
 {
     unsigned char *base = reinterpret_cast<unsigned char *>(a.out) + (long long)x.b * a.o_sb * 2;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const unsigned off = (unsigned)__shfl((int)x.o_off, 8 * u + (X.lane >> 3), 64);
         unsigned char *dst = base + (off + 16u * (X.lane & 7));
-        __builtin_nontemporal_store(uintx4{0, 0, 0, 0}, reinterpret_cast<uintx4 *>(dst));
-        __builtin_nontemporal_store(uintx4{0, 0, 0, 0}, reinterpret_cast<uintx4 *>(dst + 128));
+        if (8 * u + (X.lane >> 3) < rows) {
+            __builtin_nontemporal_store(uintx4{0, 0, 0, 0}, reinterpret_cast<uintx4 *>(dst));
+            __builtin_nontemporal_store(uintx4{0, 0, 0, 0}, reinterpret_cast<uintx4 *>(dst + 128));
+        }
     }
-    if (a.lse && X.h == 0)
+    if (a.lse && X.h == 0 && X.c32 < rows)
         a.lse[((long long)x.b * a.Hq + x.rh) * a.S + x.ri] = -INFINITY;
 }
 

@@ -12,7 +12,8 @@
 // scratch tile.
 //
 // Two kernels share this layout.  The general one handles any shape.  The pipelined one
-// handles the common case in which every 32-row block lies inside one candidate and the
+// handles the common case in which every 32-row block lies inside one candidate (because the
+// candidates' rows fill whole blocks, or nearly, each then taking blocks of its own) and the
 // suffix fits one 32-key step: it overlaps, inside each wavefront, the score product of the
 // next tile (matrix cores) with the exponentials of the current one (vector ALU), requests
 // everything it needs from global memory a full block ahead, and never branches on data.
@@ -120,9 +121,8 @@ void resident_general_kernel(Args a, int per_vh, int vh_slots, int max_tiles)
 }
 
 // ------------------------------------------------------------------------------------------
-// Pipelined path.  Preconditions (checked by the launcher): S*G is a multiple of 32, so a
-// 32-row block lies inside one candidate; S <= 32, so the suffix is one 32-key step; and the
-// prefix has at least three tiles.
+// Pipelined path.  Preconditions (checked by the launcher): every 32-row block lies inside one
+// candidate; S <= 32, so the suffix is one 32-key step; and the prefix has at least three tiles.
 //
 // Softmax without per-tile maxima: the first prefix tile fixes the row's reference maximum;
 // later tiles take exp2 relative to it whatever their own maximum is (a larger score just gives
@@ -131,14 +131,19 @@ void resident_general_kernel(Args a, int per_vh, int vh_slots, int max_tiles)
 // the general path after its main loop (rare; kept out of the main loop so that it costs it no
 // registers).
 // ------------------------------------------------------------------------------------------
+// WHOLE: S*G is a multiple of 32, the blocks are those of the stacked rows.  Otherwise a candidate has
+// nb blocks of its own, the last one being what is left (its rows past the candidate's stand in for the
+// last one and are not stored).
+template <bool WHOLE>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
-void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles)
+void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles, int nb, FastDiv div_nb)
 {
     extern __shared__ __align__(16) unsigned char smem_generic[];
     lds_u8 *smem = (lds_u8 *)smem_generic;
     const int tid = threadIdx.x;
     Ctx X = make_ctx(a, smem, max_tiles, tid);
-    const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows;
+    const int rows_c = a.S * a.G; // rows of a candidate
+    const int nblocks = WHOLE ? (X.Mtot + kBlockRows - 1) / kBlockRows : a.C * nb;
     const int VH = a.Np * a.Hkv;
     auto kimg = [&](int t) { return X.k_lane + t * kTileBytes; };
     auto vimg = [&](int t) { return X.v_lane + t * kTileBytes; };
@@ -146,8 +151,30 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles)
     // Candidate (within the instruction) and first suffix position of a block, from its index:
     // block blk covers rows [32*blk, 32*blk+31] of candidate 32*blk / (S*G).
     // A block whose first row is already past its candidate's length holds nothing but padding.
-    auto block_cand = [&](int blk) { return (int)fdiv(fdiv(blk * kBlockRows, a.div_g), a.div_s); };
-    auto block_i_lo = [&](int blk) { return (int)fdiv(blk * kBlockRows, a.div_g) - block_cand(blk) * a.S; };
+    auto block_cand = [&](int blk) { return WHOLE ? (int)fdiv(fdiv(blk * kBlockRows, a.div_g), a.div_s) : (int)fdiv(blk, div_nb); };
+    // (not WHOLE) first row of the block within its candidate, rows that exist from there on
+    auto block_row = [&](int blk) { return (blk - block_cand(blk) * nb) * kBlockRows; };
+    auto block_rows = [&](int blk) { return WHOLE ? kBlockRows : rows_c - block_row(blk); };
+    auto block_i_lo = [&](int blk) {
+        return WHOLE ? (int)fdiv(blk * kBlockRows, a.div_g) - block_cand(blk) * a.S : (int)fdiv(block_row(blk), a.div_g);
+    };
+    auto decode = [&](int blk) __attribute__((always_inline)) {
+        if constexpr (WHOLE)
+            return decode_block(a, X, blk, X.head, X.cand0);
+        const int r = block_row(blk) + X.c32;
+        return decode_candidate_row(a, X.cand0 + __builtin_amdgcn_readfirstlane(block_cand(blk)), r < rows_c ? r : rows_c - 1, X.head);
+    };
+    // The block on the general path (not WHOLE: its candidate as a problem of one candidate).
+    auto general = [&](int T, int blk) __attribute__((always_inline)) {
+        if constexpr (WHOLE) {
+            general_block(a, X, T, blk);
+        } else {
+            Ctx Y = X;
+            Y.cand0 = X.cand0 + block_cand(blk);
+            Y.Mtot = rows_c;
+            general_block(a, Y, T, blk - block_cand(blk) * nb);
+        }
+    };
     // Advance to the next block of this wavefront that has a valid row; blocks of pure padding
     // on the way are stored as zeros here and now.
     // Every wavefront takes one contiguous range of blocks, so that a candidate's suffix K/V, which
@@ -164,9 +191,9 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles)
     const int part_lo = wg_lo + (wg_hi - wg_lo) * simd / 4, part_hi = wg_lo + (wg_hi - wg_lo) * (simd + 1) / 4;
     const int split = part_lo + ((part_hi - part_lo) * 7 + 6) / 12;
     const int blk_lo = wslot < 4 ? part_lo : split, blk_hi = wslot < 4 ? split : part_hi;
-    auto skip_padding = [&](int blk) {
+    auto skip_padding = [&](int blk) __attribute__((always_inline)) {
         while (blk < blk_hi && block_i_lo(blk) >= len_uniform(a, X.cand0 + block_cand(blk))) {
-            store_zero_block_rows(a, X, decode_block(a, X, blk, X.head, X.cand0));
+            store_zero_block_rows(a, X, decode(blk), block_rows(blk));
             ++blk;
         }
         return blk;
@@ -180,7 +207,7 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles)
     const int first_blk = blk_lo;
     bool any_bad = false;
     int blk = skip_padding(first_blk);
-    BlockRows nxt = decode_block(a, X, blk < blk_hi ? blk : nblocks - 1, X.head, X.cand0);
+    BlockRows nxt = decode(blk < blk_hi ? blk : nblocks - 1);
     uintx4 q[8]; // this block's Q fragments until their last use, then the next block's
     load_q_block(a, X, nxt, q);
 
@@ -190,14 +217,16 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles)
 
     if (T < 3) { // this instruction's prefix is too short for the pipeline: general path
         for (int b2 = first_blk; b2 < blk_hi; ++b2)
-            general_block(a, X, T, b2);
+            general(T, b2);
         continue;
     }
 
     while (blk < blk_hi) {
         const BlockRows row = nxt;
         // the block's suffix step: keys 0..skmax of its candidate
-        const int i_hi = (int)fdiv(blk * kBlockRows + kBlockRows - 1, a.div_g) - (row.b - X.cand0) * a.S;
+        const int rows = block_rows(blk);
+        const int i_hi = WHOLE ? (int)fdiv(blk * kBlockRows + kBlockRows - 1, a.div_g) - (row.b - X.cand0) * a.S
+                               : (int)fdiv(rows > kBlockRows ? block_row(blk) + kBlockRows - 1 : rows_c - 1, a.div_g);
         const int skmax = i_hi < row.len - 1 ? i_hi : row.len - 1;
         // Loads are retired in issue order, so what is needed last is requested first.
         uintx4 skf[8], svf[2][4];
@@ -261,7 +290,7 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles)
         // (Requested unconditionally, for a clamped block index past the end: a load under a
         // branch would have to be waited for and copied at the join.)
         blk = skip_padding(blk + 1);
-        nxt = decode_block(a, X, blk < blk_hi ? blk : nblocks - 1, X.head, X.cand0);
+        nxt = decode(blk < blk_hi ? blk : nblocks - 1);
         load_q_block(a, X, nxt, q);
 
         // ---- suffix step: causal mask and weights under the value product of the last prefix
@@ -273,14 +302,14 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles)
         pv_from_scratch(X, svf[1], as_bf16x8(pB[1]), o);
 
         any_bad |= __builtin_amdgcn_ballot_w64(row.ri < row.len && !(l < kBig)) != 0;
-        store_block_rows(a, X, row, m, l, o);
+        store_block_rows(a, X, row, m, l, o, rows);
     }
 
     // Rare: some row met scores far above its first tile's maximum.  Whatever this wavefront
     // stored is replaced by the general path's result.
     if (any_bad)
         for (int b2 = first_blk; b2 < blk_hi; ++b2)
-            general_block(a, X, T, b2);
+            general(T, b2);
     } // virtual heads
 }
 
@@ -299,16 +328,25 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
         const int max_lds = 2 * kMaxTiles * kTileBytes + kNW * kScrBytes;
         hipError_t s = hipFuncSetAttribute(reinterpret_cast<const void *>(resident_general_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
-        if (s == hipSuccess)
-            s = hipFuncSetAttribute(reinterpret_cast<const void *>(resident_pipelined_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
+        for (auto kernel : {resident_pipelined_kernel<true>, resident_pipelined_kernel<false>})
+            if (s == hipSuccess)
+                s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
         return s;
     });
     if (num_cu == 0)
         return e;
     const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
     const long long rows = (long long)a.C * a.S * a.G; // stacked rows of one virtual head
-    const long long nblocks = (rows + kBlockRows - 1) / kBlockRows;
+    // Candidates whose rows fill no whole number of blocks: blocks of their own and the pipelined kernel where
+    // those come out full to 13/16, the general kernel on full blocks that span candidates where not.  us, general and
+    // pipelined: 2048 candidates x 120 rows (8 KV heads, P 100): 265, 227; 1024 x 133 of 160 (4 heads, P 256): 103, 93;
+    // 512 x 28 of 32 (32 heads, P 128): 94, 87; 1024 x 52 of 64 (8 heads, P 200): 84, 78; below: 1024 x 77 of 96: 64,
+    // 66; 512 x 24 of 32: 84, 84; 512 x 20 of 32: 65, 67 (P 256: 77, 84); 512 x 12 of 32: 42, 53.
+    const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows; // rows and own blocks of a candidate
+    const bool whole = rows_c % kBlockRows == 0;
+    const bool pipelined = a.S <= kTileKeys && max_tiles >= 3 && block_offsets_fit(a) && rows_c * 16 >= nb * kBlockRows * 13 &&
+                           a.C * nb <= 0x7fffffffLL / kBlockRows;
+    const long long nblocks = pipelined ? a.C * nb : (rows + kBlockRows - 1) / kBlockRows;
     const long long VH = (long long)a.Np * a.Hkv;
     // One workgroup per compute unit.  With fewer virtual heads than compute units the
     // workgroups are split evenly over them (never more per virtual head than there are
@@ -320,11 +358,9 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
         per_vh = useful;
     const unsigned grid = (unsigned)(per_vh * vh_slots);
     const size_t lds = (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes;
-    const bool pipelined = ((long long)a.S * a.G) % kBlockRows == 0 && a.S <= kTileKeys && max_tiles >= 3 &&
-                           block_offsets_fit(a);
     if (pipelined)
-        return launch_kernel(resident_pipelined_kernel, dim3(grid), dim3(kNW * 64), lds, stream, a, (int)per_vh,
-                           (int)vh_slots, max_tiles);
+        return launch_kernel(whole ? resident_pipelined_kernel<true> : resident_pipelined_kernel<false>, dim3(grid), dim3(kNW * 64),
+                             lds, stream, a, (int)per_vh, (int)vh_slots, max_tiles, (int)nb, make_fastdiv((unsigned)nb));
     else
         return launch_kernel(resident_general_kernel, dim3(grid), dim3(kNW * 64), lds, stream, a, (int)per_vh,
                            (int)vh_slots, max_tiles);

@@ -1,0 +1,72 @@
+"""The resident forward kernel on candidates whose rows fill no whole number of 32-row blocks (each has
+blocks of its own, the last one partly empty), against the oracle."""
+import numpy as np
+import pytest
+
+import parity_util as pu
+from paper_2603_13420_amd import inputs as gen
+
+pytestmark = pytest.mark.gpu
+
+BF16_ONE, BF16_TWELVE = 0x3F80, 0x4140
+
+
+@pytest.fixture(scope="module")
+def pk():
+    from paper_2603_13420_amd import binding
+    return binding
+
+
+def check(pk, inp):
+    import torch
+    w, d = inp.w, pu.to_device(inp)
+    print(f"[case] B={w.B} P={w.P} S={w.S} len={w.len_lo}..{w.len_hi} Hq={w.Hq} Hkv={w.Hkv} seed={w.seed}", flush=True)
+    guard = 7.5   # in front of and behind the tensors: nothing outside of them is written
+    flat = torch.full((d["q"].numel() + 8192,), guard, device="cuda:0", dtype=torch.bfloat16)
+    out = flat[4096:-4096].view(d["q"].shape)
+    out.fill_(float("nan"))
+    lse = torch.full((w.B * w.Hq * w.S + 128,), guard, device="cuda:0")
+    pk.pskv_attn_fwd(d["q"], d["k_suf"], d["v_suf"], d["k_pre"], d["v_pre"], d["suf_len"], out=out,
+                     lse=lse[64:-64].view(w.B, w.Hq, w.S), scale=inp.scale)
+    torch.cuda.synchronize()
+    assert all((t == guard).all().item() for t in (flat[:4096], flat[-4096:], lse[:64], lse[-64:]))
+    ref, ref_lse = pu.oracle_out(inp, want_lse=True)
+    pu.compare_lse(lse[64:-64].view(w.B, w.Hq, w.S).cpu().numpy().astype(np.float64), ref_lse, inp.suf_len, "bf16", w.name)
+    pu.compare(pu.out_to_f64(out), ref, inp.suf_len, "bf16", w.name)
+
+
+@pytest.mark.parametrize("B,P,S,lo,hi,Hq,Hkv", [
+    (5, 65, 31, 0, 31, 2, 2),       # one block, one row short; candidates may be empty; a ragged third tile
+    (600, 96, 26, 26, 26, 4, 4),    # 26 of 32 rows, the least that takes this path; more blocks than wavefronts of a head
+    (600, 96, 25, 25, 25, 4, 4),    # one row less: the general kernel
+    (3, 256, 19, 1, 19, 6, 2),      # 57 rows, the whole prefix
+    (4, 129, 31, 0, 31, 7, 1),      # 217 rows, group 7: blocks of pure padding in between
+    (1, 200, 9, 9, 9, 28, 4),       # 63 rows
+])
+def test_own_blocks(pk, B, P, S, lo, hi, Hq, Hkv):
+    w = gen.custom_workload(f"own_{B}_{P}_{S}", B, P, S, lo, hi, Hq, Hkv, 128, "bf16", index=1900 + B + P)
+    check(pk, gen.make_inputs(w, pad="nan"))
+
+
+def test_own_blocks_scores_far_above_the_first_tile(pk):
+    """A late key of 130 and more above everything before it: the general path takes the wavefront's blocks."""
+    w = gen.custom_workload("own_spike", 6, 100, 27, 20, 27, 4, 2, 128, "bf16", index=1950)
+    inp = gen.make_inputs(w, pad="nan")
+    inp.q[1, :inp.suf_len[1]] = BF16_ONE
+    inp.k_pre[97] = BF16_TWELVE
+    check(pk, inp)
+
+
+def test_own_blocks_multi_instruction(pk):
+    """Prefixes of their own lengths, some too short for the pipeline, one empty."""
+    import torch
+    w = gen.custom_multi_workload("own_multi", 5, 7, 100, 0, 100, 13, 0, 13, 8, 2, 128, "bf16", index=1960)
+    inp = gen.make_multi_inputs(w, pad="nan")
+    inp.pre_len[:2] = 0, min(40, inp.pre_len[1])
+    inp.k_pre[0] = inp.v_pre[0] = 0x7FC0
+    inp.k_pre[1, :60] = inp.v_pre[1, :60] = 0x7FC0
+    d = pu.to_device_multi(inp)
+    out = pk.pskv_attn_fwd_multi(d["q"], d["k_suf"], d["v_suf"], d["k_pre"], d["v_pre"], d["pre_len"], d["suf_len"],
+                                 scale=inp.scale)
+    torch.cuda.synchronize()
+    pu.compare(pu.out_to_f64(out), pu.oracle_out_multi(inp), inp.suf_len, "bf16", w.name)
