@@ -799,11 +799,14 @@ __device__ inline Pass make_pass(const Args &a, int p, int npasses, int nblocks,
 }
 
 // Pass ids of the streamed kernels (see make_pass).
+inline long long stream_pass_ids(const Args &a, long long nblocks)
+{
+    const long long ngroups = (nblocks + kNW - 1) / kNW;
+    return 8 * pass_ids_per_xcd((long long)a.Np * a.Hkv * ngroups, ngroups);
+}
 inline long long stream_pass_ids(const Args &a)
 {
-    const long long rows = (long long)a.C * a.S * a.G;
-    const long long ngroups = ((rows + kBlockRows - 1) / kBlockRows + kNW - 1) / kNW;
-    return 8 * pass_ids_per_xcd((long long)a.Np * a.Hkv * ngroups, ngroups);
+    return stream_pass_ids(a, ((long long)a.C * a.S * a.G + kBlockRows - 1) / kBlockRows);
 }
 
 // Fragments 0 and 1 of the images a pipeline step starts with, read during the step before.

@@ -54,11 +54,16 @@ __device__ inline Ctx make_stream_ctx(const Args &a, lds_u8 *smem, int tid)
 // ------------------------------------------------------------------------------------------
 // General pass: classic online softmax, tiles double-buffered in slots 0 and 1.  Every thread
 // of the workgroup must call it (barriers inside), whether or not its wavefront has a block.
+// cand, rows_c: with rows_c > 0, blk counts within that candidate of the instruction, a problem of its own.
 // ------------------------------------------------------------------------------------------
 __device__ __attribute__((always_inline)) void general_pass(const Args &a, Ctx &X, lds_u8 *smem, int tid, int vh, int blk,
-                                                            bool active)
+                                                            bool active, int cand = 0, int rows_c = 0)
 {
     set_vhead(a, X, vh);
+    if (rows_c > 0) {
+        X.cand0 += cand;
+        X.Mtot = rows_c;
+    }
     const int ntiles = (X.P + kTileKeys - 1) / kTileKeys;
     const TileSlot t = make_tile_slot(tid);
     const int r0 = blk * kBlockRows;
@@ -123,10 +128,12 @@ void stream_general_kernel(Args a, int npasses)
 }
 
 // ------------------------------------------------------------------------------------------
-// Pipelined passes.  Preconditions (checked by the launcher): S*G is a multiple of 32, so a
-// 32-row block lies inside one candidate; the padded prefix has at least three tiles; one head's prefix
+// Pipelined passes.  Preconditions (checked by the launcher): every 32-row block lies inside one candidate; the padded prefix has at least three tiles; one head's prefix
 // spans less than 2^31 bytes, so tile addresses are a scalar base plus a 32-bit lane offset.
 // ONE_STEP: S <= 32, the suffix is a single 32-key step.
+// WHOLE: S*G is a multiple of 32, the blocks are those of the stacked rows.  Otherwise a candidate has nb
+// blocks of its own, the last one being what is left (its rows past the candidate's stand in for the last
+// one and are not stored), here and in the candidate passes further down.
 //
 // Ring protocol.  Step t of a pass (see pipe_tile) reads the K images of tiles t+1 and t+2 and
 // the V images of tiles t-1 and t.  Steps are taken two at a time.  Tiles are requested with
@@ -169,16 +176,29 @@ __device__ inline void request_to_lds(const unsigned char *gbase, unsigned voff,
 // s_waitcnt immediate (gfx9 encoding): vector memory counter at most n (n < 16), the others untouched
 #define PSKV_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | (n))
 
-template <bool ONE_STEP>
+template <bool WHOLE> __device__ inline BlockRows decode_own(const Args &a, const Ctx &X, int blk, int head, int cand0, int cand, int nb)
+{
+    if constexpr (WHOLE)
+        return decode_block(a, X, blk, head, cand0);
+    const int rows_c = a.S * a.G, r = (blk - cand * nb) * kBlockRows + X.c32;
+    return decode_candidate_row(a, cand0 + __builtin_amdgcn_readfirstlane(cand), r < rows_c ? r : rows_c - 1, head);
+}
+
+template <bool ONE_STEP, bool WHOLE>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
-void stream_pipelined_kernel(Args a, int npasses)
+void stream_pipelined_kernel(Args a, int npasses, int nb, FastDiv div_nb)
 {
     extern __shared__ __align__(16) unsigned char smem_generic[];
     lds_u8 *smem = (lds_u8 *)smem_generic;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     Ctx X = make_stream_ctx(a, smem, tid);
-    const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows;
+    const int rows_c = a.S * a.G; // rows of a candidate
+    const int nblocks = WHOLE ? (X.Mtot + kBlockRows - 1) / kBlockRows : a.C * nb;
+    auto cand_of = [&](int blk) { return WHOLE ? 0 : (int)fdiv(blk, div_nb); }; // (not WHOLE) candidate within the instruction
+    auto decode = [&](const Pass &ps) __attribute__((always_inline)) {
+        return decode_own<WHOLE>(a, X, ps.blk, ps.head, ps.cand0, cand_of(ps.blk), nb);
+    };
     auto kimg = [&](int t) { return X.k_lane + (t & (kRing - 1)) * kSlotBytes; };
     auto vimg = [&](int t) { return X.v_lane + (t & (kRing - 1)) * kSlotBytes; };
     // this thread's two requests for tile kt (kt <= the last tile), straight into slot kt % 8
@@ -198,7 +218,7 @@ void stream_pipelined_kernel(Args a, int npasses)
     bool wg_bad = false;
     int p = blockIdx.x;
     Pass ps = make_pass(a, p, npasses, nblocks, wave);
-    BlockRows nxt = decode_block(a, X, ps.blk, ps.head, ps.cand0);
+    BlockRows nxt = decode(ps);
     uintx4 q[8]; // this pass's Q fragments until their last use, then the next pass's
     load_q_block(a, X, nxt, q);
 
@@ -211,7 +231,7 @@ void stream_pipelined_kernel(Args a, int npasses)
             wg_short |= ps.exists;
             p += gridDim.x;
             ps = make_pass(a, p, npasses, nblocks, wave);
-            nxt = decode_block(a, X, ps.blk, ps.head, ps.cand0);
+            nxt = decode(ps);
             load_q_block(a, X, nxt, q);
             continue;
         }
@@ -256,7 +276,10 @@ void stream_pipelined_kernel(Args a, int npasses)
         };
 
         // the block's suffix: candidate sb, keys 0..skmax
-        const int i_hi = (int)fdiv(r0 + kBlockRows - 1, a.div_g) - (row.b - X.cand0) * a.S;
+        const int r_own = WHOLE ? 0 : r0 - cand_of(blk) * nb * kBlockRows; // (not WHOLE) first row within the candidate
+        const int rows = WHOLE ? kBlockRows : rows_c - r_own;
+        const int i_hi = WHOLE ? (int)fdiv(r0 + kBlockRows - 1, a.div_g) - (row.b - X.cand0) * a.S
+                               : (int)fdiv(r_own + kBlockRows - 1, a.div_g);
         const int skmax = i_hi < row.len - 1 ? i_hi : row.len - 1;
         const int skld = skmax > 0 ? skmax : 0; // row the suffix loads are clamped to (a candidate may be empty)
 
@@ -340,7 +363,7 @@ void stream_pipelined_kernel(Args a, int npasses)
         // the next pass's Q takes its place.
         const bool more = !ONE_STEP && skmax >= kTileKeys;
         if (!more) {
-            nxt = decode_block(a, X, ps.blk, ps.head, ps.cand0);
+            nxt = decode(ps);
             load_q_block(a, X, nxt, q);
         }
 
@@ -356,7 +379,7 @@ void stream_pipelined_kernel(Args a, int npasses)
             uintx4 qn[8];
             load_suffix_k_block(a, X, row.b, kTileKeys, skmax, skf);
             load_suffix_v_block(a, X, row.b, kTileKeys, skmax, svf);
-            nxt = decode_block(a, X, ps.blk, ps.head, ps.cand0);
+            nxt = decode(ps);
             load_q_block(a, X, nxt, qn);
             for (int k0 = kTileKeys;; k0 += kTileKeys) {
 #pragma unroll
@@ -380,7 +403,7 @@ void stream_pipelined_kernel(Args a, int npasses)
 
         const bool bad = __builtin_amdgcn_ballot_w64(rvalid && !(l < kBig)) != 0;
         if (active)
-            store_block_rows(a, X, row, m, l, o);
+            store_block_rows(a, X, row, m, l, o, rows);
         // the wavefront's verdict goes into the first word of its own scratch tile
         if (X.lane == 0)
             *(lds_int *)X.scr = bad ? 1 : 0;
@@ -397,7 +420,7 @@ void stream_pipelined_kernel(Args a, int npasses)
             const Pass ps2 = make_pass(a, p2, npasses, nblocks, wave);
             set_vhead(a, X, ps2.vh);
             if (ps2.exists && (wg_bad || (X.P + kTileKeys - 1) / kTileKeys < kMinTiles))
-                general_pass(a, X, smem, tid, ps2.vh, ps2.blk, ps2.active);
+                general_pass(a, X, smem, tid, ps2.vh, ps2.blk - cand_of(ps2.blk) * nb, ps2.active, cand_of(ps2.blk), WHOLE ? 0 : rows_c);
         }
 }
 
@@ -420,7 +443,7 @@ void stream_pipelined_kernel(Args a, int npasses)
 // Preconditions (launcher): those of the pipelined passes above, and S*ks_stride_s*2 < 2^31.
 // ------------------------------------------------------------------------------------------
 struct CandShape {
-    int nblk_c; // 32-row blocks per candidate (S*G/32)
+    int nblk_c; // 32-row blocks per candidate (S*G/32, rounded up)
     int ngrp;   // passes per (candidate, KV head) unit
     int bpp;    // blocks per pass (the last pass of a unit may hold fewer)
 };
@@ -500,6 +523,7 @@ __device__ inline void pv_tile(lds_u8 *v_img, const uintx4 (&pp)[2], floatx16 (&
                                                             o[ks & 3], 0, 0, 0);
 }
 
+template <bool WHOLE>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
 void stream_candidate_kernel(Args a, int npasses, CandShape cs)
 {
@@ -508,6 +532,13 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     Ctx X = make_stream_ctx(a, smem, tid);
+    const int rows_c = a.S * a.G; // rows of a candidate
+    auto decode = [&](const CandPass &ps) __attribute__((always_inline)) {
+        return decode_own<WHOLE>(a, X, ps.blk, ps.head, ps.cand0, ps.b - ps.cand0, cs.nblk_c);
+    };
+    // the block within its candidate, and the rows that exist from its first one on
+    auto block_in_cand = [&](const CandPass &ps) { return ps.blk - (ps.b - ps.cand0) * cs.nblk_c; };
+    auto block_rows = [&](const CandPass &ps) { return WHOLE ? kBlockRows : rows_c - block_in_cand(ps) * kBlockRows; };
     auto kimg = [&](int t) { return X.k_lane + (t & (kRing - 1)) * kSlotBytes; };
     auto vimg = [&](int t) { return X.v_lane + (t & (kRing - 1)) * kSlotBytes; };
     auto stage_write = [&](int kt, const uintx4 &kv, const uintx4 &vv) {
@@ -530,7 +561,7 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
     bool wg_bad = false, wg_short = false;
     int p = blockIdx.x;
     CandPass ps = make_cand_pass(a, cs, p, npasses, wave);
-    BlockRows nxt = decode_block(a, X, ps.blk, ps.head, ps.cand0);
+    BlockRows nxt = decode(ps);
     uintx4 q[8]; // this pass's Q fragments until their last use, then the next pass's
     load_q_block(a, X, nxt, q);
 
@@ -544,10 +575,10 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
             if (!nothing)
                 wg_short = true; // prefix too short for the pipeline: left to the general sweep below
             else if (ps.active)
-                store_zero_block_rows(a, X, nxt);
+                store_zero_block_rows(a, X, nxt, block_rows(ps));
             p += gridDim.x;
             ps = make_cand_pass(a, cs, p, npasses, wave);
-            nxt = decode_block(a, X, ps.blk, ps.head, ps.cand0);
+            nxt = decode(ps);
             load_q_block(a, X, nxt, q);
             continue;
         }
@@ -571,7 +602,7 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
         // This wavefront's own share of the pass's tiles: the prefix and the suffix tiles up to the
         // last key its own block sees (Tw <= T); none at all if it has no block or its block holds
         // nothing but padding (then it only stores zeros).
-        const int cblk = ps.blk - (ps.b - ps.cand0) * cs.nblk_c; // block within the candidate
+        const int cblk = block_in_cand(ps), rows = block_rows(ps);
         const int i_lo_w = (int)fdiv(cblk * kBlockRows, a.div_g);
         const int i_hi_w = (int)fdiv(cblk * kBlockRows + kBlockRows - 1, a.div_g);
         const bool active = ps.active && i_lo_w < len;
@@ -609,7 +640,7 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
         // neighbour: same barriers, in the same order, as the path below.
         if (!active) {
             if (ps.active)
-                store_zero_block_rows(a, X, row);
+                store_zero_block_rows(a, X, row, rows);
             for (int t = 2; t + 1 <= T - 2; t += 2) {
                 stage_write(t + 2, kv0, vv0);
                 stage_write(t + 3, kv1, vv1);
@@ -619,7 +650,7 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
             }
             p += gridDim.x;
             ps = make_cand_pass(a, cs, p, npasses, wave);
-            nxt = decode_block(a, X, ps.blk, ps.head, ps.cand0);
+            nxt = decode(ps);
             load_q_block(a, X, nxt, q);
             if (X.lane == 0)
                 *(lds_int *)X.scr = 0;
@@ -696,7 +727,7 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
         // Q has been used for the last time: the next pass's Q takes its place
         p += gridDim.x;
         ps = make_cand_pass(a, cs, p, npasses, wave);
-        nxt = decode_block(a, X, ps.blk, ps.head, ps.cand0);
+        nxt = decode(ps);
         load_q_block(a, X, nxt, q);
 
         // ---- last tile: its weights under the value product of the tile before, then its own ----
@@ -714,7 +745,7 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
             cand_stage_load(g, t + 5, kv1, vv1);
             __syncthreads();
         }
-        store_block_rows(a, X, row, m, l, o);
+        store_block_rows(a, X, row, m, l, o, rows);
         if (X.lane == 0)
             *(lds_int *)X.scr = bad ? 1 : 0;
         __syncthreads(); // ends the pass: the ring is free, the verdicts are visible
@@ -728,7 +759,8 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
             const CandPass ps2 = make_cand_pass(a, cs, p2, npasses, wave);
             set_vhead(a, X, ps2.vh);
             if (ps2.exists && (wg_bad || (X.P + kTileKeys - 1) / kTileKeys < kMinTiles))
-                general_pass(a, X, smem, tid, ps2.vh, ps2.blk, ps2.active);
+                general_pass(a, X, smem, tid, ps2.vh, WHOLE ? ps2.blk : block_in_cand(ps2), ps2.active, WHOLE ? 0 : ps2.b - ps2.cand0,
+                             WHOLE ? 0 : rows_c);
         }
 }
 
@@ -738,17 +770,22 @@ int device_cu_count(hipError_t &e)
     return device_setup_once(cu_by_device, e, [] {
         hipError_t s = hipFuncSetAttribute(reinterpret_cast<const void *>(stream_general_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-        if (s == hipSuccess)
-            s = hipFuncSetAttribute(reinterpret_cast<const void *>(stream_pipelined_kernel<true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-        if (s == hipSuccess)
-            s = hipFuncSetAttribute(reinterpret_cast<const void *>(stream_pipelined_kernel<false>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-        if (s == hipSuccess)
-            s = hipFuncSetAttribute(reinterpret_cast<const void *>(stream_candidate_kernel),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        for (auto kernel : {stream_pipelined_kernel<true, true>, stream_pipelined_kernel<true, false>, stream_pipelined_kernel<false, true>,
+                            stream_pipelined_kernel<false, false>})
+            if (s == hipSuccess)
+                s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        for (auto kernel : {stream_candidate_kernel<true>, stream_candidate_kernel<false>})
+            if (s == hipSuccess)
+                s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
         return s;
     });
+}
+
+// Whether the pipelined kernels' blocks, each inside one candidate, are the better ones: see launch_resident.
+bool own_blocks_fit(const Args &a)
+{
+    const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows;
+    return rows_c * 16 >= nb * kBlockRows * 13 && a.C * nb <= 0x7fffffffLL / kBlockRows - kNW && stream_pass_ids(a, a.C * nb) <= 0x7fffffffLL - 8;
 }
 
 } // namespace
@@ -768,7 +805,14 @@ hipError_t launch_mfma(const Args &a, hipStream_t stream)
     // suffix step against the fixed reference, the resident kernels would fall back to their
     // general path for such shapes.
     const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
-    const bool long_suffix = a.S > kTileKeys && ((long long)a.S * a.G) % kBlockRows == 0 && max_tiles >= kMinTiles &&
+    const bool whole = (long long)a.S * a.G % kBlockRows == 0;
+    // Rows that fill no whole number of blocks: only where the candidate passes come out full to three quarters.  us,
+    // resident general kernel and candidate passes, P 128: 256 candidates x 159 positions (28/4 heads, 35 blocks in 5
+    // passes of 8): 240, 211; 256 x 150 (32/8, 19 in 3): 263, 239; 16 x 90 (32/8, 12 in 2): 16, 12; below: 64 x 141
+    // (32/32, 5 in 1): 81, 101; with the pipelined passes 128 x 70 (32/8, 9 in 2): 49, 62.
+    const long long nb = ((long long)a.S * a.G + kBlockRows - 1) / kBlockRows, ngrp = (nb + kNW - 1) / kNW;
+    const bool long_suffix = a.S > kTileKeys && (whole || (own_blocks_fit(a) && block_offsets_fit(a) && nb * 4 >= ngrp * kNW * 3 &&
+                                                           (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL)) && max_tiles >= kMinTiles &&
                              (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL;
     return resident_supported(a) && !long_suffix ? launch_resident(a, stream) : launch_stream(a, stream);
 }
@@ -780,15 +824,14 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
     if (e != hipSuccess)
         return e;
     const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
-    const long long npasses = stream_pass_ids(a);
-    const unsigned grid = (unsigned)(npasses < num_cu ? npasses : num_cu);
-    const bool pipelined = ((long long)a.S * a.G) % kBlockRows == 0 && max_tiles >= kMinTiles &&
-                           (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && block_offsets_fit(a);
+    const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows; // rows and own blocks of a candidate
+    const bool whole = rows_c % kBlockRows == 0;
+    bool pipelined = own_blocks_fit(a) && max_tiles >= kMinTiles && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && block_offsets_fit(a);
     // Long suffix-side segments whose candidates fill most of a workgroup's eight wavefronts
     // take the candidate passes.
     if (pipelined && a.S > kTileKeys && (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL) {
         CandShape cs;
-        const long long nblk_c = (long long)a.S * a.G / kBlockRows;
+        const long long nblk_c = nb;
         cs.nblk_c = (int)nblk_c;
         cs.ngrp = (int)((nblk_c + kNW - 1) / kNW);
         // Full passes first; the last one takes what is left.  With up to four blocks left every
@@ -798,15 +841,22 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
         const long long cpasses = (units + 7) / 8 * 8 * cs.ngrp;
         if (nblk_c * 10 >= (long long)cs.ngrp * kNW * 6 && cpasses <= 0x7fffffffLL - 8) {
             const unsigned cgrid = (unsigned)(cpasses < num_cu ? cpasses : num_cu);
-            return launch_kernel(stream_candidate_kernel, dim3(cgrid), dim3(kNW * 64), kLdsBytes, stream, a, (int)cpasses, cs);
+            return launch_kernel(whole ? stream_candidate_kernel<true> : stream_candidate_kernel<false>, dim3(cgrid), dim3(kNW * 64), kLdsBytes, stream, a, (int)cpasses, cs);
         }
     }
+    // Own blocks make more passes, each in 0.7 of the general kernel's time: not where that costs a round of the chip.
+    // us, general and pipelined: 512 candidates x 29 positions (32/32 heads, P 512): 252, 189; 512 x 26: 221, 178; 1024
+    // x 30 (32/8): 388, 313; 300 x 13 (32/8, P 700; 2 rounds, 3 rounds): 66, 69.
+    auto rounds = [&](long long passes) { return (passes + num_cu - 1) / num_cu; };
+    if (pipelined && !whole)
+        pipelined = rounds(stream_pass_ids(a, a.C * nb)) * 7 <= rounds(stream_pass_ids(a)) * 10;
+    const long long npasses = pipelined ? stream_pass_ids(a, a.C * nb) : stream_pass_ids(a);
+    const unsigned grid = (unsigned)(npasses < num_cu ? npasses : num_cu);
     if (!pipelined)
         return launch_kernel(stream_general_kernel, dim3(grid), dim3(kNW * 64), kLdsBytes, stream, a, (int)npasses);
-    else if (a.S <= kTileKeys)
-        return launch_kernel(stream_pipelined_kernel<true>, dim3(grid), dim3(kNW * 64), kLdsBytes, stream, a, (int)npasses);
-    else
-        return launch_kernel(stream_pipelined_kernel<false>, dim3(grid), dim3(kNW * 64), kLdsBytes, stream, a, (int)npasses);
+    auto kernel = a.S <= kTileKeys ? (whole ? stream_pipelined_kernel<true, true> : stream_pipelined_kernel<true, false>)
+                                   : (whole ? stream_pipelined_kernel<false, true> : stream_pipelined_kernel<false, false>);
+    return launch_kernel(kernel, dim3(grid), dim3(kNW * 64), kLdsBytes, stream, a, (int)npasses, (int)nb, make_fastdiv((unsigned)nb));
 }
 
 } // namespace pskv

@@ -1,4 +1,4 @@
-"""The resident forward kernel on candidates whose rows fill no whole number of 32-row blocks (each has
+"""The pipelined forward kernels on candidates whose rows fill no whole number of 32-row blocks (each has
 blocks of its own, the last one partly empty), against the oracle."""
 import numpy as np
 import pytest
@@ -42,29 +42,39 @@ def check(pk, inp):
     (3, 256, 19, 1, 19, 6, 2),      # 57 rows, the whole prefix
     (4, 129, 31, 0, 31, 7, 1),      # 217 rows, group 7: blocks of pure padding in between
     (1, 200, 9, 9, 9, 28, 4),       # 63 rows
+    (3, 257, 27, 0, 27, 4, 2),      # streamed prefix; 54 rows
+    (40, 350, 30, 30, 30, 32, 8),   # ... 120 rows, more passes than compute units for some heads
+    (2, 300, 53, 0, 53, 4, 4),      # ... two suffix steps
+    (300, 300, 13, 0, 13, 32, 8),   # ... the general kernel: own blocks would take a round more
+    (5, 130, 91, 20, 91, 32, 32),   # long suffix, prefix resident: the general kernel, its passes being 3/8 full
+    (3, 130, 71, 20, 71, 7, 1),     # a candidate's passes, its own keys staged like the prefix; 497 rows
+    (5, 70, 65, 0, 65, 28, 4),      # ... 455 rows, the third own tile holds one key; empty candidates
+    (2, 700, 35, 1, 35, 28, 4),     # ... behind a long prefix
 ])
 def test_own_blocks(pk, B, P, S, lo, hi, Hq, Hkv):
     w = gen.custom_workload(f"own_{B}_{P}_{S}", B, P, S, lo, hi, Hq, Hkv, 128, "bf16", index=1900 + B + P)
     check(pk, gen.make_inputs(w, pad="nan"))
 
 
-def test_own_blocks_scores_far_above_the_first_tile(pk):
-    """A late key of 130 and more above everything before it: the general path takes the wavefront's blocks."""
-    w = gen.custom_workload("own_spike", 6, 100, 27, 20, 27, 4, 2, 128, "bf16", index=1950)
+@pytest.mark.parametrize("P,S,lo,Hq,Hkv", [(100, 27, 20, 4, 2), (300, 27, 20, 4, 2), (300, 53, 40, 4, 4), (130, 71, 60, 7, 1)])
+def test_own_blocks_scores_far_above_the_first_tile(pk, P, S, lo, Hq, Hkv):
+    """A late key of 130 and more above everything before it: the general path takes over."""
+    w = gen.custom_workload(f"own_spike_{P}_{S}", 6, P, S, lo, S, Hq, Hkv, 128, "bf16", index=1950 + P + S)
     inp = gen.make_inputs(w, pad="nan")
     inp.q[1, :inp.suf_len[1]] = BF16_ONE
-    inp.k_pre[97] = BF16_TWELVE
+    inp.k_pre[P - 3] = BF16_TWELVE
     check(pk, inp)
 
 
-def test_own_blocks_multi_instruction(pk):
+@pytest.mark.parametrize("P,S", [(100, 13), (300, 13), (300, 53), (100, 71)])
+def test_own_blocks_multi_instruction(pk, P, S):
     """Prefixes of their own lengths, some too short for the pipeline, one empty."""
     import torch
-    w = gen.custom_multi_workload("own_multi", 5, 7, 100, 0, 100, 13, 0, 13, 8, 2, 128, "bf16", index=1960)
+    w = gen.custom_multi_workload(f"own_multi_{P}_{S}", 5, 7, P, 0, P, S, 0, S, 8, 2, 128, "bf16", index=2000 + P + S)
     inp = gen.make_multi_inputs(w, pad="nan")
     inp.pre_len[:2] = 0, min(40, inp.pre_len[1])
     inp.k_pre[0] = inp.v_pre[0] = 0x7FC0
-    inp.k_pre[1, :60] = inp.v_pre[1, :60] = 0x7FC0
+    inp.k_pre[1, :P - 40] = inp.v_pre[1, :P - 40] = 0x7FC0
     d = pu.to_device_multi(inp)
     out = pk.pskv_attn_fwd_multi(d["q"], d["k_suf"], d["v_suf"], d["k_pre"], d["v_pre"], d["pre_len"], d["suf_len"],
                                  scale=inp.scale)
