@@ -44,7 +44,16 @@ struct Arg {
         t = &THPVariable_Unpack(o);
         return true;
     }
+    // Throws for a tensor without storage (one that torch.vmap or torch.func.grad hands in is of the exact type Tensor).
     void *data() const { return t ? t->data_ptr() : nullptr; }
+};
+
+// The interpreter's lock given up for as long as the object lives, whatever ends that.
+struct WithoutGil {
+    PyThreadState *save = PyEval_SaveThread();
+    WithoutGil() = default;
+    WithoutGil(const WithoutGil &) = delete;
+    ~WithoutGil() { PyEval_RestoreThread(save); }
 };
 
 bool same_layout(const at::Tensor &x, const at::Tensor &y)
@@ -186,18 +195,18 @@ template <bool MULTI> PyObject *forward(PyObject *, PyObject *const *args, Py_ss
     void *stream;
     if (!stream_of(args[10 + kLen], *q.t, stream))
         return nullptr;
+    const void *q_p = q.data(), *ks_p = ks.data(), *vs_p = vs.data(), *kp_p = kp.data(), *vp_p = vp.data();
+    const auto *pre_len = static_cast<const int32_t *>(pl.data()), *suf_len = static_cast<const int32_t *>(sl.data());
+    void *out_p = out.data();
+    auto *lse_p = static_cast<float *>(lse.data());
     pskv_status rc;
     {
         const c10::DeviceGuard guard(q.t->device());
-        PyThreadState *save = PyEval_SaveThread();
-        const auto *suf_len = static_cast<const int32_t *>(sl.data());
-        auto *l = static_cast<float *>(lse.data());
+        const WithoutGil no_gil;
         if constexpr (MULTI)
-            rc = lib_fwd_multi(&m, q.data(), ks.data(), vs.data(), kp.data(), vp.data(), static_cast<const int32_t *>(pl.data()), suf_len,
-                               out.data(), l, nullptr, 0, stream);
+            rc = lib_fwd_multi(&m, q_p, ks_p, vs_p, kp_p, vp_p, pre_len, suf_len, out_p, lse_p, nullptr, 0, stream);
         else
-            rc = lib_fwd(&m.base, q.data(), ks.data(), vs.data(), kp.data(), vp.data(), suf_len, out.data(), l, nullptr, 0, stream);
-        PyEval_RestoreThread(save);
+            rc = lib_fwd(&m.base, q_p, ks_p, vs_p, kp_p, vp_p, suf_len, out_p, lse_p, nullptr, 0, stream);
     }
     if (rc != PSKV_OK)
         return PyLong_FromLong(rc);
@@ -264,22 +273,21 @@ template <Bwd KIND> PyObject *backward(PyObject *, PyObject *const *args, Py_ssi
         }
         ws_bytes = ws.t ? (size_t)ws.t->numel() * ws.t->element_size() : 0;
     }
+    const void *q_p = q.data(), *ks_p = ks.data(), *vs_p = vs.data(), *kp_p = kp.data(), *vp_p = vp.data(), *out_p = out.data(),
+               *dout_p = dout.data();
+    const auto *pre_len = static_cast<const int32_t *>(pl.data()), *suf_len = static_cast<const int32_t *>(sl.data());
+    const auto *lse_p = static_cast<const float *>(lse.data());
+    void *dq_p = dq.data(), *dk_p = dk.data(), *dv_p = dv.data(), *ws_p = ws.data();
     pskv_status rc;
     {
         const c10::DeviceGuard guard(q.t->device());
-        PyThreadState *save = PyEval_SaveThread();
-        const auto *suf_len = static_cast<const int32_t *>(sl.data());
-        const auto *l = static_cast<const float *>(lse.data());
+        const WithoutGil no_gil;
         if constexpr (kMulti)
-            rc = lib_bwd_multi(&m, q.data(), ks.data(), vs.data(), kp.data(), vp.data(), static_cast<const int32_t *>(pl.data()), suf_len,
-                               out.data(), l, dout.data(), dq.data(), dk.data(), dv.data(), ws.data(), ws_bytes, stream);
+            rc = lib_bwd_multi(&m, q_p, ks_p, vs_p, kp_p, vp_p, pre_len, suf_len, out_p, lse_p, dout_p, dq_p, dk_p, dv_p, ws_p, ws_bytes, stream);
         else if constexpr (kNoAlloc)
-            rc = lib_bwd_noalloc(&m.base, q.data(), ks.data(), vs.data(), kp.data(), vp.data(), suf_len, out.data(), l, dout.data(), dq.data(),
-                                 dk.data(), dv.data(), stream);
+            rc = lib_bwd_noalloc(&m.base, q_p, ks_p, vs_p, kp_p, vp_p, suf_len, out_p, lse_p, dout_p, dq_p, dk_p, dv_p, stream);
         else
-            rc = lib_bwd(&m.base, q.data(), ks.data(), vs.data(), kp.data(), vp.data(), suf_len, out.data(), l, dout.data(), dq.data(),
-                         dk.data(), dv.data(), ws.data(), ws_bytes, stream);
-        PyEval_RestoreThread(save);
+            rc = lib_bwd(&m.base, q_p, ks_p, vs_p, kp_p, vp_p, suf_len, out_p, lse_p, dout_p, dq_p, dk_p, dv_p, ws_p, ws_bytes, stream);
     }
     if (rc != PSKV_OK)
         return PyLong_FromLong(rc);
