@@ -215,11 +215,14 @@ __device__ inline long long tile_row(const Tile &t, int j)
 // The four wavefronts' accumulators, each scaled by its `f`, summed, scaled by `inv` and stored at `row`
 // (zeros when not valid): wavefront w takes the elements r = w.  64 columns at a time, so that the
 // buffer (kGatherBytes, free when this is called) is no larger than what the tiles needed.
+//
+// Returns whether one of the lane's sums is NaN in a valid row: see finish_alone.
 constexpr size_t kGatherBytes = (size_t)kWaves * 4 * 4 * 64 * sizeof(double);
 template <int D>
-__device__ inline void gather_store(double *buf, int wave, int lane, const doublex4 (&x)[D / 16], double f, float *row, double inv,
+__device__ inline bool gather_store(double *buf, int wave, int lane, const doublex4 (&x)[D / 16], double f, float *row, double inv,
                                     bool exists, bool valid)
 {
+    bool nan = false;
     row += (4 * wave + (lane >> 4)) * (D / 16); // the run of columns of element r = wave
 #pragma unroll
     for (int i = 0; i < D / 64; ++i) {
@@ -231,18 +234,63 @@ __device__ inline void gather_store(double *buf, int wave, int lane, const doubl
             for (int r = 0; r < 4; ++r)
                 buf[((wave * 4 + r) * 4 + j) * 64 + lane] = x[4 * i + j][r] * f;
         __syncthreads();
-        floatx4 y;
+        doublex4 sum = zero4();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            double sum = 0.;
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int w = 0; w < kWaves; ++w)
-                sum += buf[((w * 4 + wave) * 4 + j) * 64 + lane];
-            y[j] = valid ? (float)(sum * inv) : 0.f;
-        }
+                sum[j] += buf[((w * 4 + wave) * 4 + j) * 64 + lane];
+        floatx4 y;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            y[j] = valid ? (float)(sum[j] * inv) : 0.f;
+        nan |= y[0] != y[0] || y[1] != y[1] || y[2] != y[2] || y[3] != y[3];
         if (exists)
             *reinterpret_cast<floatx4 *>(row + 4 * i) = y;
     }
+    return nan;
+}
+
+// The products take hidden terms - another candidate's keys, keys behind the row's position - with a weight
+// of zero, and zero times an infinity or NaN among them is NaN.  That is all such a term can do (the
+// scores are replaced before anything is made of them), so a lane that finds a NaN among its sums
+// forms those columns anew, alone, from the terms that its row has, and stores them over the others:
+// each(term) calls term(weight, row) for these.  Kept behind the last use of the accumulators: no
+// registers are held for it, and a row without NaN pays a comparison.
+template <int D> __device__ inline double lane_dot(const float *x, const float *y)
+{
+    double acc = 0.;
+#pragma unroll 4
+    for (int d = 0; d < D; ++d)
+        acc += (double)x[d] * (double)y[d];
+    return acc;
+}
+template <int D, typename F> __device__ inline void finish_alone(int wave, int lane, float *row, double inv, F each)
+{
+    asm volatile("" : "+v"(lane)); // (nothing of this is worked out ahead)
+    const int col = (4 * wave + (lane >> 4)) * (D / 16);
+    for (int c0 = col; c0 < col + D / 16; c0 += 4) {
+        doublex4 sum = zero4();
+        each([&](double w, const float *r) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                sum[j] += w * (double)r[c0 + j];
+        });
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            row[c0 + j] = (float)(sum[j] * inv);
+    }
+}
+// Calls f(K row, V row) for the keys that the lane's row sees.
+template <typename F> __device__ inline void for_visible_keys(const Args &a, const Block &x, F f)
+{
+    const float *kp = reinterpret_cast<const float *>(a.kp) + x.pre, *vp = reinterpret_cast<const float *>(a.vp) + x.pre;
+    for (int j = 0; j < x.P; ++j)
+        f(kp + (long long)j * a.kp_sp, vp + (long long)j * a.kp_sp);
+    const long long own = (long long)x.b * a.ks_sb + (long long)x.k * a.ks_sh;
+    const float *ks = reinterpret_cast<const float *>(a.ks) + own, *vs = reinterpret_cast<const float *>(a.vs) + own;
+    for (int j = 0; j <= x.i; ++j)
+        f(ks + (long long)j * a.ks_ss, vs + (long long)j * a.ks_ss);
 }
 
 template <int D>
@@ -321,11 +369,15 @@ void f32_fwd_kernel(Args a, int nblk)
 #pragma unroll
     for (int w = 0; w < kWaves; ++w)
         sum += st[w * 32 + 16 + c] * exp(st[w * 32 + c] - top);
-    gather_store<D>(buf, wave, lane, o, exp(m - top),
-                    reinterpret_cast<float *>(a.out) + (long long)x.b * a.o_sb + (long long)x.i * a.o_ss + (long long)x.h * a.o_sh,
-                    1. / sum, x.exists, x.valid);
+    float *out = reinterpret_cast<float *>(a.out) + (long long)x.b * a.o_sb + (long long)x.i * a.o_ss + (long long)x.h * a.o_sh;
+    const bool nan = gather_store<D>(buf, wave, lane, o, exp(m - top), out, 1. / sum, x.exists, x.valid);
     if (x.exists && a.lse && kq == 0 && wave == 0)
         a.lse[((long long)x.b * a.Hq + x.h) * a.S + x.i] = x.valid ? (float)(top + log(sum)) : -INFINITY;
+    if (nan)
+        finish_alone<D>(wave, lane, out, 1. / sum, [&](auto term) {
+            const float *q = reinterpret_cast<const float *>(a.q) + (long long)x.b * a.q_sb + (long long)x.i * a.q_ss + (long long)x.h * a.q_sh;
+            for_visible_keys(a, x, [&](const float *k, const float *v) { term(exp(lane_dot<D>(q, k) * (double)a.scale - top), v); });
+        });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -396,8 +448,17 @@ template <int D> __device__ __attribute__((always_inline)) void dq_block(const B
         }
     }
     __syncthreads(); // nobody reads q and dout any more: their place is free
-    gather_store<D>(reinterpret_cast<double *>(smem), wave, lane, dq, 1., reinterpret_cast<float *>(g.dq) + row + (long long)x.i * a.q_ss,
-                    (double)a.scale, x.exists, x.valid);
+    float *dst = reinterpret_cast<float *>(g.dq) + row + (long long)x.i * a.q_ss;
+    if (gather_store<D>(reinterpret_cast<double *>(smem), wave, lane, dq, 1., dst, (double)a.scale, x.exists, x.valid))
+        finish_alone<D>(wave, lane, dst, (double)a.scale, [&](auto term) {
+            const long long at = orow + (long long)x.i * a.o_ss;
+            const float *q = reinterpret_cast<const float *>(a.q) + row + (long long)x.i * a.q_ss, *dout = reinterpret_cast<const float *>(g.dout) + at;
+            const double lse = (double)a.lse[((long long)x.b * a.Hq + x.h) * a.S + x.i];
+            const double drow = lane_dot<D>(dout, reinterpret_cast<const float *>(a.out) + at);
+            for_visible_keys(a, x, [&](const float *k, const float *v) {
+                term(exp(lane_dot<D>(q, k) * (double)a.scale - lse) * (lane_dot<D>(dout, v) - drow), k);
+            });
+        });
 }
 
 template <int D> __device__ __attribute__((always_inline)) void dkv_unit(const BwdArgs &g, int nkt, int id, unsigned char *smem)
@@ -464,10 +525,32 @@ template <int D> __device__ __attribute__((always_inline)) void dkv_unit(const B
     }
     double *buf = reinterpret_cast<double *>(smem);
     const long long at = koff + (long long)(key < a.S ? key : 0) * a.ks_ss;
+    float *dst_k = reinterpret_cast<float *>(g.dk) + at, *dst_v = reinterpret_cast<float *>(g.dv) + at;
     __syncthreads();
-    gather_store<D>(buf, wave, lane, dk, 1., reinterpret_cast<float *>(g.dk) + at, (double)a.scale, key < a.S, key < len);
+    const bool nan_k = gather_store<D>(buf, wave, lane, dk, 1., dst_k, (double)a.scale, key < a.S, key < len);
     __syncthreads();
-    gather_store<D>(buf, wave, lane, dv, 1., reinterpret_cast<float *>(g.dv) + at, 1., key < a.S, key < len);
+    const bool nan_v = gather_store<D>(buf, wave, lane, dv, 1., dst_v, 1., key < a.S, key < len);
+    // the rows that see the lane's key
+    auto for_rows = [&](auto f) {
+        const float *kr = reinterpret_cast<const float *>(a.ks) + at, *vr = reinterpret_cast<const float *>(a.vs) + at;
+        for (int rl = key * a.G; rl < len * a.G; ++rl) {
+            const int i = (int)fdiv(rl, a.div_g), h = k * a.G + rl - i * a.G;
+            const long long oo = (long long)b * a.o_sb + (long long)i * a.o_ss + (long long)h * a.o_sh;
+            const float *q = reinterpret_cast<const float *>(a.q) + (long long)b * a.q_sb + (long long)i * a.q_ss + (long long)h * a.q_sh;
+            const float *dout = reinterpret_cast<const float *>(g.dout) + oo, *out = reinterpret_cast<const float *>(a.out) + oo;
+            f(q, dout, out, exp(lane_dot<D>(q, kr) * (double)a.scale - (double)a.lse[((long long)b * a.Hq + h) * a.S + i]), vr);
+        }
+    };
+    if (nan_k)
+        finish_alone<D>(wave, lane, dst_k, (double)a.scale, [&](auto term) {
+            for_rows([&](const float *q, const float *dout, const float *out, double p, const float *vr) {
+                term(p * (lane_dot<D>(dout, vr) - lane_dot<D>(dout, out)), q);
+            });
+        });
+    if (nan_v)
+        finish_alone<D>(wave, lane, dst_v, 1., [&](auto term) {
+            for_rows([&](const float *, const float *dout, const float *, double p, const float *) { term(p, dout); });
+        });
 }
 
 // One launch for all three gradients, neither of which needs anything of the other's: the dk/dv units,
