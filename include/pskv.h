@@ -13,7 +13,11 @@
  *
  * which is exactly what a Standard KV cache (Eq. 3: prefix repeated B times) computes.
  * Rows i >= suf_len[b] are written as 0 (lse: -inf); padded Q/K/V rows may hold anything,
- * NaN included, and never influence a valid row.
+ * NaN included, and never influence a valid row.  A VALID row that holds an infinity or NaN reaches
+ * the rows that see it and no others, except on the matrix-core path of bf16 tensors with D == 128:
+ * there hidden keys of a 32-key step take part with a weight of zero, and a non-finite one among them can
+ * turn rows that do not see it (earlier positions of the same candidate, neighbours in a 32-row
+ * block) into NaN.  PSKV_IMPL_SIMPLE keeps such rows apart for every shape it covers.
  *
  * All pointers except the params struct and the returned strings are DEVICE pointers owned
  * by the caller.  The library allocates, frees and retains no device memory and keeps no

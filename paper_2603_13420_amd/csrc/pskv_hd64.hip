@@ -197,6 +197,84 @@ __device__ inline void store_transposed(unsigned short *row, int h, bool exists,
         }
 }
 
+// ------------------------------------------------------------------------------------------
+// The products take hidden terms - keys of the block's other candidates, keys behind the row's position,
+// rows that do not see the key - with a weight of zero, and zero times an infinity or NaN among them is NaN.
+// That is all such a term can do (hidden scores are replaced before anything is made of them).  So a wavefront
+// whose valid sums hold a NaN goes over its blocks once more behind its loops (where this costs the loops
+// no registers): every lane forms those columns of the rows it has stored anew, alone, from the terms that the row
+// has, and stores them over the others.
+// ------------------------------------------------------------------------------------------
+__device__ inline float lane_dot(const unsigned short *x, const unsigned short *y)
+{
+    float acc = 0.f;
+#pragma unroll 1
+    for (int c = 0; c < kW; c += 8) {
+        const uintx4 u = ld_global16(x + c), v = ld_global16(y + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            acc = __builtin_fmaf(__uint_as_float(u[e] << 16), __uint_as_float(v[e] << 16), acc);
+            acc = __builtin_fmaf(__uint_as_float(u[e] & 0xffff0000u), __uint_as_float(v[e] & 0xffff0000u), acc);
+        }
+    }
+    return acc;
+}
+// Eight columns of a sum over rows.
+struct Columns {
+    float v[8] = {};
+    __device__ void add(float w, const unsigned short *row)
+    {
+        const uintx4 u = ld_global16(row);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[2 * e] = __builtin_fmaf(w, __uint_as_float(u[e] << 16), v[2 * e]);
+            v[2 * e + 1] = __builtin_fmaf(w, __uint_as_float(u[e] & 0xffff0000u), v[2 * e + 1]);
+        }
+    }
+    __device__ void store(unsigned short *row, float scale) const
+    {
+        uintx4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            y[e] = pack_bf16(v[2 * e] * scale, v[2 * e + 1] * scale);
+        *reinterpret_cast<uintx4 *>(row) = y;
+    }
+};
+// Whether eight stored columns are to be formed anew: a NaN is among them, or nothing but zeros (what a row without a
+// finite score was stored as).
+__device__ inline bool to_form_anew(const unsigned short *row)
+{
+    const uintx4 y = ld_global16(row);
+    bool nan = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float lo = __uint_as_float(y[e] << 16), hi = __uint_as_float(y[e] & 0xffff0000u);
+        nan |= lo != lo || hi != hi;
+    }
+    return nan || (y[0] | y[1] | y[2] | y[3]) == 0;
+}
+// Calls f(K row, V row) for the keys that the lane's row sees.
+template <typename F> __device__ inline void for_visible_keys(const Args &a, const Ctx &X, const Rows &x, F f)
+{
+#pragma unroll 1
+    for (int j = 0; j < X.P; ++j)
+        f(X.kpg + (long long)j * a.kp_sp, X.vpg + (long long)j * a.kp_sp);
+    const unsigned short *ks = X.ksg + (long long)x.b * a.ks_sb, *vs = X.vsg + (long long)x.b * a.ks_sb;
+#pragma unroll 1
+    for (int j = 0; j <= x.i; ++j)
+        f(ks + (long long)j * a.ks_ss, vs + (long long)j * a.ks_ss);
+}
+__device__ inline bool has_nan(const floatx16 (&o)[kDT])
+{
+    bool nan = false;
+#pragma unroll
+    for (int dt = 0; dt < kDT; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            nan |= o[dt][e] != o[dt][e];
+    return nan;
+}
+
 __device__ inline Ctx make_hd64_ctx(const Args &a, int tid)
 {
     Ctx X;
@@ -262,6 +340,24 @@ struct Spread {
     int per_vh, vh_slots, chunk; // workgroups per pair, pairs served at a time, tiles that fit into LDS
 };
 
+// f(arguments, context, row) for the valid rows of this wavefront's blocks in a walk of `waves` wavefronts per workgroup, for
+// a path hardly ever taken.  (A kernel's first parameter is, or begins with, Args.)
+template <typename F> __device__ inline void for_stored_rows(const Spread &sp, int waves, int tid, F f)
+{
+    const Args &a = first_parameter<Args>();
+    asm volatile("" : "+v"(tid)); // (nothing of this is worked out ahead)
+    Ctx X = make_hd64_ctx(a, tid);
+    const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int vh = blockIdx.x % sp.vh_slots; vh < a.Np * a.Hkv; vh += sp.vh_slots) {
+        set_vhead(a, X, vh);
+        for (int blk = (blockIdx.x / sp.vh_slots) * waves + wave; blk < nblocks; blk += sp.per_vh * waves) {
+            const Rows x = make_rows(a, X, blk);
+            if (x.valid)
+                f(a, X, x);
+        }
+    }
+}
+
 struct FwdState {
     float m, l;
     floatx16 o[kDT];
@@ -319,6 +415,7 @@ void hd64_fwd_kernel(Args a, Spread sp)
     Ctx X = make_hd64_ctx(a, tid);
     X.scr = img + sp.chunk * 2 * kImg + wave * kImg;
     const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows, VH = a.Np * a.Hkv;
+    bool bad = false;
 
     for (int vh = blockIdx.x % sp.vh_slots; vh < VH; vh += sp.vh_slots) {
         set_vhead(a, X, vh);
@@ -388,11 +485,32 @@ void hd64_fwd_kernel(Args a, Spread sp)
                 store_transposed(reinterpret_cast<unsigned short *>(a.out) + (long long)x.b * a.o_sb + (long long)x.i * a.o_ss +
                                      (long long)x.h * a.o_sh,
                                  X.h, x.exists, x.valid, 1.0f / l, st.o);
+                const float lse2 = l != 0.f ? st.m + __builtin_log2f(l) : NAN; // (no sum: every score is -inf, and the result NaN)
                 if (a.lse && x.exists && X.h == 0)
-                    a.lse[((long long)x.b * a.Hq + x.h) * a.S + x.i] = x.valid ? (st.m + __builtin_log2f(l)) * kLn2 : -INFINITY;
+                    a.lse[((long long)x.b * a.Hq + x.h) * a.S + x.i] = x.valid ? lse2 * kLn2 : -INFINITY;
+                bad |= __builtin_amdgcn_ballot_w64(x.valid && (has_nan(st.o) || l == 0.f)) != 0;
             }
         }
     }
+    if (bad) // (see to_form_anew)
+        for_stored_rows(sp, kFwdWaves, tid, [](const Args &a, const Ctx &X, const Rows &x) {
+            unsigned short *out = reinterpret_cast<unsigned short *>(a.out) + (long long)x.b * a.o_sb + (long long)x.i * a.o_ss + (long long)x.h * a.o_sh;
+            const unsigned short *q = reinterpret_cast<const unsigned short *>(a.q) + (long long)x.b * a.q_sb + (long long)x.i * a.q_ss + (long long)x.h * a.q_sh;
+#pragma unroll 1
+            for (int c = 8 * X.h; c < kW; c += 16) {
+                if (!to_form_anew(out + c))
+                    continue;
+                float m = -INFINITY, l = 0.f;
+                for_visible_keys(a, X, x, [&](const unsigned short *k, const unsigned short *) { m = fmaxf(m, lane_dot(q, k) * X.c); });
+                Columns y;
+                for_visible_keys(a, X, x, [&](const unsigned short *k, const unsigned short *v) {
+                    const float p = fast_exp2(__builtin_fmaf(lane_dot(q, k), X.c, -m));
+                    l += p;
+                    y.add(p, v + c);
+                });
+                y.store(out + c, 1.0f / l);
+            }
+        });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -441,6 +559,7 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
     Ctx X = make_hd64_ctx(a, tid);
     X.scr = img + sp.chunk * 3 * kImg + wave * kImg;
     const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows, VH = a.Np * a.Hkv;
+    bool bad = false;
 
     for (int vh = blockIdx.x % sp.vh_slots; vh < VH; vh += sp.vh_slots) {
         set_vhead(a, X, vh);
@@ -512,12 +631,34 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
                     __builtin_amdgcn_wave_barrier();
                 }
             }
-            if (has)
+            if (has) {
                 store_transposed(reinterpret_cast<unsigned short *>(g.dq) + (long long)x.b * a.q_sb + (long long)x.i * a.q_ss +
                                      (long long)x.h * a.q_sh,
                                  X.h, x.exists, x.valid, a.scale, dq);
+                bad |= __builtin_amdgcn_ballot_w64(x.valid && has_nan(dq)) != 0;
+            }
         }
     }
+    if (bad)
+        for_stored_rows(sp, kBwdWaves, tid, [](const Args &a, const Ctx &X, const Rows &x) {
+            const BwdArgs &g = first_parameter<BwdArgs>();
+            const long long at = (long long)x.b * a.q_sb + (long long)x.i * a.q_ss + (long long)x.h * a.q_sh;
+            const long long oo = (long long)x.b * a.o_sb + (long long)x.i * a.o_ss + (long long)x.h * a.o_sh;
+            unsigned short *dq = reinterpret_cast<unsigned short *>(g.dq) + at;
+            const unsigned short *q = reinterpret_cast<const unsigned short *>(a.q) + at, *dout = reinterpret_cast<const unsigned short *>(g.dout) + oo;
+            const float lse2 = a.lse[((long long)x.b * a.Hq + x.h) * a.S + x.i] * kLog2e;
+            const float drow = lane_dot(dout, reinterpret_cast<const unsigned short *>(a.out) + oo);
+#pragma unroll 1
+            for (int c = 8 * X.h; c < kW; c += 16) {
+                if (!to_form_anew(dq + c))
+                    continue;
+                Columns y;
+                for_visible_keys(a, X, x, [&](const unsigned short *k, const unsigned short *v) {
+                    y.add(fast_exp2(__builtin_fmaf(lane_dot(q, k), X.c, -lse2)) * (lane_dot(dout, v) - drow), k + c);
+                });
+                y.store(dq + c, a.scale);
+            }
+        });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -619,6 +760,7 @@ void hd64_bwd_dkv_kernel(BwdArgs g, int nkt)
     // pair pr = w % 2 (elements 8pr .. 8pr + 7).
     const int dt = wave >> 1, pr = wave & 1;
     const long long at = koff + (long long)(key < a.S ? key : 0) * a.ks_ss;
+    unsigned long long nan[2]; // lanes with a NaN among their sums
 #pragma unroll
     for (int which = 0; which < 2; ++which) {
         __syncthreads();
@@ -636,6 +778,11 @@ void hd64_bwd_dkv_kernel(BwdArgs g, int nkt)
 #pragma unroll
             for (int i = 0; i < 2; ++i)
                 y[i] += *(lds_f32x4 *)(smem + ((w * kDT + dt) * 4 + 2 * pr + i) * 1024 + X.lane * 16);
+        bool bad = false;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            bad |= y[0][t] != y[0][t] || y[1][t] != y[1][t];
+        nan[which] = __builtin_amdgcn_ballot_w64(key < len && bad);
         const float f = which == 0 ? a.scale : 1.f;
         unsigned w[4];
 #pragma unroll
@@ -646,6 +793,26 @@ void hd64_bwd_dkv_kernel(BwdArgs g, int nkt)
         if (key < a.S)
             *reinterpret_cast<uintx4 *>(reinterpret_cast<unsigned short *>(which == 0 ? g.dk : g.dv) + at + 32 * dt + 16 * pr + 8 * X.h) =
                 uintx4{u[0], v[0], u[1], v[1]};
+    }
+    // (see to_form_anew)
+#pragma unroll 1
+    for (int which = 0; which < 2; ++which) {
+        if (!(((unsigned)(nan[which] | (nan[which] >> 32)) >> X.c32) & 1u))
+            continue;
+        const unsigned short *krow = reinterpret_cast<const unsigned short *>(a.ks) + at, *vrow = reinterpret_cast<const unsigned short *>(a.vs) + at;
+        const int c = 32 * dt + 16 * pr + 8 * X.h;
+        Columns y;
+#pragma unroll 1
+        for (int rl = key * a.G; rl < len * a.G; ++rl) { // the rows that see the key
+            const int i = (int)fdiv(rl, a.div_g), h = k * a.G + rl - i * a.G;
+            const long long oo = (long long)b * a.o_sb + (long long)i * a.o_ss + (long long)h * a.o_sh;
+            const unsigned short *q = reinterpret_cast<const unsigned short *>(a.q) + (long long)b * a.q_sb + (long long)i * a.q_ss + (long long)h * a.q_sh;
+            const unsigned short *dout = reinterpret_cast<const unsigned short *>(g.dout) + oo, *out = reinterpret_cast<const unsigned short *>(a.out) + oo;
+            const float lse2 = a.lse[((long long)b * a.Hq + h) * a.S + i] * kLog2e;
+            const float p = fast_exp2(__builtin_fmaf(lane_dot(q, krow), X.c, -lse2));
+            y.add(which == 0 ? p * (lane_dot(dout, vrow) - lane_dot(dout, out)) : p, (which == 0 ? q : dout) + c);
+        }
+        y.store(reinterpret_cast<unsigned short *>(which == 0 ? g.dk : g.dv) + at + c, which == 0 ? a.scale : 1.f);
     }
 }
 static_assert(kDkvW == 2 * kDT && kDkvW * kDT * 4 * 1024 <= kDkvLds, "LDS of the final sum");

@@ -48,6 +48,16 @@ struct Args {
     long long o_sb, o_ss, o_sh;
 };
 
+// The kernel's first parameter once more, for a path that is hardly ever taken: what only such a path needs of it is
+// then loaded there and holds no registers before.
+template <typename T> __device__ inline const T &first_parameter()
+{
+    typedef const __attribute__((address_space(4))) T *param_ptr;
+    param_ptr p = (param_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p)); // (loads through it are loads of their own to the compiler)
+    return *(const T *)p;
+}
+
 // Whether one candidate's part of q, of out and of the suffix K/V each spans less than 2^31
 // bytes (16-bit elements), so that kernels may address rows within a candidate by 32-bit offsets.
 inline bool block_offsets_fit(const Args &a)

@@ -58,6 +58,9 @@ def agree(got, ref, tol, what):
     ("f32", 64, 19, 5, 3, 4, 4, 12),     # three candidates and more in a block of 16 rows
     ("f32", 128, 16, 18, 9, 4, 2, 4),    # blocks that straddle two candidates, two key tiles each
     ("f32", 64, 0, 3, 1, 14, 2, 9),
+    ("bf16", 64, 40, 7, 3, 4, 4, 12),    # five candidates in a block of 32 rows, their keys in one step; ragged prefix
+    ("bf16", 64, 32, 37, 33, 4, 2, 4),   # blocks that straddle two candidates, two own steps each
+    ("bf16", 64, 0, 3, 1, 14, 2, 9),
 ])
 def test_hidden_values_stay_hidden(pk, impl, dtype, D, P, S, lo, Hq, Hkv, B):
     import torch
