@@ -3,11 +3,11 @@
 //
 // Layouts and formulation are those of pskv_mfma.hpp (32-row blocks of the stacked rows
 // r = (b*S + i)*G + g, 32-key tiles, a lane owns a query column), with two differences.
-//   - Weights, and score gradients, enter the second products as TWO bf16 numbers, hi + lo: hi is the
-//     weight rounded to bf16 and lo what that left, rounded in turn (16 significant bits together).
-//     The vector kernels that serve the other head dimensions keep weights in fp32; half the
-//     columns leave the matrix cores with time to spare, so a second product with lo costs less than
-//     the precision is worth.
+//   - Weights, and score gradients, enter the second products as THREE bf16 numbers that add up to the
+//     fp32 number to the last bit (8 of its 24 significant bits each, cut off and not rounded), as the vector
+//     kernels that serve the other head dimensions have them in fp32.  Half the columns leave the matrix
+//     cores with time to spare: two further products cost less than the precision is worth (7 to 16 % of a call
+//     over two parts, which hold 16 bits).
 //   - The own suffix keys of all candidates a block of rows touches form ONE list, cut into 32-key
 //     steps: a row sees a contiguous run of it, and a block that straddles short candidates takes one
 //     or two steps where one step (or more) per candidate would be mostly empty.
@@ -16,7 +16,7 @@
 // persistent workgroup of 8 wavefronts, two per compute unit, copies as much of its head's prefix
 // into LDS as fits - transposed there once, so that every operand read is a 16-byte one - and its
 // wavefronts walk over the row blocks independently.  Longer prefixes go through the same LDS in
-// chunks.  256 candidates of 5 to 33 rows, 177 prefix rows, 14/2 heads: 300 us in the vector kernel, 20 us here.
+// chunks.  256 candidates of 5 to 33 rows, 177 prefix rows, 14/2 heads: 300 us in the vector kernel, 22 us here.
 #include "pskv_mfma.hpp"
 
 namespace pskv {
@@ -41,23 +41,30 @@ __device__ inline floatx16 zero16()
 __device__ inline floatx16 mma(bf16x8 a, bf16x8 b, floatx16 c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
 __device__ inline bf16x8 lds_frag(lds_u8 *p) { return as_bf16x8(*(lds_u128 *)p); }
 
-// hi and lo fragments (contraction steps 0 and 1) of 16 values.
+// Fragments (contraction steps 0 and 1) of 16 values in three parts: p[0] + p[1] + p[2] is the value, exactly.
+// (An infinity leaves NaN in the later parts: see to_form_anew.)
+constexpr int kParts = 3;
 struct Split {
-    bf16x8 hi[2], lo[2];
+    bf16x8 p[kParts][2];
 };
-__device__ inline Split split16(const float (&p)[16])
+__device__ inline Split split16(float (&v)[16])
 {
-    unsigned h[8], l[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        h[i] = pack_bf16(p[2 * i], p[2 * i + 1]);
-        l[i] = pack_bf16(p[2 * i] - __uint_as_float(h[i] << 16), p[2 * i + 1] - __uint_as_float(h[i] & 0xffff0000u));
-    }
     Split s;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        s.hi[j] = as_bf16x8(uintx4{h[4 * j], h[4 * j + 1], h[4 * j + 2], h[4 * j + 3]});
-        s.lo[j] = as_bf16x8(uintx4{l[4 * j], l[4 * j + 1], l[4 * j + 2], l[4 * j + 3]});
+    for (int part = 0; part < kParts; ++part) {
+        unsigned w[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            // the upper halves of two numbers
+            w[i] = __builtin_amdgcn_perm(__float_as_uint(v[2 * i + 1]), __float_as_uint(v[2 * i]), 0x07060302);
+            if (part + 1 < kParts) {
+                v[2 * i] -= __uint_as_float(w[i] << 16);
+                v[2 * i + 1] -= __uint_as_float(w[i] & 0xffff0000u);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            s.p[part][j] = as_bf16x8(uintx4{w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]});
     }
     return s;
 }
@@ -401,8 +408,9 @@ template <typename VF> __device__ inline void weigh_tile(const floatx16 &s, floa
 #pragma unroll
         for (int dt = 0; dt < kDT; ++dt) {
             const bf16x8 v = vf(dt, j);
-            st.o[dt] = mma(v, w.hi[j], st.o[dt]);
-            st.o[dt] = mma(v, w.lo[j], st.o[dt]);
+#pragma unroll
+            for (int part = kParts - 1; part >= 0; --part) // (the small ones first)
+                st.o[dt] = mma(v, w.p[part][j], st.o[dt]);
         }
 }
 
@@ -544,8 +552,9 @@ __device__ inline void dq_tile(const floatx16 &s, const floatx16 &dp, float c, f
 #pragma unroll
         for (int dt = 0; dt < kDT; ++dt) {
             const bf16x8 k = kf(dt, j);
-            dq[dt] = mma(k, w.hi[j], dq[dt]);
-            dq[dt] = mma(k, w.lo[j], dq[dt]);
+#pragma unroll
+            for (int part = kParts - 1; part >= 0; --part)
+                dq[dt] = mma(k, w.p[part][j], dq[dt]);
         }
 }
 
@@ -747,10 +756,11 @@ void hd64_bwd_dkv_kernel(BwdArgs g, int nkt)
 #pragma unroll
                 for (int dt = 0; dt < kDT; ++dt) {
                     const bf16x8 x = frag_tr(doi, dt, j, X.lane), y = frag_tr(qi, dt, j, X.lane);
-                    dv[dt] = mma(x, wp.hi[j], dv[dt]);
-                    dk[dt] = mma(y, ws.hi[j], dk[dt]);
-                    dv[dt] = mma(x, wp.lo[j], dv[dt]);
-                    dk[dt] = mma(y, ws.lo[j], dk[dt]);
+#pragma unroll
+                    for (int part = kParts - 1; part >= 0; --part) {
+                        dv[dt] = mma(x, wp.p[part][j], dv[dt]);
+                        dk[dt] = mma(y, ws.p[part][j], dk[dt]);
+                    }
                 }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();

@@ -86,3 +86,66 @@ def test_hd64_multi_instruction(pk):
                                  scale=inp.scale)
     torch.cuda.synchronize()
     pu.compare(pu.out_to_f64(out), pu.oracle_out_multi(inp), inp.suf_len, "bf16", w.name)
+
+
+@pytest.mark.parametrize("impl", ["simple", "auto"])
+def test_hd64_weights_in_full(pk, impl):
+    """Weights and score gradients enter the sums over keys and rows with the 24 bits that they are computed to.
+    Every sum here is over three terms whose weights are known beforehand and whose other factors are
+    chosen, one after the other, to cancel what is there so far: the result is some 2^-17 of the terms, which an
+    error of 2^-17 in a weight (16 bits) changes entirely.  The bound: 2^-20 of the terms' magnitudes - an
+    exponential to one unit (2^-23), its argument from a 32-term fp32 sum (2^-22 together with the scale), three
+    fp32 additions (2^-24 each) - and the result's own rounding to bf16."""
+    import torch
+    rng = np.random.default_rng(1890)
+    n, D, half, G = 32, 64, 32, 4
+    bf16 = lambda x: gen.bf16_bits_to_f32(gen.f32_to_bf16_bits(np.asarray(x, np.float32))).astype(np.float64)
+
+    def cancelling(w):
+        """[n,3,D] bf16 values whose sums weighted by w [n,3] nearly vanish, column by column."""
+        x = np.zeros((n, 3, D))
+        x[:, 0] = bf16(256 * rng.uniform(1, 2, (n, D)))
+        for t in (1, 2):
+            x[:, t] = bf16(-np.einsum("nt,ntd->nd", w, x) / w[:, t, None])
+        return x
+
+    # one candidate of one row and a prefix of two for each of n instructions, four query heads; scores are made by the
+    # first half of the columns, the other half of q and of K is zero or free
+    q, K = bf16(rng.standard_normal((n, G, D))), bf16(rng.standard_normal((n, 3, D)))
+    q[:, :, half:] = K[:, :, half:] = 0
+    scale = float(np.float32(D ** -0.5))
+    s = np.einsum("ngd,ntd->ngt", q, K) * scale
+    lse = np.log(np.exp(s).sum(-1))
+    p = np.exp(s - lse[..., None])                                          # [n,G,3]
+
+    def dev(x):
+        return torch.from_numpy(gen.f32_to_bf16_bits(x.astype(np.float32))).view(torch.bfloat16).to("cuda:0")
+
+    def call(q, K, V, dout=None):
+        args = (dev(q[:, None]), dev(K[:, 2:, None]), dev(V[:, 2:, None]), dev(K[:, :2, None]), dev(V[:, :2, None]))
+        if dout is None:
+            return pk.pskv_attn_fwd_multi(*args, impl=impl, scale=scale)
+        # (a result of zeros: <dout,out> is zero, and a score gradient the weight times <dout,V>)
+        return pk.pskv_attn_bwd_multi(*args, None, None, torch.zeros_like(args[0]),
+                                      torch.from_numpy(lse.astype(np.float32)[..., None]).to("cuda:0"), dev(dout[:, None]), impl=impl,
+                                      scale=scale)
+
+    def check(got, ref, mag, what):
+        err, bound = np.abs(pu.out_to_f64(got).reshape(ref.shape) - ref), 2.0 ** -20 * mag + 2.0 ** -8 * np.abs(ref)
+        print(f"[case] weights in full {impl} {what}: {(err / bound).max():.3f} of the bound", flush=True)
+        assert (err <= bound).all(), f"{what}: {(err / bound).max():.2f} times the bound"
+
+    V = cancelling(p[:, 0])
+    check(call(q, K, V), np.einsum("ngt,ntd->ngd", p, V), np.einsum("ngt,ntd->ngd", p, np.abs(V)), "out")
+    # dv of the own key: over three of the query heads
+    dout = np.concatenate([cancelling(p[:, :3, 2]), np.zeros((n, 1, D))], axis=1)
+    check(call(q, K, V, dout)[2], np.einsum("ng,ngd->nd", p[..., 2], dout), np.einsum("ng,ngd->nd", p[..., 2], np.abs(dout)), "dv")
+    # dq and dk: score gradients p <dout,V> of small whole numbers, exact in fp32
+    V, dout = rng.integers(1, 4, (n, 3, D)).astype(np.float64), rng.integers(1, 4, (n, G, D)).astype(np.float64)
+    ds = p * np.einsum("ngd,ntd->ngt", dout, V)
+    K2 = K.copy()
+    K2[:, :, half:] = cancelling(ds[:, 0])[:, :, half:]
+    check(call(q, K2, V, dout)[0], scale * np.einsum("ngt,ntd->ngd", ds, K2), scale * np.einsum("ngt,ntd->ngd", ds, np.abs(K2)), "dq")
+    q2 = q.copy()
+    q2[:, :3, half:] = cancelling(ds[:, :3, 2])[:, :, half:]
+    check(call(q2, K, V, dout)[1], scale * np.einsum("ng,ngd->nd", ds[..., 2], q2), scale * np.einsum("ng,ngd->nd", ds[..., 2], np.abs(q2)), "dk")
