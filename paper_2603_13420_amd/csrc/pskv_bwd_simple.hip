@@ -231,7 +231,7 @@ size_t bwd_dkv_lds_bytes(const Args &a, int dtype)
 hipError_t launch_bwd_dq_simple(const BwdArgs &g, int dtype, hipStream_t stream)
 {
     const Args &a = g.f;
-    if (f32_mfma_supported(a, dtype))
+    if (f32_bwd_supported(a, dtype))
         return launch_f32_bwd(g, stream); // dk and dv as well
     if (hd64_supported(a, dtype))
         return launch_hd64_bwd_dq(g, stream);
@@ -246,9 +246,9 @@ hipError_t launch_bwd_dq_simple(const BwdArgs &g, int dtype, hipStream_t stream)
 hipError_t launch_bwd_dkv_simple(const BwdArgs &g, int dtype, hipStream_t stream)
 {
     const Args &a = g.f;
-    if (f32_mfma_supported(a, dtype))
+    if (f32_bwd_supported(a, dtype))
         return hipSuccess; // launched with dq
-    if (hd64_supported(a, dtype))
+    if (hd64_dkv_supported(a, dtype))
         return launch_hd64_bwd_dkv(g, stream);
     const long long rows = (long long)a.B * a.S * a.Hkv;
     const size_t lds = bwd_dkv_lds_bytes(a, dtype);

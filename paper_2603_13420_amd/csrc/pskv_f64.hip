@@ -570,33 +570,41 @@ void f32_bwd_kernel(BwdArgs g, int nblk, int nkt, int nunits)
 static_assert(2 * kWideBytes<128> <= kGatherBytes && kGatherBytes + kWaves * 256 <= 64 * 1024, "LDS layout");
 constexpr size_t kFwdLdsBytes = kGatherBytes + kWaves * 32 * sizeof(double), kBwdLdsBytes = kGatherBytes;
 
+constexpr int kThreads = kWaves * 64;
+
+// Blocks of rows, and dk/dv units, of all (instruction, KV head) pairs.
 long long blocks_per_head(const Args &a) { return ((long long)a.C * a.S * a.G + kTR - 1) / kTR; }
+long long all_blocks(const Args &a) { return blocks_per_head(a) * a.Np * a.Hkv; }
+long long all_units(const Args &a) { return (long long)a.B * a.Hkv * ((a.S + kTR - 1) / kTR); }
 
 } // namespace
 
-// (B*S*Hq fits 31 bits - see resolve() - and with it the number of blocks and units.)
-bool f32_mfma_supported(const Args &a, int dtype) { return dtype == 0 && !a.plain && (a.D == 64 || a.D == 128); }
+bool f32_fwd_supported(const Args &a, int dtype)
+{
+    return dtype == 0 && !a.plain && (a.D == 64 || a.D == 128) && launch_fits(all_blocks(a), kThreads);
+}
+bool f32_bwd_supported(const Args &a, int dtype)
+{
+    return dtype == 0 && !a.plain && (a.D == 64 || a.D == 128) && launch_fits(all_units(a) + all_blocks(a), kThreads);
+}
 
 hipError_t launch_f32_fwd(const Args &a, hipStream_t stream)
 {
-    const long long nblk = blocks_per_head(a);
-    const dim3 grid((unsigned)(nblk * a.Np * a.Hkv));
+    const dim3 grid((unsigned)all_blocks(a));
+    const int nblk = (int)blocks_per_head(a);
     if (a.D == 64)
-        return launch_kernel(f32_fwd_kernel<64>, grid, dim3(256), kFwdLdsBytes, stream, a, (int)nblk);
-    return launch_kernel(f32_fwd_kernel<128>, grid, dim3(256), kFwdLdsBytes, stream, a, (int)nblk);
+        return launch_kernel(f32_fwd_kernel<64>, grid, dim3(kThreads), kFwdLdsBytes, stream, a, nblk);
+    return launch_kernel(f32_fwd_kernel<128>, grid, dim3(kThreads), kFwdLdsBytes, stream, a, nblk);
 }
 
 hipError_t launch_f32_bwd(const BwdArgs &g, hipStream_t stream)
 {
     const Args &a = g.f;
-    const long long nblk = blocks_per_head(a);
-    const int nkt = (a.S + kTR - 1) / kTR;
-    const long long nunits = (long long)a.B * a.Hkv * nkt, all = nunits + nblk * a.Np * a.Hkv;
-    if (all > 0x7fffffffLL)
-        return hipErrorInvalidValue;
+    const int nblk = (int)blocks_per_head(a), nkt = (a.S + kTR - 1) / kTR, nunits = (int)all_units(a);
+    const dim3 grid((unsigned)(all_units(a) + all_blocks(a)));
     if (a.D == 64)
-        return launch_kernel(f32_bwd_kernel<64>, dim3((unsigned)all), dim3(256), kBwdLdsBytes, stream, g, (int)nblk, nkt, (int)nunits);
-    return launch_kernel(f32_bwd_kernel<128>, dim3((unsigned)all), dim3(256), kBwdLdsBytes, stream, g, (int)nblk, nkt, (int)nunits);
+        return launch_kernel(f32_bwd_kernel<64>, grid, dim3(kThreads), kBwdLdsBytes, stream, g, nblk, nkt, nunits);
+    return launch_kernel(f32_bwd_kernel<128>, grid, dim3(kThreads), kBwdLdsBytes, stream, g, nblk, nkt, nunits);
 }
 
 } // namespace pskv

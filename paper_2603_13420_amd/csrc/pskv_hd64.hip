@@ -871,8 +871,12 @@ Shape make_shape(const Args &a, int num_cu, int waves, int images, int most_per_
 
 bool hd64_supported(const Args &a, int dtype)
 {
-    return dtype == 1 && !a.plain && a.D == kW && (long long)a.C * a.S * a.G <= 0x7fffffffLL - kBlockRows &&
-           (long long)a.B * a.Hkv * ((a.S + kTileKeys - 1) / kTileKeys) <= 0x7fffffffLL;
+    return dtype == 1 && !a.plain && a.D == kW && (long long)a.C * a.S * a.G <= 0x7fffffffLL - kBlockRows;
+}
+
+bool hd64_dkv_supported(const Args &a, int dtype)
+{
+    return hd64_supported(a, dtype) && launch_fits((long long)a.B * a.Hkv * ((a.S + kTileKeys - 1) / kTileKeys), kDkvW * 64);
 }
 
 hipError_t launch_hd64_fwd(const Args &a, hipStream_t stream)

@@ -99,16 +99,21 @@ hipError_t launch_simple(const Args &a, int dtype, hipStream_t stream);
 // Dynamic LDS that the vector kernel needs for this problem, in bytes.
 size_t simple_lds_bytes(const Args &a, int dtype);
 
+// Whether a launch fits HIP's limit of fewer than 2^32 work-items per dimension.
+inline bool launch_fits(long long groups, int threads) { return groups * threads < (1LL << 32); }
+
 // Double-precision matrix-core kernels for f32 tensors (D == 64 or 128, unless the vector kernels are
-// asked for): they serve such problems behind launch_simple and launch_bwd_*_simple and need no
-// dynamic LDS that grows with the problem.
-bool f32_mfma_supported(const Args &a, int dtype);
+// asked for or a launch would not fit): they serve such problems behind launch_simple and
+// launch_bwd_*_simple and need no dynamic LDS that grows with the problem.
+bool f32_fwd_supported(const Args &a, int dtype);
+bool f32_bwd_supported(const Args &a, int dtype);
 hipError_t launch_f32_fwd(const Args &a, hipStream_t stream);
 hipError_t launch_f32_bwd(const BwdArgs &g, hipStream_t stream); // all three gradients: launch_bwd_dkv_simple adds nothing
 
 // Matrix-core kernels for bf16 tensors with D == 64 (unless the vector kernels are asked for), reached in
 // the same way.
 bool hd64_supported(const Args &a, int dtype);
+bool hd64_dkv_supported(const Args &a, int dtype); // the same for launch_hd64_bwd_dkv
 hipError_t launch_hd64_fwd(const Args &a, hipStream_t stream);
 hipError_t launch_hd64_bwd_dq(const BwdArgs &g, hipStream_t stream);
 hipError_t launch_hd64_bwd_dkv(const BwdArgs &g, hipStream_t stream);

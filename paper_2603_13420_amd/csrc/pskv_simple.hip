@@ -143,7 +143,7 @@ size_t simple_lds_bytes(const Args &a, int dtype)
 
 hipError_t launch_simple(const Args &a, int dtype, hipStream_t stream)
 {
-    if (f32_mfma_supported(a, dtype))
+    if (f32_fwd_supported(a, dtype))
         return launch_f32_fwd(a, stream);
     if (hd64_supported(a, dtype))
         return launch_hd64_fwd(a, stream);
