@@ -1220,39 +1220,41 @@ hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream)
     const long long rows = (long long)a.C * a.S * a.G, rows_c = (long long)a.S * a.G;
     const long long nb = (rows_c + kBlockRows - 1) / kBlockRows; // blocks per candidate
     const bool fit = block_offsets_fit(a);
+    // Short prefixes may stay resident in LDS (the split of the workgroups over the (instruction, KV
+    // head) pairs is that of the resident forward kernel).  A candidate's last block may be partly empty, its only
+    // one mostly: down to three rows in eight (12 rows per candidate, P 128: 158 us for the whole backward pass,
+    // 162 us with the streaming kernel, whose blocks are full but span candidates; 8 rows: 146 and 132 us;
+    // 20 rows: 217 and 242 us).
+    const bool resident = a.P <= kDqMaxTiles * kTileKeys && rows_c * 8 >= nb * kBlockRows * 3 && fit && a.C * nb <= 0x7fffffffLL / 2;
+    const ResidentSplit split = resident_split(a, a.C * nb, kNW, num_cu);
     // Passes of four blocks of one candidate, where they come out full: at less than four blocks in five the
     // wavefronts without one cost more than sharing the tiles saves (five blocks in two passes, 40 positions x
     // 4 heads, P 128: 156 us against 130 us of the resident kernel and 141 us of the streaming one; four in one,
     // 27 x 4: 73 us, 91 us streamed; seven in two, 30 x 7: 153 us, 187 us streamed; 576 rows at P 128: 600 us for
-    // the whole backward pass, 675 us without it).
+    // the whole backward pass, 675 us without it).  They fetch the prefix once per pass, the resident kernel once per
+    // launch: it is the better one where its wavefronts take three blocks or more and the passes, in rounds
+    // of the chip against blocks per wavefront, make up more than 9/11 of the blocks' keys by their prefixes.  us for
+    // the whole backward pass, passes and resident: 32 positions x 4 heads, 8 KV heads, P 256: 1024 candidates: 496,
+    // 431; 512: 250, 232; 64: 31, 33; P 128, 512: 209, 215; P 64, 512: 192, 208; 30 x 7, 4 KV heads, 512
+    // candidates, P 256: 205, 173; P 64: 145, 141; 144 x 4, 8 KV heads, 128 candidates, P 256: 355, 325; P 64: 272, 286.
     {
         UnitShape us;
         us.npc = (int)((nb + kUnitWaves - 1) / kUnitWaves);
         const long long npasses = ((long long)a.B * a.Hkv + 7) / 8 * 8 * us.npc;
-        if (fit && nb * 5 >= (long long)us.npc * kUnitWaves * 4 && npasses <= 0x7fffffffLL - 2 * num_cu) {
+        const long long rounds = (npasses + 2 * num_cu - 1) / (2 * num_cu);
+        const bool stay = resident && split.each >= 3 && rounds * a.P * 11 > split.each * (a.P + (a.S + kTileKeys) / 2) * 9;
+        if (!stay && fit && nb * 5 >= (long long)us.npc * kUnitWaves * 4 && npasses <= 0x7fffffffLL - 2 * num_cu) {
             us.div_npc = make_fastdiv((unsigned)us.npc);
             us.div_hkv = make_fastdiv((unsigned)a.Hkv);
             const unsigned grid = (unsigned)(npasses < 2 * num_cu ? npasses : 2 * num_cu);
             return launch_kernel(bwd_dq_unit_kernel, dim3(grid), dim3(kUnitWaves * 64), kUnitLdsBytes, stream, g, us, (int)npasses);
         }
     }
-    // Short prefixes stay resident in LDS (the split of the workgroups over the (instruction, KV
-    // head) pairs is that of the resident forward kernel).  A candidate's last block may be partly empty, its only
-    // one mostly: down to three rows in eight (12 rows per candidate, P 128: 158 us for the whole backward pass,
-    // 162 us with the streaming kernel, whose blocks are full but span candidates; 8 rows: 146 and 132 us;
-    // 20 rows: 217 and 242 us).
-    if (a.P <= kDqMaxTiles * kTileKeys && rows_c * 8 >= nb * kBlockRows * 3 && fit && a.C * nb <= 0x7fffffffLL / 2) {
+    if (resident) {
         const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
-        const long long nblocks = a.C * nb;
-        const long long VH = (long long)a.Np * a.Hkv;
-        const long long vh_slots = VH < num_cu ? VH : num_cu;
-        long long per_vh = num_cu / vh_slots;
-        const long long useful = (nblocks + kNW - 1) / kNW;
-        if (per_vh > useful)
-            per_vh = useful;
         const size_t lds = (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes;
-        return launch_kernel(bwd_dq_resident_kernel, dim3((unsigned)(per_vh * vh_slots)), dim3(kNW * 64), lds, stream, g, (int)nb,
-                             make_fastdiv((unsigned)nb), (int)per_vh, (int)vh_slots, max_tiles);
+        return launch_kernel(bwd_dq_resident_kernel, dim3((unsigned)(split.per_vh * split.vh_slots)), dim3(kNW * 64), lds, stream, g, (int)nb,
+                             make_fastdiv((unsigned)nb), (int)split.per_vh, (int)split.vh_slots, max_tiles);
     }
     const long long npasses = ((rows + kBwdPassRows - 1) / kBwdPassRows) * a.Np * a.Hkv;
     // two workgroups fit a compute unit's LDS; registers allow one, so one per compute unit

@@ -58,6 +58,24 @@ template <typename T> __device__ inline const T &first_parameter()
     return *(const T *)p;
 }
 
+// The row blocks of the Np*Hkv virtual heads, `blocks` of each, split over num_cu workgroups of `waves` wavefronts that keep
+// one virtual head's prefix at a time.  With fewer virtual heads than workgroups these are split evenly over
+// them (never more per virtual head than there are groups of `waves` row blocks); with more, every workgroup takes
+// several in turn.
+struct ResidentSplit {
+    long long vh_slots, per_vh; // virtual heads at a time, workgroups for each
+    long long each;             // row blocks per wavefront, all virtual heads together
+};
+inline ResidentSplit resident_split(const Args &a, long long blocks, int waves, int num_cu)
+{
+    ResidentSplit s;
+    const long long VH = (long long)a.Np * a.Hkv, useful = (blocks + waves - 1) / waves;
+    s.vh_slots = VH < num_cu ? VH : num_cu;
+    s.per_vh = num_cu / s.vh_slots < useful ? num_cu / s.vh_slots : useful;
+    s.each = (blocks + s.per_vh * waves - 1) / (s.per_vh * waves) * ((VH + s.vh_slots - 1) / s.vh_slots);
+    return s;
+}
+
 // Whether one candidate's part of q, of out and of the suffix K/V each spans less than 2^31
 // bytes (16-bit elements), so that kernels may address rows within a candidate by 32-bit offsets.
 inline bool block_offsets_fit(const Args &a)

@@ -1,0 +1,24 @@
+"""Which kernel takes a problem, on either side of the lines that the launchers draw, at problems timed through
+both (the times stand beside the rules)."""
+import pytest
+
+from paper_2603_13420_amd import binding as pk
+import launch_notes as notes
+
+
+def check(tmp_path, call, problems):
+    cases = [notes.case(call, "bf16", 128, *p[:-1]) for p in problems]
+    for (*_, kernel), c, (rc, got) in zip(problems, cases, notes.launches(tmp_path, cases)):
+        assert rc == pk.PSKV_OK and kernel in got[0][2], (c, kernel, got)
+
+
+def test_dq_kernels(tmp_path):
+    # B, P, S, Hq, Hkv, Np, kernel: what is fetched once per pass against what is fetched once per launch
+    check(tmp_path, "bwd", [
+        (1024, 256, 32, 32, 8, 1, "bwd_dq_resident"), (512, 256, 32, 32, 8, 1, "bwd_dq_resident"),
+        (64, 256, 32, 32, 8, 1, "bwd_dq_unit"), (512, 128, 32, 32, 8, 1, "bwd_dq_unit"), (512, 64, 32, 32, 8, 1, "bwd_dq_unit"),
+        (512, 256, 30, 28, 4, 1, "bwd_dq_resident"), (128, 256, 144, 32, 8, 1, "bwd_dq_resident"),
+        (128, 64, 144, 32, 8, 1, "bwd_dq_unit"), (512, 257, 32, 32, 8, 1, "bwd_dq_unit"),
+        (512, 256, 32, 32, 8, 8, "bwd_dq_resident"), (256, 128, 20, 32, 8, 1, "bwd_dq_resident"),
+        (512, 128, 8, 32, 32, 1, "bwd_dq_mfma"), (512, 600, 20, 32, 8, 1, "bwd_dq_mfma"),
+    ])
