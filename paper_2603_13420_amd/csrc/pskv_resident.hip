@@ -164,17 +164,6 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles, 
         const int r = block_row(blk) + X.c32;
         return decode_candidate_row(a, X.cand0 + __builtin_amdgcn_readfirstlane(block_cand(blk)), r < rows_c ? r : rows_c - 1, X.head);
     };
-    // The block on the general path (not WHOLE: its candidate as a problem of one candidate).
-    auto general = [&](int T, int blk) __attribute__((always_inline)) {
-        if constexpr (WHOLE) {
-            general_block(a, X, T, blk);
-        } else {
-            Ctx Y = X;
-            Y.cand0 = X.cand0 + block_cand(blk);
-            Y.Mtot = rows_c;
-            general_block(a, Y, T, blk - block_cand(blk) * nb);
-        }
-    };
     // Advance to the next block of this wavefront that has a valid row; blocks of pure padding
     // on the way are stored as zeros here and now.
     // Every wavefront takes one contiguous range of blocks, so that a candidate's suffix K/V, which
@@ -206,19 +195,25 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles, 
     // first block of this wavefront: request its row decode and Q before the prefix copy
     const int first_blk = blk_lo;
     bool any_bad = false;
-    int blk = skip_padding(first_blk);
-    BlockRows nxt = decode(blk < blk_hi ? blk : nblocks - 1);
+    const bool is_short = !WHOLE && T < 3; // this instruction's prefix is too short for the pipeline: see below
+    int blk = is_short ? blk_hi : skip_padding(first_blk);
+    BlockRows nxt;
     uintx4 q[8]; // this block's Q fragments until their last use, then the next block's
-    load_q_block(a, X, nxt, q);
+    if (!is_short) {
+        nxt = decode(blk < blk_hi ? blk : nblocks - 1);
+        load_q_block(a, X, nxt, q);
+    }
 
     __syncthreads(); // every wavefront is done with the images of the virtual head before
     stage_prefix(a, X, T, smem, smem + max_tiles * kTileBytes, tid);
     __syncthreads();
 
-    if (T < 3) { // this instruction's prefix is too short for the pipeline: general path
-        for (int b2 = first_blk; b2 < blk_hi; ++b2)
-            general(T, b2);
-        continue;
+    if constexpr (WHOLE) {
+        if (T < 3) { // this instruction's prefix is too short for the pipeline: general path
+            for (int b2 = first_blk; b2 < blk_hi; ++b2)
+                general_block(a, X, T, b2);
+            continue;
+        }
     }
 
     while (blk < blk_hi) {
@@ -306,10 +301,26 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles, 
     }
 
     // Rare: some row met scores far above its first tile's maximum.  Whatever this wavefront
-    // stored is replaced by the general path's result.
-    if (any_bad)
-        for (int b2 = first_blk; b2 < blk_hi; ++b2)
-            general(T, b2);
+    // stored is replaced by the general path's result, its blocks' candidates taken as problems of one candidate.
+    // is_short: the general path gains nothing by that and takes the stacked rows' blocks (multi-instruction, 32/8
+    // heads, P 96 with prefixes of 60 rows: 400 candidates of 29 positions: 47 us in the general kernel, 57 with own
+    // blocks, 48 us so; 24 of 27, 32/32: 10.7, 12.0, 11.5; 23 of 31: 8.4, 11.1, 8.5).
+    if constexpr (WHOLE) {
+        if (any_bad)
+            for (int b2 = first_blk; b2 < blk_hi; ++b2)
+                general_block(a, X, T, b2);
+    } else if (any_bad || is_short) {
+        const int nstacked = (X.Mtot + kBlockRows - 1) / kBlockRows;
+        const int share = (int)((unsigned)(nstacked + per_vh - 1) / (unsigned)per_vh); // of a workgroup
+        const int end = (slice + 1) * share, hi = !is_short ? blk_hi : end < nstacked ? end : nstacked;
+        for (int b2 = is_short ? slice * share + wslot : first_blk; b2 < hi; b2 += is_short ? kNW : 1) {
+            Ctx Y = X;
+            const int cand = is_short ? 0 : block_cand(b2);
+            Y.cand0 = X.cand0 + cand;
+            Y.Mtot = is_short ? X.Mtot : rows_c;
+            general_block(a, Y, T, b2 - cand * nb);
+        }
+    }
     } // virtual heads
 }
 

@@ -66,7 +66,7 @@ def test_own_blocks_scores_far_above_the_first_tile(pk, P, S, lo, Hq, Hkv):
     check(pk, inp)
 
 
-@pytest.mark.parametrize("P,S", [(100, 13), (300, 13), (300, 53), (100, 71)])
+@pytest.mark.parametrize("P,S", [(100, 13), (130, 29), (300, 13), (300, 53), (100, 71)])
 def test_own_blocks_multi_instruction(pk, P, S):
     """Prefixes of their own lengths, some too short for the pipeline, one empty."""
     import torch
