@@ -351,30 +351,35 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
     // Candidates whose rows fill no whole number of blocks: blocks of their own and the pipelined kernel where
     // those come out full to 13/16, the general kernel on full blocks that span candidates where not.  us, general and
     // pipelined: 2048 candidates x 120 rows (8 KV heads, P 100): 265, 227; 1024 x 133 of 160 (4 heads, P 256): 103, 93;
-    // 512 x 28 of 32 (32 heads, P 128): 94, 87; 1024 x 52 of 64 (8 heads, P 200): 84, 78; below: 1024 x 77 of 96: 64,
+    // 437 x 27 of 32 (32 heads, P 219): 104, 78 (512 x 28, P 128, whose bytes alone take 92: 98, 104); 1024 x 52 of 64 (8 heads, P 200): 84, 78; below: 1024 x 77 of 96: 64,
     // 66; 512 x 24 of 32: 84, 84; 512 x 20 of 32: 65, 67 (P 256: 77, 84); 512 x 12 of 32: 42, 53.
+    // Own blocks are more blocks.  A block's time is taken as its tiles and its own step, times 1.7 in the general
+    // kernel, which takes one more own step for every candidate that its blocks straddle; the pipelined one has a
+    // beginning of four tiles' time.  191 candidates x 84 rows (4 heads, P 75; a wavefront has 1 block or 2): 11.8, 14.3;
+    // 94 x 84 (8 heads, P 81; 1, 2): 11.8, 14.4; 89 x 84 (8 heads, P 171; 1, 2): 15.0, 17.8; 24 x 176 (4 heads, P 99;
+    // 1, 1): 11.8, 12.6; 148 x 203 (4 heads, P 141; 2, 3): 23.2, 24.0; and 10 x 27 (32 heads, P 151; 1, 1): 13.9,
+    // 12.1; 274 x 108 (8 heads, P 153; 4, 5): 44.8, 39.1; 213 x 203 (4 heads, P 142; 3, 3): 30.4, 28.2.
     const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows; // rows and own blocks of a candidate
+    const long long stacked = (rows + kBlockRows - 1) / kBlockRows, own = a.C * nb;
     const bool whole = rows_c % kBlockRows == 0;
-    const bool pipelined = a.S <= kTileKeys && max_tiles >= 3 && block_offsets_fit(a) && rows_c * 16 >= nb * kBlockRows * 13 &&
-                           a.C * nb <= 0x7fffffffLL / kBlockRows;
-    const long long nblocks = pipelined ? a.C * nb : (rows + kBlockRows - 1) / kBlockRows;
-    const long long VH = (long long)a.Np * a.Hkv;
-    // One workgroup per compute unit.  With fewer virtual heads than compute units the
-    // workgroups are split evenly over them (never more per virtual head than there are
-    // groups of 8 row blocks); with more, every workgroup takes several in turn.
-    const long long vh_slots = VH < num_cu ? VH : num_cu;
-    long long per_vh = num_cu / vh_slots;
-    const long long useful = (nblocks + kNW - 1) / kNW;
-    if (per_vh > useful)
-        per_vh = useful;
-    const unsigned grid = (unsigned)(per_vh * vh_slots);
+    bool pipelined = a.S <= kTileKeys && max_tiles >= 3 && block_offsets_fit(a) && rows_c * 16 >= nb * kBlockRows * 13 &&
+                     own <= 0x7fffffffLL / kBlockRows;
+    if (pipelined && !whole) {
+        const double straddled = rows_c < kBlockRows ? 1. : (double)kBlockRows / rows_c;
+        const long long each_own = resident_split(a, own, kNW, num_cu).each, each_stacked = resident_split(a, stacked, kNW, num_cu).each;
+        pipelined = each_own * (max_tiles + 1) + 4 <= 1.7 * each_stacked * (max_tiles + 1 + straddled);
+    }
+    // One workgroup per compute unit.
+    const ResidentSplit split = resident_split(a, pipelined ? own : stacked, kNW, num_cu);
+    const int per_vh = (int)split.per_vh, vh_slots = (int)split.vh_slots;
+    const unsigned grid = (unsigned)(split.per_vh * split.vh_slots);
     const size_t lds = (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes;
     if (pipelined)
         return launch_kernel(whole ? resident_pipelined_kernel<true> : resident_pipelined_kernel<false>, dim3(grid), dim3(kNW * 64),
-                             lds, stream, a, (int)per_vh, (int)vh_slots, max_tiles, (int)nb, make_fastdiv((unsigned)nb));
+                             lds, stream, a, per_vh, vh_slots, max_tiles, (int)nb, make_fastdiv((unsigned)nb));
     else
-        return launch_kernel(resident_general_kernel, dim3(grid), dim3(kNW * 64), lds, stream, a, (int)per_vh,
-                           (int)vh_slots, max_tiles);
+        return launch_kernel(resident_general_kernel, dim3(grid), dim3(kNW * 64), lds, stream, a, per_vh,
+                           vh_slots, max_tiles);
 }
 
 } // namespace pskv

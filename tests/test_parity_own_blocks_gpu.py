@@ -37,7 +37,8 @@ def check(pk, inp):
 
 @pytest.mark.parametrize("B,P,S,lo,hi,Hq,Hkv", [
     (5, 65, 31, 0, 31, 2, 2),       # one block, one row short; candidates may be empty; a ragged third tile
-    (600, 96, 26, 26, 26, 4, 4),    # 26 of 32 rows, the least that takes this path; more blocks than wavefronts of a head
+    (600, 96, 26, 26, 26, 4, 4),    # 26 of 32 rows, the least that can take this path; here a wavefront would have two blocks for one
+    (1200, 96, 26, 26, 26, 4, 4),   # ... and takes it: three blocks for two
     (600, 96, 25, 25, 25, 4, 4),    # one row less: the general kernel
     (3, 256, 19, 1, 19, 6, 2),      # 57 rows, the whole prefix
     (4, 129, 31, 0, 31, 7, 1),      # 217 rows, group 7: blocks of pure padding in between

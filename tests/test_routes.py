@@ -22,3 +22,14 @@ def test_dq_kernels(tmp_path):
         (512, 256, 32, 32, 8, 8, "bwd_dq_resident"), (256, 128, 20, 32, 8, 1, "bwd_dq_resident"),
         (512, 128, 8, 32, 32, 1, "bwd_dq_mfma"), (512, 600, 20, 32, 8, 1, "bwd_dq_mfma"),
     ])
+
+
+def test_forward_own_blocks(tmp_path):
+    # rows that fill no whole number of blocks: what their own blocks cost against what the pipelined kernels gain
+    check(tmp_path, "fwd", [
+        (191, 75, 12, 28, 4, 1, "resident_general"), (94, 81, 21, 32, 8, 1, "resident_general"), (89, 171, 21, 32, 8, 1, "resident_general"),
+        (24, 99, 22, 32, 4, 1, "resident_general"), (148, 141, 29, 28, 4, 1, "resident_general"),
+        (10, 151, 27, 32, 32, 1, "resident_pipelined"), (274, 153, 27, 32, 8, 1, "resident_pipelined"), (213, 142, 29, 28, 4, 1, "resident_pipelined"),
+        (512, 128, 28, 32, 32, 1, "resident_pipelined"), (512, 128, 20, 32, 32, 1, "resident_general"),
+        (24, 99, 24, 32, 4, 1, "resident_pipelined"),       # (whole blocks: always)
+    ])
