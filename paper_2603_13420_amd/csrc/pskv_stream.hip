@@ -806,14 +806,31 @@ hipError_t launch_mfma(const Args &a, hipStream_t stream)
     // general path for such shapes.
     const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
     const bool whole = (long long)a.S * a.G % kBlockRows == 0;
-    // Rows that fill no whole number of blocks: only where the candidate passes come out full to three quarters.  us,
-    // resident general kernel and candidate passes, P 128: 256 candidates x 159 positions (28/4 heads, 35 blocks in 5
-    // passes of 8): 240, 211; 256 x 150 (32/8, 19 in 3): 263, 239; 16 x 90 (32/8, 12 in 2): 16, 12; below: 64 x 141
-    // (32/32, 5 in 1): 81, 101; with the pipelined passes 128 x 70 (32/8, 9 in 2): 49, 62.
-    const long long nb = ((long long)a.S * a.G + kBlockRows - 1) / kBlockRows, ngrp = (nb + kNW - 1) / kNW;
-    const bool long_suffix = a.S > kTileKeys && (whole || (own_blocks_fit(a) && block_offsets_fit(a) && nb * 4 >= ngrp * kNW * 3 &&
-                                                           (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL)) && max_tiles >= kMinTiles &&
-                             (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL;
+    bool long_suffix = a.S > kTileKeys && max_tiles >= kMinTiles && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL;
+    // Rows that fill no whole number of blocks: only where the candidate passes come out full to three quarters, and
+    // their rounds of the chip are no more than 10/9 of the blocks that a wavefront of the resident general kernel
+    // has.  us, resident general kernel and candidate passes: P 128: 16 candidates x 90 positions (32/8 heads, 12 blocks
+    // in 2 passes of 8; 1 block, 1 round): 16, 12; P 205: 21 x 118 (32/4; 2, 2): 32.8, 26.8; P 222: 37 x 158 (28/4; 3,
+    // 3): 56, 45; P 70: 124 x 87 (32/4; 6, 6): 58.9, 51.9; P 167: 156 x 123 (28/4; 9, 10): 137, 127; beyond: P 147: 17 x
+    // 136 (28/4; 1, 2): 20.5, 23.6; P 169: 49 x 74 (32/4; 2, 3): 28.7, 31.0; P 145: 247 x 22 .. 45 (32/8; 6, 8): 57, 74;
+    // P 164: 161 x 113 (32/4; 9, 11): 114, 133.  A last pass of up to four blocks takes 0.6 of the others' time, where a
+    // workgroup takes such and others in turn: P 88: 595 x 90 (28/4, 20 blocks in 3 passes; 23, 28): 325, 274; P 93: 73 x
+    // 147 (32/8, 19 in 3; 6, 7): 84.6, 67.7; P 72: 188 x 155 (28/4, 34 in 5; 13, 15): 164, 143; beyond: P 169: 49 x 74.  Less than
+    // three quarters: 64 x 141 (32/32, 5 in 1, P 128): 81, 101; with the pipelined passes 128 x 70 (32/8, 9 in 2): 49, 62.
+    if (long_suffix && !whole && resident_supported(a)) {
+        hipError_t e;
+        const int num_cu = device_cu_count(e);
+        if (e != hipSuccess)
+            return e;
+        const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows, ngrp = (nb + kNW - 1) / kNW;
+        const long long passes = ((long long)a.B * a.Hkv + 7) / 8 * 8 * ngrp, rounds = (passes + num_cu - 1) / num_cu;
+        const long long each = resident_split(a, (a.C * rows_c + kBlockRows - 1) / kBlockRows, kNW, num_cu).each;
+        // a workgroup takes a candidate's different passes in turn unless their number divides its stride (see make_cand_pass)
+        const bool in_turn = (num_cu / 8) % ngrp != 0 && rounds >= ngrp, half = nb % kNW >= 1 && nb % kNW <= 4;
+        const long long tenths = in_turn && half ? rounds * (10 * ngrp - 4) / ngrp : rounds * 10;
+        long_suffix = own_blocks_fit(a) && block_offsets_fit(a) && nb * 4 >= ngrp * kNW * 3 && (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL &&
+                      tenths * 9 <= each * 100;
+    }
     return resident_supported(a) && !long_suffix ? launch_resident(a, stream) : launch_stream(a, stream);
 }
 
@@ -827,6 +844,8 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
     const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows; // rows and own blocks of a candidate
     const bool whole = rows_c % kBlockRows == 0;
     bool pipelined = own_blocks_fit(a) && max_tiles >= kMinTiles && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && block_offsets_fit(a);
+    auto rounds = [&](long long passes) { return (passes + num_cu - 1) / num_cu; };
+    const long long full_rounds = rounds(stream_pass_ids(a));
     // Long suffix-side segments whose candidates fill most of a workgroup's eight wavefronts
     // take the candidate passes.
     if (pipelined && a.S > kTileKeys && (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL) {
@@ -839,17 +858,21 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
         cs.bpp = cs.nblk_c < kNW ? cs.nblk_c : kNW;
         const long long units = (long long)a.B * a.Hkv;
         const long long cpasses = (units + 7) / 8 * 8 * cs.ngrp;
-        if (nblk_c * 10 >= (long long)cs.ngrp * kNW * 6 && cpasses <= 0x7fffffffLL - 8) {
+        // Rows that fill no whole number of blocks: a candidate pass takes 0.7 of a general pass' time, and there are
+        // more of them.  us, general and candidate passes (rounds of the chip): 64 candidates x 109 positions (32/8 heads, P
+        // 464; 4, 4): 121, 84; 50 x 148 (32/8, P 424; 4, 5): 105, 81; 12 x 156 (32/32, P 2018; 1, 2): 84, 103; 34 x 111
+        // (28/4, P 1114; 2, 3): 100, 104; 245 x 34 (32/8, P 676; 5, 8): 169, 161 (pipelined passes 131).
+        if (nblk_c * 10 >= (long long)cs.ngrp * kNW * 6 && cpasses <= 0x7fffffffLL - 8 && (whole || rounds(cpasses) * 7 <= full_rounds * 10)) {
             const unsigned cgrid = (unsigned)(cpasses < num_cu ? cpasses : num_cu);
             return launch_kernel(whole ? stream_candidate_kernel<true> : stream_candidate_kernel<false>, dim3(cgrid), dim3(kNW * 64), kLdsBytes, stream, a, (int)cpasses, cs);
         }
     }
-    // Own blocks make more passes, each in 0.7 of the general kernel's time: not where that costs a round of the chip.
+    // Own blocks make more passes, each in 0.7 of the general kernel's time, 0.8 with the second own step: not where
+    // that costs a round of the chip.
     // us, general and pipelined: 512 candidates x 29 positions (32/32 heads, P 512): 252, 189; 512 x 26: 221, 178; 1024
-    // x 30 (32/8): 388, 313; 300 x 13 (32/8, P 700; 2 rounds, 3 rounds): 66, 69.
-    auto rounds = [&](long long passes) { return (passes + num_cu - 1) / num_cu; };
+    // x 30 (32/8): 388, 313; 300 x 13 (32/8, P 700; 2 rounds, 3 rounds): 66, 69; 43 x 113 (40/40, P 603; 3, 4): 109, 113.
     if (pipelined && !whole)
-        pipelined = rounds(stream_pass_ids(a, a.C * nb)) * 7 <= rounds(stream_pass_ids(a)) * 10;
+        pipelined = rounds(stream_pass_ids(a, a.C * nb)) * (a.S <= kTileKeys ? 7 : 8) <= full_rounds * 10;
     const long long npasses = pipelined ? stream_pass_ids(a, a.C * nb) : stream_pass_ids(a);
     const unsigned grid = (unsigned)(npasses < num_cu ? npasses : num_cu);
     if (!pipelined)
