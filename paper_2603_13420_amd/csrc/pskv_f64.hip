@@ -2,8 +2,8 @@
 // the suffix side, in double precision from the exactly widened inputs to the one final rounding,
 // like the vector kernels of pskv_simple.hip and pskv_bwd_simple.hip.
 //
-// What bounds this path is double-precision arithmetic (67 TFLOP/s in a large library product, a
-// 32nd of the bf16 rate), so everything here serves v_mfma_f64_16x16x4_f64 (64 cycles each): a
+// What bounds this path is double-precision arithmetic (72 TFLOP/s in a large library product, a
+// nineteenth of what a bf16 one reaches), so everything here serves v_mfma_f64_16x16x4_f64 (64 cycles each): a
 // wavefront owns 16 query rows (or 16 suffix keys) and meets 16 keys (rows) at a time, 4 KB or 8 KB
 // of K and as much of V per 2000 to 4000 cycles of matrix work, which L1 and L2 deliver straight
 // into registers: no staging of tiles, no barrier between them.  The vector kernels it takes the place
