@@ -808,15 +808,14 @@ hipError_t launch_mfma(const Args &a, hipStream_t stream)
     const bool whole = (long long)a.S * a.G % kBlockRows == 0;
     bool long_suffix = a.S > kTileKeys && max_tiles >= kMinTiles && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL;
     // Rows that fill no whole number of blocks: only where the candidate passes come out full to three quarters, and
-    // their rounds of the chip are no more than 10/9 of the blocks that a wavefront of the resident general kernel
-    // has.  us, resident general kernel and candidate passes: P 128: 16 candidates x 90 positions (32/8 heads, 12 blocks
-    // in 2 passes of 8; 1 block, 1 round): 16, 12; P 205: 21 x 118 (32/4; 2, 2): 32.8, 26.8; P 222: 37 x 158 (28/4; 3,
-    // 3): 56, 45; P 70: 124 x 87 (32/4; 6, 6): 58.9, 51.9; P 167: 156 x 123 (28/4; 9, 10): 137, 127; beyond: P 147: 17 x
-    // 136 (28/4; 1, 2): 20.5, 23.6; P 169: 49 x 74 (32/4; 2, 3): 28.7, 31.0; P 145: 247 x 22 .. 45 (32/8; 6, 8): 57, 74;
-    // P 164: 161 x 113 (32/4; 9, 11): 114, 133.  A last pass of up to four blocks takes 0.6 of the others' time, where a
-    // workgroup takes such and others in turn: P 88: 595 x 90 (28/4, 20 blocks in 3 passes; 23, 28): 325, 274; P 93: 73 x
-    // 147 (32/8, 19 in 3; 6, 7): 84.6, 67.7; P 72: 188 x 155 (28/4, 34 in 5; 13, 15): 164, 143; beyond: P 169: 49 x 74.  Less than
-    // three quarters: 64 x 141 (32/32, 5 in 1, P 128): 81, 101; with the pipelined passes 128 x 70 (32/8, 9 in 2): 49, 62.
+    // their rounds of the chip are no more than the blocks that a wavefront of the resident general kernel has, or
+    // one and a half times as many with more than four own steps, which that kernel takes one by one.  us, resident
+    // general kernel and candidate passes: P 128: 16 candidates x 90 positions (32/8 heads, 12 blocks in 2 passes of 8; 1
+    // block, 1 round): 16, 12; P 205: 21 x 118 (32/4; 2, 2): 32.8, 26.8; P 70: 124 x 87 (32/4; 6, 6): 58.9, 51.9; beyond: P
+    // 169: 49 x 74 (32/4; 2, 3): 28.7, 31.0; P 145: 247 x 22 .. 45 (32/8; 6, 8): 57, 74; P 164: 161 x 113 (32/4; 9, 11):
+    // 114, 133; with more than four steps: P 222: 37 x 158 (28/4; 3, 3): 56, 45; P 93: 73 x 147 (32/8; 6, 7): 84.6, 67.7; P
+    // 72: 188 x 155 (28/4; 13, 15): 164, 143; beyond: P 147: 17 x 136 (28/4; 1, 2): 20.5, 23.6.  Less than three quarters:
+    // 64 x 141 (32/32, 5 in 1, P 128): 81, 101; with the pipelined passes 128 x 70 (32/8, 9 in 2): 49, 62.
     if (long_suffix && !whole && resident_supported(a)) {
         hipError_t e;
         const int num_cu = device_cu_count(e);
@@ -825,11 +824,8 @@ hipError_t launch_mfma(const Args &a, hipStream_t stream)
         const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows, ngrp = (nb + kNW - 1) / kNW;
         const long long passes = ((long long)a.B * a.Hkv + 7) / 8 * 8 * ngrp, rounds = (passes + num_cu - 1) / num_cu;
         const long long each = resident_split(a, (a.C * rows_c + kBlockRows - 1) / kBlockRows, kNW, num_cu).each;
-        // a workgroup takes a candidate's different passes in turn unless their number divides its stride (see make_cand_pass)
-        const bool in_turn = (num_cu / 8) % ngrp != 0 && rounds >= ngrp, half = nb % kNW >= 1 && nb % kNW <= 4;
-        const long long tenths = in_turn && half ? rounds * (10 * ngrp - 4) / ngrp : rounds * 10;
         long_suffix = own_blocks_fit(a) && block_offsets_fit(a) && nb * 4 >= ngrp * kNW * 3 && (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL &&
-                      tenths * 9 <= each * 100;
+                      rounds * 2 <= each * (a.S > 4 * kTileKeys ? 3 : 2);
     }
     return resident_supported(a) && !long_suffix ? launch_resident(a, stream) : launch_stream(a, stream);
 }
@@ -859,10 +855,10 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
         const long long units = (long long)a.B * a.Hkv;
         const long long cpasses = (units + 7) / 8 * 8 * cs.ngrp;
         // Rows that fill no whole number of blocks: a candidate pass takes 0.7 of a general pass' time, and there are
-        // more of them.  us, general and candidate passes (rounds of the chip): 64 candidates x 109 positions (32/8 heads, P
+        // more of them (short prefixes come here for these passes: launch_mfma has their rule).  us, general and candidate passes (rounds of the chip): 64 candidates x 109 positions (32/8 heads, P
         // 464; 4, 4): 121, 84; 50 x 148 (32/8, P 424; 4, 5): 105, 81; 12 x 156 (32/32, P 2018; 1, 2): 84, 103; 34 x 111
         // (28/4, P 1114; 2, 3): 100, 104; 245 x 34 (32/8, P 676; 5, 8): 169, 161 (pipelined passes 131).
-        if (nblk_c * 10 >= (long long)cs.ngrp * kNW * 6 && cpasses <= 0x7fffffffLL - 8 && (whole || rounds(cpasses) * 7 <= full_rounds * 10)) {
+        if (nblk_c * 10 >= (long long)cs.ngrp * kNW * 6 && cpasses <= 0x7fffffffLL - 8 && (whole || resident_supported(a) || rounds(cpasses) * 7 <= full_rounds * 10)) {
             const unsigned cgrid = (unsigned)(cpasses < num_cu ? cpasses : num_cu);
             return launch_kernel(whole ? stream_candidate_kernel<true> : stream_candidate_kernel<false>, dim3(cgrid), dim3(kNW * 64), kLdsBytes, stream, a, (int)cpasses, cs);
         }

@@ -38,9 +38,9 @@ def test_forward_own_blocks(tmp_path):
 def test_forward_candidate_passes(tmp_path):
     check(tmp_path, "fwd", [
         (16, 128, 90, 32, 8, 1, "stream_candidate"), (21, 205, 118, 32, 4, 1, "stream_candidate"), (37, 222, 158, 28, 4, 1, "stream_candidate"),
-        (156, 167, 123, 28, 4, 1, "stream_candidate"), (17, 147, 136, 28, 4, 1, "resident_general"), (49, 169, 74, 32, 4, 1, "resident_general"), (247, 145, 45, 32, 8, 1, "resident_general"),
+        (17, 147, 136, 28, 4, 1, "resident_general"), (49, 169, 74, 32, 4, 1, "resident_general"), (247, 145, 45, 32, 8, 1, "resident_general"),
         (161, 164, 113, 32, 4, 1, "resident_general"), (64, 128, 141, 32, 32, 1, "resident_general"),
-        (595, 88, 90, 28, 4, 1, "stream_candidate"), (73, 93, 147, 32, 8, 1, "stream_candidate"), (188, 72, 155, 28, 4, 1, "stream_candidate"),
+        (73, 93, 147, 32, 8, 1, "stream_candidate"), (23, 85, 157, 32, 8, 1, "stream_candidate"), (188, 72, 155, 28, 4, 1, "stream_candidate"),
         (161, 164, 112, 32, 4, 1, "stream_candidate"),      # (whole blocks)
         (64, 464, 109, 32, 8, 1, "stream_candidate"), (50, 424, 148, 32, 8, 1, "stream_candidate"), (12, 2018, 156, 32, 32, 1, "stream_pipelined"),
         (34, 1114, 111, 28, 4, 1, "stream_pipelined"), (245, 676, 34, 32, 8, 1, "stream_pipelined"), (43, 603, 113, 40, 40, 1, "stream_general"),
