@@ -295,8 +295,9 @@ template <typename F> __device__ inline void for_visible_keys(const Args &a, con
 
 template <int D>
 __global__ __attribute__((amdgpu_flat_work_group_size(256, 256), amdgpu_waves_per_eu(2)))
-void f32_fwd_kernel(Args a, int nblk)
+void f32_fwd_kernel(Args a_, int nblk)
 {
+    const Args &a = a_;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 15, kq = lane >> 4;
     const int vh = blockIdx.x / nblk, blk = blockIdx.x - vh * nblk;
@@ -373,8 +374,12 @@ void f32_fwd_kernel(Args a, int nblk)
     const bool nan = gather_store<D>(buf, wave, lane, o, exp(m - top), out, 1. / sum, x.exists, x.valid);
     if (x.exists && a.lse && kq == 0 && wave == 0)
         a.lse[((long long)x.b * a.Hq + x.h) * a.S + x.i] = x.valid ? (float)(top + log(sum)) : -INFINITY;
+    // (128 columns: the arguments are loaded anew there, as holding them costs the tiles scalar registers: 8 candidates x 34
+    // positions, P 253, 8/2 heads: 20.1 us, 19.7 so, 19.6 without the check; for 64 columns, and in the backward pass, the
+    // loads cost 1 to 3 % more than they save.)
     if (nan)
         finish_alone<D>(wave, lane, out, 1. / sum, [&](auto term) {
+            const Args &a = D == 128 ? first_parameter<Args>() : a_;
             const float *q = reinterpret_cast<const float *>(a.q) + (long long)x.b * a.q_sb + (long long)x.i * a.q_ss + (long long)x.h * a.q_sh;
             for_visible_keys(a, x, [&](const float *k, const float *v) { term(exp(lane_dot<D>(q, k) * (double)a.scale - top), v); });
         });
