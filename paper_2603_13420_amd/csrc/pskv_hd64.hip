@@ -12,12 +12,19 @@
 //     steps: a row sees a contiguous run of it, and a block that straddles short candidates takes one
 //     or two steps where one step (or more) per candidate would be mostly empty.
 //
-// At these sizes (heads of half the width belong to small models) everything is latency: a
+// At these sizes (heads of half the width belong to small models) much is latency: a
 // persistent workgroup of 8 wavefronts, two per compute unit, copies as much of its head's prefix
-// into LDS as fits - transposed there once, so that every operand read is a 16-byte one - and its
-// wavefronts walk over the row blocks independently.  Longer prefixes go through the same LDS in
-// chunks.  256 candidates of 5 to 33 rows, 177 prefix rows, 14/2 heads: 300 us in the vector kernel, 22 us here.
+// into LDS as fits, and its wavefronts walk over the row blocks independently.  Longer prefixes go
+// through the same LDS in chunks.
+//
+// 256 candidates of 5 to 33 rows, 177 prefix rows, 14/2 heads: 300 us in the vector kernel, 20.1 us here, of which the prefix
+// takes 4 and the tiles 6 to 13: two to four wavefronts of a SIMD have a block of their own, and a tile takes
+// 1300 cycles of one, the sum of its matrix instructions (512) and of its vector ones.  (22.4 us with the prefix
+// copied through registers, 32 bytes of a row at a time, and transposed in LDS; blocks that straddle
+// candidates spread over the chip, so that blocks of padding come to all of it alike, and the first tile's
+// maximum taken without trying it as a later tile: 1 us of these.)
 #include "pskv_mfma.hpp"
+#include <type_traits>
 
 namespace pskv {
 namespace {
@@ -69,8 +76,8 @@ __device__ inline Split split16(float (&v)[16])
     return s;
 }
 
-// Fragment (column tile dt, contraction step j) of a transposed operand.
-//   From a "transposable" image (the V image of pskv_mfma.hpp): through the transposing read ...
+// Fragment (column tile dt, contraction step j) of a transposed operand
+// from a "transposable" image (the V image of pskv_mfma.hpp), through the transposing read.
 __device__ inline bf16x8 frag_tr(lds_u8 *img, int dt, int j, int lane)
 {
     short4v lo = lds_read_tr(img + ((dt * 2 + j) * 2 + 0) * 512 + lane * 8), hi = lds_read_tr(img + ((dt * 2 + j) * 2 + 1) * 512 + lane * 8);
@@ -79,9 +86,6 @@ __device__ inline bf16x8 frag_tr(lds_u8 *img, int dt, int j, int lane)
     __builtin_memcpy(&f, &v8, 16);
     return f;
 }
-//   ... from a transposed one, which holds the result of that read: 16 bytes per lane.
-__device__ inline bf16x8 frag_t(lds_u8 *img, int dt, int j, int lane) { return lds_frag(img + (dt * 2 + j) * 1024 + lane * 16); }
-
 // Which 16-byte chunk (key, column chunk) belongs at chunk position p (0..255) of an image.
 __device__ inline void row_major_slot(int p, int &key, int &chunk) { key = p & 31, chunk = p >> 5; }
 __device__ inline void transposable_slot(int p, int &key, int &chunk)
@@ -96,7 +100,24 @@ struct Rows {
     int b, i, h, len;        // candidate, suffix position, query head, clamped suffix length
     bool exists, valid;
     int bl0, bl1, tok0, tok1; // candidates within the instruction and tokens that the block covers
+    int n, first;             // the list of own keys (see own_keys): its slots, and where those of the lane's row begin
 };
+
+// The list of own keys: keys 0 .. n_c - 1 of every candidate c of the block, in order; n_c is one more
+// than the last key that any of the block's rows sees.  visit(candidate, its length, first slot, n_c).
+template <typename F> __device__ inline int own_keys(const Args &a, const Ctx &X, const Rows &x, F visit)
+{
+    int n = 0;
+    for (int bl = x.bl0; bl <= x.bl1; ++bl) {
+        const int b = X.cand0 + bl, len = len_uniform(a, b);
+        const int lo = x.tok0 - bl * a.S > 0 ? x.tok0 - bl * a.S : 0;
+        const int hi = x.tok1 - bl * a.S < len - 1 ? x.tok1 - bl * a.S : len - 1;
+        const int nc = lo < len ? hi + 1 : 0;
+        visit(b, len, n, nc);
+        n += nc;
+    }
+    return n;
+}
 __device__ inline Rows make_rows(const Args &a, const Ctx &X, int blk)
 {
     Rows x;
@@ -107,40 +128,29 @@ __device__ inline Rows make_rows(const Args &a, const Ctx &X, int blk)
     x.b = X.cand0 + bl;
     x.i = tok - bl * a.S;
     x.h = X.head * a.G + (r - tok * a.G);
-    x.len = a.len ? clamp_len(a, a.len[x.b]) : a.S;
-    x.valid = x.exists && x.i < x.len;
     x.tok0 = (int)fdiv(r0, a.div_g);
     x.tok1 = (int)fdiv(last, a.div_g);
     x.bl0 = (int)fdiv(x.tok0, a.div_s);
     x.bl1 = (int)fdiv(x.tok1, a.div_s);
+    // (lengths by scalar loads: a vector load of the lane's own would have to wait for the requests in flight)
+    x.len = x.first = 0;
+    x.n = own_keys(a, X, x, [&](int b, int len, int first, int) {
+        x.len = b == x.b ? len : x.len;
+        x.first = b == x.b ? first : x.first;
+    });
+    x.valid = x.exists && x.i < x.len;
     return x;
 }
 
-// The list of own keys: keys 0 .. n_c - 1 of every candidate c of the block, in order; n_c is one more
-// than the last key that any of the block's rows sees.  visit(candidate, first slot, n_c).
-template <typename F> __device__ inline int own_keys(const Args &a, const Ctx &X, const Rows &x, F visit)
-{
-    int n = 0;
-    for (int bl = x.bl0; bl <= x.bl1; ++bl) {
-        const int b = X.cand0 + bl, len = len_uniform(a, b);
-        const int lo = x.tok0 - bl * a.S > 0 ? x.tok0 - bl * a.S : 0;
-        const int hi = x.tok1 - bl * a.S < len - 1 ? x.tok1 - bl * a.S : len - 1;
-        const int nc = lo < len ? hi + 1 : 0;
-        visit(b, n, nc);
-        n += nc;
-    }
-    return n;
-}
-
 // Element offset (from the suffix tensors of this head) of the row in slot k0 + c32 of the list, the last
-// slot standing in for those behind it.
-__device__ inline long long own_row(const Args &a, const Ctx &X, const Rows &x, int n, int k0)
+// slot standing in for those behind it.  (The list holds at least one.)
+__device__ inline long long own_row(const Args &a, const Ctx &X, const Rows &x, int k0)
 {
-    const int slot = k0 + X.c32 < n - 1 ? k0 + X.c32 : n - 1;
+    const int slot = k0 + X.c32;
     long long off = 0;
-    own_keys(a, X, x, [&](int b, int first, int nc) {
-        if (slot >= first && slot < first + nc)
-            off = (long long)b * a.ks_sb + (long long)(slot - first) * a.ks_ss;
+    own_keys(a, X, x, [&](int b, int, int first, int nc) {
+        if (nc > 0 && slot >= first)
+            off = (long long)b * a.ks_sb + (long long)(slot - first < nc ? slot - first : nc - 1) * a.ks_ss;
     });
     return off;
 }
@@ -293,59 +303,70 @@ __device__ inline Ctx make_hd64_ctx(const Args &a, int tid)
     return X;
 }
 
-// Prefix rows of tiles t0 .. t0 + n - 1 into LDS (whole workgroup): K row-major; V, or for the
-// gradients K once more, transposed.  Rows behind the prefix are zeros.  Ends with a barrier.
-//   images of tile t: img + (t - t0) * tile_bytes: K row-major, K or V transposed, (V row-major)
-template <bool BWD> __device__ inline void stage_tiles(const Args &a, const Ctx &X, lds_u8 *img, int t0, int n, int tid)
+// Prefix rows of tiles t0 .. t0 + n - 1 into LDS (whole workgroup of 8 wavefronts), K and V of tile t as half images
+// (pskv_mfma.hpp; at 64 columns an image is a whole tile) at img + (t - t0) * kTile.  The last row stands in for
+// rows behind the prefix (never visible).
+// All 1 KB pieces - 8 rows, whole cache lines - are requested straight into LDS at once: no registers, one round
+// trip.  Between the request and the barrier that ends stage_finish there is room for other requests.
+constexpr int kTile = 2 * kImg;
+__device__ inline void stage_request(const Args &a, const Ctx &X, lds_u8 *img, int t0, int n, int tid)
 {
-    constexpr int kTile = (BWD ? 3 : 2) * kImg;
-    const int nt = blockDim.x;
+    asm volatile("" : "+v"(tid)); // (worked out here: nothing held across the callers' loops)
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int g = wave & 3; // this wavefront's pieces: rows 8g .. 8g+7 of a tile
+    const unsigned short *src = wave & 4 ? X.vpg : X.kpg;
+    const unsigned k = ((unsigned)lane >> 3) ^ (g & 1); // what half_put puts at lane*16
+    const int row = 8 * g + (int)k, chunk = (int)(((unsigned)lane & 7) ^ half_swz(k)), last = X.P - 1; // (P > 0: there is a tile)
     __syncthreads(); // every wavefront is done with what was there
-    auto copy = [&](const unsigned short *src, int place, bool transposable) {
-        for (int p0 = tid; p0 < n * 256; p0 += 4 * nt) { // four requests in flight per thread
-            uintx4 v[4];
-            bool real[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int p = p0 + i * nt;
-                int key, chunk;
-                if (transposable)
-                    transposable_slot(p & 255, key, chunk);
-                else
-                    row_major_slot(p & 255, key, chunk);
-                key += (t0 + (p >> 8)) * kTileKeys;
-                real[i] = key < X.P;
-                v[i] = ld_global16(src + (long long)(real[i] ? key : X.P - 1) * a.kp_sp + chunk * 8); // (P > 0: there is a tile)
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int p = p0 + i * nt;
-                if (p < n * 256)
-                    *(lds_u128 *)(img + (p >> 8) * kTile + place * kImg + (p & 255) * 16) = real[i] ? v[i] : uintx4{0, 0, 0, 0};
-            }
-        }
-    };
-    copy(X.kpg, 0, false);
-    copy(BWD ? X.kpg : X.vpg, 1, true);
-    if (BWD)
-        copy(X.vpg, 2, false);
-    __syncthreads();
-    // transposed in place, a fragment pair (1 KB) at a time, each by one wavefront
-    for (int f = tid >> 6; f < n * 4; f += nt >> 6) {
-        lds_u8 *at = img + (f >> 2) * kTile + kImg + (f & 3) * 1024;
-        short4v lo = lds_read_tr(at + X.lane * 8), hi = lds_read_tr(at + 512 + X.lane * 8);
-        short8v v8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        uintx4 v;
-        __builtin_memcpy(&v, &v8, 16);
-        *(lds_u128 *)(at + X.lane * 16) = v;
+    for (int t = 0; t < n; ++t) {
+        const int key = (t0 + t) * kTileKeys + row;
+        request_to_lds(src + ((long long)(key < last ? key : last) * a.kp_sp + chunk * 8), img + t * kTile + wave * 1024);
     }
+}
+__device__ inline void stage_finish()
+{
+    PSKV_WAIT_VM(0);
     __syncthreads();
+}
+
+// The lane's places in a tile's images.
+struct TilePlaces {
+    unsigned row[kKS]; // row-major fragments
+    unsigned col[kDT][2]; // transposed ones: even and odd pieces
+};
+__device__ inline TilePlaces tile_places(int lane)
+{
+    const HalfPlaces hp = half_places(lane);
+    TilePlaces x;
+#pragma unroll
+    for (int i = 0; i < kKS; ++i)
+        x.row[i] = hp.row ^ (i << 5);
+#pragma unroll
+    for (int d = 0; d < kDT; ++d)
+        x.col[d][0] = hp.col ^ (d << 6), x.col[d][1] = hp.col ^ (d << 6) ^ 128;
+    return x;
+}
+__device__ inline bf16x8 tile_row_frag(const TilePlaces &x, lds_u8 *img, int i) { return lds_frag(img + x.row[i]); }
+__device__ inline bf16x8 tile_col_frag(const TilePlaces &x, lds_u8 *img, int d, int j)
+{
+    short4v lo = lds_read_tr(img + x.col[d][0] + j * 2048), hi = lds_read_tr(img + x.col[d][1] + j * 2048 + 1024);
+    short8v v8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    bf16x8 f;
+    __builtin_memcpy(&f, &v8, 16);
+    return f;
 }
 
 // How a persistent grid is laid over the (instruction, KV head) pairs: see resident_general_kernel.
 struct Spread {
     int per_vh, vh_slots, chunk; // workgroups per pair, pairs served at a time, tiles that fit into LDS
+    int wg_step, wave_step;      // blocks from one workgroup to the next, from one wavefront to the next
 };
+// The block that a wavefront takes in round `it` (at or behind the number of blocks: none; wavefront 0's is the
+// first of a workgroup's).
+__device__ inline int spread_block(const Spread &sp, int waves, int wave, int it)
+{
+    return (blockIdx.x / sp.vh_slots) * sp.wg_step + wave * sp.wave_step + it * sp.per_vh * waves;
+}
 
 // f(arguments, context, row) for the valid rows of this wavefront's blocks in a walk of `waves` wavefronts per workgroup, for
 // a path hardly ever taken.  (A kernel's first parameter is, or begins with, Args.)
@@ -357,7 +378,7 @@ template <typename F> __device__ inline void for_stored_rows(const Spread &sp, i
     const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int vh = blockIdx.x % sp.vh_slots; vh < a.Np * a.Hkv; vh += sp.vh_slots) {
         set_vhead(a, X, vh);
-        for (int blk = (blockIdx.x / sp.vh_slots) * waves + wave; blk < nblocks; blk += sp.per_vh * waves) {
+        for (int it = 0, blk; (blk = spread_block(sp, waves, wave, it)) < nblocks; ++it) {
             const Rows x = make_rows(a, X, blk);
             if (x.valid)
                 f(a, X, x);
@@ -370,8 +391,25 @@ struct FwdState {
     floatx16 o[kDT];
 };
 
+// O^T += V^T P^T (FRESH: O^T = V^T P^T); vf(dt, j) hands out the V^T fragments.
+template <bool FRESH, typename VF> __device__ inline void add_products(float (&p)[16], FwdState &st, VF vf)
+{
+    const Split w = split16(p);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int dt = 0; dt < kDT; ++dt) {
+            const bf16x8 v = vf(dt, j);
+            if (FRESH && j == 0)
+                st.o[dt] = zero16();
+#pragma unroll
+            for (int part = kParts - 1; part >= 0; --part) // (the small ones first)
+                st.o[dt] = mma(v, w.p[part][j], st.o[dt]);
+        }
+}
+
 // Softmax of a tile's raw scores (-inf: not visible) against the row's reference, rescaling only when a weight
-// comes out huge (cf. softmax_tile), and the value product; vf(dt, j) hands out the V^T fragments.
+// comes out huge (cf. softmax_tile), and the value product.
 template <typename VF> __device__ inline void weigh_tile(const floatx16 &s, float c, FwdState &st, VF vf)
 {
     float p[16], rs = 0.f;
@@ -402,26 +440,37 @@ template <typename VF> __device__ inline void weigh_tile(const floatx16 &s, floa
         }
     }
     st.l += rs;
-    const Split w = split16(p);
+    add_products<false>(p, st, vf);
+}
+
+// The same for a row's first tile.
+template <typename VF> __device__ inline void weigh_first(const floatx16 &s, float c, FwdState &st, VF vf)
+{
+    float tmax = s[0];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int e = 1; e < 16; ++e)
+        tmax = fmaxf(tmax, s[e]);
+    st.m = fmaxf(tmax, __shfl_xor(tmax, 32, 64)) * c;
+    const float msafe = st.m == -INFINITY ? 0.f : st.m;
+    float p[16];
+    st.l = 0.f;
 #pragma unroll
-        for (int dt = 0; dt < kDT; ++dt) {
-            const bf16x8 v = vf(dt, j);
-#pragma unroll
-            for (int part = kParts - 1; part >= 0; --part) // (the small ones first)
-                st.o[dt] = mma(v, w.p[part][j], st.o[dt]);
-        }
+    for (int e = 0; e < 16; ++e) {
+        p[e] = fast_exp2(__builtin_fmaf(s[e], c, -msafe));
+        st.l += p[e];
+    }
+    add_products<true>(p, st, vf);
 }
 
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(4)))
 void hd64_fwd_kernel(Args a, Spread sp)
 {
-    extern __shared__ __align__(16) unsigned char smem_generic[];
+    extern __shared__ __align__(256) unsigned char smem_generic[];
     lds_u8 *img = (lds_u8 *)smem_generic;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     Ctx X = make_hd64_ctx(a, tid);
-    X.scr = img + sp.chunk * 2 * kImg + wave * kImg;
+    X.scr = img + sp.chunk * kTile + wave * kImg;
+    const TilePlaces tp = tile_places(X.lane);
     const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows, VH = a.Np * a.Hkv;
     bool bad = false;
 
@@ -429,16 +478,25 @@ void hd64_fwd_kernel(Args a, Spread sp)
         set_vhead(a, X, vh);
         const int T = (X.P + kTileKeys - 1) / kTileKeys;
         const bool resident = T <= sp.chunk;
-        if (resident)
-            stage_tiles<false>(a, X, img, 0, T, tid);
-        // (The workgroup's wavefronts go through this loop together - barriers inside - unless the prefix is resident.)
-        for (int base = (blockIdx.x / sp.vh_slots) * kFwdWaves; base < nblocks; base += sp.per_vh * kFwdWaves) {
-            const bool has = base + wave < nblocks;
-            const int blk = has ? base + wave : nblocks - 1;
-            const Rows x = make_rows(a, X, blk);
-            const bool work = has && __builtin_amdgcn_ballot_w64(x.valid) != 0;
-            uintx4 q[kKS];
+        // A block's query rows are requested while the prefix is on its way (the first block) or the block before
+        // is being stored.
+        Rows x;
+        bool has;
+        uintx4 q[kKS];
+        auto begin = [&](int it) __attribute__((always_inline)) {
+            const int blk = spread_block(sp, kFwdWaves, wave, it);
+            has = blk < nblocks;
+            x = make_rows(a, X, has ? blk : nblocks - 1);
             load_row(a.q, (long long)x.b * a.q_sb + (long long)(x.valid ? x.i : 0) * a.q_ss + (long long)x.h * a.q_sh, X.h, q);
+        };
+        if (resident)
+            stage_request(a, X, img, 0, T, tid);
+        begin(0);
+        if (resident)
+            stage_finish();
+        // (The workgroup's wavefronts go through this loop together - barriers inside - unless the prefix is resident.)
+        for (int it = 0;;) {
+            const bool work = has && __builtin_amdgcn_ballot_w64(x.valid) != 0;
             FwdState st;
             st.m = -INFINITY;
             st.l = 0.f;
@@ -448,30 +506,39 @@ void hd64_fwd_kernel(Args a, Spread sp)
 
             for (int t0 = 0; t0 < T; t0 += sp.chunk) {
                 const int n = T - t0 < sp.chunk ? T - t0 : sp.chunk;
-                if (!resident)
-                    stage_tiles<false>(a, X, img, t0, n, tid);
+                if (!resident) {
+                    stage_request(a, X, img, t0, n, tid);
+                    stage_finish();
+                }
                 if (!work)
                     continue;
-                for (int t = 0; t < n; ++t) {
-                    lds_u8 *ki = img + t * 2 * kImg, *vi = ki + kImg;
+                auto tile = [&](int t, auto first) __attribute__((always_inline)) {
+                    lds_u8 *ki = img + t * kTile, *vi = ki + kImg;
                     floatx16 s = zero16();
 #pragma unroll
                     for (int ks = 0; ks < kKS; ++ks)
-                        s = mma(lds_frag(ki + ks * 1024 + X.lane * 16), as_bf16x8(q[ks]), s);
+                        s = mma(tile_row_frag(tp, ki, ks), as_bf16x8(q[ks]), s);
                     const int nv = X.P - (t0 + t) * kTileKeys - 4 * X.h; // element e holds key 8*(e/4) + e%4 + 4*h of the tile
                     if ((t0 + t + 1) * kTileKeys > X.P)
 #pragma unroll
                         for (int e = 0; e < 16; ++e)
                             if (8 * (e >> 2) + (e & 3) >= nv)
                                 s[e] = -INFINITY;
-                    weigh_tile(s, X.c, st, [&](int dt, int j) { return frag_t(vi, dt, j, X.lane); });
-                }
+                    auto v = [&](int dt, int j) { return tile_col_frag(tp, vi, dt, j); };
+                    if constexpr (decltype(first)::value)
+                        weigh_first(s, X.c, st, v);
+                    else
+                        weigh_tile(s, X.c, st, v);
+                };
+                int t = 0;
+                if (t0 == 0)
+                    tile(t++, std::true_type{});
+                for (; t < n; ++t)
+                    tile(t, std::false_type{});
             }
             if (work) {
-                int first = 0; // where the own keys of the lane's row begin in the list
-                const int n = own_keys(a, X, x, [&](int b, int f, int) { first = b == x.b ? f : first; });
-                for (int k0 = 0; k0 < n; k0 += kTileKeys) {
-                    const long long row = own_row(a, X, x, n, k0);
+                for (int k0 = 0; k0 < x.n; k0 += kTileKeys) {
+                    const long long row = own_row(a, X, x, k0);
                     uintx4 kf[kKS];
                     load_row(X.ksg, row, X.h, kf);
                     own_to_scratch(X, X.vsg, row);
@@ -479,7 +546,7 @@ void hd64_fwd_kernel(Args a, Spread sp)
 #pragma unroll
                     for (int ks = 0; ks < kKS; ++ks)
                         s = mma(as_bf16x8(kf[ks]), as_bf16x8(q[ks]), s);
-                    const int rel = k0 + 4 * X.h - first; // the row sees slots first .. first + i
+                    const int rel = k0 + 4 * X.h - x.first; // the row sees slots first .. first + i
 #pragma unroll
                     for (int e = 0; e < 16; ++e)
                         s[e] = (unsigned)(rel + 8 * (e >> 2) + (e & 3)) <= (unsigned)x.i ? s[e] : -INFINITY;
@@ -498,6 +565,9 @@ void hd64_fwd_kernel(Args a, Spread sp)
                     a.lse[((long long)x.b * a.Hq + x.h) * a.S + x.i] = x.valid ? lse2 * kLn2 : -INFINITY;
                 bad |= __builtin_amdgcn_ballot_w64(x.valid && (has_nan(st.o) || l == 0.f)) != 0;
             }
+            if (spread_block(sp, kFwdWaves, 0, ++it) >= nblocks)
+                break;
+            begin(it);
         }
     }
     if (bad) // (see to_form_anew)
@@ -562,11 +632,12 @@ __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_pe
 void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
 {
     const Args &a = g.f;
-    extern __shared__ __align__(16) unsigned char smem_generic[];
+    extern __shared__ __align__(256) unsigned char smem_generic[];
     lds_u8 *img = (lds_u8 *)smem_generic;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     Ctx X = make_hd64_ctx(a, tid);
-    X.scr = img + sp.chunk * 3 * kImg + wave * kImg;
+    X.scr = img + sp.chunk * kTile + wave * kImg;
+    const TilePlaces tp = tile_places(X.lane);
     const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows, VH = a.Np * a.Hkv;
     bool bad = false;
 
@@ -574,12 +645,16 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
         set_vhead(a, X, vh);
         const int T = (X.P + kTileKeys - 1) / kTileKeys;
         const bool resident = T <= sp.chunk;
-        if (resident)
-            stage_tiles<true>(a, X, img, 0, T, tid);
-        for (int base = (blockIdx.x / sp.vh_slots) * kBwdWaves; base < nblocks; base += sp.per_vh * kBwdWaves) {
-            const bool has = base + wave < nblocks;
-            const int blk = has ? base + wave : nblocks - 1;
-            const Rows x = make_rows(a, X, blk);
+        // (Nothing requested in between, unlike the forward kernel: 48 candidates x 29 positions, P 206, 14/2 heads:
+        // 27.4 us with the first block's rows asked for there, 26.1 so.)
+        if (resident) {
+            stage_request(a, X, img, 0, T, tid);
+            stage_finish();
+        }
+        for (int it = 0; spread_block(sp, kBwdWaves, 0, it) < nblocks; ++it) {
+            const int blk = spread_block(sp, kBwdWaves, wave, it);
+            const bool has = blk < nblocks;
+            const Rows x = make_rows(a, X, has ? blk : nblocks - 1);
             const bool work = has && __builtin_amdgcn_ballot_w64(x.valid) != 0;
             const int ri = x.valid ? x.i : 0; // padded rows take row 0 of their candidate and are stored as zero
             const float lse2 = a.lse[((long long)x.b * a.Hq + x.h) * a.S + ri] * kLog2e;
@@ -599,28 +674,35 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
                 dq[dt] = zero16();
             for (int t0 = 0; t0 < T; t0 += sp.chunk) {
                 const int n = T - t0 < sp.chunk ? T - t0 : sp.chunk;
-                if (!resident)
-                    stage_tiles<true>(a, X, img, t0, n, tid);
+                if (!resident) {
+                    stage_request(a, X, img, t0, n, tid);
+                    stage_finish();
+                }
                 if (!work)
                     continue;
-                for (int t = 0; t < n; ++t) {
-                    lds_u8 *ki = img + t * 3 * kImg;
+                auto tile = [&](int t, auto vis) __attribute__((always_inline)) {
+                    lds_u8 *ki = img + t * kTile, *vi = ki + kImg;
                     floatx16 s = zero16(), dp = zero16();
 #pragma unroll
                     for (int ks = 0; ks < kKS; ++ks) {
-                        s = mma(lds_frag(ki + ks * 1024 + X.lane * 16), as_bf16x8(q[ks]), s);
-                        dp = mma(lds_frag(ki + 2 * kImg + ks * 1024 + X.lane * 16), as_bf16x8(dof[ks]), dp);
+                        s = mma(tile_row_frag(tp, ki, ks), as_bf16x8(q[ks]), s);
+                        dp = mma(tile_row_frag(tp, vi, ks), as_bf16x8(dof[ks]), dp);
                     }
+                    dq_tile(s, dp, X.c, lse2, drow, vis, [&](int dt, int j) { return tile_col_frag(tp, ki, dt, j); }, dq);
+                };
+                // whole tiles, seen by every row, and the prefix's last, ragged one
+                const int whole = X.P / kTileKeys - t0 < n ? X.P / kTileKeys - t0 : n;
+                int t = 0;
+                for (; t < whole; ++t)
+                    tile(t, [](int) { return true; });
+                if (t < n) {
                     const int nv = X.P - (t0 + t) * kTileKeys - 4 * X.h;
-                    dq_tile(s, dp, X.c, lse2, drow, [&](int e) { return 8 * (e >> 2) + (e & 3) < nv; },
-                            [&](int dt, int j) { return frag_t(ki + kImg, dt, j, X.lane); }, dq);
+                    tile(t, [&](int e) { return 8 * (e >> 2) + (e & 3) < nv; });
                 }
             }
             if (work) {
-                int first = 0;
-                const int n = own_keys(a, X, x, [&](int b, int f, int) { first = b == x.b ? f : first; });
-                for (int k0 = 0; k0 < n; k0 += kTileKeys) {
-                    const long long row = own_row(a, X, x, n, k0);
+                for (int k0 = 0; k0 < x.n; k0 += kTileKeys) {
+                    const long long row = own_row(a, X, x, k0);
                     uintx4 kf[kKS], vf[kKS];
                     load_row(X.ksg, row, X.h, kf);
                     load_row(X.vsg, row, X.h, vf);
@@ -633,7 +715,7 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
                         s = mma(as_bf16x8(kf[ks]), as_bf16x8(q[ks]), s);
                         dp = mma(as_bf16x8(vf[ks]), as_bf16x8(dof[ks]), dp);
                     }
-                    const int rel = k0 + 4 * X.h - first;
+                    const int rel = k0 + 4 * X.h - x.first;
                     dq_tile(s, dp, X.c, lse2, drow, [&](int e) { return (unsigned)(rel + 8 * (e >> 2) + (e & 3)) <= (unsigned)x.i; },
                             [&](int dt, int j) { return frag_tr(X.scr, dt, j, X.lane); }, dq);
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -840,7 +922,7 @@ int device_cu_count(hipError_t &e)
     });
 }
 
-// Grid, LDS and chunk size for a walk with `waves` wavefronts per workgroup and `images` images per prefix tile:
+// Grid, LDS and chunk size for a walk with `waves` wavefronts per workgroup:
 // half of a compute unit's LDS where the whole prefix fits into that (two workgroups per compute unit), all
 // of it otherwise, in chunks if need be.
 struct Shape {
@@ -848,9 +930,9 @@ struct Shape {
     size_t lds;
     Spread sp;
 };
-Shape make_shape(const Args &a, int num_cu, int waves, int images, int most_per_cu)
+Shape make_shape(const Args &a, int num_cu, int waves, int most_per_cu)
 {
-    const int T = (a.P + kTileKeys - 1) / kTileKeys, tile = images * kImg, scratch = waves * kImg;
+    const int T = (a.P + kTileKeys - 1) / kTileKeys, tile = kTile, scratch = waves * kImg;
     const int half = (kMaxLds / 2 - scratch) / tile, whole = (kMaxLds - scratch) / tile;
     Shape s;
     const bool two = most_per_cu > 1 && T <= half;
@@ -863,6 +945,12 @@ Shape make_shape(const Args &a, int num_cu, int waves, int images, int most_per_
     per_vh = per_vh < useful ? per_vh : useful;
     s.sp.per_vh = (int)per_vh;
     s.sp.vh_slots = (int)vh_slots;
+    const bool once = nblocks <= per_vh * waves;
+    // Blocks side by side share their candidates' keys, and a workgroup takes them together.  Where nobody takes a second
+    // block, though, they come in one round to all workgroups alike: the blocks behind the candidates' lengths, which cost
+    // nothing, lie together.
+    s.sp.wg_step = once ? 1 : waves;
+    s.sp.wave_step = once ? (int)per_vh : 1;
     s.grid = (unsigned)(per_vh * vh_slots);
     return s;
 }
@@ -885,7 +973,7 @@ hipError_t launch_hd64_fwd(const Args &a, hipStream_t stream)
     const int num_cu = device_cu_count(e);
     if (num_cu == 0)
         return e;
-    const Shape s = make_shape(a, num_cu, kFwdWaves, 2, 2);
+    const Shape s = make_shape(a, num_cu, kFwdWaves, 2);
     return launch_kernel(hd64_fwd_kernel, dim3(s.grid), dim3(kFwdWaves * 64), s.lds, stream, a, s.sp);
 }
 
@@ -895,7 +983,7 @@ hipError_t launch_hd64_bwd_dq(const BwdArgs &g, hipStream_t stream)
     const int num_cu = device_cu_count(e);
     if (num_cu == 0)
         return e;
-    const Shape s = make_shape(g.f, num_cu, kBwdWaves, 3, 1);
+    const Shape s = make_shape(g.f, num_cu, kBwdWaves, 1);
     return launch_kernel(hd64_bwd_dq_kernel, dim3(s.grid), dim3(kBwdWaves * 64), s.lds, stream, g, s.sp);
 }
 

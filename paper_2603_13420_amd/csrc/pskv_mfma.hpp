@@ -710,6 +710,34 @@ __device__ inline bf16x8 half_col_frag(const HalfPlaces &x, lds_u8 *img, int d, 
     return f;
 }
 
+// One 16-byte request per lane straight into LDS: lane l's bytes, fetched from gbase + voff (gbase
+// the same for the whole wavefront and held in scalar registers, voff the lane's own 32-bit
+// offset), land at lds_base + 16*l (lds_base is the same for the whole wavefront).
+// Written as an instruction rather than through the
+// compiler's builtin: the compiler would make every later LDS read wait for all such requests
+// still in flight.  Its own bookkeeping of the vector memory counter stays on the safe side:
+// requests it does not know of can only make its waits longer.  M0 carries the LDS address and
+// is declared clobbered: the statement then counts as a write of M0 for the compiler's passes
+// that merge and hoist its own M0 set-ups, which keeps them from moving one across it.  (M0 is a
+// reserved register, never allocated, which is all the warning silenced here has to say.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ inline void request_to_lds(const unsigned char *gbase, unsigned voff, lds_u8 *lds_base)
+{
+    const unsigned lds_addr = (unsigned)(unsigned long long)lds_base;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(gbase)
+                 : "memory", "m0");
+}
+// The same with a 64-bit address of each lane's own.
+__device__ inline void request_to_lds(const void *addr, lds_u8 *lds_base)
+{
+    const unsigned lds_addr = (unsigned)(unsigned long long)lds_base;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_addr), "v"(addr) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+// s_waitcnt immediate (gfx9 encoding): vector memory counter at most n (n < 16), the others untouched
+#define PSKV_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(0x0F70 | (n))
+
 // Orders a wavefront's own accesses to its scratch.
 __device__ inline void scratch_fence()
 {
