@@ -329,23 +329,6 @@ __device__ inline void stage_finish()
     __syncthreads();
 }
 
-// The lane's places in a tile's images.
-struct TilePlaces {
-    unsigned row[kKS]; // row-major fragments
-    unsigned col[kDT][2]; // transposed ones: even and odd pieces
-};
-__device__ inline TilePlaces tile_places(int lane)
-{
-    const HalfPlaces hp = half_places(lane);
-    TilePlaces x;
-#pragma unroll
-    for (int i = 0; i < kKS; ++i)
-        x.row[i] = hp.row ^ (i << 5);
-#pragma unroll
-    for (int d = 0; d < kDT; ++d)
-        x.col[d][0] = hp.col ^ (d << 6), x.col[d][1] = hp.col ^ (d << 6) ^ 128;
-    return x;
-}
 __device__ inline bf16x8 tile_row_frag(const TilePlaces &x, lds_u8 *img, int i) { return lds_frag(img + x.row[i]); }
 __device__ inline bf16x8 tile_col_frag(const TilePlaces &x, lds_u8 *img, int d, int j)
 {
@@ -470,7 +453,7 @@ void hd64_fwd_kernel(Args a, Spread sp)
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     Ctx X = make_hd64_ctx(a, tid);
     X.scr = img + sp.chunk * kTile + wave * kImg;
-    const TilePlaces tp = tile_places(X.lane);
+    const TilePlaces tp = tile_places(half_places(X.lane));
     const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows, VH = a.Np * a.Hkv;
     bool bad = false;
 
@@ -637,7 +620,7 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     Ctx X = make_hd64_ctx(a, tid);
     X.scr = img + sp.chunk * kTile + wave * kImg;
-    const TilePlaces tp = tile_places(X.lane);
+    const TilePlaces tp = tile_places(half_places(X.lane));
     const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows, VH = a.Np * a.Hkv;
     bool bad = false;
 

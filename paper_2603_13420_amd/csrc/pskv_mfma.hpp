@@ -710,6 +710,23 @@ __device__ inline bf16x8 half_col_frag(const HalfPlaces &x, lds_u8 *img, int d, 
     return f;
 }
 
+// The lane's place for each fragment of a half image, so that a loop over images adds and does nothing else: 16-column
+// row-major fragments, and the transposed ones' even and odd pieces for either group of 32 columns (see half_row_frag and half_col_frag).
+struct TilePlaces {
+    unsigned row[4], col[2][2];
+};
+__device__ inline TilePlaces tile_places(const HalfPlaces &hp)
+{
+    TilePlaces x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        x.row[i] = hp.row ^ (i << 5);
+#pragma unroll
+    for (int d = 0; d < 2; ++d)
+        x.col[d][0] = hp.col ^ (d << 6), x.col[d][1] = hp.col ^ (d << 6) ^ 128;
+    return x;
+}
+
 // One 16-byte request per lane straight into LDS: lane l's bytes, fetched from gbase + voff (gbase
 // the same for the whole wavefront and held in scalar registers, voff the lane's own 32-bit
 // offset), land at lds_base + 16*l (lds_base is the same for the whole wavefront).

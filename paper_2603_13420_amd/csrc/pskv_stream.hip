@@ -13,13 +13,14 @@
 // read from HBM about once per XCD: pass ids are laid out so that the workgroups of one XCD
 // (workgroup ids go round the XCDs) work on one head at a time, and find it in that XCD's L2.
 //
-// Three kernels.  The pipelined one (every 32-row block inside one candidate) is the software
+// Four kernels.  The pipelined one (every 32-row block inside one candidate) is the software
 // pipeline of the resident-prefix kernel with the tile images taken from the ring, the suffix
 // handled after the prefix, and a fixed per-row reference maximum; when a row turns out to
 // need rescaling, the workgroup repeats its passes on the general path.  The general one
 // (any shape) is the classic online softmax, one tile at a time.  The third (further down) is
 // for suffix-side segments of several tiles: its passes are cut out of one candidate, whose own
-// suffix K/V then goes through the ring like the prefix.
+// suffix K/V then goes through the ring like the prefix.  The fourth is the third with passes of half the size, two at
+// a time on a compute unit.
 // Operand layouts and the pieces shared with the resident kernels are in pskv_mfma.hpp.
 #include "pskv_mfma.hpp"
 
@@ -56,6 +57,7 @@ __device__ inline Ctx make_stream_ctx(const Args &a, lds_u8 *smem, int tid)
 // of the workgroup must call it (barriers inside), whether or not its wavefront has a block.
 // cand, rows_c: with rows_c > 0, blk counts within that candidate of the instruction, a problem of its own.
 // ------------------------------------------------------------------------------------------
+template <int THREADS = 512>
 __device__ __attribute__((always_inline)) void general_pass(const Args &a, Ctx &X, lds_u8 *smem, int tid, int vh, int blk,
                                                             bool active, int cand = 0, int rows_c = 0)
 {
@@ -65,7 +67,11 @@ __device__ __attribute__((always_inline)) void general_pass(const Args &a, Ctx &
         X.Mtot = rows_c;
     }
     const int ntiles = (X.P + kTileKeys - 1) / kTileKeys;
-    const TileSlot t = make_tile_slot(tid);
+    constexpr int kParts = 512 / THREADS; // chunks of a tile's K, and of its V, per thread
+    TileSlot t[kParts];
+#pragma unroll
+    for (int i = 0; i < kParts; ++i)
+        t[i] = make_tile_slot(tid + i * THREADS);
     const int r0 = blk * kBlockRows;
     const Row row = decode_row(a, X, blk);
     const bool rvalid = active && row.rin && (int)row.ri < clamp_len(a, row.rlen);
@@ -83,21 +89,28 @@ __device__ __attribute__((always_inline)) void general_pass(const Args &a, Ctx &
             st.o[dt][e] = 0.f;
 
     if (ntiles > 0) {
-        uintx4 kv, vv;
-        load_tile_chunks(a, X, t, 0, kv, vv);
+        uintx4 kv[kParts], vv[kParts];
+        auto load = [&](int kt) {
+#pragma unroll
+            for (int i = 0; i < kParts; ++i)
+                load_tile_chunks(a, X, t[i], kt, kv[i], vv[i]);
+        };
+        auto write = [&](int kt, lds_u8 *slot) {
+#pragma unroll
+            for (int i = 0; i < kParts; ++i)
+                write_tile_chunks(X, t[i], kt, slot, slot + kTileBytes, tid + i * THREADS, kv[i], vv[i]);
+        };
+        load(0);
         __syncthreads(); // whatever the ring held has been used by every wavefront
-        write_tile_chunks(X, t, 0, smem, smem + kTileBytes, tid, kv, vv);
+        write(0, smem);
         __syncthreads();
         for (int kt = 0; kt < ntiles; ++kt) {
-            const int ktn = kt + 1 < ntiles ? kt + 1 : kt;
-            load_tile_chunks(a, X, t, ktn, kv, vv);
+            load(kt + 1 < ntiles ? kt + 1 : kt);
             if (work)
                 prefix_tile_classic(X, X.k_lane + (kt & 1) * kSlotBytes, X.v_lane + (kt & 1) * kSlotBytes,
                                     X.P - kt * kTileKeys, q, st);
-            if (kt + 1 < ntiles) {
-                lds_u8 *slot = smem + ((kt + 1) & 1) * kSlotBytes;
-                write_tile_chunks(X, t, kt + 1, slot, slot + kTileBytes, tid, kv, vv);
-            }
+            if (kt + 1 < ntiles)
+                write(kt + 1, smem + ((kt + 1) & 1) * kSlotBytes);
             __syncthreads();
         }
     }
@@ -742,6 +755,342 @@ void stream_candidate_kernel(Args a, int npasses, CandShape cs)
         }
 }
 
+// ------------------------------------------------------------------------------------------
+// Candidate passes of four blocks: workgroups of four wavefronts, two on a compute unit, so that one works while the
+// other one waits for the first tiles of a pass, stores, or meets at the end of a pass - half of the time of a pass of
+// eight, which nothing covers there.
+//
+// K and V have rings of their own, five tiles each, half images (pskv_mfma.hpp) filled by direct-to-LDS
+// requests: 8 rows x 128 bytes each, 17 cycles of a compute unit where 32 rows x 32 bytes take 58, which at one
+// request per 128 rows of queries instead of 256 would fill its address units.  Wavefronts 0 and 1
+// fetch K (64 columns each), 2 and 3 V.  With s(t) the step of tile t, which reads K t+1 (and the beginning of t+2)
+// and V t-1 (and the beginning of V t): barriers stand before the steps t = 1, 3, 5, ..., where everything requested before
+// has landed.  Requested there, for the next pair: K t+4, t+5 - the slots of K t-1 and t, read before - and V t+2, t+3 -
+// of V t-3 and t-2.  What the pair reads, K up to t+3 and V up to t+1, was requested a pair ago; tiles 0 .. 4 when the
+// pass begins.
+//
+// What bounds it: instruction issue - a step is 16 matrix instructions and 64 vector ones, 32 more where
+// the step masks - and the two wavefronts of a SIMD being served unevenly.  256 candidates x 128..160 positions, 28/4
+// heads, P 128: 213 us in passes of eight, 197 us here; 300 x 96, 32/8, P 512: 388, 307.  (With a register spill in the steps
+// 350: its reload waits for all requests in flight.  Hence the lane's places worked out by exclusive ors from two
+// registers, and nothing else held that a step does not need.)
+// ------------------------------------------------------------------------------------------
+constexpr int kCW = 4;                          // wavefronts
+constexpr int kCRing = 5;                       // tiles of K, and of V, in LDS
+constexpr int kCLdsBytes = 2 * kCRing * kTileBytes; // half of a compute unit's
+
+// pipe_tile with the images as half images (two per tile of K or V).  The lane's addresses in an image are
+// worked out once, by the step that reads its first fragments, and handed on.
+struct HalfPre {
+    uintx4 k[kDist];
+    bf16x8 v[kDist];
+    unsigned ka[4], va[2][2]; // of the K image read next, of the V image read next
+};
+__device__ inline uintx4 k_frag(const unsigned (&at)[4], int i) { return *(lds_u128 *)(lds_at(at[i & 3]) + (i >> 2) * kHalfBytes); }
+__device__ inline bf16x8 v_frag(const unsigned (&at)[2][2], int i)
+{
+    const int dt = i & 3, j = i >> 2;
+    const int off = (dt >> 1) * kHalfBytes + j * 2048;
+    short4v lo = lds_read_tr(lds_at(at[dt & 1][0]) + off), hi = lds_read_tr(lds_at(at[dt & 1][1]) + off + 1024);
+    short8v v8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    bf16x8 f;
+    __builtin_memcpy(&f, &v8, 16);
+    return f;
+}
+__device__ inline void k_places(const HalfPlaces &hp, unsigned img, unsigned (&at)[4])
+{
+    unsigned first = hp.row + img;
+    asm volatile("" : "+v"(first));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        at[i] = first ^ (i << 5);
+}
+__device__ inline void v_places(const HalfPlaces &hp, unsigned img, unsigned (&at)[2][2])
+{
+    unsigned first = hp.col + img;
+    asm volatile("" : "+v"(first));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        at[i >> 1][i & 1] = first ^ ((i >> 1) << 6) ^ ((i & 1) << 7);
+}
+template <bool HAS_QK, bool HAS_PV, bool FRESH, bool MASK, bool NEXT_K, bool NEXT_V>
+__device__ __attribute__((always_inline)) void pipe_half(const HalfPlaces &hp, unsigned k_after, unsigned v_cur, HalfPre &pre, const uintx4 (&q)[8],
+                                                         const floatx16 &s, floatx16 &sn, float c, float m, int lim, float &l,
+                                                         const uintx4 (&pp)[2], uintx4 (&pc)[2], floatx16 (&o)[4])
+{
+    uintx4 kfr[8];
+    bf16x8 vfr[8];
+    unsigned pk[8];
+    float rs = 0.f;
+    if (HAS_QK) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            sn[e] = 0.f;
+#pragma unroll
+        for (int i = 0; i < kDist; ++i)
+            kfr[i] = pre.k[i];
+    }
+    if (HAS_PV) {
+#pragma unroll
+        for (int i = 0; i < kDist; ++i)
+            vfr[i] = pre.v[i];
+    }
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+        if (HAS_QK && ks + kDist < 8)
+            kfr[ks + kDist] = k_frag(pre.ka, ks + kDist);
+        if (HAS_PV && ks + kDist < 8)
+            vfr[ks + kDist] = v_frag(pre.va, ks + kDist);
+        if (NEXT_K && ks == 8 - kDist)
+            k_places(hp, k_after, pre.ka);
+        if (NEXT_V && ks == 8 - kDist)
+            v_places(hp, v_cur, pre.va);
+        if (NEXT_K && ks >= 8 - kDist)
+            pre.k[ks - (8 - kDist)] = k_frag(pre.ka, ks - (8 - kDist));
+        if (NEXT_V && ks >= 8 - kDist)
+            pre.v[ks - (8 - kDist)] = v_frag(pre.va, ks - (8 - kDist));
+        if (HAS_QK)
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kfr[ks]), as_bf16x8(q[ks]), sn, 0, 0, 0);
+        if (HAS_PV) {
+            floatx16 acc = o[ks & 3];
+            if (FRESH && ks < 4) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    acc[e] = 0.f;
+            }
+            o[ks & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[ks], as_bf16x8(pp[ks >> 2]), acc, 0, 0, 0);
+        }
+        float s0 = s[2 * ks], s1 = s[2 * ks + 1];
+        if (MASK) {
+            s0 = 8 * ((2 * ks) >> 2) + ((2 * ks) & 3) <= lim ? s0 : -INFINITY;
+            s1 = 8 * ((2 * ks + 1) >> 2) + ((2 * ks + 1) & 3) <= lim ? s1 : -INFINITY;
+        }
+        const float p0 = fast_exp2(__builtin_fmaf(s0, c, -m));
+        const float p1 = fast_exp2(__builtin_fmaf(s1, c, -m));
+        pk[ks] = pack_bf16(p0, p1);
+        rs += p0;
+        rs += p1;
+        asm volatile("" : "+v"(rs), "+v"(pk[ks]));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    l += rs;
+    pc[0] = uintx4{pk[0], pk[1], pk[2], pk[3]};
+    pc[1] = uintx4{pk[4], pk[5], pk[6], pk[7]};
+}
+
+template <bool WHOLE>
+__global__ __attribute__((amdgpu_flat_work_group_size(kCW * 64, kCW * 64), amdgpu_waves_per_eu(2, 2)))
+void stream_candidate4_kernel(Args a, int npasses, CandShape cs)
+{
+    extern __shared__ __align__(256) unsigned char smem_generic[];
+    lds_u8 *smem = (lds_u8 *)smem_generic;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    Ctx X = make_stream_ctx(a, smem, tid);
+    X.scr = smem + wave * kScrBytes; // (in the ring of K, which is free when a block is stored)
+    const HalfPlaces hp = half_places(X.lane);
+    const int rows_c = a.S * a.G; // rows of a candidate
+    auto decode = [&](const CandPass &ps) __attribute__((always_inline)) {
+        return decode_own<WHOLE>(a, X, ps.blk, ps.head, ps.cand0, ps.b - ps.cand0, cs.nblk_c);
+    };
+    auto block_in_cand = [&](const CandPass &ps) { return ps.blk - (ps.b - ps.cand0) * cs.nblk_c; };
+    auto block_rows = [&](const CandPass &ps) { return WHOLE ? kBlockRows : rows_c - block_in_cand(ps) * kBlockRows; };
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane(lds_addr(smem));
+    auto kimg = [&](int t) { return lds0 + ((unsigned)t % kCRing) * kTileBytes; };
+    auto vimg = [&](int t) { return lds0 + (kCRing + (unsigned)t % kCRing) * kTileBytes; };
+
+    // Staging: this wavefront's image of a tile (K or V, columns 0..63 or 64..127), four pieces of 8 rows x 128 bytes, as half_put
+    // would put them: the lane's row and 16-byte chunk in even and in odd pieces.
+    auto row_of = [&](int lane, int g) { return ((unsigned)lane >> 3) ^ (g & 1); };
+    auto col_of = [&](int lane, int g) { return ((((unsigned)lane & 7u) ^ half_swz(row_of(lane, g))) << 4) + 128u * (wave & 1); };
+    lds_u8 *const ring = smem + (wave < 2 ? 0 : kCRing * kTileBytes) + (wave & 1) * kHalfBytes;
+    const unsigned pre_stride = (unsigned)a.kp_sp * 2u, own_stride = (unsigned)a.ks_ss * 2u; // bytes per row
+    const unsigned pre_e = row_of(X.lane, 0) * pre_stride + col_of(X.lane, 0), pre_o = row_of(X.lane, 1) * pre_stride + col_of(X.lane, 1);
+    const unsigned own_e = row_of(X.lane, 0) * own_stride + col_of(X.lane, 0), own_o = row_of(X.lane, 1) * own_stride + col_of(X.lane, 1);
+
+    bool bad = false, wg_short = false;
+    int p = blockIdx.x;
+    CandPass ps = make_cand_pass(a, cs, p, npasses, wave);
+    BlockRows nxt = decode(ps);
+    uintx4 q[8]; // this pass's Q fragments until their last use, then the next pass's
+    load_q_block(a, X, nxt, q);
+
+    while (p < npasses) {
+        set_vhead(a, X, ps.vh);
+        const int Tp = (X.P + kTileKeys - 1) / kTileKeys;
+        const int len = len_uniform(a, ps.b);
+        const int i_lo = (int)fdiv(ps.cblk0 * kBlockRows, a.div_g); // first suffix position of the pass
+        const bool nothing = !ps.exists || i_lo >= len;             // no unit, or nothing but padding
+        if (nothing || Tp < kMinTiles) {
+            if (!nothing)
+                wg_short = true; // prefix too short for the pipeline: left to the general sweep below
+            else if (ps.active)
+                store_zero_block_rows(a, X, nxt, block_rows(ps));
+            p += gridDim.x;
+            ps = make_cand_pass(a, cs, p, npasses, wave);
+            nxt = decode(ps);
+            load_q_block(a, X, nxt, q);
+            continue;
+        }
+        const int i_hi = (int)fdiv(ps.cblk_last * kBlockRows + kBlockRows - 1, a.div_g);
+        const int skmax = i_hi < len - 1 ? i_hi : len - 1;
+        const int T = Tp + skmax / kTileKeys + 1;
+        const unsigned char *const pre_base = reinterpret_cast<const unsigned char *>(wave < 2 ? X.kpg : X.vpg);
+        const unsigned char *const own_base = reinterpret_cast<const unsigned char *>(wave < 2 ? X.ksg : X.vsg) + (long long)ps.b * a.ks_sb * 2;
+        auto request = [&](int u) { // this wavefront's part of tile u
+            const bool own = u >= Tp;
+            const unsigned stride = own ? own_stride : pre_stride;
+            const int first = (own ? u - Tp : u) * kTileKeys, last = own ? skmax : X.P - 1;
+            const unsigned char *base = own ? own_base : pre_base;
+            lds_u8 *img = ring + ((unsigned)u % kCRing) * kTileBytes;
+            if (first + kTileKeys - 1 <= last) {
+                base += (unsigned long long)(unsigned)first * stride;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    request_to_lds(base, own ? (g & 1 ? own_o : own_e) : (g & 1 ? pre_o : pre_e), img + g * 1024);
+                    base += 8 * stride;
+                }
+            } else { // (the last row stands in for those behind it: never visible)
+                int lane = X.lane;
+                asm volatile("" : "+v"(lane)); // (nothing of this is held across the steps)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int row = first + 8 * g + (int)row_of(lane, g);
+                    request_to_lds(base, (unsigned)(row < last ? row : last) * stride + col_of(lane, g), img + g * 1024);
+                }
+            }
+        };
+        const BlockRows row = nxt;
+        const int cblk = block_in_cand(ps), rows = block_rows(ps);
+        const int i_lo_w = (int)fdiv(cblk * kBlockRows, a.div_g);
+        const int i_hi_w = (int)fdiv(cblk * kBlockRows + kBlockRows - 1, a.div_g);
+        const bool active = ps.active && i_lo_w < len;
+        const int Tw = Tp + (i_hi_w < skmax ? i_hi_w : skmax) / kTileKeys + 1;
+        const bool rvalid = active && row.ri < row.len;
+
+        // The rings are free here (the barrier that ended the previous pass).
+#pragma unroll
+        for (int u = 0; u < kCRing; ++u)
+            if (u < T)
+                request(u);
+        if (T >= kCRing)
+            PSKV_WAIT_VM(8);
+        else
+            PSKV_WAIT_VM(0);
+        __syncthreads();
+        auto top = [&](int t) { // of the steps t and t+1, t odd
+            PSKV_WAIT_VM(0);
+            __syncthreads();
+            const int u = wave < 2 ? t + 4 : t + 2;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                if (u + i >= kCRing && u + i <= T - 1)
+                    request(u + i);
+        };
+
+        const int lim_suffix = row.ri - 4 * X.h + Tp * kTileKeys;
+        const int lim_last_prefix = X.P - (Tp - 1) * kTileKeys - 1 - 4 * X.h;
+        auto lim_of = [&](int t) { return t >= Tp ? lim_suffix - t * kTileKeys : (t == Tp - 1 ? lim_last_prefix : 1 << 20); };
+        const int tm = X.P / kTileKeys; // first tile with keys that some row does not see (>= 2)
+
+        if (!active) { // takes part in the staging and in the barriers only
+            for (int t = 1; t <= T - 1; t += 2)
+                top(t);
+            if (ps.active)
+                store_zero_block_rows(a, X, row, rows);
+            p += gridDim.x;
+            ps = make_cand_pass(a, cs, p, npasses, wave);
+            nxt = decode(ps);
+            load_q_block(a, X, nxt, q);
+            __syncthreads(); // ends the pass
+            continue;
+        }
+        float l = 0.f;
+        floatx16 o[4];
+        floatx16 sA, sB;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            sA[e] = 0.f;
+        HalfPre pre;
+        k_places(hp, kimg(0), pre.ka);
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
+            sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(k_frag(pre.ka, ks)), as_bf16x8(q[ks]), sA, 0, 0, 0);
+        k_places(hp, kimg(1), pre.ka);
+#pragma unroll
+        for (int i = 0; i < kDist; ++i)
+            pre.k[i] = k_frag(pre.ka, i);
+        float m = sA[0];
+#pragma unroll
+        for (int e = 1; e < 16; ++e)
+            m = fmaxf(m, sA[e]);
+        m = fmaxf(m, __shfl_xor(m, 32, 64)) * X.c;
+        uintx4 pA[2], pB[2];
+        pipe_half<true, false, false, false, true, true>(hp, kimg(2), vimg(0), pre, q, sA, sB, X.c, m, 0, l, pA, pA, o);
+#define PSKV_CAND4_PAIR(FRESH, MASK1, MASK2)                                                                                  \
+    do {                                                                                                                     \
+        top(t);                                                                                                              \
+        pipe_half<true, true, FRESH, MASK1, true, true>(hp, kimg(t + 2), vimg(t), pre, q, sB, sA, X.c, m, lim_of(t), l, pA, \
+                                                         pB, o);                                                             \
+        pipe_half<true, true, false, MASK2, true, true>(hp, kimg(t + 3 < Tw ? t + 3 : Tw - 1), vimg(t + 1), pre, q, sA, sB, \
+                                                         X.c, m, lim_of(t + 1), l, pB, pA, o);                               \
+    } while (0)
+        int t = 1;
+        PSKV_CAND4_PAIR(true, false, true); // (tile 2 may be the prefix's ragged last one)
+        t = 3;
+        for (; t + 1 <= Tw - 2 && t + 1 < tm; t += 2)
+            PSKV_CAND4_PAIR(false, false, false);
+        for (; t + 1 <= Tw - 2; t += 2)
+            PSKV_CAND4_PAIR(false, true, true);
+#undef PSKV_CAND4_PAIR
+        top(t); // (t: Tw - 2 or Tw - 1, in either case the last pair's first step)
+        if (t <= Tw - 2) {
+            pipe_half<true, true, false, true, false, true>(hp, 0, vimg(t), pre, q, sB, sA, X.c, m, lim_of(t), l, pA, pB, o);
+            sB = sA;
+            pA[0] = pB[0];
+            pA[1] = pB[1];
+            ++t;
+        }
+        // Q has been used for the last time: the next pass's Q takes its place
+        p += gridDim.x;
+        ps = make_cand_pass(a, cs, p, npasses, wave);
+        nxt = decode(ps);
+        load_q_block(a, X, nxt, q);
+        // ---- last tile: its weights under the value product of the tile before, then its own ----
+        pipe_half<false, true, false, true, false, false>(hp, 0, 0, pre, q, sB, sB, X.c, m, lim_of(Tw - 1), l, pA, pB, o);
+        v_places(hp, vimg(Tw - 1), pre.va);
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_frag(pre.va, i), as_bf16x8(pB[i >> 2]), o[i & 3], 0, 0, 0);
+        // staging for the wavefronts whose blocks see further (before this wavefront's store: they are the ones the pass
+        // is waiting for)
+        for (t = Tw | 1; t <= T - 1; t += 2)
+            top(t);
+        // (the slots of K that tiles T and T + 1 would take: nobody reads there any more)
+        X.scr = smem + ((unsigned)(T + (wave >> 1)) % kCRing) * kTileBytes + (wave & 1) * kScrBytes;
+        bad |= __builtin_amdgcn_ballot_w64(rvalid && !(l < kBig)) != 0;
+        store_block_rows(a, X, row, m, l, o, rows);
+        __syncthreads(); // ends the pass: the rings are free
+    }
+
+    // The general sweep, as in the pipelined kernel above.
+    if (X.lane == 0)
+        *(lds_int *)(smem + wave * 4) = bad ? 1 : 0;
+    __syncthreads();
+    const bool wg_bad = __builtin_amdgcn_ballot_w64(*(lds_int *)(smem + (X.lane & (kCW - 1)) * 4) != 0) != 0;
+    __syncthreads();
+    if (wg_bad || wg_short) {
+        X.scr = smem + 2 * kSlotBytes + wave * kScrBytes;
+        for (int p2 = blockIdx.x; p2 < npasses; p2 += gridDim.x) {
+            const CandPass ps2 = make_cand_pass(a, cs, p2, npasses, wave);
+            set_vhead(a, X, ps2.vh);
+            if (ps2.exists && (wg_bad || (X.P + kTileKeys - 1) / kTileKeys < kMinTiles))
+                general_pass<kCW * 64>(a, X, smem, tid, ps2.vh, WHOLE ? ps2.blk : block_in_cand(ps2), ps2.active, WHOLE ? 0 : ps2.b - ps2.cand0,
+                                       WHOLE ? 0 : rows_c);
+        }
+    }
+}
+
 int device_cu_count(hipError_t &e)
 {
     static DeviceSlots cu_by_device;
@@ -752,6 +1101,9 @@ int device_cu_count(hipError_t &e)
                             stream_pipelined_kernel<false, false>})
             if (s == hipSuccess)
                 s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        for (auto kernel : {stream_candidate4_kernel<true>, stream_candidate4_kernel<false>})
+            if (s == hipSuccess)
+                s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kCLdsBytes);
         for (auto kernel : {stream_candidate_kernel<true>, stream_candidate_kernel<false>})
             if (s == hipSuccess)
                 s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
@@ -785,25 +1137,32 @@ hipError_t launch_mfma(const Args &a, hipStream_t stream)
     const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
     const bool whole = (long long)a.S * a.G % kBlockRows == 0;
     bool long_suffix = a.S > kTileKeys && max_tiles >= kMinTiles && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL;
-    // Rows that fill no whole number of blocks: only where the candidate passes come out full to three quarters, and
-    // their rounds of the chip are no more than the blocks that a wavefront of the resident general kernel has, or
-    // one and a half times as many with more than four own steps, which that kernel takes one by one.  us, resident
-    // general kernel and candidate passes: P 128: 16 candidates x 90 positions (32/8 heads, 12 blocks in 2 passes of 8; 1
-    // block, 1 round): 16, 12; P 205: 21 x 118 (32/4; 2, 2): 32.8, 26.8; P 70: 124 x 87 (32/4; 6, 6): 58.9, 51.9; beyond: P
-    // 169: 49 x 74 (32/4; 2, 3): 28.7, 31.0; P 145: 247 x 22 .. 45 (32/8; 6, 8): 57, 74; P 164: 161 x 113 (32/4; 9, 11):
-    // 114, 133; with more than four steps: P 222: 37 x 158 (28/4; 3, 3): 56, 45; P 93: 73 x 147 (32/8; 6, 7): 84.6, 67.7; P
-    // 72: 188 x 155 (28/4; 13, 15): 164, 143; beyond: P 147: 17 x 136 (28/4; 1, 2): 20.5, 23.6.  Less than three quarters:
-    // 64 x 141 (32/32, 5 in 1, P 128): 81, 101; with the pipelined passes 128 x 70 (32/8, 9 in 2): 49, 62.
+    // Rows that fill no whole number of blocks: only where the candidate passes come out full to three quarters, and what a
+    // compute unit then takes of them is no more than the blocks that a wavefront of the resident general kernel has (one and
+    // a half times as many with more than four own steps, which that kernel takes one by one).  us, resident
+    // general kernel and candidate passes: passes of eight (their rounds of the chip after the blocks): P 128: 16 candidates
+    // x 90 positions (32/8 heads; 1, 1): 16, 12; P 205: 21 x 118 (32/4; 2, 2): 32.8, 26.8; P 70: 124 x 87 (32/4; 6, 6):
+    // 58.9, 51.9; beyond: P 169: 49 x 74 (32/4; 2, 3): 28.7, 31.0; P 145: 247 x 22 .. 45 (32/8; 6, 8): 57, 74; with more
+    // than four steps: P 222: 37 x 158 (28/4; 3, 3): 56, 45; P 93: 73 x 147 (32/8; 6, 7): 84.6, 67.7; beyond: P 147: 17 x 136
+    // (28/4; 1, 2): 20.5, 23.6.  Less than three quarters: 64 x 141 (32/32, 5 blocks in 8, P 128): 81, 101.
+    // Passes of four, two at a time (how many a compute unit takes after the blocks): P 169: 21 x 88 (28/4; 1, 2): 18.5, 14.5;
+    // P 213: 153 x 78 (28/4; 6, 13): 80, 74; P 162: 79 x 122 (32/32; 5, 10): 79, 67; P 121: 111 x 79 (32/8; 5, 11): 56, 48; P 245:
+    // 28 x 135 (32/8; 2, 5): 39.3, 34.5; beyond: P 164: 161 x 113 (32/4; 9, 21): 112, 128; P 251: 250 x 94 (28/4; 11, 24):
+    // 149, 160; P 178: 253 x 59 (28/4; 7, 16): 82, 93; full to 5/8: P 239: 153 x 133 (32/32): 216, 281.  (Up to two
+    // own steps the lines of the passes of eight hold.)
     if (long_suffix && !whole && resident_supported(a)) {
         hipError_t e;
         const int num_cu = device_cu_count(e);
         if (e != hipSuccess)
             return e;
-        const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows, ngrp = (nb + kNW - 1) / kNW;
-        const long long passes = ((long long)a.B * a.Hkv + 7) / 8 * 8 * ngrp, rounds = (passes + num_cu - 1) / num_cu;
+        const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows;
+        const long long units = ((long long)a.B * a.Hkv + 7) / 8 * 8, ngrp8 = (nb + kNW - 1) / kNW, ngrp4 = (nb + kCW - 1) / kCW;
+        const long long r8 = (units * ngrp8 + num_cu - 1) / num_cu, r4 = (units * ngrp4 + num_cu - 1) / num_cu; // passes per compute unit
         const long long each = resident_split(a, (a.C * rows_c + kBlockRows - 1) / kBlockRows, kNW, num_cu).each;
-        long_suffix = own_blocks_fit(a) && block_offsets_fit(a) && nb * 4 >= ngrp * kNW * 3 && (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL &&
-                      rounds * 2 <= each * (a.S > 4 * kTileKeys ? 3 : 2);
+        const bool many = a.S > 4 * kTileKeys;
+        const bool eight = nb * 4 >= ngrp8 * kNW * 3 && r8 * 2 <= each * (many ? 3 : 2);
+        const bool four = nb * 4 >= ngrp4 * kCW * 3 && a.S * 5 > 12 * kTileKeys && r4 * 10 <= each * (many ? 28 : max_tiles < kNW ? 22 : 20);
+        long_suffix = own_blocks_fit(a) && block_offsets_fit(a) && (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL && (eight || four);
     }
     return resident_supported(a) && !long_suffix ? launch_resident(a, stream) : launch_stream(a, stream);
 }
@@ -820,25 +1179,42 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
     bool pipelined = own_blocks_fit(a) && max_tiles >= kMinTiles && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && block_offsets_fit(a);
     auto rounds = [&](long long passes) { return (passes + num_cu - 1) / num_cu; };
     const long long full_rounds = rounds(stream_pass_ids(a));
-    // Long suffix-side segments whose candidates fill most of a workgroup's eight wavefronts
-    // take the candidate passes.
+    // Long suffix-side segments: candidate passes of eight blocks, candidate passes of four, two at a time on a compute
+    // unit, or the pipelined passes, whose blocks fetch their own keys by themselves.
+    // Passes of eight (60 % full and more) only where a compute unit takes twice as many passes of four: they fetch the tiles
+    // half as often.  us, of eight and of four, 32/8 heads (what a compute unit takes of either): 300 candidates: P 1500: 128
+    // positions (19, 38): 924, 960; 64 (10, 19): 474, 458; 96 (19, 29): 869, 711; P 512: 104 (19, 38): 386, 400; 64: 205,
+    // 190; 96: 388, 307; 24 candidates x 64 (1, 2): P 1500: 44.8, 46.4; P 512: 21.2, 21.5; P 128: 300 x 120 (19, 38): 205,
+    // 213; 300 x 64: 96, 88; P 206: 18 x 49 (32/4; 1, 2): 13.0, 14.4.
+    // Pipelined passes against passes of four: the former lose some three tiles' time to the own keys.  us (rounds of the chip;
+    // passes of four per compute unit): 250 candidates, P 600: 128 positions, 32/32 heads (16, 32): 508, 427; 96 (12, 32): 358,
+    // 389; 72, 32/8 (9, 24): 221, 246; 88 (11, 24): 353 in passes of eight, 275; P 1500: 39 x 28/4 (5, 12): 239, 263; P 300:
+    // 96, 32/32 (12, 32): 263, 249; P 128: 215, 177; 64 candidates, P 1500, 39 x 28/4 (2, 3): 87, 70; 300 x 40, 32/8, P 512 (6,
+    // 19): 121, 153.
+    // Rows that fill no whole number of blocks: against the general passes, as long as there are hardly more of the others
+    // and up to 1024 prefix rows (short prefixes come here for the candidate passes: launch_mfma has their rule).  us, general
+    // and passes of eight (rounds of the chip): 64 x 109 (32/8, P 464; 4, 4): 121, 84; 50 x 148 (32/8, P 424; 4, 5): 105,
+    // 81; 12 x 156 (32/32, P 2018; 1, 2): 84, 103; 245 x 34 (32/8, P 676; 5, 8): 169, 161 (pipelined passes 131).
     if (pipelined && a.S > kTileKeys && (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL) {
-        CandShape cs;
-        const long long nblk_c = nb;
-        cs.nblk_c = (int)nblk_c;
-        cs.ngrp = (int)((nblk_c + kNW - 1) / kNW);
-        // Full passes first; the last one takes what is left.  With up to four blocks left every
-        // SIMD has at most one busy wavefront in it and the pass runs twice as fast.
-        cs.bpp = cs.nblk_c < kNW ? cs.nblk_c : kNW;
-        const long long units = (long long)a.B * a.Hkv;
-        const long long cpasses = (units + 7) / 8 * 8 * cs.ngrp;
-        // Rows that fill no whole number of blocks: a candidate pass takes 0.7 of a general pass' time, and there are
-        // more of them (short prefixes come here for these passes: launch_mfma has their rule).  us, general and candidate passes (rounds of the chip): 64 candidates x 109 positions (32/8 heads, P
-        // 464; 4, 4): 121, 84; 50 x 148 (32/8, P 424; 4, 5): 105, 81; 12 x 156 (32/32, P 2018; 1, 2): 84, 103; 34 x 111
-        // (28/4, P 1114; 2, 3): 100, 104; 245 x 34 (32/8, P 676; 5, 8): 169, 161 (pipelined passes 131).
-        if (nblk_c * 10 >= (long long)cs.ngrp * kNW * 6 && cpasses <= 0x7fffffffLL - 8 && (whole || resident_supported(a) || rounds(cpasses) * 7 <= full_rounds * 10)) {
-            const unsigned cgrid = (unsigned)(cpasses < num_cu ? cpasses : num_cu);
-            return launch_kernel(whole ? stream_candidate_kernel<true> : stream_candidate_kernel<false>, dim3(cgrid), dim3(kNW * 64), kLdsBytes, stream, a, (int)cpasses, cs);
+        const long long units = ((long long)a.B * a.Hkv + 7) / 8 * 8;
+        auto shape = [&](int waves) { return CandShape{(int)nb, (int)((nb + waves - 1) / waves), nb < waves ? (int)nb : waves}; };
+        const CandShape c8 = shape(kNW), c4 = shape(kCW);
+        const long long passes8 = units * c8.ngrp, passes4 = units * c4.ngrp;
+        const long long r8 = rounds(passes8), r4 = rounds(passes4), rp = rounds(stream_pass_ids(a, a.C * nb));
+        const bool any = whole || resident_supported(a);
+        const bool fit8 = nb * 10 >= (long long)c8.ngrp * kNW * 6 && passes8 <= 0x7fffffffLL - 8 && (any || r8 * 7 <= full_rounds * 10);
+        const bool eight = fit8 && r4 >= 2 * r8;
+        const bool four = !eight && passes4 <= 0x7fffffffLL - 2 * num_cu && r4 * max_tiles <= 2 * rp * (max_tiles + 3) &&
+                          (any || fit8 || (r4 * 10 <= full_rounds * 22 && a.P <= 1024));
+        if (eight) {
+            const unsigned grid = (unsigned)(passes8 < num_cu ? passes8 : num_cu);
+            return launch_kernel(whole ? stream_candidate_kernel<true> : stream_candidate_kernel<false>, dim3(grid), dim3(kNW * 64), kLdsBytes, stream, a,
+                                 (int)passes8, c8);
+        }
+        if (four) {
+            const unsigned grid = (unsigned)(passes4 < 2 * num_cu ? passes4 : 2 * num_cu);
+            return launch_kernel(whole ? stream_candidate4_kernel<true> : stream_candidate4_kernel<false>, dim3(grid), dim3(kCW * 64), kCLdsBytes, stream, a,
+                                 (int)passes4, c4);
         }
     }
     // Own blocks make more passes, each in 0.7 of the general kernel's time, 0.8 with the second own step: not where
