@@ -1137,7 +1137,7 @@ __device__ __attribute__((always_inline)) void bwd_dkv_unit(const BwdArgs &g, ld
 
 template <bool HAS_DELTA, bool FIT>
 __global__ __attribute__((amdgpu_flat_work_group_size(kDkvWaves * 64, kDkvWaves * 64), amdgpu_waves_per_eu(2, 4)))
-void bwd_dkv_mfma_kernel(BwdArgs g, int nkt)
+void bwd_dkv_mfma_kernel(BwdArgs g, int nkt, int down)
 {
     extern __shared__ __align__(256) unsigned char smem_generic[];
     lds_u8 *smem = (lds_u8 *)smem_generic;
@@ -1147,9 +1147,11 @@ void bwd_dkv_mfma_kernel(BwdArgs g, int nkt)
     // consecutive ids on ONE of them, so that they run there at the same time and share its L2.
     const int x = blockIdx.x & 7, y = blockIdx.x >> 3;
     const int grp = y / nkt, kt = y - grp * nkt;
-    const long long bk = (long long)grp * 8 + x;
-    if (bk >= (long long)g.f.B * g.f.Hkv) // the pairs are padded to a multiple of 8 (the same for the whole workgroup)
+    long long bk = (long long)grp * 8 + x;
+    const long long pairs = (long long)g.f.B * g.f.Hkv;
+    if (bk >= pairs) // the pairs are padded to a multiple of 8 (the same for the whole workgroup)
         return;
+    bk = down ? pairs - 1 - bk : bk;
     // (wave-uniform branch; both sides meet the same workgroup barriers the same number of times)
     if (__builtin_amdgcn_readfirstlane(tid >> 6))
         bwd_dkv_unit<1, HAS_DELTA, FIT>(g, smem, tid, (int)bk, kt);
@@ -1174,7 +1176,13 @@ hipError_t launch_bwd_dkv_mfma(const BwdArgs &g, hipStream_t stream)
     const bool fit = block_offsets_fit(a);
     auto kernel = g.delta ? (fit ? bwd_dkv_mfma_kernel<true, true> : bwd_dkv_mfma_kernel<true, false>)
                           : (fit ? bwd_dkv_mfma_kernel<false, true> : bwd_dkv_mfma_kernel<false, false>);
-    return launch_kernel(kernel, dim3((unsigned)nunits), dim3(kDkvWaves * 64), kDkvLdsBytes, stream, g, nkt);
+    // Where the tensors of query rows do not fit the last-level cache (256 MB), the pairs go from the last one down: what the dq
+    // kernel has just read, the last candidates' q and dout, is still there.  us for the whole backward pass, upwards and
+    // downwards: 1024 candidates x 16..24 positions x 4 heads, 8 KV heads, P 256 (805 MB of q, dout, out and dq): 300, 294; 1045
+    // x 31 x 7, 4 KV heads, P 52 (930 MB): 326, 316; 244 x 77 x 4, 8 KV heads, P 203 (615 MB): 286, 280; 589 x 25 x 7,
+    // 4 KV heads, P 753 (422 MB): 326, 325; 82 x 25 x 4, 8 KV heads, P 43 (67 MB): 28.9, 29.5.
+    const int down = (double)a.B * a.S * a.Hq * a.D * 2 * 4 > 512e6;
+    return launch_kernel(kernel, dim3((unsigned)nunits), dim3(kDkvWaves * 64), kDkvLdsBytes, stream, g, nkt, down);
 }
 
 hipError_t noalloc_scratch(void **ptr)
