@@ -20,9 +20,8 @@
 // 256 candidates of 5 to 33 rows, 177 prefix rows, 14/2 heads: 300 us in the vector kernel, 20.1 us here, of which the prefix
 // takes 4 and the tiles 6 to 13: two to four wavefronts of a SIMD have a block of their own, and a tile takes
 // 1300 cycles of one, the sum of its matrix instructions (512) and of its vector ones.  (22.4 us with the prefix
-// copied through registers, 32 bytes of a row at a time, and transposed in LDS; blocks that straddle
-// candidates spread over the chip, so that blocks of padding come to all of it alike, and the first tile's
-// maximum taken without trying it as a later tile: 1 us of these.)
+// copied through registers, 32 bytes of a row at a time, and transposed in LDS, and the first tile tried as a later
+// one before its maximum was taken: 0.7 us of these.)
 #include "pskv_mfma.hpp"
 #include <type_traits>
 
@@ -342,14 +341,9 @@ __device__ inline bf16x8 tile_col_frag(const TilePlaces &x, lds_u8 *img, int d, 
 // How a persistent grid is laid over the (instruction, KV head) pairs: see resident_general_kernel.
 struct Spread {
     int per_vh, vh_slots, chunk; // workgroups per pair, pairs served at a time, tiles that fit into LDS
-    int wg_step, wave_step;      // blocks from one workgroup to the next, from one wavefront to the next
 };
-// The block that a wavefront takes in round `it` (at or behind the number of blocks: none; wavefront 0's is the
-// first of a workgroup's).
-__device__ inline int spread_block(const Spread &sp, int waves, int wave, int it)
-{
-    return (blockIdx.x / sp.vh_slots) * sp.wg_step + wave * sp.wave_step + it * sp.per_vh * waves;
-}
+// The first of the blocks that this workgroup's wavefronts take in their round `it` (at or behind the number of blocks: none).
+__device__ inline int round_base(const Spread &sp, int waves, int it) { return ((blockIdx.x / sp.vh_slots) + it * sp.per_vh) * waves; }
 
 // f(arguments, context, row) for the valid rows of this wavefront's blocks in a walk of `waves` wavefronts per workgroup, for
 // a path hardly ever taken.  (A kernel's first parameter is, or begins with, Args.)
@@ -361,7 +355,7 @@ template <typename F> __device__ inline void for_stored_rows(const Spread &sp, i
     const int nblocks = (X.Mtot + kBlockRows - 1) / kBlockRows, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     for (int vh = blockIdx.x % sp.vh_slots; vh < a.Np * a.Hkv; vh += sp.vh_slots) {
         set_vhead(a, X, vh);
-        for (int it = 0, blk; (blk = spread_block(sp, waves, wave, it)) < nblocks; ++it) {
+        for (int it = 0, blk; (blk = round_base(sp, waves, it) + wave) < nblocks; ++it) {
             const Rows x = make_rows(a, X, blk);
             if (x.valid)
                 f(a, X, x);
@@ -467,7 +461,7 @@ void hd64_fwd_kernel(Args a, Spread sp)
         bool has;
         uintx4 q[kKS];
         auto begin = [&](int it) __attribute__((always_inline)) {
-            const int blk = spread_block(sp, kFwdWaves, wave, it);
+            const int blk = round_base(sp, kFwdWaves, it) + wave;
             has = blk < nblocks;
             x = make_rows(a, X, has ? blk : nblocks - 1);
             load_row(a.q, (long long)x.b * a.q_sb + (long long)(x.valid ? x.i : 0) * a.q_ss + (long long)x.h * a.q_sh, X.h, q);
@@ -548,7 +542,7 @@ void hd64_fwd_kernel(Args a, Spread sp)
                     a.lse[((long long)x.b * a.Hq + x.h) * a.S + x.i] = x.valid ? lse2 * kLn2 : -INFINITY;
                 bad |= __builtin_amdgcn_ballot_w64(x.valid && (has_nan(st.o) || l == 0.f)) != 0;
             }
-            if (spread_block(sp, kFwdWaves, 0, ++it) >= nblocks)
+            if (round_base(sp, kFwdWaves, ++it) >= nblocks)
                 break;
             begin(it);
         }
@@ -634,8 +628,8 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
             stage_request(a, X, img, 0, T, tid);
             stage_finish();
         }
-        for (int it = 0; spread_block(sp, kBwdWaves, 0, it) < nblocks; ++it) {
-            const int blk = spread_block(sp, kBwdWaves, wave, it);
+        for (int it = 0; round_base(sp, kBwdWaves, it) < nblocks; ++it) {
+            const int blk = round_base(sp, kBwdWaves, it) + wave;
             const bool has = blk < nblocks;
             const Rows x = make_rows(a, X, has ? blk : nblocks - 1);
             const bool work = has && __builtin_amdgcn_ballot_w64(x.valid) != 0;
@@ -928,12 +922,6 @@ Shape make_shape(const Args &a, int num_cu, int waves, int most_per_cu)
     per_vh = per_vh < useful ? per_vh : useful;
     s.sp.per_vh = (int)per_vh;
     s.sp.vh_slots = (int)vh_slots;
-    const bool once = nblocks <= per_vh * waves;
-    // Blocks side by side share their candidates' keys, and a workgroup takes them together.  Where nobody takes a second
-    // block, though, they come in one round to all workgroups alike: the blocks behind the candidates' lengths, which cost
-    // nothing, lie together.
-    s.sp.wg_step = once ? 1 : waves;
-    s.sp.wave_step = once ? (int)per_vh : 1;
     s.grid = (unsigned)(per_vh * vh_slots);
     return s;
 }

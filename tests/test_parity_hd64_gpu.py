@@ -54,7 +54,7 @@ def check(pk, inp, what, backward=True):
     (9, 192, 10, 1, 10, 4, 4),      # the longest prefix that leaves room for two workgroups
     (4, 193, 70, 30, 70, 4, 1),     # ... one row more; three steps of own keys
     (3, 513, 20, 4, 20, 6, 2),      # prefix in chunks, forward and backward
-    (300, 40, 24, 12, 24, 16, 16),  # one round of blocks, spread over the workgroups, the last slots empty
+    (300, 40, 24, 12, 24, 16, 16),  # one round of blocks, the last slots empty
     (400, 40, 24, 12, 24, 16, 16),  # more blocks than wavefronts
     (3, 512, 20, 4, 20, 6, 2),      # the longest prefix that stays in LDS
     (2, 1, 40, 0, 40, 4, 4),        # a prefix of one row, which stands in for the rest of its tile
