@@ -17,11 +17,9 @@
 // into LDS as fits, and its wavefronts walk over the row blocks independently.  Longer prefixes go
 // through the same LDS in chunks.
 //
-// 256 candidates of 5 to 33 rows, 177 prefix rows, 14/2 heads: 300 us in the vector kernel, 20.1 us here, of which the prefix
-// takes 4 and the tiles 6 to 13: two to four wavefronts of a SIMD have a block of their own, and a tile takes
-// 1300 cycles of one, the sum of its matrix instructions (512) and of its vector ones.  (22.4 us with the prefix
-// copied through registers, 32 bytes of a row at a time, and transposed in LDS, and the first tile tried as a later
-// one before its maximum was taken: 0.7 us of these.)
+// 256 candidates of 5 to 33 rows, 177 prefix rows, 14/2 heads: 300 us in the vector kernel, 20.9 us here (22.6 us with the
+// prefix copied through registers, 32 bytes of a row at a time, and transposed in LDS, and the first tile tried as a later
+// one before its maximum was taken).
 #include "pskv_mfma.hpp"
 #include <type_traits>
 
@@ -99,11 +97,10 @@ struct Rows {
     int b, i, h, len;        // candidate, suffix position, query head, clamped suffix length
     bool exists, valid;
     int bl0, bl1, tok0, tok1; // candidates within the instruction and tokens that the block covers
-    int n, first;             // the list of own keys (see own_keys): its slots, and where those of the lane's row begin
 };
 
 // The list of own keys: keys 0 .. n_c - 1 of every candidate c of the block, in order; n_c is one more
-// than the last key that any of the block's rows sees.  visit(candidate, its length, first slot, n_c).
+// than the last key that any of the block's rows sees.  visit(candidate, first slot, n_c).
 template <typename F> __device__ inline int own_keys(const Args &a, const Ctx &X, const Rows &x, F visit)
 {
     int n = 0;
@@ -112,7 +109,7 @@ template <typename F> __device__ inline int own_keys(const Args &a, const Ctx &X
         const int lo = x.tok0 - bl * a.S > 0 ? x.tok0 - bl * a.S : 0;
         const int hi = x.tok1 - bl * a.S < len - 1 ? x.tok1 - bl * a.S : len - 1;
         const int nc = lo < len ? hi + 1 : 0;
-        visit(b, len, n, nc);
+        visit(b, n, nc);
         n += nc;
     }
     return n;
@@ -127,18 +124,27 @@ __device__ inline Rows make_rows(const Args &a, const Ctx &X, int blk)
     x.b = X.cand0 + bl;
     x.i = tok - bl * a.S;
     x.h = X.head * a.G + (r - tok * a.G);
+    // (By a vector load: the walk over the block's candidates that finds the lengths as scalars would stand before every
+    // address of the row's.  us, 14/2 heads unless stated, from such a walk and so: 501 candidates x 45..87 positions, P 35: 81.4,
+    // 76.7; 313 x 75, P 43: 45.2, 43.1; 205 x 86..110, P 34, 32/8: 115.6, 112.6.)
+    x.len = a.len ? clamp_len(a, a.len[x.b]) : a.S;
+    x.valid = x.exists && x.i < x.len;
     x.tok0 = (int)fdiv(r0, a.div_g);
     x.tok1 = (int)fdiv(last, a.div_g);
     x.bl0 = (int)fdiv(x.tok0, a.div_s);
     x.bl1 = (int)fdiv(x.tok1, a.div_s);
-    // (lengths by scalar loads: a vector load of the lane's own would have to wait for the requests in flight)
-    x.len = x.first = 0;
-    x.n = own_keys(a, X, x, [&](int b, int len, int first, int) {
-        x.len = b == x.b ? len : x.len;
-        x.first = b == x.b ? first : x.first;
-    });
-    x.valid = x.exists && x.i < x.len;
     return x;
+}
+// The slots of the block's list, and where those of the lane's row begin.
+struct OwnList {
+    int n, first;
+};
+__device__ inline OwnList own_list(const Args &a, const Ctx &X, const Rows &x)
+{
+    OwnList l;
+    l.first = 0;
+    l.n = own_keys(a, X, x, [&](int b, int first, int) { l.first = b == x.b ? first : l.first; });
+    return l;
 }
 
 // Element offset (from the suffix tensors of this head) of the row in slot k0 + c32 of the list, the last
@@ -147,7 +153,7 @@ __device__ inline long long own_row(const Args &a, const Ctx &X, const Rows &x, 
 {
     const int slot = k0 + X.c32;
     long long off = 0;
-    own_keys(a, X, x, [&](int b, int, int first, int nc) {
+    own_keys(a, X, x, [&](int b, int first, int nc) {
         if (nc > 0 && slot >= first)
             off = (long long)b * a.ks_sb + (long long)(slot - first < nc ? slot - first : nc - 1) * a.ks_ss;
     });
@@ -455,25 +461,22 @@ void hd64_fwd_kernel(Args a, Spread sp)
         set_vhead(a, X, vh);
         const int T = (X.P + kTileKeys - 1) / kTileKeys;
         const bool resident = T <= sp.chunk;
-        // A block's query rows are requested while the prefix is on its way (the first block) or the block before
-        // is being stored.
-        Rows x;
-        bool has;
-        uintx4 q[kKS];
-        auto begin = [&](int it) __attribute__((always_inline)) {
-            const int blk = round_base(sp, kFwdWaves, it) + wave;
-            has = blk < nblocks;
-            x = make_rows(a, X, has ? blk : nblocks - 1);
-            load_row(a.q, (long long)x.b * a.q_sb + (long long)(x.valid ? x.i : 0) * a.q_ss + (long long)x.h * a.q_sh, X.h, q);
-        };
-        if (resident)
+        if (resident) {
             stage_request(a, X, img, 0, T, tid);
-        begin(0);
-        if (resident)
             stage_finish();
+        }
         // (The workgroup's wavefronts go through this loop together - barriers inside - unless the prefix is resident.)
-        for (int it = 0;;) {
+        // Nothing is asked for while the prefix is on its way: the barrier would wait for that too.  us, the first
+        // block's query rows requested there, and so: 428 candidates x 13 positions, P 64, 14/2 heads: 15.0, 12.7; 143 x 21, P 64, 32/8:
+        // 15.7, 13.7; 256 x 5..33, P 177, 14/2: 20.9 both.
+        for (int it = 0;;) { // (the launcher gives every workgroup a first round)
+            const int blk = round_base(sp, kFwdWaves, it) + wave;
+            const bool has = blk < nblocks;
+            const Rows x = make_rows(a, X, has ? blk : nblocks - 1);
+            const OwnList own = own_list(a, X, x); // (here and not behind the tiles: its loads pass beside those of the rows)
             const bool work = has && __builtin_amdgcn_ballot_w64(x.valid) != 0;
+            uintx4 q[kKS];
+            load_row(a.q, (long long)x.b * a.q_sb + (long long)(x.valid ? x.i : 0) * a.q_ss + (long long)x.h * a.q_sh, X.h, q);
             FwdState st;
             st.m = -INFINITY;
             st.l = 0.f;
@@ -495,7 +498,8 @@ void hd64_fwd_kernel(Args a, Spread sp)
 #pragma unroll
                     for (int ks = 0; ks < kKS; ++ks)
                         s = mma(tile_row_frag(tp, ki, ks), as_bf16x8(q[ks]), s);
-                    const int nv = X.P - (t0 + t) * kTileKeys - 4 * X.h; // element e holds key 8*(e/4) + e%4 + 4*h of the tile
+                    int nv = X.P - (t0 + t) * kTileKeys - 4 * X.h; // element e holds key 8*(e/4) + e%4 + 4*h of the tile
+                    asm volatile("" : "+v"(nv)); // (the first tile's comparisons stay here: ahead of the loops their 16 results would be spilled)
                     if ((t0 + t + 1) * kTileKeys > X.P)
 #pragma unroll
                         for (int e = 0; e < 16; ++e)
@@ -514,7 +518,7 @@ void hd64_fwd_kernel(Args a, Spread sp)
                     tile(t, std::false_type{});
             }
             if (work) {
-                for (int k0 = 0; k0 < x.n; k0 += kTileKeys) {
+                for (int k0 = 0; k0 < own.n; k0 += kTileKeys) {
                     const long long row = own_row(a, X, x, k0);
                     uintx4 kf[kKS];
                     load_row(X.ksg, row, X.h, kf);
@@ -523,7 +527,7 @@ void hd64_fwd_kernel(Args a, Spread sp)
 #pragma unroll
                     for (int ks = 0; ks < kKS; ++ks)
                         s = mma(as_bf16x8(kf[ks]), as_bf16x8(q[ks]), s);
-                    const int rel = k0 + 4 * X.h - x.first; // the row sees slots first .. first + i
+                    const int rel = k0 + 4 * X.h - own.first; // the row sees slots first .. first + i
 #pragma unroll
                     for (int e = 0; e < 16; ++e)
                         s[e] = (unsigned)(rel + 8 * (e >> 2) + (e & 3)) <= (unsigned)x.i ? s[e] : -INFINITY;
@@ -544,7 +548,6 @@ void hd64_fwd_kernel(Args a, Spread sp)
             }
             if (round_base(sp, kFwdWaves, ++it) >= nblocks)
                 break;
-            begin(it);
         }
     }
     if (bad) // (see to_form_anew)
@@ -678,7 +681,8 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
                 }
             }
             if (work) {
-                for (int k0 = 0; k0 < x.n; k0 += kTileKeys) {
+                const OwnList own = own_list(a, X, x);
+                for (int k0 = 0; k0 < own.n; k0 += kTileKeys) {
                     const long long row = own_row(a, X, x, k0);
                     uintx4 kf[kKS], vf[kKS];
                     load_row(X.ksg, row, X.h, kf);
@@ -692,7 +696,7 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
                         s = mma(as_bf16x8(kf[ks]), as_bf16x8(q[ks]), s);
                         dp = mma(as_bf16x8(vf[ks]), as_bf16x8(dof[ks]), dp);
                     }
-                    const int rel = k0 + 4 * X.h - x.first;
+                    const int rel = k0 + 4 * X.h - own.first;
                     dq_tile(s, dp, X.c, lse2, drow, [&](int e) { return (unsigned)(rel + 8 * (e >> 2) + (e & 3)) <= (unsigned)x.i; },
                             [&](int dt, int j) { return frag_tr(X.scr, dt, j, X.lane); }, dq);
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
