@@ -596,6 +596,11 @@ __device__ inline void dq_tile(const floatx16 &s, const floatx16 &dp, float c, f
 #pragma unroll
     for (int e = 0; e < 16; ++e)
         ds[e] = vis(e) ? fast_exp2(__builtin_fmaf(s[e], c, -lse2)) * (dp[e] - drow) : 0.f;
+    // (The products as fp32 numbers, which split16 cuts into three: without the test the compiler would take each into the
+    // first of its subtractions, and a key of a whole prefix tile weigh otherwise than of a ragged one or of a candidate's own.)
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+        asm volatile("" : "+v"(ds[e]));
     const Split w = split16(ds);
 #pragma unroll
     for (int j = 0; j < 2; ++j)
@@ -625,7 +630,7 @@ void hd64_bwd_dq_kernel(BwdArgs g, Spread sp)
         set_vhead(a, X, vh);
         const int T = (X.P + kTileKeys - 1) / kTileKeys;
         const bool resident = T <= sp.chunk;
-        // (Nothing requested in between, unlike the forward kernel: 48 candidates x 29 positions, P 206, 14/2 heads:
+        // (Nothing requested in between, as in the forward kernel: 48 candidates x 29 positions, P 206, 14/2 heads:
         // 27.4 us with the first block's rows asked for there, 26.1 so.)
         if (resident) {
             stage_request(a, X, img, 0, T, tid);

@@ -152,3 +152,30 @@ def test_hd64_weights_in_full(pk, impl):
     q2 = q.copy()
     q2[:, :3, half:] = cancelling(ds[:, :3, 2])[:, :, half:]
     check(call(q2, K, V, dout)[1], scale * np.einsum("ng,ngd->nd", ds[..., 2], q2), scale * np.einsum("ng,ngd->nd", ds[..., 2], np.abs(q2)), "dk")
+
+
+def test_a_key_weighs_the_same_as_prefix_and_as_own_key(pk):
+    """The gradient of a row that sees 32 prefix keys (a whole tile) and one own key, and of one that sees the same 33 as
+    its own: the same numbers in the same order, so the same bits (two million of them: one product in some hundred
+    thousand shows in a bf16 result when it is rounded at another place)."""
+    import torch
+    g = torch.Generator(device="cuda:0").manual_seed(11)
+    def normal(*shape):
+        return torch.randn(shape, generator=g, device="cuda:0", dtype=torch.bfloat16)
+    B, H, D = 1024, 32, 64                               # one KV head: a block of rows is one position
+    q, k1, v1, dout = normal(B, 1, H, D), normal(B, 1, 1, D), normal(B, 1, 1, D), normal(B, 1, H, D)
+    kp, vp = normal(32, 1, D), normal(32, 1, D)
+    one = torch.full((B,), 1, dtype=torch.int32, device="cuda:0")
+    lse = torch.empty((B, H, 1), device="cuda:0")
+    out = pk.pskv_attn_fwd(q, k1, v1, kp, vp, one, lse=lse)
+    dq, _, _ = pk.pskv_attn_bwd(q, k1, v1, kp, vp, one, out, lse, dout)
+    # the same 33 keys as a candidate's own; the row is its last
+    def last(x):
+        return torch.cat([x.new_zeros((B, 32) + x.shape[2:]), x], 1).contiguous()
+    def own(x, pre):
+        return torch.cat([pre[None].expand(B, 32, 1, D), x], 1).contiguous()
+    lse_own = torch.cat([torch.zeros((B, H, 32), device="cuda:0"), lse], 2).contiguous()
+    none = torch.empty((0, 1, D), dtype=torch.bfloat16, device="cuda:0")
+    dq_own, _, _ = pk.pskv_attn_bwd(last(q), own(k1, kp), own(v1, vp), none, none, one + 32, last(out), lse_own, last(dout))
+    torch.cuda.synchronize()
+    assert torch.equal(dq_own[:, 32:], dq)
