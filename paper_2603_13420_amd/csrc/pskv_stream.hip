@@ -1118,6 +1118,74 @@ bool own_blocks_fit(const Args &a)
     return rows_c * 16 >= nb * kBlockRows * 13 && a.C * nb <= 0x7fffffffLL / kBlockRows - kNW && stream_pass_ids(a, a.C * nb) <= 0x7fffffffLL - 8;
 }
 
+// The candidate passes that take a problem, if any: the one place where this is decided.
+enum class CandPasses { none, four, eight };
+CandPasses candidate_passes(const Args &a, int num_cu)
+{
+    const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
+    const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows; // rows and own blocks of a candidate
+    if (a.S <= kTileKeys || max_tiles < kMinTiles || (long long)a.P * a.kp_sp * 2 >= 0x7fffffffLL || (long long)a.S * a.ks_ss * 2 >= 0x7fffffffLL ||
+        !own_blocks_fit(a) || !block_offsets_fit(a))
+        return CandPasses::none;
+    const bool whole = rows_c % kBlockRows == 0, resident = resident_supported(a);
+    auto rounds = [&](long long passes) { return (passes + num_cu - 1) / num_cu; };
+    const long long units = ((long long)a.B * a.Hkv + 7) / 8 * 8, ngrp8 = (nb + kNW - 1) / kNW, ngrp4 = (nb + kCW - 1) / kCW;
+    const long long r8 = rounds(units * ngrp8), r4 = rounds(units * ngrp4); // passes per compute unit
+    const bool fit8 = units * ngrp8 <= 0x7fffffffLL - 8, fit4 = units * ngrp4 <= 0x7fffffffLL - 2 * num_cu;
+
+    // Passes of eight, only where a compute unit takes twice as many passes of four: they fetch the tiles half as often, which
+    // long prefixes gain by.  us, of eight and of four, 32/8 heads (what a compute unit takes of either): 300 candidates: P 1500: 128
+    // positions (19, 38): 924, 960; 64 (10, 19): 474, 458; 96 (19, 29): 869, 711; P 512: 104 (19, 38): 386, 400; 64: 205,
+    // 190; 96: 388, 307; 24 candidates x 64 (1, 2): P 1500: 44.8, 46.4.
+    // Resident prefixes: no difference on the whole (P 128: 300 x 120 (19, 38): 209, 218; 60 x 48..64 (2, 4): 23.0, 21.1; P 200:
+    // 300 x 120: 271, 260; P 256: 60 x 120 (4, 8): 55.5, 57.2), but of three tiles (P 78: 220 x 115 (14, 28): 162, 143; P 79: 122 x
+    // 21..40: 35, 30; P 94: 14 x 77 (1, 2): 12.3, 11.0).
+    bool eight = fit8 && r4 >= 2 * r8 && nb * 10 >= ngrp8 * kNW * 6 && !(resident && max_tiles == kMinTiles);
+
+    if (resident && !whole) {
+        // Against the resident general kernel, whose wavefronts have `each` blocks and take the own steps one by one.
+        const long long each = resident_split(a, (a.C * rows_c + kBlockRows - 1) / kBlockRows, kNW, num_cu).each;
+        const bool many = a.S > 4 * kTileKeys;
+        // Passes of eight, two thirds full and more: as many as blocks, one and a half times with more than four own steps.  us,
+        // general kernel and passes of eight (`each`, passes per compute unit): P 99: 12 candidates x 87 positions (32/8 heads; 1, 1):
+        // 16.9, 13.0; P 151: 20 x 132 (32/8; 2, 2): 30.3, 25.2; beyond: P 169: 49 x 74 (32/4; 2, 3): 30.2, 33.0; P 145: 247 x 22..45
+        // (32/8; 6, 8): 64, 76; P 164: 161 x 113 (32/4; 9, 11): 136, 142; more own steps: P 222: 37 x 158 (28/4; 3, 3): 56, 45.
+        // Passes of four, three quarters full and more: up to 9 for 4 blocks, 3 for 1 with more than four own steps.  us, general
+        // kernel and passes of four (`each`, passes per compute unit): P 213: 10 x 69 (32/8; 1, 1): 17.8, 11.1; P 70: 35 x 56..66 (32/4;
+        // 2, 3): 22.1, 15.6; P 189: 28 x 26..38 (32/4; 1, 2): 15.6, 12.6; P 169: 49 x 74 (32/4; 2, 4): 30.2, 26.6; P 162: 199 x 53
+        // (28/4; 5, 10): 56.9, 57.5; beyond: P 227: 237 x 65 (32/4; 8, 19): 117, 119; P 164: 161 x 113 (32/4; 9, 21): 136, 139; P 242:
+        // 116 x 70 (32/4; 4, 10): 57, 61; P 206: 203 x 41 (28/4; 4, 10): 51, 55; P 171: 198 x 58 (28/4; 5, 13): 59, 68; more own
+        // steps: P 77: 13 x 135 (32/8; 1, 3): 20.1, 16.9; five eighths full: P 78: 97 x 159 (40/40; 11, 31): 221, 165; P 168: 265 x 58..157
+        // (32/32; 28, 83): 448, 512; P 157: 48 x 60..151 (32/32; 4, 12): 66, 73; P 126: 37 x 130 (32/32; 3, 10): 48, 54.
+        // Prefixes of their own lengths may be too short for these passes, which then sweep them on the general path: where the longest has
+        // three or four tiles, up to 7 and 8 for 4.  us, real prefixes a third of P and more: P 93: 264 x 87 (40/40, eight instructions;
+        // 24, 42): 376, 292; P 116: 20 x 148 (32/8, two; 2, 4): 33.7, 22.6 (passes of eight); beyond:
+        // P 86: 112 x 77 (32/8, two; 5, 11): 49.5, 57.7; P 69: 48 x 85..123 (32/8, two; 3, 6): 35.5, 47.1; P 115: 222 x 46..52 (28/4,
+        // two; 5, 11): 55.2, 67.8.
+        const int most = a.plen && max_tiles <= kMinTiles + 1 ? max_tiles + 4 : many ? 12 : 9; // passes for 4 blocks
+        if (nb * 4 < ngrp4 * kCW * 3 || r4 * 4 > most * each)
+            return CandPasses::none;
+        eight = eight && nb * 3 >= ngrp8 * kNW * 2 && r8 * 2 <= each * (many ? 3 : 2);
+        return eight ? CandPasses::eight : fit4 ? CandPasses::four : CandPasses::none;
+    }
+    // Against the pipelined passes, whose blocks fetch their own keys by themselves and lose some three tiles' time to them.
+    // us, pipelined passes and passes of four (rounds of the chip; passes of four per compute unit): 250 candidates, P 600: 128
+    // positions, 32/32 heads (16, 32): 508, 427; 96 (12, 32): 358, 389; 72, 32/8 (9, 24): 221, 246; P 1500: 39 x 28/4 (5, 12): 239,
+    // 263; P 128: 215, 177; 64 candidates, P 1500, 39 x 28/4 (2, 3): 87, 70; 300 x 40, 32/8, P 512 (6, 19): 121, 153; 181 x 88,
+    // 32/8, P 1750 (8, 17): 441, 474; at the line: 70 x 133, 32/8, P 834 (5, 11): 175, 160; just beyond: P 300: 250 x 96, 32/32 (12, 32):
+    // 263, 249; P 834: 100 x 133, 32/8 (7, 16): 250, 242.
+    // Long prefixes and rows that fill no whole number of blocks: against the general passes as well, as long as there are hardly more of
+    // the others and up to 1024 prefix rows.  us, general passes and passes of eight (rounds of the chip): 64 x 109 (32/8, P 464;
+    // 4, 4): 121, 84; 50 x 148 (32/8, P 424; 4, 5): 105, 81; 12 x 156 (32/32, P 2018; 1, 2): 84, 103; 245 x 34 (32/8, P 676; 5, 8):
+    // 169, 161 (pipelined passes 131).
+    const long long rp = rounds(stream_pass_ids(a, a.C * nb)), full_rounds = rounds(stream_pass_ids(a));
+    const bool any = whole || resident, full8 = fit8 && nb * 10 >= ngrp8 * kNW * 6 && (any || r8 * 7 <= full_rounds * 10);
+    if (eight && full8)
+        return CandPasses::eight;
+    return fit4 && r4 * max_tiles <= 2 * rp * (max_tiles + 3) && (any || full8 || (r4 * 10 <= full_rounds * 22 && a.P <= 1024)) ? CandPasses::four
+                                                                                                                            : CandPasses::none;
+}
+
 } // namespace
 
 bool mfma_supported(const Args &a, int dtype)
@@ -1130,41 +1198,22 @@ bool mfma_supported(const Args &a, int dtype)
 
 hipError_t launch_mfma(const Args &a, hipStream_t stream)
 {
+    if (!resident_supported(a))
+        return launch_stream(a, stream);
     // Suffix-side segments longer than one 32-key step (suffix, template and target together,
-    // Sec. 3) go to the streamed kernel whenever its pipelined pass applies: it runs every
-    // suffix step against the fixed reference, the resident kernels would fall back to their
-    // general path for such shapes.
+    // Sec. 3) go to the streamed kernels, which run every suffix step against the fixed reference, where
+    // the resident kernels would fall back to their general path for such shapes: all that fill
+    // whole blocks of rows, and of the others those that the candidate passes are better at.
     const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
-    const bool whole = (long long)a.S * a.G % kBlockRows == 0;
     bool long_suffix = a.S > kTileKeys && max_tiles >= kMinTiles && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL;
-    // Rows that fill no whole number of blocks: only where the candidate passes come out full to three quarters, and what a
-    // compute unit then takes of them is no more than the blocks that a wavefront of the resident general kernel has (one and
-    // a half times as many with more than four own steps, which that kernel takes one by one).  us, resident
-    // general kernel and candidate passes: passes of eight (their rounds of the chip after the blocks): P 128: 16 candidates
-    // x 90 positions (32/8 heads; 1, 1): 16, 12; P 205: 21 x 118 (32/4; 2, 2): 32.8, 26.8; P 70: 124 x 87 (32/4; 6, 6):
-    // 58.9, 51.9; beyond: P 169: 49 x 74 (32/4; 2, 3): 28.7, 31.0; P 145: 247 x 22 .. 45 (32/8; 6, 8): 57, 74; with more
-    // than four steps: P 222: 37 x 158 (28/4; 3, 3): 56, 45; P 93: 73 x 147 (32/8; 6, 7): 84.6, 67.7; beyond: P 147: 17 x 136
-    // (28/4; 1, 2): 20.5, 23.6.  Less than three quarters: 64 x 141 (32/32, 5 blocks in 8, P 128): 81, 101.
-    // Passes of four, two at a time (how many a compute unit takes after the blocks): P 169: 21 x 88 (28/4; 1, 2): 18.5, 14.5;
-    // P 213: 153 x 78 (28/4; 6, 13): 80, 74; P 162: 79 x 122 (32/32; 5, 10): 79, 67; P 121: 111 x 79 (32/8; 5, 11): 56, 48; P 245:
-    // 28 x 135 (32/8; 2, 5): 39.3, 34.5; beyond: P 164: 161 x 113 (32/4; 9, 21): 112, 128; P 251: 250 x 94 (28/4; 11, 24):
-    // 149, 160; P 178: 253 x 59 (28/4; 7, 16): 82, 93; full to 5/8: P 239: 153 x 133 (32/32): 216, 281.  (Up to two
-    // own steps the lines of the passes of eight hold.)
-    if (long_suffix && !whole && resident_supported(a)) {
+    if (long_suffix && (long long)a.S * a.G % kBlockRows != 0) {
         hipError_t e;
         const int num_cu = device_cu_count(e);
         if (e != hipSuccess)
             return e;
-        const long long rows_c = (long long)a.S * a.G, nb = (rows_c + kBlockRows - 1) / kBlockRows;
-        const long long units = ((long long)a.B * a.Hkv + 7) / 8 * 8, ngrp8 = (nb + kNW - 1) / kNW, ngrp4 = (nb + kCW - 1) / kCW;
-        const long long r8 = (units * ngrp8 + num_cu - 1) / num_cu, r4 = (units * ngrp4 + num_cu - 1) / num_cu; // passes per compute unit
-        const long long each = resident_split(a, (a.C * rows_c + kBlockRows - 1) / kBlockRows, kNW, num_cu).each;
-        const bool many = a.S > 4 * kTileKeys;
-        const bool eight = nb * 4 >= ngrp8 * kNW * 3 && r8 * 2 <= each * (many ? 3 : 2);
-        const bool four = nb * 4 >= ngrp4 * kCW * 3 && a.S * 5 > 12 * kTileKeys && r4 * 10 <= each * (many ? 28 : max_tiles < kNW ? 22 : 20);
-        long_suffix = own_blocks_fit(a) && block_offsets_fit(a) && (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL && (eight || four);
+        long_suffix = candidate_passes(a, num_cu) != CandPasses::none;
     }
-    return resident_supported(a) && !long_suffix ? launch_resident(a, stream) : launch_stream(a, stream);
+    return long_suffix ? launch_stream(a, stream) : launch_resident(a, stream);
 }
 
 hipError_t launch_stream(const Args &a, hipStream_t stream)
@@ -1179,43 +1228,16 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
     bool pipelined = own_blocks_fit(a) && max_tiles >= kMinTiles && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && block_offsets_fit(a);
     auto rounds = [&](long long passes) { return (passes + num_cu - 1) / num_cu; };
     const long long full_rounds = rounds(stream_pass_ids(a));
-    // Long suffix-side segments: candidate passes of eight blocks, candidate passes of four, two at a time on a compute
-    // unit, or the pipelined passes, whose blocks fetch their own keys by themselves.
-    // Passes of eight (60 % full and more) only where a compute unit takes twice as many passes of four: they fetch the tiles
-    // half as often.  us, of eight and of four, 32/8 heads (what a compute unit takes of either): 300 candidates: P 1500: 128
-    // positions (19, 38): 924, 960; 64 (10, 19): 474, 458; 96 (19, 29): 869, 711; P 512: 104 (19, 38): 386, 400; 64: 205,
-    // 190; 96: 388, 307; 24 candidates x 64 (1, 2): P 1500: 44.8, 46.4; P 512: 21.2, 21.5; P 128: 300 x 120 (19, 38): 205,
-    // 213; 300 x 64: 96, 88; P 206: 18 x 49 (32/4; 1, 2): 13.0, 14.4.
-    // Pipelined passes against passes of four: the former lose some three tiles' time to the own keys.  us (rounds of the chip;
-    // passes of four per compute unit): 250 candidates, P 600: 128 positions, 32/32 heads (16, 32): 508, 427; 96 (12, 32): 358,
-    // 389; 72, 32/8 (9, 24): 221, 246; 88 (11, 24): 353 in passes of eight, 275; P 1500: 39 x 28/4 (5, 12): 239, 263; P 300:
-    // 96, 32/32 (12, 32): 263, 249; P 128: 215, 177; 64 candidates, P 1500, 39 x 28/4 (2, 3): 87, 70; 300 x 40, 32/8, P 512 (6,
-    // 19): 121, 153.
-    // Rows that fill no whole number of blocks: against the general passes, as long as there are hardly more of the others
-    // and up to 1024 prefix rows (short prefixes come here for the candidate passes: launch_mfma has their rule).  us, general
-    // and passes of eight (rounds of the chip): 64 x 109 (32/8, P 464; 4, 4): 121, 84; 50 x 148 (32/8, P 424; 4, 5): 105,
-    // 81; 12 x 156 (32/32, P 2018; 1, 2): 84, 103; 245 x 34 (32/8, P 676; 5, 8): 169, 161 (pipelined passes 131).
-    if (pipelined && a.S > kTileKeys && (long long)a.S * a.ks_ss * 2 < 0x7fffffffLL) {
-        const long long units = ((long long)a.B * a.Hkv + 7) / 8 * 8;
-        auto shape = [&](int waves) { return CandShape{(int)nb, (int)((nb + waves - 1) / waves), nb < waves ? (int)nb : waves}; };
-        const CandShape c8 = shape(kNW), c4 = shape(kCW);
-        const long long passes8 = units * c8.ngrp, passes4 = units * c4.ngrp;
-        const long long r8 = rounds(passes8), r4 = rounds(passes4), rp = rounds(stream_pass_ids(a, a.C * nb));
-        const bool any = whole || resident_supported(a);
-        const bool fit8 = nb * 10 >= (long long)c8.ngrp * kNW * 6 && passes8 <= 0x7fffffffLL - 8 && (any || r8 * 7 <= full_rounds * 10);
-        const bool eight = fit8 && r4 >= 2 * r8;
-        const bool four = !eight && passes4 <= 0x7fffffffLL - 2 * num_cu && r4 * max_tiles <= 2 * rp * (max_tiles + 3) &&
-                          (any || fit8 || (r4 * 10 <= full_rounds * 22 && a.P <= 1024));
-        if (eight) {
-            const unsigned grid = (unsigned)(passes8 < num_cu ? passes8 : num_cu);
-            return launch_kernel(whole ? stream_candidate_kernel<true> : stream_candidate_kernel<false>, dim3(grid), dim3(kNW * 64), kLdsBytes, stream, a,
-                                 (int)passes8, c8);
-        }
-        if (four) {
-            const unsigned grid = (unsigned)(passes4 < 2 * num_cu ? passes4 : 2 * num_cu);
-            return launch_kernel(whole ? stream_candidate4_kernel<true> : stream_candidate4_kernel<false>, dim3(grid), dim3(kCW * 64), kCLdsBytes, stream, a,
-                                 (int)passes4, c4);
-        }
+    // Long suffix-side segments: candidate passes of eight blocks, or of four, two at a time on a compute unit.
+    if (const CandPasses passes = candidate_passes(a, num_cu); passes != CandPasses::none) {
+        const bool eight = passes == CandPasses::eight;
+        const int waves = eight ? kNW : kCW;
+        const CandShape cs = {(int)nb, (int)((nb + waves - 1) / waves), nb < waves ? (int)nb : waves};
+        const long long npasses = ((long long)a.B * a.Hkv + 7) / 8 * 8 * cs.ngrp, places = eight ? num_cu : 2 * num_cu;
+        auto kernel = eight ? (whole ? stream_candidate_kernel<true> : stream_candidate_kernel<false>)
+                            : (whole ? stream_candidate4_kernel<true> : stream_candidate4_kernel<false>);
+        return launch_kernel(kernel, dim3((unsigned)(npasses < places ? npasses : places)), dim3(waves * 64), eight ? kLdsBytes : kCLdsBytes, stream,
+                             a, (int)npasses, cs);
     }
     // Own blocks make more passes, each in 0.7 of the general kernel's time, 0.8 with the second own step: not where
     // that costs a round of the chip.

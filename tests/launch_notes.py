@@ -51,14 +51,22 @@ vp = ctypes.c_void_p
 t = [vp((1 + i) << 42) for i in range(14)]          # addresses 4 TB apart
 for c in json.load(sys.stdin):
     p = pk.make_multi_params(pk.make_params(c["B"], c["S"], c["P"], c["Hq"], c["Hkv"], c["D"], c["dtype"]), c["Np"])
+    lens = (t[13] if c["Np"] > 1 else None, None)
     if c["call"] == "fwd":
-        rc = lib.pskv_attn_fwd_multi(ctypes.byref(p), *t[:5], None, None, t[5], None, None, 0, None)
+        rc = lib.pskv_attn_fwd_multi(ctypes.byref(p), *t[:5], *lens, t[5], None, None, 0, None)
     else:
-        rc = lib.pskv_attn_bwd_multi(ctypes.byref(p), *t[:5], None, None, *t[5:11], None, 0, None)
+        rc = lib.pskv_attn_bwd_multi(ctypes.byref(p), *t[:5], *lens, *t[5:11], None, 0, None)
     got = (ctypes.c_ulonglong * 32)()
     k = stand_ins.take_launches(got)
     print(json.dumps([rc, [[got[2 * i], got[2 * i + 1], stand_ins.launched(i).decode()] for i in range(k)]]), flush=True)
 """
+
+
+def named(mangled, kernel):
+    """Whether a mangled name is that of `kernel`_kernel, "<true>" or "<false>" behind it standing for its first template argument."""
+    name, _, arg = kernel.partition("<")
+    name += "_kernel"
+    return f"{len(name)}{name}" + {"": "", "true>": "ILb1E", "false>": "ILb0E"}[arg] in mangled
 
 
 def case(call, dtype, D, B, P, S, Hq, Hkv, Np=1):

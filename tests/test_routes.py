@@ -7,9 +7,10 @@ import launch_notes as notes
 
 
 def check(tmp_path, call, problems):
+    """The kernel's whole name, and with "<true>" or "<false>" its first template argument."""
     cases = [notes.case(call, "bf16", 128, *p[:-1]) for p in problems]
     for (*_, kernel), c, (rc, got) in zip(problems, cases, notes.launches(tmp_path, cases)):
-        assert rc == pk.PSKV_OK and kernel in got[0][2], (c, kernel, got)
+        assert rc == pk.PSKV_OK and notes.named(got[0][2], kernel), (c, kernel, got)
 
 
 def test_dq_kernels(tmp_path):
@@ -36,13 +37,27 @@ def test_forward_own_blocks(tmp_path):
 
 
 def test_forward_candidate_passes(tmp_path):
+    four, eight = "stream_candidate4", "stream_candidate"
     check(tmp_path, "fwd", [
-        (16, 128, 90, 32, 8, 1, "stream_candidate"), (21, 205, 118, 32, 4, 1, "stream_candidate"), (37, 222, 158, 28, 4, 1, "stream_candidate"),
-        (17, 147, 136, 28, 4, 1, "resident_general"), (49, 169, 74, 32, 4, 1, "resident_general"), (247, 145, 45, 32, 8, 1, "resident_general"),
-        (161, 164, 113, 32, 4, 1, "resident_general"), (64, 128, 141, 32, 32, 1, "resident_general"),
-        (73, 93, 147, 32, 8, 1, "stream_candidate"), (23, 85, 157, 32, 8, 1, "stream_candidate"), (188, 72, 155, 28, 4, 1, "stream_candidate"),
-        (161, 164, 112, 32, 4, 1, "stream_candidate"),      # (whole blocks)
-        (64, 464, 109, 32, 8, 1, "stream_candidate"), (50, 424, 148, 32, 8, 1, "stream_candidate"), (12, 2018, 156, 32, 32, 1, "stream_pipelined"),
-        (34, 1114, 111, 28, 4, 1, "stream_pipelined"), (245, 676, 34, 32, 8, 1, "stream_pipelined"), (43, 603, 113, 40, 40, 1, "stream_general"),
-        (300, 700, 13, 32, 8, 1, "stream_general"), (512, 512, 29, 32, 32, 1, "stream_pipelined"),
+        # rows that fill no whole number of blocks, resident prefixes: the resident general kernel, passes of four and of eight
+        (10, 213, 69, 32, 8, 1, four + "<false>"), (35, 70, 66, 32, 4, 1, four + "<false>"), (49, 169, 74, 32, 4, 1, four + "<false>"),
+        (199, 162, 53, 28, 4, 1, four + "<false>"), (237, 227, 65, 32, 4, 1, "resident_general"),
+        (161, 164, 113, 32, 4, 1, "resident_general"), (203, 206, 41, 28, 4, 1, "resident_general"), (198, 171, 58, 28, 4, 1, "resident_general"),
+        (247, 145, 45, 32, 8, 1, "resident_general"), (64, 128, 141, 32, 32, 1, "resident_general"),
+        (13, 77, 135, 32, 8, 1, four + "<false>"), (265, 168, 157, 32, 32, 1, "resident_general"), (48, 157, 151, 32, 32, 1, "resident_general"),
+        (12, 99, 87, 32, 8, 1, eight + "<false>"), (20, 151, 132, 32, 8, 1, eight + "<false>"), (37, 222, 158, 28, 4, 1, eight + "<false>"),
+        (16, 128, 90, 32, 8, 1, eight + "<false>"), (220, 78, 115, 32, 8, 1, four + "<false>"), (14, 94, 77, 32, 8, 1, four + "<false>"),
+        # prefixes of their own lengths
+        (112, 86, 77, 32, 8, 2, "resident_general"), (48, 69, 123, 32, 8, 2, "resident_general"), (222, 115, 52, 28, 4, 2, "resident_general"),
+        (20, 116, 148, 32, 8, 2, eight + "<false>"), (264, 93, 87, 40, 40, 8, four + "<false>"), (186, 157, 87, 32, 8, 2, four + "<false>"),
+        # whole blocks, resident prefixes
+        (161, 164, 112, 32, 4, 1, four + "<true>"), (300, 128, 120, 32, 8, 1, eight + "<true>"), (122, 79, 40, 32, 8, 1, four + "<true>"),
+        # long prefixes: passes of eight, of four, pipelined and general ones
+        (300, 512, 104, 32, 8, 1, eight + "<true>"), (300, 512, 96, 32, 8, 1, four + "<true>"), (300, 1500, 128, 32, 8, 1, eight + "<true>"),
+        (300, 1500, 96, 32, 8, 1, four + "<true>"), (250, 600, 128, 32, 32, 1, four + "<true>"), (250, 600, 96, 32, 32, 1, "stream_pipelined<false>"),
+        (250, 600, 72, 32, 8, 1, "stream_pipelined<false>"), (250, 300, 96, 32, 32, 1, "stream_pipelined<false>"), (70, 834, 133, 32, 8, 1, four + "<false>"), (181, 1750, 88, 32, 8, 1, "stream_pipelined<false>"),
+        (300, 512, 40, 32, 8, 1, "stream_pipelined<false>"),
+        (64, 464, 109, 32, 8, 1, eight + "<false>"), (50, 424, 148, 32, 8, 1, four + "<false>"), (12, 2018, 156, 32, 32, 1, "stream_pipelined<false>"),
+        (34, 1114, 111, 28, 4, 1, "stream_pipelined<false>"), (245, 676, 34, 32, 8, 1, "stream_pipelined<false>"),
+        (43, 603, 113, 40, 40, 1, "stream_general"), (300, 700, 13, 32, 8, 1, "stream_general"), (512, 512, 29, 32, 32, 1, "stream_pipelined<true>"),
     ])
