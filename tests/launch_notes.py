@@ -63,10 +63,11 @@ for c in json.load(sys.stdin):
 
 
 def named(mangled, kernel):
-    """Whether a mangled name is that of `kernel`_kernel, "<true>" or "<false>" behind it standing for its first template argument."""
-    name, _, arg = kernel.partition("<")
+    """Whether a mangled name is that of `kernel`_kernel, with its first template arguments if "<true,false>" or the like is behind it."""
+    name, _, args = kernel.partition("<")
     name += "_kernel"
-    return f"{len(name)}{name}" + {"": "", "true>": "ILb1E", "false>": "ILb0E"}[arg] in mangled
+    args = "I" + args.rstrip(">").replace("true", "Lb1E").replace("false", "Lb0E").replace(",", "") if args else ""
+    return f"{len(name)}{name}{args}" in mangled
 
 
 def case(call, dtype, D, B, P, S, Hq, Hkv, Np=1):
