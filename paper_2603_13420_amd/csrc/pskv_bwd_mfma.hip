@@ -1176,8 +1176,8 @@ hipError_t launch_bwd_dkv_mfma(const BwdArgs &g, hipStream_t stream)
     const bool fit = block_offsets_fit(a);
     auto kernel = g.delta ? (fit ? bwd_dkv_mfma_kernel<true, true> : bwd_dkv_mfma_kernel<true, false>)
                           : (fit ? bwd_dkv_mfma_kernel<false, true> : bwd_dkv_mfma_kernel<false, false>);
-    // Where the tensors of query rows do not fit the last-level cache (256 MB), the pairs go from the last one down: what the dq
-    // kernel has just read, the last candidates' q and dout, is still there.  us for the whole backward pass, upwards and
+    // Where the tensors of query rows are twice the last-level cache (256 MB) and more, the pairs go from the last one down: what the
+    // dq kernel has just read, the last candidates' q and dout, is still there.  us for the whole backward pass, upwards and
     // downwards: 1024 candidates x 16..24 positions x 4 heads, 8 KV heads, P 256 (805 MB of q, dout, out and dq): 300, 294; 1045
     // x 31 x 7, 4 KV heads, P 52 (930 MB): 326, 316; 244 x 77 x 4, 8 KV heads, P 203 (615 MB): 286, 280; 589 x 25 x 7,
     // 4 KV heads, P 753 (422 MB): 326, 325; 82 x 25 x 4, 8 KV heads, P 43 (67 MB): 28.9, 29.5.

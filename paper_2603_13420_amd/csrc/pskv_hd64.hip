@@ -83,8 +83,7 @@ __device__ inline bf16x8 frag_tr(lds_u8 *img, int dt, int j, int lane)
     __builtin_memcpy(&f, &v8, 16);
     return f;
 }
-// Which 16-byte chunk (key, column chunk) belongs at chunk position p (0..255) of an image.
-__device__ inline void row_major_slot(int p, int &key, int &chunk) { key = p & 31, chunk = p >> 5; }
+// Which 16-byte chunk (key, column chunk) belongs at chunk position p (0..255) of a transposable image.
 __device__ inline void transposable_slot(int p, int &key, int &chunk)
 {
     const int f = p >> 5, q = p & 31; // fragment (dt, j, u), slot pair within it
