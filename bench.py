@@ -82,15 +82,15 @@ def alg_counts(w, suf_len, pre_len=None):
 # kernel sources they were taken on (kernel_source_rev()).  When the sources have changed since, the
 # bench line reports no traffic and says why, instead of a figure that no longer holds.
 HBM_TRAFFIC = {
-    "gqa8b_bf16": {"file": "resident_pipelined_kernel_gqa8b_bf16_hbm_traffic.txt", "rev": "ecbd54fa46e5", "mfma_flops": 111887253504.0, "fetch_kib": 142145.9, "fetch_scale": 2.0, "write_kib": 197632.7, "write_scale": 1.0},
-    "ldec_gqa8b_bf16": {"file": "stream_candidate4_kernel_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "ecbd54fa46e5", "mfma_flops": 134809124864.0, "fetch_kib": 224522.5, "fetch_scale": 2.0, "write_kib": 327680.0, "write_scale": 1.0},
-    "ldec_qwen7b_bf16": {"file": "stream_candidate4_kernel_ldec_qwen7b_bf16_hbm_traffic.txt", "rev": "ecbd54fa46e5", "mfma_flops": 116735868928.0, "fetch_kib": 168944.1, "fetch_scale": 2.0, "write_kib": 286720.0, "write_scale": 1.0},
-    "longprefix_bf16": {"file": "stream_pipelined_kernel_longprefix_bf16_hbm_traffic.txt", "rev": "ecbd54fa46e5", "mfma_flops": 279172874240.0, "fetch_kib": 63853.3, "fetch_scale": 2.0, "write_kib": 66566.0, "write_scale": 1.0},
-    "mha13b_bf16": {"file": "stream_pipelined_kernel_mha13b_bf16_hbm_traffic.txt", "rev": "ecbd54fa46e5", "mfma_flops": 3004086353920.0, "fetch_kib": 3172276.4, "fetch_scale": 2.0, "write_kib": 2625024.0, "write_scale": 1.0},
-    "mha7b_bf16": {"file": "resident_general_kernel_mha7b_bf16_hbm_traffic.txt", "rev": "ecbd54fa46e5", "mfma_flops": 34359738368.0, "fetch_kib": 127362.9, "fetch_scale": 2.0, "write_kib": 81920.7, "write_scale": 1.0},
-    "multi32_gqa8b_bf16": {"file": "resident_pipelined_kernel_multi32_gqa8b_bf16_hbm_traffic.txt", "rev": "ecbd54fa46e5", "mfma_flops": 85198897152.0, "fetch_kib": 151797.7, "fetch_scale": 2.0, "write_kib": 197632.0, "write_scale": 1.0},
-    "multi4_long_bf16": {"file": "stream_pipelined_kernel_multi4_long_bf16_hbm_traffic.txt", "rev": "ecbd54fa46e5", "mfma_flops": 73014444032.0, "fetch_kib": 53989.4, "fetch_scale": 2.0, "write_kib": 66584.8, "write_scale": 1.0},
-    "multi8_gqa8b_bf16": {"file": "resident_pipelined_kernel_multi8_gqa8b_bf16_hbm_traffic.txt", "rev": "ecbd54fa46e5", "mfma_flops": 93021274112.0, "fetch_kib": 142853.7, "fetch_scale": 2.0, "write_kib": 197632.0, "write_scale": 1.0},
+    "gqa8b_bf16": {"file": "resident_pipelined_kernel_gqa8b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 111887253504.0, "fetch_kib": 142277.4, "fetch_scale": 2.0, "write_kib": 197632.3, "write_scale": 1.0},
+    "ldec_gqa8b_bf16": {"file": "stream_candidate4_kernel_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 134809124864.0, "fetch_kib": 224628.3, "fetch_scale": 2.0, "write_kib": 327680.0, "write_scale": 1.0},
+    "ldec_qwen7b_bf16": {"file": "stream_candidate4_kernel_ldec_qwen7b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 116735868928.0, "fetch_kib": 169132.7, "fetch_scale": 2.0, "write_kib": 286720.0, "write_scale": 1.0},
+    "longprefix_bf16": {"file": "stream_pipelined_kernel_longprefix_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 279172874240.0, "fetch_kib": 63734.2, "fetch_scale": 2.0, "write_kib": 66563.0, "write_scale": 1.0},
+    "mha13b_bf16": {"file": "stream_pipelined_kernel_mha13b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 3004086353920.0, "fetch_kib": 3171534.3, "fetch_scale": 2.0, "write_kib": 2625024.0, "write_scale": 1.0},
+    "mha7b_bf16": {"file": "resident_general_kernel_mha7b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 34359738368.0, "fetch_kib": 127414.3, "fetch_scale": 2.0, "write_kib": 81921.1, "write_scale": 1.0},
+    "multi32_gqa8b_bf16": {"file": "resident_pipelined_kernel_multi32_gqa8b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 85198897152.0, "fetch_kib": 151799.7, "fetch_scale": 2.0, "write_kib": 197632.0, "write_scale": 1.0},
+    "multi4_long_bf16": {"file": "stream_pipelined_kernel_multi4_long_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 73014444032.0, "fetch_kib": 53989.3, "fetch_scale": 2.0, "write_kib": 66579.1, "write_scale": 1.0},
+    "multi8_gqa8b_bf16": {"file": "resident_pipelined_kernel_multi8_gqa8b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 93021274112.0, "fetch_kib": 142678.2, "fetch_scale": 2.0, "write_kib": 197632.0, "write_scale": 1.0},
 }
 
 
@@ -138,10 +138,10 @@ def cpu_baseline_multi(inp, budget_s=12.0):
 
 # The same for one backward call (its two kernels together).
 HBM_TRAFFIC_BWD = {
-    "gqa8b_bf16": {"file": "bwd_kernels_gqa8b_bf16_hbm_traffic.txt", "rev": "7ccdc52dfc6a", "mfma_flops": 192694714368.0, "fetch_kib": 515452.7, "fetch_scale": 2.0, "write_kib": 300646.8, "write_scale": 1.0},
-    "ldec_gqa8b_bf16": {"file": "bwd_kernels_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "7ccdc52dfc6a", "mfma_flops": 313824116736.0, "fetch_kib": 905107.6, "fetch_scale": 2.0, "write_kib": 496137.0, "write_scale": 1.0},
-    "longprefix_bf16": {"file": "bwd_kernels_longprefix_bf16_hbm_traffic.txt", "rev": "7ccdc52dfc6a", "mfma_flops": 427349245952.0, "fetch_kib": 219126.5, "fetch_scale": 2.0, "write_kib": 99369.9, "write_scale": 1.0},
-    "mha7b_bf16": {"file": "bwd_kernels_mha7b_bf16_hbm_traffic.txt", "rev": "7ccdc52dfc6a", "mfma_flops": 81604378624.0, "fetch_kib": 374522.4, "fetch_scale": 2.0, "write_kib": 250368.5, "write_scale": 1.0},
+    "gqa8b_bf16": {"file": "bwd_kernels_gqa8b_bf16_hbm_traffic.txt", "rev": "ec609a1c48e7", "mfma_flops": 192694714368.0, "fetch_kib": 515239.8, "fetch_scale": 2.0, "write_kib": 300628.8, "write_scale": 1.0},
+    "ldec_gqa8b_bf16": {"file": "bwd_kernels_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "ec609a1c48e7", "mfma_flops": 313824116736.0, "fetch_kib": 904500.7, "fetch_scale": 2.0, "write_kib": 496137.0, "write_scale": 1.0},
+    "longprefix_bf16": {"file": "bwd_kernels_longprefix_bf16_hbm_traffic.txt", "rev": "ec609a1c48e7", "mfma_flops": 427349245952.0, "fetch_kib": 216854.5, "fetch_scale": 2.0, "write_kib": 99374.5, "write_scale": 1.0},
+    "mha7b_bf16": {"file": "bwd_kernels_mha7b_bf16_hbm_traffic.txt", "rev": "ec609a1c48e7", "mfma_flops": 81604378624.0, "fetch_kib": 374523.8, "fetch_scale": 2.0, "write_kib": 250368.6, "write_scale": 1.0},
 }
 
 
