@@ -49,6 +49,17 @@ constexpr float kBig = 1.0e18f;         // row sums at or above this trigger a r
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
 typedef __attribute__((address_space(3))) uintx4 lds_u128;
 
+__device__ inline unsigned lds_addr(lds_u8 *p) { return (unsigned)(unsigned long long)p; }
+__device__ inline lds_u8 *lds_at(unsigned addr) { return (lds_u8 *)(unsigned long long)addr; }
+
+// p + n (n the same for the whole wavefront), added here: what is read from there then has immediate offsets, where the
+// compiler would form each fragment's address outside the loop and spill it (and a reload waits for every request in flight).
+__device__ inline lds_u8 *added_here(lds_u8 *p, int n)
+{
+    asm volatile("" : "+s"(n));
+    return lds_at(lds_addr(p) + (unsigned)n);
+}
+
 __device__ inline unsigned fdiv(unsigned n, FastDiv d) { return (unsigned)(((unsigned long long)n * d.mul) >> d.shift); }
 
 __device__ inline uintx4 ld_global16(const unsigned short *p) { return *reinterpret_cast<const uintx4 *>(p); }
@@ -61,6 +72,18 @@ __device__ inline bf16x8 as_bf16x8(uintx4 v)
 }
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// max and sum of the values that the two lanes sharing a row hold (lane l and l + 32): one swap of half-waves.
+__device__ inline float max_of_halves(float x)
+{
+    const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(y[0]), __uint_as_float(y[1]));
+}
+__device__ inline float sum_of_halves(float x)
+{
+    const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(y[0]) + __uint_as_float(y[1]);
+}
 
 // a * b with the rule that zero times anything, infinities and NaN included, is zero
 // (v_mul_legacy_f32).  Bound to the compiler's own intrinsic rather than written as an inline
@@ -95,6 +118,23 @@ __device__ inline bf16x8 v_fragment(lds_u8 *vt_lane, int dt, int j)
     bf16x8 vf;
     __builtin_memcpy(&vf, &v8, 16);
     return vf;
+}
+
+// p where bit `bit` of `bits` is set, else 0 (also where p is NaN or infinite): the bit as a mask, two instructions (the
+// empty asm keeps the compiler from making a comparison and a select of them).
+__device__ inline float keep_if_bit(float p, int bits, int bit)
+{
+    int mask = __builtin_amdgcn_sbfe(bits, bit, 1);
+    asm("" : "+v"(mask));
+    return __int_as_float(__float_as_int(p) & mask);
+}
+
+// s where that bit is set, else minus infinity (in the same manner).
+__device__ inline float hide_unless_bit(float s, int bits, int bit)
+{
+    int mask = __builtin_amdgcn_sbfe(bits, bit, 1);
+    asm("" : "+v"(mask));
+    return __int_as_float((__float_as_int(s) & mask) | (__float_as_int(-INFINITY) & ~mask));
 }
 
 struct RowState {
@@ -166,6 +206,19 @@ struct Ctx {
     int sv_chunk_lo;  // ... and its 16-byte chunk (+ 4*(fragment >> 1))
     const unsigned short *ksg, *vsg; // suffix K/V of this KV head
 };
+
+// The context with the lane's own values worked out anew, from a lane number that the compiler cannot trace back: used
+// where they are needed once per block, so that they are not kept (and, with all registers taken, spilled) in between.
+__device__ inline Ctx fresh_lane(const Ctx &X)
+{
+    Ctx Y = X;
+    asm volatile("" : "+v"(Y.lane));
+    Y.h = Y.lane >> 5;
+    Y.c32 = Y.lane & 31;
+    Y.sv_row_lo = 4 * ((Y.c32 >> 4) & 1) + ((Y.c32 >> 1) & 3);
+    Y.sv_chunk_lo = 2 * ((Y.c32 >> 3) & 1) + (Y.c32 & 1);
+    return Y;
+}
 
 // Points the context at virtual head vh = instruction * Hkv + KV head: the instruction's real
 // prefix rows are the last plen[instruction] of its P padded rows (App. F.1: the prefix is
@@ -679,8 +732,6 @@ __device__ inline HalfPlaces half_places(int lane)
     return x;
 }
 
-__device__ inline unsigned lds_addr(lds_u8 *p) { return (unsigned)(unsigned long long)p; }
-__device__ inline lds_u8 *lds_at(unsigned addr) { return (lds_u8 *)(unsigned long long)addr; }
 
 // (Images begin at multiples of 256 bytes, so that an exclusive or steps from one of the lane's places to another.)
 __device__ inline void half_put(const HalfPlaces &x, lds_u8 *img, const uintx4 (&raw)[4])
@@ -864,9 +915,10 @@ struct Pre {
 // One tile step of the three-stage software pipeline.  With t the current tile, the step
 //   - computes the raw scores of tile t+1 into sn     (HAS_QK; K fragments from LDS image k_next,
 //                                                      or from the registers skf when FROM_REGS),
-//   - turns the raw scores s of tile t into weights   (relative to the fixed reference m; MASK:
+//   - turns the raw scores s of tile t into weights   (relative to the fixed reference m; MASK 1:
 //     pc, packed bf16, and adds their sum to l         element e is visible iff its key offset
-//                                                      8*(e/4) + e%4 is <= lim),
+//                                                      8*(e/4) + e%4 is <= lim; MASK 2: iff that
+//                                                      bit of lim is set),
 //   - adds tile t-1 to the output: O^T += V^T P^T     (HAS_PV; V image v_prev, weights pp;
 //                                                      FRESH: the accumulators start from zero).
 // Each of its eight sub-steps issues one score MFMA, one value MFMA and the vector work of two
@@ -874,7 +926,7 @@ struct Pre {
 // sum uses plain additions: next to MFMA work the bf16 dot-product instruction costs several
 // times more issue time than two additions.)  LDS fragments are read two sub-steps ahead; the first fragments of the images the following step starts with
 // (k_after when NEXT_K, v_cur when NEXT_V) are read during sub-steps 6 and 7 into `pre`.
-template <bool HAS_QK, bool FROM_REGS, bool HAS_PV, bool FRESH, bool MASK, bool NEXT_K, bool NEXT_V>
+template <bool HAS_QK, bool FROM_REGS, bool HAS_PV, bool FRESH, int MASK, bool NEXT_K, bool NEXT_V>
 __device__ __attribute__((always_inline)) void pipe_tile(lds_u8 *k_next, const uintx4 (&skf)[8], lds_u8 *v_prev,
                                                          lds_u8 *k_after, lds_u8 *v_cur, Pre &pre,
                                                          const uintx4 (&q)[8], const floatx16 &s, floatx16 &sn, float c,
@@ -926,12 +978,16 @@ __device__ __attribute__((always_inline)) void pipe_tile(lds_u8 *k_next, const u
         }
         // vector ALU: weights of elements 2ks and 2ks+1 of the current tile
         float s0 = s[2 * ks], s1 = s[2 * ks + 1];
-        if (MASK) {
+        if (MASK == 1) {
             s0 = 8 * ((2 * ks) >> 2) + ((2 * ks) & 3) <= lim ? s0 : -INFINITY;
             s1 = 8 * ((2 * ks + 1) >> 2) + ((2 * ks + 1) & 3) <= lim ? s1 : -INFINITY;
         }
-        const float p0 = fast_exp2(__builtin_fmaf(s0, c, -m));
-        const float p1 = fast_exp2(__builtin_fmaf(s1, c, -m));
+        float p0 = fast_exp2(__builtin_fmaf(s0, c, -m));
+        float p1 = fast_exp2(__builtin_fmaf(s1, c, -m));
+        if (MASK == 2) {
+            p0 = keep_if_bit(p0, lim, 8 * ((2 * ks) >> 2) + ((2 * ks) & 3));
+            p1 = keep_if_bit(p1, lim, 8 * ((2 * ks + 1) >> 2) + ((2 * ks + 1) & 3));
+        }
         pk[ks] = pack_bf16(p0, p1);
         rs += p0;
         rs += p1;

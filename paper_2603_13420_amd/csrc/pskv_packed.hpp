@@ -1,0 +1,459 @@
+// Packed rows: the valid query rows of one (instruction, KV head) pair, candidate by candidate, each candidate's rows
+// (row i*G + g of position i and head g of the group) filled up to a multiple of `align`:
+//   1   nothing between candidates, blocks of 32 rows whatever candidates they belong to, so that no matrix work is
+//       spent on padding (a seventh of the blocks with lengths of 16..24 of 24 and four heads in a group, three eighths with 20 rows of 32);
+//   32  every block inside one candidate, which has as many as its valid rows need.
+// The keys that a block's rows see besides the prefix lie in one WINDOW, the positions of the block's candidates
+// from the first one's first to the last row's own, and a row sees those from its candidate's first one to itself.
+//
+// The lengths are in device memory.  Every workgroup adds them up (`PackedList`), finds the candidate of the row it begins
+// with and goes on from candidate to candidate (`Walk`).
+#pragma once
+#include "pskv_mfma.hpp"
+
+namespace pskv {
+
+// What a kernel over packed rows is given besides the problem.  Strides in bytes.
+struct PackedArgs {
+    unsigned q_sb, q_ss, q_sh, o_sb, o_ss, o_sh, k_sb, k_ss;
+    int span;       // candidates of one block at most, counted from its first one, for which 32-bit offsets from that one's rows reach
+    int dense;      // windows of align 1 fit (64 positions, so that lane l describes position l)
+    FastDiv div_n;  // division by the number of workgroups that share a list
+    FastDiv div_w;  // ... of wavefronts
+};
+
+// False: a stride is too long for the 24-bit multiplications of the offsets (16 MB), or a candidate for 32-bit ones.
+inline bool packed_args(const Args &a, unsigned sharers, int waves, PackedArgs &x)
+{
+    const long long strides[] = {a.q_sb, a.q_ss, a.q_sh, a.o_sb, a.o_ss, a.o_sh, a.ks_sb, a.ks_ss};
+    long long sb = 1;
+    for (const long long s : strides) {
+        if (s < 0 || s * 2 >= 1 << 24)
+            return false;
+        sb = s > sb ? s : sb;
+    }
+    if (!block_offsets_fit(a) || a.S > 2 * 32)
+        return false;
+    x.q_sb = (unsigned)a.q_sb * 2, x.q_ss = (unsigned)a.q_ss * 2, x.q_sh = (unsigned)a.q_sh * 2;
+    x.o_sb = (unsigned)a.o_sb * 2, x.o_ss = (unsigned)a.o_ss * 2, x.o_sh = (unsigned)a.o_sh * 2;
+    x.k_sb = (unsigned)a.ks_sb * 2, x.k_ss = (unsigned)a.ks_ss * 2;
+    const long long one = 0x7fffffffLL / 2, span = one / sb; // what block_offsets_fit grants one candidate, elements
+    x.span = (int)(span < 1 << 20 ? span : 1 << 20); // (a window entry has 26 bits for it)
+    x.div_n = make_fastdiv(sharers);
+    x.div_w = make_fastdiv(sharers * (unsigned)waves);
+    return true;
+}
+
+// Positions of a window of align 1 at most.
+inline long long packed_window(const Args &a)
+{
+    const long long tokens = 32 % a.G == 0 ? 32 / a.G : (a.G + 30) / a.G + 1;
+    return a.S - 1 + tokens;
+}
+
+namespace {
+
+typedef __attribute__((address_space(3))) int lds_int;
+
+struct Walk {
+    int b, first, len; // candidate (global index), its first packed row, its length: wave-uniform
+};
+
+// Length of candidate b, b the same for the whole wavefront (as len_uniform; there are lengths).
+__device__ inline int packed_len(const Args &a, int b)
+{
+    typedef const __attribute__((address_space(4))) int *const_int_ptr;
+    return clamp_len(a, ((const_int_ptr)(unsigned long long)a.len)[__builtin_amdgcn_readfirstlane(b)]);
+}
+
+__device__ inline int packed_run(const Args &a, int len, int align) { return (len * a.G + align - 1) & -align; }
+
+// Sum over the lanes up to and with this one.
+__device__ inline int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false); // row_shr:1, 2, 4, 8 ...
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false); // ... row_bcast:15 into rows 1 and 3, row_bcast:31 into rows 2 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+    return v;
+}
+
+// The list of one instruction's packed rows, for a workgroup of 512 threads: the candidates in 256 chunks, one per thread
+// of the first four wavefronts (the others request the prefix meanwhile).
+constexpr int kLenWaves = 4, kLenChunks = kLenWaves * 64, kLenPerLane = kLenChunks / 64;
+constexpr int kLenRound = 8;        // lengths per chunk that a thread fetches, and LDS holds, at a time
+constexpr int kListInts = kLenChunks * (kLenRound + 2) + 2 * kLenWaves; // LDS words, in use from count_lengths to find_row
+static_assert(kListInts * 4 <= kNW * kScrBytes, "the list's tables stand in the scratch tiles");
+
+struct PackedList {
+    int total, align; // rows
+    int per_chunk;
+    lds_int *lens;    // first, second, ... lengths of the chunks (of the last round), then rows of a wavefront's chunks up to and with each, for align 1 and for 32, and the wavefronts' rows
+};
+
+// Lengths k0 .. k0 + n - 1 (n <= kLenRound) of this thread's chunk.
+__device__ inline void load_lengths(const Args &a, int cand0, int per_chunk, int k0, int n, int tid, int (&len)[kLenRound])
+{
+    const int lo = tid * per_chunk + k0;
+#pragma unroll
+    for (int k = 0; k < kLenRound; ++k) {
+        len[k] = 0;
+        if (k < n)
+            len[k] = a.len[cand0 + (lo + k < a.C ? lo + k : a.C - 1)];
+    }
+}
+
+// This thread's part: its chunk's rows for align 1 and 32.
+struct ChunkRows {
+    int rows, rows32;
+};
+__device__ inline void count_lengths(const Args &a, int per_chunk, int k0, int n, const int (&len)[kLenRound], lds_int *lens, int tid, ChunkRows &c)
+{
+#pragma unroll
+    for (int k = 0; k < kLenRound; ++k)
+        if (k < n) {
+            const int l = tid * per_chunk + k0 + k < a.C ? clamp_len(a, len[k]) : 0;
+            lens[k * kLenChunks + tid] = l;
+            c.rows += l * a.G;
+            c.rows32 += packed_run(a, l, kBlockRows);
+        }
+}
+
+// Adds the chunks up (the first four wavefronts; a workgroup barrier follows).
+__device__ inline void add_up(const ChunkRows &c, lds_int *lens, int tid)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    lds_int *const tables = lens + kLenRound * kLenChunks, *const sums = tables + 2 * kLenChunks;
+    const int upto = wave_scan(c.rows), upto32 = wave_scan(c.rows32);
+    tables[tid] = upto;
+    tables[kLenChunks + tid] = upto32;
+    if ((tid & 63) == 63) {
+        sums[wave] = upto;
+        sums[kLenWaves + wave] = upto32;
+    }
+}
+
+// Chooses the alignment.  Blocks across candidates are fewer, but their
+// windows may go on to a second step: where a candidate's positions and a block's are more than 32, which with lengths of n
+// is one block in n / (n + 32/G - 32).  A block takes the time of its tiles and some 6 more; a second step is counted
+// as 18 - 1.4 for every prefix tile, what it costs and what blocks that memory bounds do not gain by being fewer.  us, across
+// candidates and inside them, 1500 candidates, P 200 (500, P 250; 700, P 128): 32/32 heads: 20 positions: 222, 237 (81, 91; 107, 106);
+// 17..25: 252, 246 (92, 94; 117, 114); 11..28: 246, 242 (87, 92; 119, 115); 22..32: 320, 300 (114, 103; 154, 143); 32/8: 28 positions: 217, 234 (83,
+// 89; 96, 95); 32: 245, 243 (94, 93; 105, 105); 22..32: 217, 225 (84, 85; 93, 91); no second steps: 20: 153, 172 (57, 63; 65, 69).
+// Where every wavefront has at most one block either way, blocks inside candidates: they take the shorter walk (32 candidates of 8..20,
+// 32/8 heads, P 128: 11.6 us across, 11.1 inside).
+template <bool TWO>
+__device__ inline PackedList choose_list(const Args &a, const PackedArgs &pa, int tiles, int waves, int per_chunk, lds_int *lens)
+{
+    lds_int *const sums = lens + (kLenRound + 2) * kLenChunks;
+    int total = 0, total32 = 0;
+#pragma unroll
+    for (int i = 0; i < kLenWaves; ++i) {
+        total += sums[i];
+        total32 += sums[kLenWaves + i];
+    }
+    total = __builtin_amdgcn_readfirstlane(total);
+    total32 = __builtin_amdgcn_readfirstlane(total32);
+    long long second = TWO ? total - 32LL * (a.G - 1) * a.C : 0; // rows of blocks with a second step
+    second = second > 0 ? second : 0;
+    const int second_cost = tiles < 10 ? 180 - 14 * tiles : 40; // (tenths of a tile's time)
+    const bool one = pa.dense && total32 > 32 * waves && (long long)total * (10 * (tiles + 6)) + second_cost * second < (long long)total32 * (10 * (tiles + 6));
+    PackedList x;
+    x.align = one ? 1 : kBlockRows;
+    x.total = one ? total : total32;
+    x.per_chunk = per_chunk;
+    x.lens = lens;
+    return x;
+}
+
+// The candidate of packed row r0 (one that exists).
+__device__ inline Walk find_row(const Args &a, const PackedList &x, int cand0, int r0, int lane)
+{
+    lds_int *const tables = x.lens + kLenRound * kLenChunks, *const before = x.align == 1 ? tables : tables + kLenChunks;
+    lds_int *const sums = tables + 2 * kLenChunks + (x.align == 1 ? 0 : kLenWaves);
+    constexpr int n = kLenPerLane;
+    int upto = before[n * lane + n - 1]; // lane j: rows of the first n*(j + 1) chunks
+#pragma unroll
+    for (int i = 0; i < kLenWaves - 1; ++i)
+        upto += i < (lane / (64 / kLenWaves)) ? sums[i] : 0;
+    const int g = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= r0)); // (below 64: the row exists)
+    const int base = g > 0 ? __builtin_amdgcn_readlane(upto, g > 0 ? g - 1 : 0) : 0;
+    const int part = before[n * g + (lane & (n - 1))] + (g % (64 / kLenWaves) ? base - before[g > 0 ? n * g - 1 : 0] : base);
+    const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < n && part <= r0));
+    Walk w;
+    w.b = __builtin_amdgcn_readfirstlane(cand0 + (n * g + c) * x.per_chunk);
+    w.first = c > 0 ? __builtin_amdgcn_readlane(part, c > 0 ? c - 1 : 0) : base;
+    const int chunk = n * g + c;
+    w.len = x.per_chunk <= kLenRound ? __builtin_amdgcn_readfirstlane(x.lens[chunk]) : packed_len(a, w.b);
+    return w;
+}
+
+// One block of 32 packed rows.
+template <bool TWO> struct PackedBlock {
+    int r0, rows;   // its first row; rows of the list from there on (of them 32 are the block's)
+    int b, first;   // the window's first candidate and that one's first packed row
+    int width;      // the window's positions
+    unsigned win;   // lane l (TWO; else lanes l and l + 32): window position l (the last one past the end): (candidate - b) << 6 | position
+    unsigned o_off; // byte offset of the lane's row from the first candidate's first out row; bit 0: stored as zero
+    unsigned sees;  // the window's keys that the lane's row sees: as bits, or (TWO) their last one and 256 times their first
+    bool wide;      // the candidates lie too far apart for 32-bit offsets from the first one's rows
+};
+
+// One lane's row of a packed block.  A row past its candidate's length (align 32) takes the query row and the keys of
+// the last position that the block sees and is stored as zero; rows past the list's or the candidate's end are the last one once more.
+struct PackedRow {
+    int pos, gq;        // window position of its key, query head within the group
+    unsigned from, own; // entries (as in `win`) of the row it loads and of the row it stores
+};
+
+template <bool TWO> __device__ inline PackedRow packed_row(const Args &a, const PackedBlock<TWO> &x, int row, int align)
+{
+    PackedRow y;
+    const int most = align > 1 ? a.S * a.G - 1 : x.r0 - x.first + x.rows - 1;
+    int j = x.r0 - x.first + row;
+    j = j < most ? j : most;
+    const int pos = (int)fdiv(j, a.div_g);
+    y.gq = j - pos * a.G;
+    y.pos = pos < x.width ? pos : x.width - 1;
+    y.from = (unsigned)__shfl((int)x.win, y.pos, 64);
+    y.own = pos < x.width ? y.from : (unsigned)pos;
+    return y;
+}
+
+// Byte offset of an entry's row from that of the block's first candidate's first one.
+__device__ inline unsigned packed_off(unsigned entry, unsigned sb, unsigned ss) { return __umul24(entry >> 6, sb) + __umul24(entry & 63, ss); }
+
+// The block of packed rows r0..; w at or before the candidate of row r0, and left at its last row's.  q_off: byte offset of the
+// lane's query row from the first candidate's first one.
+template <bool TWO>
+__device__ inline PackedBlock<TWO> packed_block(const Args &a, const PackedArgs &pa, const Ctx &X, Walk &w, int r0, const PackedList &list, unsigned &q_off)
+{
+    PackedBlock<TWO> x;
+    x.r0 = r0;
+    x.rows = list.total - r0;
+    const int last = x.rows < kBlockRows ? list.total - 1 : r0 + kBlockRows - 1;
+    int end = w.first + packed_run(a, w.len, list.align);
+    while (end <= r0) {
+        w.first = end;
+        ++w.b;
+        w.len = packed_len(a, w.b);
+        end += packed_run(a, w.len, list.align);
+    }
+    x.b = w.b;
+    x.first = w.first;
+    const int l = TWO ? X.lane : X.c32;
+    unsigned entry = l; // as if all were the first candidate's
+    int at = 0;         // window position of the walk's candidate's first
+    while (end <= last) {
+        at += w.len;
+        w.first = end;
+        ++w.b;
+        w.len = packed_len(a, w.b);
+        end += packed_run(a, w.len, list.align);
+        entry = l >= at ? (unsigned)((w.b - x.b) << 6 | (l - at)) : entry;
+    }
+    const int upto = __builtin_amdgcn_readfirstlane((int)fdiv(last - w.first, a.div_g)) + 1; // the last candidate's positions
+    const int more = upto < w.len ? upto : w.len;
+    x.width = at + more;
+    const unsigned end_entry = (unsigned)((w.b - x.b) << 6 | (more - 1));
+    x.win = l < x.width ? entry : end_entry;
+    x.wide = w.b - x.b >= pa.span;
+    if (x.wide)
+        x.win = 0;
+    const PackedRow y = packed_row(a, x, X.c32, list.align);
+    const unsigned rh = (unsigned)(X.head * a.G + y.gq);
+    q_off = packed_off(y.from, pa.q_sb, pa.q_ss) + __umul24(rh, pa.q_sh);
+    x.o_off = (packed_off(y.own, pa.o_sb, pa.o_ss) + __umul24(rh, pa.o_sh)) | (y.own == y.from ? 0u : 1u);
+    const int lo = y.pos - (int)(y.from & 63); // the window's keys from its candidate's first to its own
+    x.sees = TWO ? (unsigned)(y.pos | lo << 8) : (2u << y.pos) - (1u << lo);
+    return x;
+}
+
+// The bits of the keys that the lane's row sees of window positions k0 .. k0 + 31, element e's at 8*(e/4) + e%4.
+template <bool TWO> __device__ inline int sees_bits(const PackedBlock<TWO> &x, int k0, int h)
+{
+    unsigned bits = x.sees;
+    if constexpr (TWO) {
+        const int end = (int)(x.sees & 255) + 1 - k0, lo = (int)(x.sees >> 8) - k0; // one past the last key, the first one
+        bits = (end >= 32 ? ~0u : end > 0 ? (1u << end) - 1u : 0u) & (lo <= 0 ? ~0u : lo < 32 ? ~0u << lo : 0u);
+    }
+    return (int)(bits >> (4 * h));
+}
+
+// Q fragments of the block (layout as in load_q).
+__device__ inline void load_q_packed(const Args &a, const PackedArgs &pa, const Ctx &X, int b, unsigned q_off, uintx4 (&dst)[8])
+{
+    const unsigned char *qrow = reinterpret_cast<const unsigned char *>(a.q) + (unsigned long long)(unsigned)b * pa.q_sb + (q_off + 16u * X.h);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+        dst[ks] = *reinterpret_cast<const uintx4 *>(qrow + 32 * ks);
+}
+
+// K fragments and V rows of the window's positions k0..k0+31 (layouts as in load_suffix_k and load_suffix_v; past the
+// window its last position, which no row takes for that one's).
+template <bool TWO> __device__ inline void load_window_k(const PackedArgs &pa, const Ctx &X, const PackedBlock<TWO> &x, int k0, uintx4 (&kf)[8])
+{
+    const unsigned e = TWO ? (unsigned)__shfl((int)x.win, k0 + X.c32, 64) : x.win;
+    const unsigned char *kp = reinterpret_cast<const unsigned char *>(X.ksg) + (unsigned long long)(unsigned)x.b * pa.k_sb +
+                              (packed_off(e, pa.k_sb, pa.k_ss) + 16u * X.h);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks)
+        kf[ks] = *reinterpret_cast<const uintx4 *>(kp + 32 * ks);
+}
+
+template <bool TWO> __device__ inline void load_window_v(const PackedArgs &pa, const Ctx &X, const PackedBlock<TWO> &x, int k0, uintx4 (&vf)[2][4])
+{
+    const unsigned char *base = reinterpret_cast<const unsigned char *>(X.vsg) + (unsigned long long)(unsigned)x.b * pa.k_sb;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) { // (fragment (dt, u) = (it, h) of load_suffix_v)
+        const unsigned e = (unsigned)__shfl((int)x.win, k0 + 16 * j + 8 * X.h + X.sv_row_lo, 64);
+        const unsigned char *vp = base + (packed_off(e, pa.k_sb, pa.k_ss) + (unsigned)X.sv_chunk_lo * 16u);
+#pragma unroll
+        for (int it = 0; it < 4; ++it)
+            vf[j][it] = *reinterpret_cast<const uintx4 *>(vp + 64 * it);
+    }
+}
+
+// Normalise and store the block (as store_block).
+template <bool TWO>
+__device__ inline void store_packed(const Args &a, const PackedArgs &pa, const Ctx &X, const PackedBlock<TWO> &x, int align, float m, float l, const floatx16 (&o)[4])
+{
+    const float ltot = sum_of_halves(l);
+    const float inv = 1.0f / ltot;
+    const bool rvalid = !(x.o_off & 1);
+    unsigned char *base = reinterpret_cast<unsigned char *>(a.out) + (unsigned long long)(unsigned)x.b * pa.o_sb;
+    unsigned short *dst[4];
+    bool dst_ok[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const unsigned off = (unsigned)__shfl((int)x.o_off, 8 * u + (X.lane >> 3), 64) & ~1u;
+        dst[u] = reinterpret_cast<unsigned short *>(base + (off + 16u * (X.lane & 7)));
+        // (lanes past the last row are that row once more, with its bits: stored too, so that the number of stores in flight is
+        // known and the wait for the next block's Q, requested before them, is not one for the stores)
+        dst_ok[u] = true;
+    }
+    store_rows(X, dst, dst_ok, rvalid, inv, o);
+    if (a.lse) {
+        const PackedRow y = packed_row(a, x, X.c32, align); // (takes entries from all lanes)
+        if (X.h == 0)
+            a.lse[((long long)(x.b + (int)(y.own >> 6)) * a.Hq + X.head * a.G + y.gq) * a.S + (int)(y.own & 63)] =
+                rvalid ? (m + __builtin_log2f(ltot)) * kLn2 : -INFINITY;
+    }
+}
+
+// A window step after the first: raw scores s of 32 positions of which the row sees those whose bits are set (shifted for
+// the lane's half), weights relative to the fixed reference m, value product through the scratch tile.
+__device__ inline void window_step_fixed(const Ctx &X, int bits, const floatx16 &s, float m, float &l, const uintx4 (&svf)[2][4], floatx16 (&o)[4])
+{
+    unsigned pk[8];
+    float rs = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+        const float p0 = keep_if_bit(fast_exp2(__builtin_fmaf(s[e], X.c, -m)), bits, 8 * (e >> 2) + (e & 3));
+        const float p1 = keep_if_bit(fast_exp2(__builtin_fmaf(s[e + 1], X.c, -m)), bits, 8 * ((e + 1) >> 2) + ((e + 1) & 3));
+        rs += p0;
+        rs += p1;
+        pk[e >> 1] = pack_bf16(p0, p1);
+    }
+    l += rs;
+    pv_from_scratch(X, svf[0], as_bf16x8(uintx4{pk[0], pk[1], pk[2], pk[3]}), o);
+    pv_from_scratch(X, svf[1], as_bf16x8(uintx4{pk[4], pk[5], pk[6], pk[7]}), o);
+}
+
+// Zeros for candidate b's rows past those that its blocks store, of this KV head's query heads (whole rows, 16 lanes each).
+__device__ inline void store_padding(const Args &a, const PackedArgs &pa, const Ctx &X, int b, int align)
+{
+    const int all = a.S * a.G, from = packed_run(a, packed_len(a, b), align);
+    unsigned char *base = reinterpret_cast<unsigned char *>(a.out) + (unsigned long long)(unsigned)b * pa.o_sb + (unsigned)(X.head * a.G) * pa.o_sh;
+    for (int r = from + (X.lane >> 4); r < all; r += 4) {
+        const unsigned t = fdiv(r, a.div_g), gq = r - t * a.G;
+        __builtin_nontemporal_store(uintx4{0, 0, 0, 0}, reinterpret_cast<uintx4 *>(base + (__umul24(t, pa.o_ss) + __umul24(gq, pa.o_sh) + 16u * (X.lane & 15))));
+    }
+    if (a.lse)
+        for (int r = from + X.lane; r < all; r += 64) {
+            const unsigned t = fdiv(r, a.div_g), gq = r - t * a.G;
+            a.lse[((long long)b * a.Hq + X.head * a.G + (int)gq) * a.S + (int)t] = -INFINITY;
+        }
+}
+
+// The classic online softmax over a packed block whatever its rows and prefix are (prefix images in LDS).
+__device__ __attribute__((always_inline)) void packed_general_block(const Args &a, const PackedArgs &pa, const Ctx &X, int ntiles, const Walk &begin, int r0, const PackedList &list)
+{
+    Walk w = begin;
+    unsigned q_off;
+    PackedArgs far = pa;
+    far.span = 1 << 26; // (the offsets that do not reach are not used here)
+    const PackedBlock<true> x = packed_block<true>(a, far, X, w, r0, list, q_off);
+    const PackedRow y = packed_row(a, x, X.c32, list.align);
+    Row row;
+    row.rb = x.b + (y.from >> 6);
+    row.ri = y.from & 63;
+    row.rh = X.head * a.G + y.gq;
+    uintx4 q[8];
+    load_q(a, X, row, q);
+    RowState st;
+    st.m = -INFINITY;
+    st.l = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            st.o[dt][e] = 0.f;
+    for (int kt = 0; kt < ntiles; ++kt)
+        prefix_tile_classic(X, X.k_lane + kt * kTileBytes, X.v_lane + kt * kTileBytes, X.P - kt * kTileKeys, q, st);
+    for (int k0 = 0; k0 < x.width; k0 += kTileKeys) {
+        uintx4 kf[8], vf[2][4];
+        auto row_of = [&](const unsigned short *base, int pos) {
+            const unsigned e = (unsigned)__shfl((int)x.win, pos, 64);
+            return base + (long long)(x.b + (int)(e >> 6)) * a.ks_sb + (long long)(e & 63) * a.ks_ss;
+        };
+        const unsigned short *kp = row_of(X.ksg, k0 + X.c32) + 8 * X.h;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
+            kf[ks] = ld_global16(kp + 16 * ks);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const unsigned short *vp = row_of(X.vsg, k0 + 16 * j + 8 * X.h + X.sv_row_lo) + 8 * X.sv_chunk_lo;
+#pragma unroll
+            for (int it = 0; it < 4; ++it)
+                vf[j][it] = ld_global16(vp + 32 * it);
+        }
+        const unsigned bits = (unsigned)sees_bits(x, k0, X.h);
+        floatx16 s;
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            s[e] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks)
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), as_bf16x8(q[ks]), s, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+            s[e] = bits >> (8 * (e >> 2) + (e & 3)) & 1 ? s[e] : -INFINITY;
+        bf16x8 pf[2];
+        softmax_tile(s, st, X.c, pf);
+        pv_from_scratch(X, vf[0], pf[0], st.o);
+        pv_from_scratch(X, vf[1], pf[1], st.o);
+    }
+    const float ltot = sum_of_halves(st.l);
+    const unsigned at = y.own; // (entries and heads of the rows that this lane stores come from the lanes that own them)
+    unsigned short *dst[4];
+    bool dst_ok[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int from = 8 * u + (X.lane >> 3);
+        const unsigned e = (unsigned)__shfl((int)at, from, 64);
+        const int rh = __shfl(row.rh, from, 64);
+        dst[u] = reinterpret_cast<unsigned short *>(a.out) + (long long)(x.b + (int)(e >> 6)) * a.o_sb + (long long)(e & 63) * a.o_ss + (long long)rh * a.o_sh +
+                 8 * (X.lane & 7);
+        dst_ok[u] = true;
+    }
+    store_rows(X, dst, dst_ok, y.own == y.from, 1.0f / ltot, st.o);
+    if (a.lse && X.h == 0)
+        a.lse[((long long)(x.b + (int)(y.own >> 6)) * a.Hq + row.rh) * a.S + (int)(y.own & 63)] =
+            y.own == y.from ? (st.m + __builtin_log2f(ltot)) * kLn2 : -INFINITY;
+}
+
+} // namespace
+} // namespace pskv

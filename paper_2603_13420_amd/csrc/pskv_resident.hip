@@ -17,8 +17,10 @@
 // suffix fits one 32-key step: it overlaps, inside each wavefront, the score product of the
 // next tile (matrix cores) with the exponentials of the current one (vector ALU), requests
 // everything it needs from global memory a full block ahead, and never branches on data.
+// The third takes calls that bring suffix lengths (and the same suffix and prefix sizes as the pipelined one): the same pipeline over
+// packed rows, valid ones only (pskv_packed.hpp).
 // Operand layouts and the pieces shared with the streaming kernels are in pskv_mfma.hpp.
-#include "pskv_mfma.hpp"
+#include "pskv_packed.hpp"
 
 namespace pskv {
 namespace {
@@ -324,6 +326,233 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles, 
     } // virtual heads
 }
 
+// ------------------------------------------------------------------------------------------
+// Pipelined path over packed rows (see pskv_packed.hpp).  Preconditions (checked by the launcher): suffix lengths; S <= 32; a window
+// of at most 32 positions unless TWO; padded prefix of at least three tiles, one head's of less than 2^31 bytes.
+//
+// Bound by the instructions of a block, as the kernel above, and by memory where the prefix is short; what it gains is blocks: 20480
+// instead of 23700 for 1024 candidates of 16..24 of 24 positions, 32/8 heads, P 256 (129 -> 120 us; the same with eight instructions 118 -> 109).
+// A block costs some 15 % more vector instructions than there (places of rows and keys, masks with two ends).  Two things cost
+// more than they look: a spilled register's reload in the block loop waits for every request in flight (six of them took back all of the
+// gain), and a store under a branch makes the wait for the next block's Q one for the stores.
+// Small calls take a workgroup per block while there are compute units: a wavefront alone on its SIMD gets through a block in
+// little more than half the time (32 candidates of 20 positions, 32/8 heads, P 128: 11.2 us with eight blocks to a workgroup, 8.5 so; 12 before).
+// ------------------------------------------------------------------------------------------
+template <bool TWO>
+__global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
+void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int max_tiles)
+{
+    extern __shared__ __align__(16) unsigned char smem_generic[];
+    lds_u8 *smem = (lds_u8 *)smem_generic;
+    const int tid = threadIdx.x;
+    Ctx X = make_ctx(a, smem, max_tiles, tid);
+    const int VH = a.Np * a.Hkv;
+    auto kimg = [&](int t) { return X.k_lane + t * kTileBytes; };
+    auto vimg = [&](int t) { return X.v_lane + t * kTileBytes; };
+    const int wslot = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slice = blockIdx.x / vh_slots;
+    const int per_chunk = (a.C + kLenChunks - 1) / kLenChunks, waves = per_vh * kNW, me = slice * kNW + wslot;
+    lds_int *const lens = (lds_int *)(smem + 2 * max_tiles * kTileBytes); // (in the scratch)
+
+    for (int vh = blockIdx.x % vh_slots; vh < VH; vh += vh_slots) {
+        set_vhead(a, X, vh);
+        const int T = (X.P + kTileKeys - 1) / kTileKeys;
+        __syncthreads(); // every wavefront is done with the images and the scratch of the virtual head before
+
+        PackedList list;
+        int blk = 0, blk_lo = 0, blk_hi = 0;
+        Walk w, begin;
+        PackedBlock<TWO> nxt = {0, 1, X.cand0, 0, 1, 0u, 0u, 1u, false};
+        unsigned q_off = (unsigned)(X.head * a.G) * pa.q_sh;
+        uintx4 q[8]; // this block's Q fragments until their last use, then the next block's
+        bool any_bad = false;
+        // Moves on to the next block whose candidates lie close enough together; w and nxt stay where they are past the last one.
+        auto advance = [&](int n) __attribute__((always_inline)) {
+            for (; n < blk_hi; ++n) {
+                nxt = packed_block<TWO>(a, pa, fresh_lane(X), w, n * kBlockRows, list, q_off);
+                if (!nxt.wide)
+                    break;
+                any_bad = true;
+            }
+            return n;
+        };
+        // Four wavefronts fetch the lengths and add them up while the other four request the prefix straight into LDS (rows past it
+        // take its last row's place).
+        int fresh = tid; // (what is worked out from it is not kept over the block loop)
+        asm volatile("" : "+v"(fresh));
+        if (wslot < kLenWaves) {
+            ChunkRows mine = {0, 0};
+            for (int k0 = 0; k0 < per_chunk; k0 += kLenRound) {
+                int len[kLenRound];
+                const int n = per_chunk - k0 < kLenRound ? per_chunk - k0 : kLenRound;
+                load_lengths(a, X.cand0, per_chunk, k0, n, fresh, len);
+                count_lengths(a, per_chunk, k0, n, len, lens, fresh, mine);
+            }
+            add_up(mine, lens, fresh);
+        } else {
+            const TileSlot ts = make_tile_slot(fresh - kLenWaves * 64);
+            const unsigned row = (unsigned)a.kp_sp * 2u;
+            for (int t = 0; t < T; ++t) {
+                const int left = X.P - t * kTileKeys - 1; // the last row's place in the tile
+                lds_u8 *const at = smem + t * kTileBytes + (wslot - kLenWaves) * 1024;
+                const unsigned char *const k0 = reinterpret_cast<const unsigned char *>(X.kpg) + (unsigned)t * kTileKeys * row;
+                const unsigned char *const v0 = reinterpret_cast<const unsigned char *>(X.vpg) + (unsigned)t * kTileKeys * row;
+                const unsigned ko = (unsigned)(ts.k_row < left ? ts.k_row : left) * row + ts.k_chunk * 16u, vo = (unsigned)(ts.v_row < left ? ts.v_row : left) * row + ts.v_chunk * 16u;
+                request_to_lds(k0, ko, at); // (half of the image per request: columns 0..63, then 64..127)
+                request_to_lds(k0 + 128, ko, at + kTileBytes / 2);
+                request_to_lds(v0, vo, at + max_tiles * kTileBytes);
+                request_to_lds(v0 + 128, vo, at + max_tiles * kTileBytes + kTileBytes / 2);
+            }
+        }
+        __syncthreads();
+        list = choose_list<TWO>(a, pa, T, waves, per_chunk, lens);
+        {
+            // Shares as in the kernel above: contiguous ranges, a quarter of the workgroup's per SIMD, 7/12 of that for the first of its two.
+            const int nblocks = (list.total + kBlockRows - 1) / kBlockRows, each = (int)fdiv(nblocks, pa.div_n), over = nblocks - each * per_vh;
+            const int wg_lo = slice * each + (slice < over ? slice : over), wg_n = each + (slice < over ? 1 : 0), simd = wslot & 3;
+            const int part_lo = wg_lo + (wg_n * simd >> 2), part_hi = wg_lo + (wg_n * (simd + 1) >> 2);
+            const int split = part_lo + ((part_hi - part_lo) * 7 + 6) / 12;
+            blk_lo = wslot < 4 ? part_lo : split, blk_hi = wslot < 4 ? split : part_hi;
+            if (blk_lo < blk_hi)
+                begin = w = find_row(a, list, X.cand0, blk_lo * kBlockRows, fresh & 63);
+            blk = T < 3 ? blk_hi : advance(blk_lo);
+            load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
+        }
+        asm volatile("" ::: "memory"); // (Q's eight requests stand before this)
+        if (wslot >= kLenWaves) {
+            PSKV_WAIT_VM(8);
+            if (T > 0) { // zeros where the last tile has no row
+                const TileSlot ts = make_tile_slot(fresh - kLenWaves * 64);
+                const int left = X.P - (T - 1) * kTileKeys - 1;
+                lds_u8 *const at = smem + (T - 1) * kTileBytes + (fresh - kLenWaves * 64) * 16;
+                if (ts.k_row > left) {
+                    *(lds_u128 *)at = uintx4{0, 0, 0, 0};
+                    *(lds_u128 *)(at + kTileBytes / 2) = uintx4{0, 0, 0, 0};
+                }
+                if (ts.v_row > left) {
+                    *(lds_u128 *)(at + max_tiles * kTileBytes) = uintx4{0, 0, 0, 0};
+                    *(lds_u128 *)(at + max_tiles * kTileBytes + kTileBytes / 2) = uintx4{0, 0, 0, 0};
+                }
+            }
+        }
+        __syncthreads();
+
+        // Padding: the instruction's candidates are dealt out over the wavefronts, and their rows past their lengths stored a
+        // few candidates per block.
+        int pad = me;
+        int shares = (int)fdiv(a.C + waves - 1, pa.div_w);
+        asm volatile("" : "+s"(shares));
+        const int pads = waves * __builtin_amdgcn_readfirstlane((int)((float)shares * __builtin_amdgcn_rcpf((float)(blk_hi > blk ? blk_hi - blk : 1))) + 1);
+
+        while (blk < blk_hi) {
+            const PackedBlock<TWO> x = nxt;
+            // Loads are retired in issue order, so what is needed last is requested first.
+            uintx4 skf[8], svf[2][4];
+            load_window_k(pa, fresh_lane(X), x, 0, skf);
+
+            // ---- first prefix tile: scores, reference maximum ----
+            floatx16 sA, sB; // raw scores of the current and of the next tile, roles alternating
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                sA[e] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks)
+                sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*(lds_u128 *)(X.k_lane + ks * 1024)), as_bf16x8(q[ks]),
+                                                             sA, 0, 0, 0);
+            Pre pre;
+#pragma unroll
+            for (int i = 0; i < kDist; ++i)
+                pre.k[i] = *(lds_u128 *)(kimg(1) + i * 1024);
+            float m = sA[0];
+#pragma unroll
+            for (int e = 1; e < 16; ++e)
+                m = fmaxf(m, sA[e]);
+            m = max_of_halves(m) * X.c; // (the other half-wave holds the other 16 keys)
+            // (Stores whose number the compiler does not know stand where the next wait for a load is far: after Q's, before K's.)
+            for (const int to = pad + pads < a.C ? pad + pads : a.C; pad < to; pad += waves)
+                store_padding(a, pa, fresh_lane(X), X.cand0 + pad, list.align);
+            float l = 0.f;
+            floatx16 o[4];
+            uintx4 pA[2], pB[2]; // packed weights of the current and of the previous tile, roles alternating
+
+            // ---- pipeline over the prefix tiles: step t = scores of tile t+1, weights of tile t,
+            //      value product of tile t-1 ----
+            pipe_tile<true, false, false, false, 0, true, true>(kimg(1), skf, vimg(0), kimg(2), vimg(0), pre, q, sA, sB,
+                                                                X.c, m, 0, l, pA, pA, o);
+            pipe_tile<true, false, true, true, 0, true, true>(kimg(2), skf, vimg(0), added_here(X.k_lane, (3 < T ? 3 : T - 1) * kTileBytes), vimg(1), pre,
+                                                              q, sB, sA, X.c, m, 0, l, pA, pB, o);
+            int t = 2;
+            for (; t + 1 <= T - 2; t += 2) {
+                pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 1), skf, vimg(t - 1), kimg(t + 2), vimg(t), pre,
+                                                                   q, sA, sB, X.c, m, 0, l, pB, pA, o);
+                pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 2), skf, vimg(t), kimg(t + 3 < T ? t + 3 : T - 1),
+                                                                   vimg(t + 1), pre, q, sB, sA, X.c, m, 0, l, pA, pB, o);
+            }
+            if (t <= T - 2) { // one step left over: do it and put scores and weights back in their places
+                pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 1), skf, vimg(t - 1), kimg(T - 1), vimg(t), pre,
+                                                                   q, sA, sB, X.c, m, 0, l, pB, pA, o);
+                sA = sB;
+                pB[0] = pA[0];
+                pB[1] = pA[1];
+            }
+            if (X.P & (kTileKeys - 1)) { // ragged last prefix tile: keys past the prefix are not visible
+                int bits = (1 << (X.P - (T - 1) * kTileKeys)) - 1;
+                bits >>= 4 * fresh_lane(X).h; // element e holds key 8*(e/4) + e%4 + 4*h of the tile
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    sA[e] = hide_unless_bit(sA[e], bits, 8 * (e >> 2) + (e & 3));
+            }
+            load_window_v(pa, fresh_lane(X), x, 0, svf); // one step ahead of its use
+            lds_u8 *const v_last = added_here(X.v_lane, (T - 1) * kTileBytes);
+            // ---- last prefix tile: the "next scores" are the window's first ones, from the K registers ----
+            pipe_tile<true, true, true, false, 0, false, true>(kimg(0), skf, added_here(X.v_lane, (T - 2) * kTileBytes), kimg(0), v_last, pre, q, sA,
+                                                               sB, X.c, m, 0, l, pB, pA, o);
+
+            // Unless the window goes on, Q has been used for the last time: the next block's rows and Q take its place.
+            // (Requested unconditionally, past the end for the last block once more.)
+            const bool more = TWO && x.width > kTileKeys;
+            if (!more) {
+                blk = advance(blk + 1);
+                load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
+            }
+
+            // ---- first window step: mask and weights under the value product of the last prefix
+            //      tile; then its own value product through the scratch tile ----
+            pipe_tile<false, false, true, false, 2, false, false>(kimg(0), skf, v_last, kimg(0), vimg(0), pre, q, sB, sB,
+                                                                  X.c, m, sees_bits(x, 0, fresh_lane(X).h), l, pA, pB, o);
+            const Ctx Y = fresh_lane(X);
+            if (more)
+                load_window_k(pa, Y, x, kTileKeys, skf);
+            pv_from_scratch(Y, svf[0], as_bf16x8(pB[0]), o);
+            pv_from_scratch(Y, svf[1], as_bf16x8(pB[1]), o);
+            if (more) {
+                load_window_v(pa, fresh_lane(X), x, kTileKeys, svf);
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    sB[e] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks)
+                    sB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(skf[ks]), as_bf16x8(q[ks]), sB, 0, 0, 0);
+                blk = advance(blk + 1);
+                load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
+                window_step_fixed(Y, sees_bits(x, kTileKeys, Y.h), sB, m, l, svf, o);
+            }
+
+            any_bad |= __builtin_amdgcn_ballot_w64(!(l < kBig)) != 0;
+            store_packed(a, pa, fresh_lane(X), x, list.align, m, l, o);
+        }
+        for (; pad < a.C; pad += waves)
+            store_padding(a, pa, fresh_lane(X), X.cand0 + pad, list.align);
+
+        // Rare: some row met scores far above its first tile's maximum, or a block's candidates lie far apart: whatever this
+        // wavefront stored is replaced by the general path's result.  The same for an instruction whose prefix is too short for
+        // the pipeline.
+        if (any_bad || T < 3)
+            for (int b2 = blk_lo; b2 < blk_hi; ++b2)
+                packed_general_block(a, pa, X, T, begin, b2 * kBlockRows, list);
+    } // virtual heads
+}
+
 } // namespace
 
 bool resident_supported(const Args &a)
@@ -340,6 +569,9 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
         hipError_t s = hipFuncSetAttribute(reinterpret_cast<const void *>(resident_general_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
         for (auto kernel : {resident_pipelined_kernel<true>, resident_pipelined_kernel<false>})
+            if (s == hipSuccess)
+                s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
+        for (auto kernel : {resident_packed_kernel<true>, resident_packed_kernel<false>})
             if (s == hipSuccess)
                 s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
         return s;
@@ -368,6 +600,18 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
         const double straddled = rows_c < kBlockRows ? 1. : (double)kBlockRows / rows_c;
         const long long each_own = resident_split(a, own, kNW, num_cu).each, each_stacked = resident_split(a, stacked, kNW, num_cu).each;
         pipelined = each_own * (max_tiles + 1) + 4 <= 1.7 * each_stacked * (max_tiles + 1 + straddled);
+    }
+    // Rows packed by their lengths, where there are lengths: us, before and so: 32/8 heads: 1500 x 20, P 200: 177, 152; 1500 x 8..20: 145, 117; 500 x 28,
+    // P 250: 91, 82; 700 x 28, P 128: 95, 94; 500 x 32: 93, 93; 1500 x 32: 237, 242 (nothing to pack); 32/32: 1500 x 14, P 200: 182, 154; 512 x 20, P 128:
+    // 75, 75 (its bytes alone take 66); 700 x 22..32, P 128: 139, 142; 28/4: 200 x 28, P 100: 25.3, 21.8; 8 x 12..24, 32/8, P 100: 11.3, 7.8.
+    PackedArgs pa;
+    const ResidentSplit packed = resident_split(a, own * kNW, kNW, num_cu); // (a workgroup per block while there are compute units)
+    if (a.len && max_tiles >= 3 && a.S <= kTileKeys && own <= 0x7fffffffLL / kBlockRows && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && packed_args(a, (unsigned)packed.per_vh, kNW, pa)) {
+        const long long window = packed_window(a);
+        pa.dense = window <= 2 * kTileKeys;
+        return launch_kernel(window <= kTileKeys ? resident_packed_kernel<false> : resident_packed_kernel<true>,
+                             dim3((unsigned)(packed.per_vh * packed.vh_slots)), dim3(kNW * 64), (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes,
+                             stream, a, pa, (int)packed.per_vh, (int)packed.vh_slots, max_tiles);
     }
     // One workgroup per compute unit.
     const ResidentSplit split = resident_split(a, pipelined ? own : stacked, kNW, num_cu);

@@ -1,0 +1,116 @@
+"""GPU parity of the kernels over packed rows, where they can go wrong: blocks across candidates and inside them, windows of one
+step and of two, more candidates than threads, empty candidates, candidates far apart in memory, prefixes too short for the
+pipeline, rows that need rescaling.  Padded rows hold NaN; results start as NaN."""
+import numpy as np
+import pytest
+
+from paper_2603_13420_amd import inputs as gen
+import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pk():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2603_13420_amd import binding
+    binding.load()
+    return binding
+
+
+def put_lengths(inp, lens):
+    """Other lengths than the drawn ones, with the padding they mean."""
+    inp.suf_len[:] = lens
+    pad = np.arange(inp.w.S)[None, :] >= inp.suf_len[:, None]
+    rng = np.random.default_rng(inp.w.seed + 1)
+    for x in (inp.q, inp.k_suf, inp.v_suf):
+        x[...] = gen.f32_to_bf16_bits(rng.standard_normal(x.shape, dtype=np.float32))
+        x[pad] = 0x7FC0
+
+
+def check(pk, inp, q_batch_stride=0):
+    import torch
+    w, multi = inp.w, hasattr(inp, "pre_len")
+    d = (pu.to_device_multi if multi else pu.to_device)(inp)
+    print(f"[case] {w.name} P={w.P} S={w.S} Hq={w.Hq} Hkv={w.Hkv} lens={inp.suf_len.tolist()[:12]} seed={w.seed}", flush=True)
+    q = d["q"]
+    B, S, Hq, D = q.shape
+    if q_batch_stride:
+        far = torch.empty(B * q_batch_stride, dtype=q.dtype, device="cuda:0").as_strided(q.shape, (q_batch_stride, Hq * D, D, 1))
+        far.copy_(q)
+        q = far
+    out = torch.full((B, S, Hq, D), float("nan"), dtype=q.dtype, device="cuda:0")
+    lse = torch.full((B, Hq, S), 123.0, device="cuda:0")
+    args = (q, d["k_suf"], d["v_suf"], d["k_pre"], d["v_pre"]) + ((d["pre_len"],) if multi else ()) + (d["suf_len"],)
+    (pk.pskv_attn_fwd_multi if multi else pk.pskv_attn_fwd)(*args, out=out, lse=lse, scale=inp.scale)
+    torch.cuda.synchronize()
+    ref, ref_lse = (pu.oracle_out_multi if multi else pu.oracle_out)(inp, want_lse=True)
+    pu.compare_lse(lse.cpu().numpy().astype(np.float64), ref_lse, inp.suf_len, w.dtype, w.name)
+    pu.compare(pu.out_to_f64(out), ref, inp.suf_len, w.dtype, w.name)
+
+
+@pytest.mark.parametrize("B,P,S,lo,Hq,Hkv", [
+    (7, 96, 20, 1, 4, 4),        # two-step windows, three prefix tiles
+    (40, 97, 5, 0, 2, 2),        # many candidates in a block, ragged prefix
+    (9, 256, 25, 17, 8, 2),      # one-step windows across candidates, the longest resident prefix
+    (9, 255, 26, 20, 8, 2),      # ... the first suffix length whose windows go on
+    (6, 130, 32, 32, 4, 4),      # whole blocks, nothing padded
+    (6, 130, 32, 1, 4, 4),       # ... mostly padded
+    (11, 100, 19, 3, 7, 1),      # heads that do not divide a block
+    (3, 128, 31, 9, 40, 1),      # more heads than rows in a block
+    (1, 96, 1, 1, 1, 1),
+    (1300, 128, 3, 0, 2, 1),     # three candidates per thread of the workgroup that adds the lengths up
+    (4200, 96, 2, 0, 1, 1),      # more lengths than it holds at a time
+])
+def test_packed_rows(pk, B, P, S, lo, Hq, Hkv):
+    w = gen.custom_workload(f"packed_{B}_{P}_{S}", B, P, S, lo, S, Hq, Hkv, 128, "bf16", index=3100 + B + P + S)
+    check(pk, gen.make_inputs(w, pad="nan"))
+
+
+@pytest.mark.parametrize("name", ["none", "first", "last", "middle", "one", "alternate"])
+def test_empty_candidates(pk, name):
+    B, S = 70, 24
+    lens = {"none": [0] * B, "first": [0] * 40 + [S] * 30, "last": [9] * 30 + [0] * 40, "middle": [S] * 5 + [0] * 60 + [7] * 5,
+            "one": [0] * 33 + [13] + [0] * 36, "alternate": [(i % 2) * (i % S + 1) for i in range(B)]}[name]
+    w = gen.custom_workload(f"packed_empty_{name}", B, 120, S, 0, S, 4, 2, 128, "bf16", index=3200)
+    inp = gen.make_inputs(w, pad="nan")
+    put_lengths(inp, lens)
+    check(pk, inp)
+
+
+def test_candidates_far_apart(pk):
+    # 150 empty candidates between two that share a block, query rows of consecutive ones 16 MB apart: beyond 32-bit offsets
+    B, S = 300, 8
+    w = gen.custom_workload("packed_far", B, 100, S, 0, S, 2, 1, 128, "bf16", index=3201)
+    inp = gen.make_inputs(w, pad="nan")
+    put_lengths(inp, [3] + [0] * 150 + [8] * 20 + [0] * 128 + [5])
+    check(pk, inp, q_batch_stride=(1 << 23) - 8)
+
+
+@pytest.mark.parametrize("Np,C,P,S,lo,Hq,Hkv", [(6, 9, 128, 20, 1, 4, 4), (5, 30, 200, 24, 12, 8, 2), (40, 3, 100, 11, 0, 14, 2)])
+def test_several_instructions(pk, Np, C, P, S, lo, Hq, Hkv):
+    w = gen.custom_multi_workload(f"packed_multi_{Np}", Np, C, P, P, P, S, lo, S, Hq, Hkv, 128, "bf16", index=3300 + P)
+    inp = gen.make_multi_inputs(w, pad="nan")
+    inp.pre_len[:] = np.random.default_rng(w.seed).integers(0, P + 1, Np)
+    inp.pre_len[:4] = P, 0, 1, 65
+    for n in range(Np):
+        inp.k_pre[n, :P - inp.pre_len[n]] = inp.v_pre[n, :P - inp.pre_len[n]] = 0x7FC0
+    check(pk, inp)
+
+
+@pytest.mark.parametrize("S,Hq,Hkv", [(20, 4, 4), (24, 8, 2)])
+def test_rows_that_need_rescaling(pk, S, Hq, Hkv):
+    # scores some 100 above the first tile's maximum, in a prefix tile for some rows and among the own keys for others
+    w = gen.custom_workload(f"packed_rescale_{S}", 12, 200, S, 5, S, Hq, Hkv, 128, "bf16", index=3400 + S)
+    inp = gen.make_inputs(w, pad="nan")
+    loud = lambda x: gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(x) * 8)
+    inp.k_pre[150] = loud(inp.k_pre[150])
+    inp.q[2:4] = loud(inp.q[2:4])
+    inp.k_suf[7, 1] = loud(inp.k_suf[7, 1])
+    inp.q[7] = loud(inp.q[7])
+    # one key may carry a whole row: its error is up to 2 * 2^-8 |v| (weight and result rounded once each), and the absolute
+    # bar of 2e-2 is for |v| < 2.5: values of standard deviation 1/4, whose largest here is below 1.4
+    for x in (inp.v_pre, inp.v_suf):
+        x[...] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(x) * np.float32(0.25))
+    check(pk, inp)
