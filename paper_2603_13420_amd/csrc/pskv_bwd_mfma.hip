@@ -20,7 +20,7 @@
 // No running maximum is needed: lse comes from the forward pass, every weight is at most one.
 // Two kernels further down serve candidates whose rows fill their own blocks well, with the prefix
 // streamed or resident in LDS; this one takes what is left.
-#include "pskv_mfma.hpp"
+#include "pskv_packed.hpp"
 #include <type_traits>
 
 // Scratch of the entry point that allocates nothing (pskv_attn_bwd_noalloc): <dout_row, out_row> of
@@ -675,6 +675,204 @@ void bwd_dq_resident_kernel(BwdArgs g, int nb, FastDiv div_nb, int per_vh, int v
 }
 
 // ------------------------------------------------------------------------------------------
+// The same over packed rows (pskv_packed.hpp): calls with suffix lengths, S <= 64.  A block's own keys are its window's.
+// Bound as the kernel above; it has fewer blocks (20480 for 23700 at the size named there: the whole backward pass 293 -> 278 us),
+// ranges of blocks that differ by one at most, and its prefix straight into LDS.  Ranges next to each other belong to different
+// workgroups: handing a workgroup eight neighbouring ones cost 2 % over 74 calls, 7 % where a wavefront has a few blocks.
+// ------------------------------------------------------------------------------------------
+template <bool TWO>
+__global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
+void bwd_dq_packed_kernel(BwdArgs g, PackedArgs pa, int per_vh, int vh_slots, int max_tiles)
+{
+    const Args &a = g.f;
+    extern __shared__ __align__(256) unsigned char smem_generic[];
+    lds_u8 *smem = (lds_u8 *)smem_generic;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    Ctx X;
+    X.lane = tid & 63;
+    X.h = X.lane >> 5;
+    X.c32 = X.lane & 31;
+    X.c = a.scale * kLog2e;
+    X.scr = smem + 2 * max_tiles * kTileBytes + wave * kScrBytes;
+    const HalfPlaces hp = half_places(X.lane);
+    const int VH = a.Np * a.Hkv, slice = blockIdx.x / vh_slots, per_chunk = (a.C + kLenChunks - 1) / kLenChunks;
+    const int waves = per_vh * kNW, me = wave * per_vh + slice;
+    lds_int *const lens = (lds_int *)(smem + 2 * max_tiles * kTileBytes); // (in the scratch)
+    for (int vh = blockIdx.x % vh_slots; vh < VH; vh += vh_slots) {
+        set_vhead(a, X, vh);
+        const int T = (X.P + kTileKeys - 1) / kTileKeys;
+        __syncthreads(); // every wavefront is done with the images and the scratch of the virtual head before
+        int fresh = tid; // (what is worked out from it is not kept over the block loop)
+        asm volatile("" : "+v"(fresh));
+        if (wave < kLenWaves) { // four wavefronts add the lengths up ...
+            ChunkRows mine = {0, 0};
+            for (int k0 = 0; k0 < per_chunk; k0 += kLenRound) {
+                int len[kLenRound];
+                const int n = per_chunk - k0 < kLenRound ? per_chunk - k0 : kLenRound;
+                load_lengths(a, X.cand0, per_chunk, k0, n, fresh, len);
+                count_lengths(a, per_chunk, k0, n, len, lens, fresh, mine);
+            }
+            add_up(mine, lens, fresh);
+        } else { // ... and each of the others requests one half image (K or V, 64 columns) of every tile, straight into LDS:
+                 // lane l's bytes go to slot l/8 and place l%8 of a piece of eight rows (see HalfPlaces).
+                 // Rows past the prefix: its last row stands in (never visible).
+            const int which = wave & 3, slot = (fresh & 63) >> 3, place = fresh & 7;
+            const unsigned row = (unsigned)a.kp_sp * 2u;
+            const unsigned char *src = reinterpret_cast<const unsigned char *>(which < 2 ? X.kpg : X.vpg) + 128 * (which & 1);
+            for (int t = 0; t < T; ++t)
+#pragma unroll
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    const int k = slot ^ (g4 & 1), left = X.P - t * kTileKeys - 1, r = 8 * g4 + k;
+                    request_to_lds(src + (unsigned)(t * kTileKeys) * row, (unsigned)(r < left ? r : left) * row + ((place ^ half_swz(k)) << 4),
+                                   smem + t * 2 * kTileBytes + which * kHalfBytes + g4 * 1024);
+                }
+        }
+        __syncthreads();
+        const PackedList list = choose_list<TWO>(a, pa, T, waves, per_chunk, lens);
+        const int nblocks = (list.total + kBlockRows - 1) / kBlockRows;
+        const int each = (int)fdiv(nblocks, pa.div_w), over = nblocks - each * waves;
+        const int blk_lo = me * each + (me < over ? me : over), blk_hi = blk_lo + each + (me < over ? 1 : 0);
+        Walk w = {X.cand0, 0, 0};
+        if (blk_lo < blk_hi)
+            w = find_row(a, list, X.cand0, blk_lo * kBlockRows, fresh & 63);
+        PSKV_WAIT_VM(0);
+        asm volatile("" ::: "memory");
+        __syncthreads();
+
+        const int row_hi = blk_hi * kBlockRows < list.total ? blk_hi * kBlockRows : list.total;
+        int pad = me;
+        for (int r0 = blk_lo * kBlockRows; r0 < row_hi;) {
+            unsigned q_off;
+            PackedRow row;
+            const PackedBlock<TWO> x = packed_block<TWO>(a, pa, fresh_lane(X), w, r0, list, q_off, row);
+            r0 += x.rows; // (a block of 32 rows, or of fewer where the next candidate is far away)
+            const int rh = X.head * a.G + row.gq, b = x.b + (int)(row.from >> 6), ri = (int)(row.from & 63);
+
+            // requested first, so that it is there with the rows below and costs no round trip of its own
+            const float lse2 = a.lse[((long long)b * a.Hq + rh) * a.S + ri] * kLog2e;
+            uintx4 q[8], dof[8], kr[2][4], vr[2][4];
+            const unsigned char *ksb = reinterpret_cast<const unsigned char *>(X.ksg) + (unsigned long long)(unsigned)x.b * pa.k_sb;
+            const unsigned char *vsb = reinterpret_cast<const unsigned char *>(X.vsg) + (unsigned long long)(unsigned)x.b * pa.k_sb;
+            auto window_rows = [&](int k0) __attribute__((always_inline)) { // the window's rows k0 .. k0 + 31, eight per request
+#pragma unroll
+                for (int g4 = 0; g4 < 4; ++g4) {
+                    const unsigned e = (unsigned)__shfl((int)x.win, k0 + 8 * g4 + (X.lane >> 3), 64);
+                    const unsigned off = packed_off(e, pa.k_sb, pa.k_ss) + 16u * (X.lane & 7);
+                    kr[0][g4] = *reinterpret_cast<const uintx4 *>(ksb + off);
+                    kr[1][g4] = *reinterpret_cast<const uintx4 *>(ksb + (off + 128u));
+                    vr[0][g4] = *reinterpret_cast<const uintx4 *>(vsb + off);
+                    vr[1][g4] = *reinterpret_cast<const uintx4 *>(vsb + (off + 128u));
+                }
+            };
+            float drow;
+            {
+                const unsigned o_off = packed_off(row.from, pa.o_sb, pa.o_ss) + __umul24(rh, pa.o_sh);
+                const unsigned long long obase = (unsigned long long)(unsigned)x.b * pa.o_sb;
+                uintx4 qr[2][4], dor[2][4], our[2][4];
+                load_rows_block(X, reinterpret_cast<const unsigned char *>(a.q) + (unsigned long long)(unsigned)x.b * pa.q_sb, q_off, qr);
+                load_rows_block(X, reinterpret_cast<const unsigned char *>(g.dout) + obase, o_off, dor);
+                load_rows_block(X, reinterpret_cast<const unsigned char *>(a.out) + obase, o_off, our);
+                window_rows(0);
+                rows_to_fragments(X, hp, qr, q);
+                rows_to_fragments(X, hp, dor, dof);
+                drow = rows_dot(X, dor, our);
+                if (g.delta && row.own == row.from && X.h == 0)
+                    g.delta[delta_index(a, b, rh, ri)] = drow;
+            }
+            floatx16 o[4];
+            // ---- the window ----
+            auto window_step = [&](int k0, auto first) __attribute__((always_inline)) {
+                floatx16 s, dp;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    s[e] = 0.f;
+                    dp[e] = 0.f;
+                }
+                bf16x8 kt[2][4]; // K^T fragments
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    half_put(hp, X.scr, kr[half]);
+                    scratch_fence();
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(half_row_frag(hp, X.scr, i)), as_bf16x8(q[4 * half + i]), s, 0, 0, 0);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int d = 0; d < 2; ++d)
+                            kt[j][2 * half + d] = half_col_frag(hp, X.scr, d, j);
+                    scratch_fence();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    half_put(hp, X.scr, vr[half]);
+                    scratch_fence();
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(half_row_frag(hp, X.scr, i)), as_bf16x8(dof[4 * half + i]), dp, 0, 0, 0);
+                    scratch_fence();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                const int bits = sees_bits(x, k0, X.h);
+                bf16x8 pf[2];
+                ds_tile(s, dp, X.c, lse2, drow, [&](int e) { return (bits >> (8 * (e >> 2) + (e & 3)) & 1) != 0; }, pf);
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int dt = 0; dt < 4; ++dt) {
+                        if (decltype(first)::value && j == 0)
+#pragma unroll
+                            for (int e = 0; e < 16; ++e)
+                                o[dt][e] = 0.f;
+                        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[j][dt], pf[j], o[dt], 0, 0, 0);
+                    }
+            };
+            window_step(0, std::true_type{});
+            if (TWO && x.width > kTileKeys) {
+                window_rows(kTileKeys);
+                window_step(kTileKeys, std::false_type{});
+            }
+
+            // ---- prefix part: every row sees every prefix key (only a ragged last tile has keys to hide) ----
+            int kt = 0;
+            for (; kt < X.P / kTileKeys; ++kt) {
+                lds_u8 *img = smem + kt * 2 * kTileBytes;
+                dq_tile<false>(hp, img, img + kTileBytes, q, dof, X.c, lse2, drow, 0, o);
+            }
+            if (kt < T) {
+                lds_u8 *img = smem + kt * 2 * kTileBytes;
+                dq_tile<true>(hp, img, img + kTileBytes, q, dof, X.c, lse2, drow, X.P - 1 - kt * kTileKeys - 4 * X.h, o);
+            }
+
+            { // (the row is found anew: no addresses held across the block)
+                const Ctx Y = fresh_lane(X);
+                const PackedRow y = packed_row(a, x, Y.c32, list.align);
+                const unsigned off = packed_off(y.own, pa.q_sb, pa.q_ss) + __umul24(Y.head * a.G + y.gq, pa.q_sh);
+                const int rows = list.align > 1 ? a.S * a.G - (x.r0 - x.first) : x.rows; // that exist
+                unsigned char *base = reinterpret_cast<unsigned char *>(g.dq) + (unsigned long long)(unsigned)x.b * pa.q_sb;
+                unsigned short *dst[4];
+                bool dst_ok[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int rl = 8 * u + (Y.lane >> 3);
+                    dst[u] = reinterpret_cast<unsigned short *>(base + ((unsigned)__shfl((int)off, rl, 64) + 16u * (Y.lane & 7)));
+                    dst_ok[u] = rl < rows;
+                }
+                store_rows(Y, dst, dst_ok, y.own == y.from, a.scale, o);
+            }
+            if (pad < a.C) {
+                store_padding(a, fresh_lane(X), X.cand0 + pad, list.align, g.dq, pa.q_sb, pa.q_ss, pa.q_sh, nullptr);
+                pad += waves;
+            }
+        }
+        for (; pad < a.C; pad += waves)
+            store_padding(a, fresh_lane(X), X.cand0 + pad, list.align, g.dq, pa.q_sb, pa.q_ss, pa.q_sh, nullptr);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // dq with prefix and own keys shared in LDS.  A pass is four 32-row blocks of one (candidate, KV head) unit, one
 // per wavefront; the prefix tiles and then the candidate's own keys, as far as any of the four blocks sees them,
 // go through two LDS slots, one barrier per tile, the next tile's rows on their way meanwhile.  The causal
@@ -1216,6 +1414,10 @@ hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream)
     const int num_cu = device_setup_once(cu_by_device, e, [] {
         hipError_t s = hipFuncSetAttribute(reinterpret_cast<const void *>(bwd_dq_mfma_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLdsBytes);
+        for (auto kernel : {bwd_dq_packed_kernel<true>, bwd_dq_packed_kernel<false>})
+            if (s == hipSuccess)
+                s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        2 * kDqMaxTiles * kTileBytes + kNW * kScrBytes);
         if (s == hipSuccess)
             s = hipFuncSetAttribute(reinterpret_cast<const void *>(bwd_dq_resident_kernel),
                                     hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1235,6 +1437,22 @@ hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream)
     // 20 rows: 217 and 242 us).
     const bool resident = a.P <= kDqMaxTiles * kTileKeys && rows_c * 8 >= nb * kBlockRows * 3 && fit && a.C * nb <= 0x7fffffffLL / 2;
     const ResidentSplit split = resident_split(a, a.C * nb, kNW, num_cu);
+    // Rows packed by their lengths, where there are lengths: all of the resident kernel's calls and those of the streaming one up to 256 prefix
+    // rows; calls of fewer than three blocks per wavefront that fill passes of four (below) stay with those.  us for the whole
+    // backward pass, before and so: 1024 x 16..24, 32/8 heads, P 256: 293, 277; 500 x 20, P 250: 151, 142; 500 x 14..28: 171, 151; 700 x 14..28, P 128:
+    // 203, 189; 700 x 32..64: 487, 460; 700 x 10, 32/32: 223, 180; 700 x 32: 431, 441 (nothing to pack); 32 x 10, 32/8: 18.7, 15.7; 32 x 28: 19.7, 20.9 (passes).
+    const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
+    PackedArgs pa;
+    const bool small = split.each < 3 && nb * 5 >= (nb + kUnitWaves - 1) / kUnitWaves * kUnitWaves * 4;
+    if (const ResidentSplit packed = resident_split(a, a.C * nb * kNW, kNW, num_cu);
+        a.len && !small && a.P <= kDqMaxTiles * kTileKeys && a.S <= 2 * kTileKeys && a.C * nb <= 0x7fffffffLL / kBlockRows &&
+        (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && packed_args(a, (unsigned)packed.per_vh, kNW, pa)) {
+        const long long window = packed_window(a);
+        pa.dense = window <= 2 * kTileKeys;
+        return launch_kernel(window <= kTileKeys ? bwd_dq_packed_kernel<false> : bwd_dq_packed_kernel<true>,
+                             dim3((unsigned)(packed.per_vh * packed.vh_slots)), dim3(kNW * 64), (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes,
+                             stream, g, pa, (int)packed.per_vh, (int)packed.vh_slots, max_tiles);
+    }
     // Passes of four blocks of one candidate, where they come out full: at less than four blocks in five the
     // wavefronts without one cost more than sharing the tiles saves (five blocks in two passes, 40 positions x
     // 4 heads, P 128: 156 us against 130 us of the resident kernel and 141 us of the streaming one; four in one,
@@ -1259,7 +1477,6 @@ hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream)
         }
     }
     if (resident) {
-        const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
         const size_t lds = (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes;
         return launch_kernel(bwd_dq_resident_kernel, dim3((unsigned)(split.per_vh * split.vh_slots)), dim3(kNW * 64), lds, stream, g, (int)nb,
                              make_fastdiv((unsigned)nb), (int)split.per_vh, (int)split.vh_slots, max_tiles);

@@ -192,13 +192,13 @@ __device__ inline Walk find_row(const Args &a, const PackedList &x, int cand0, i
 
 // One block of 32 packed rows.
 template <bool TWO> struct PackedBlock {
-    int r0, rows;   // its first row; rows of the list from there on (of them 32 are the block's)
+    int r0, rows;   // its first row, its rows
     int b, first;   // the window's first candidate and that one's first packed row
     int width;      // the window's positions
     unsigned win;   // lane l (TWO; else lanes l and l + 32): window position l (the last one past the end): (candidate - b) << 6 | position
     unsigned o_off; // byte offset of the lane's row from the first candidate's first out row; bit 0: stored as zero
     unsigned sees;  // the window's keys that the lane's row sees: as bits, or (TWO) their last one and 256 times their first
-    bool wide;      // the candidates lie too far apart for 32-bit offsets from the first one's rows
+    bool wide;      // its rows end early: the next candidate lies too far away for 32-bit offsets from the first one's rows
 };
 
 // One lane's row of a packed block.  A row past its candidate's length (align 32) takes the query row and the keys of
@@ -226,14 +226,15 @@ template <bool TWO> __device__ inline PackedRow packed_row(const Args &a, const 
 __device__ inline unsigned packed_off(unsigned entry, unsigned sb, unsigned ss) { return __umul24(entry >> 6, sb) + __umul24(entry & 63, ss); }
 
 // The block of packed rows r0..; w at or before the candidate of row r0, and left at its last row's.  q_off: byte offset of the
-// lane's query row from the first candidate's first one.
+// lane's query row from the first candidate's first one; y: the lane's row.  Where candidates lie too far apart the block ends before
+// the first such one (`wide`).
 template <bool TWO>
-__device__ inline PackedBlock<TWO> packed_block(const Args &a, const PackedArgs &pa, const Ctx &X, Walk &w, int r0, const PackedList &list, unsigned &q_off)
+__device__ inline PackedBlock<TWO> packed_block(const Args &a, const PackedArgs &pa, const Ctx &X, Walk &w, int r0, const PackedList &list, unsigned &q_off,
+                                                PackedRow &y)
 {
     PackedBlock<TWO> x;
     x.r0 = r0;
-    x.rows = list.total - r0;
-    const int last = x.rows < kBlockRows ? list.total - 1 : r0 + kBlockRows - 1;
+    int last = list.total - r0 < kBlockRows ? list.total - 1 : r0 + kBlockRows - 1;
     int end = w.first + packed_run(a, w.len, list.align);
     while (end <= r0) {
         w.first = end;
@@ -243,10 +244,16 @@ __device__ inline PackedBlock<TWO> packed_block(const Args &a, const PackedArgs 
     }
     x.b = w.b;
     x.first = w.first;
+    x.wide = false;
     const int l = TWO ? X.lane : X.c32;
     unsigned entry = l; // as if all were the first candidate's
     int at = 0;         // window position of the walk's candidate's first
     while (end <= last) {
+        if (w.b + 1 - x.b >= pa.span) {
+            last = end - 1;
+            x.wide = true;
+            break;
+        }
         at += w.len;
         w.first = end;
         ++w.b;
@@ -254,15 +261,13 @@ __device__ inline PackedBlock<TWO> packed_block(const Args &a, const PackedArgs 
         end += packed_run(a, w.len, list.align);
         entry = l >= at ? (unsigned)((w.b - x.b) << 6 | (l - at)) : entry;
     }
+    x.rows = last - r0 + 1;
     const int upto = __builtin_amdgcn_readfirstlane((int)fdiv(last - w.first, a.div_g)) + 1; // the last candidate's positions
     const int more = upto < w.len ? upto : w.len;
     x.width = at + more;
     const unsigned end_entry = (unsigned)((w.b - x.b) << 6 | (more - 1));
     x.win = l < x.width ? entry : end_entry;
-    x.wide = w.b - x.b >= pa.span;
-    if (x.wide)
-        x.win = 0;
-    const PackedRow y = packed_row(a, x, X.c32, list.align);
+    y = packed_row(a, x, X.c32, list.align);
     const unsigned rh = (unsigned)(X.head * a.G + y.gq);
     q_off = packed_off(y.from, pa.q_sb, pa.q_ss) + __umul24(rh, pa.q_sh);
     x.o_off = (packed_off(y.own, pa.o_sb, pa.o_ss) + __umul24(rh, pa.o_sh)) | (y.own == y.from ? 0u : 1u);
@@ -362,19 +367,20 @@ __device__ inline void window_step_fixed(const Ctx &X, int bits, const floatx16 
     pv_from_scratch(X, svf[1], as_bf16x8(uintx4{pk[4], pk[5], pk[6], pk[7]}), o);
 }
 
-// Zeros for candidate b's rows past those that its blocks store, of this KV head's query heads (whole rows, 16 lanes each).
-__device__ inline void store_padding(const Args &a, const PackedArgs &pa, const Ctx &X, int b, int align)
+// Zeros for candidate b's rows past those that its blocks store, of this KV head's query heads (whole rows, 16 lanes each), in a
+// tensor with the given strides (bytes), and minus infinity in lse (null: none).
+__device__ inline void store_padding(const Args &a, const Ctx &X, int b, int align, void *out, unsigned sb, unsigned ss, unsigned sh, float *lse)
 {
     const int all = a.S * a.G, from = packed_run(a, packed_len(a, b), align);
-    unsigned char *base = reinterpret_cast<unsigned char *>(a.out) + (unsigned long long)(unsigned)b * pa.o_sb + (unsigned)(X.head * a.G) * pa.o_sh;
+    unsigned char *base = reinterpret_cast<unsigned char *>(out) + (unsigned long long)(unsigned)b * sb + (unsigned)(X.head * a.G) * sh;
     for (int r = from + (X.lane >> 4); r < all; r += 4) {
         const unsigned t = fdiv(r, a.div_g), gq = r - t * a.G;
-        __builtin_nontemporal_store(uintx4{0, 0, 0, 0}, reinterpret_cast<uintx4 *>(base + (__umul24(t, pa.o_ss) + __umul24(gq, pa.o_sh) + 16u * (X.lane & 15))));
+        __builtin_nontemporal_store(uintx4{0, 0, 0, 0}, reinterpret_cast<uintx4 *>(base + (__umul24(t, ss) + __umul24(gq, sh) + 16u * (X.lane & 15))));
     }
-    if (a.lse)
+    if (lse)
         for (int r = from + X.lane; r < all; r += 64) {
             const unsigned t = fdiv(r, a.div_g), gq = r - t * a.G;
-            a.lse[((long long)b * a.Hq + X.head * a.G + (int)gq) * a.S + (int)t] = -INFINITY;
+            lse[((long long)b * a.Hq + X.head * a.G + (int)gq) * a.S + (int)t] = -INFINITY;
         }
 }
 
@@ -383,10 +389,10 @@ __device__ __attribute__((always_inline)) void packed_general_block(const Args &
 {
     Walk w = begin;
     unsigned q_off;
+    PackedRow y;
     PackedArgs far = pa;
     far.span = 1 << 26; // (the offsets that do not reach are not used here)
-    const PackedBlock<true> x = packed_block<true>(a, far, X, w, r0, list, q_off);
-    const PackedRow y = packed_row(a, x, X.c32, list.align);
+    const PackedBlock<true> x = packed_block<true>(a, far, X, w, r0, list, q_off, y);
     Row row;
     row.rb = x.b + (y.from >> 6);
     row.ri = y.from & 63;

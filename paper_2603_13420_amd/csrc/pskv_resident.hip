@@ -369,7 +369,8 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
         // Moves on to the next block whose candidates lie close enough together; w and nxt stay where they are past the last one.
         auto advance = [&](int n) __attribute__((always_inline)) {
             for (; n < blk_hi; ++n) {
-                nxt = packed_block<TWO>(a, pa, fresh_lane(X), w, n * kBlockRows, list, q_off);
+                PackedRow row;
+                nxt = packed_block<TWO>(a, pa, fresh_lane(X), w, n * kBlockRows, list, q_off, row);
                 if (!nxt.wide)
                     break;
                 any_bad = true;
@@ -470,7 +471,7 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
             m = max_of_halves(m) * X.c; // (the other half-wave holds the other 16 keys)
             // (Stores whose number the compiler does not know stand where the next wait for a load is far: after Q's, before K's.)
             for (const int to = pad + pads < a.C ? pad + pads : a.C; pad < to; pad += waves)
-                store_padding(a, pa, fresh_lane(X), X.cand0 + pad, list.align);
+                store_padding(a, fresh_lane(X), X.cand0 + pad, list.align, a.out, pa.o_sb, pa.o_ss, pa.o_sh, a.lse);
             float l = 0.f;
             floatx16 o[4];
             uintx4 pA[2], pB[2]; // packed weights of the current and of the previous tile, roles alternating
@@ -542,7 +543,7 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
             store_packed(a, pa, fresh_lane(X), x, list.align, m, l, o);
         }
         for (; pad < a.C; pad += waves)
-            store_padding(a, pa, fresh_lane(X), X.cand0 + pad, list.align);
+            store_padding(a, fresh_lane(X), X.cand0 + pad, list.align, a.out, pa.o_sb, pa.o_ss, pa.o_sh, a.lse);
 
         // Rare: some row met scores far above its first tile's maximum, or a block's candidates lie far apart: whatever this
         // wavefront stored is replaced by the general path's result.  The same for an instruction whose prefix is too short for

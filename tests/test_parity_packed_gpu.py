@@ -29,7 +29,7 @@ def put_lengths(inp, lens):
         x[pad] = 0x7FC0
 
 
-def check(pk, inp, q_batch_stride=0):
+def check(pk, inp, q_batch_stride=0, backward=True):
     import torch
     w, multi = inp.w, hasattr(inp, "pre_len")
     d = (pu.to_device_multi if multi else pu.to_device)(inp)
@@ -48,6 +48,18 @@ def check(pk, inp, q_batch_stride=0):
     ref, ref_lse = (pu.oracle_out_multi if multi else pu.oracle_out)(inp, want_lse=True)
     pu.compare_lse(lse.cpu().numpy().astype(np.float64), ref_lse, inp.suf_len, w.dtype, w.name)
     pu.compare(pu.out_to_f64(out), ref, inp.suf_len, w.dtype, w.name)
+    if not backward:
+        return
+    dout_host, dout64 = pu.make_dout(inp, w.seed + 7)
+    dout = torch.from_numpy(dout_host).view(torch.bfloat16).to("cuda:0")
+    grads = [torch.empty_strided(x.shape, x.stride(), dtype=x.dtype, device="cuda:0").fill_(float("nan")) for x in (q, d["k_suf"], d["v_suf"])]
+    (pk.pskv_attn_bwd_multi if multi else pk.pskv_attn_bwd)(*args, out, lse, dout, dq=grads[0], dk_suf=grads[1], dv_suf=grads[2], scale=inp.scale)
+    torch.cuda.synchronize()
+    valid = np.arange(S)[None, :] < inp.suf_len[:, None]
+    for name, got, r in zip(("dq", "dk_suf", "dv_suf"), grads, (pu.oracle_bwd_multi if multi else pu.oracle_bwd)(inp, dout64)):
+        got = pu.out_to_f64(got.contiguous())
+        assert not got[~valid].any(), f"{name}: padded rows must be exactly 0"
+        pu.compare_grad(got, r, valid, w.dtype, f"{w.name} {name}")
 
 
 @pytest.mark.parametrize("B,P,S,lo,Hq,Hkv", [
@@ -61,7 +73,10 @@ def check(pk, inp, q_batch_stride=0):
     (3, 128, 31, 9, 40, 1),      # more heads than rows in a block
     (1, 96, 1, 1, 1, 1),
     (1300, 128, 3, 0, 2, 1),     # three candidates per thread of the workgroup that adds the lengths up
-    (4200, 96, 2, 0, 1, 1),      # more lengths than it holds at a time
+    (2200, 96, 2, 0, 1, 1),      # more lengths than it holds at a time
+    (7, 40, 40, 33, 8, 2),       # (backward) one prefix tile, windows of up to 48 positions
+    (6, 0, 64, 1, 4, 4),         # ... no prefix, the longest suffix
+    (5, 256, 57, 20, 14, 2),
 ])
 def test_packed_rows(pk, B, P, S, lo, Hq, Hkv):
     w = gen.custom_workload(f"packed_{B}_{P}_{S}", B, P, S, lo, S, Hq, Hkv, 128, "bf16", index=3100 + B + P + S)
@@ -113,4 +128,4 @@ def test_rows_that_need_rescaling(pk, S, Hq, Hkv):
     # bar of 2e-2 is for |v| < 2.5: values of standard deviation 1/4, whose largest here is below 1.4
     for x in (inp.v_pre, inp.v_suf):
         x[...] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(x) * np.float32(0.25))
-    check(pk, inp)
+    check(pk, inp, backward=False)
