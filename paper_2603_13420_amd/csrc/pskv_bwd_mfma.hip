@@ -680,7 +680,7 @@ void bwd_dq_resident_kernel(BwdArgs g, int nb, FastDiv div_nb, int per_vh, int v
 // ranges of blocks that differ by one at most, and its prefix straight into LDS.  Ranges next to each other belong to different
 // workgroups: handing a workgroup eight neighbouring ones cost 2 % over 74 calls, 7 % where a wavefront has a few blocks.
 // ------------------------------------------------------------------------------------------
-template <bool TWO>
+template <int STEPS>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
 void bwd_dq_packed_kernel(BwdArgs g, PackedArgs pa, int per_vh, int vh_slots, int max_tiles)
 {
@@ -729,7 +729,7 @@ void bwd_dq_packed_kernel(BwdArgs g, PackedArgs pa, int per_vh, int vh_slots, in
                 }
         }
         __syncthreads();
-        const PackedList list = choose_list<TWO>(a, pa, T, waves, per_chunk, lens);
+        const PackedList list = choose_list<STEPS>(a, pa, T, waves, per_chunk, lens);
         const int nblocks = (list.total + kBlockRows - 1) / kBlockRows;
         const int each = (int)fdiv(nblocks, pa.div_w), over = nblocks - each * waves;
         const int blk_lo = me * each + (me < over ? me : over), blk_hi = blk_lo + each + (me < over ? 1 : 0);
@@ -745,7 +745,7 @@ void bwd_dq_packed_kernel(BwdArgs g, PackedArgs pa, int per_vh, int vh_slots, in
         for (int r0 = blk_lo * kBlockRows; r0 < row_hi;) {
             unsigned q_off;
             PackedRow row;
-            const PackedBlock<TWO> x = packed_block<TWO>(a, pa, fresh_lane(X), w, r0, list, q_off, row);
+            const PackedBlock<STEPS> x = packed_block<STEPS>(a, pa, fresh_lane(X), w, r0, list, q_off, row);
             r0 += x.rows; // (a block of 32 rows, or of fewer where the next candidate is far away)
             const int rh = X.head * a.G + row.gq, b = x.b + (int)(row.from >> 6), ri = (int)(row.from & 63);
 
@@ -757,7 +757,7 @@ void bwd_dq_packed_kernel(BwdArgs g, PackedArgs pa, int per_vh, int vh_slots, in
             auto window_rows = [&](int k0) __attribute__((always_inline)) { // the window's rows k0 .. k0 + 31, eight per request
 #pragma unroll
                 for (int g4 = 0; g4 < 4; ++g4) {
-                    const unsigned e = (unsigned)__shfl((int)x.win, k0 + 8 * g4 + (X.lane >> 3), 64);
+                    const unsigned e = window_entry(x, k0 + 8 * g4 + (X.lane >> 3));
                     const unsigned off = packed_off(e, pa.k_sb, pa.k_ss) + 16u * (X.lane & 7);
                     kr[0][g4] = *reinterpret_cast<const uintx4 *>(ksb + off);
                     kr[1][g4] = *reinterpret_cast<const uintx4 *>(ksb + (off + 128u));
@@ -830,7 +830,7 @@ void bwd_dq_packed_kernel(BwdArgs g, PackedArgs pa, int per_vh, int vh_slots, in
                     }
             };
             window_step(0, std::true_type{});
-            if (TWO && x.width > kTileKeys) {
+            if (STEPS > 1 && x.width > kTileKeys) {
                 window_rows(kTileKeys);
                 window_step(kTileKeys, std::false_type{});
             }
@@ -1414,7 +1414,7 @@ hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream)
     const int num_cu = device_setup_once(cu_by_device, e, [] {
         hipError_t s = hipFuncSetAttribute(reinterpret_cast<const void *>(bwd_dq_mfma_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kBwdLdsBytes);
-        for (auto kernel : {bwd_dq_packed_kernel<true>, bwd_dq_packed_kernel<false>})
+        for (auto kernel : {bwd_dq_packed_kernel<2>, bwd_dq_packed_kernel<1>})
             if (s == hipSuccess)
                 s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                         2 * kDqMaxTiles * kTileBytes + kNW * kScrBytes);
@@ -1449,7 +1449,7 @@ hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream)
         (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && packed_args(a, (unsigned)packed.per_vh, kNW, pa)) {
         const long long window = packed_window(a);
         pa.dense = window <= 2 * kTileKeys;
-        return launch_kernel(window <= kTileKeys ? bwd_dq_packed_kernel<false> : bwd_dq_packed_kernel<true>,
+        return launch_kernel(window <= kTileKeys ? bwd_dq_packed_kernel<1> : bwd_dq_packed_kernel<2>,
                              dim3((unsigned)(packed.per_vh * packed.vh_slots)), dim3(kNW * 64), (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes,
                              stream, g, pa, (int)packed.per_vh, (int)packed.vh_slots, max_tiles);
     }

@@ -17,7 +17,7 @@ namespace pskv {
 struct PackedArgs {
     unsigned q_sb, q_ss, q_sh, o_sb, o_ss, o_sh, k_sb, k_ss;
     int span;       // candidates of one block at most, counted from its first one, for which 32-bit offsets from that one's rows reach
-    int dense;      // windows of align 1 fit (64 positions, so that lane l describes position l)
+    int dense;      // windows of align 1 fit the kernel's
     FastDiv div_n;  // division by the number of workgroups that share a list
     FastDiv div_w;  // ... of wavefronts
 };
@@ -144,7 +144,7 @@ __device__ inline void add_up(const ChunkRows &c, lds_int *lens, int tid)
 // 89; 96, 95); 32: 245, 243 (94, 93; 105, 105); 22..32: 217, 225 (84, 85; 93, 91); no second steps: 20: 153, 172 (57, 63; 65, 69).
 // Where every wavefront has at most one block either way, blocks inside candidates: they take the shorter walk (32 candidates of 8..20,
 // 32/8 heads, P 128: 11.6 us across, 11.1 inside).
-template <bool TWO>
+template <int STEPS>
 __device__ inline PackedList choose_list(const Args &a, const PackedArgs &pa, int tiles, int waves, int per_chunk, lds_int *lens)
 {
     lds_int *const sums = lens + (kLenRound + 2) * kLenChunks;
@@ -156,7 +156,7 @@ __device__ inline PackedList choose_list(const Args &a, const PackedArgs &pa, in
     }
     total = __builtin_amdgcn_readfirstlane(total);
     total32 = __builtin_amdgcn_readfirstlane(total32);
-    long long second = TWO ? total - 32LL * (a.G - 1) * a.C : 0; // rows of blocks with a second step
+    long long second = STEPS > 1 ? total - 32LL * (a.G - 1) * a.C : 0; // rows of blocks with a second step
     second = second > 0 ? second : 0;
     const int second_cost = tiles < 10 ? 180 - 14 * tiles : 40; // (tenths of a tile's time)
     const bool one = pa.dense && total32 > 32 * waves && (long long)total * (10 * (tiles + 6)) + second_cost * second < (long long)total32 * (10 * (tiles + 6));
@@ -168,16 +168,24 @@ __device__ inline PackedList choose_list(const Args &a, const PackedArgs &pa, in
     return x;
 }
 
+// Lane j: rows of the first (j + 1)/64 of the candidates (kLenPerLane chunks each).
+__device__ inline int rows_upto(const PackedList &x, int lane)
+{
+    lds_int *const tables = x.lens + kLenRound * kLenChunks, *const before = x.align == 1 ? tables : tables + kLenChunks;
+    lds_int *const sums = tables + 2 * kLenChunks + (x.align == 1 ? 0 : kLenWaves);
+    int upto = before[kLenPerLane * lane + kLenPerLane - 1];
+#pragma unroll
+    for (int i = 0; i < kLenWaves - 1; ++i)
+        upto += i < lane / (64 / kLenWaves) ? sums[i] : 0;
+    return upto;
+}
+
 // The candidate of packed row r0 (one that exists).
 __device__ inline Walk find_row(const Args &a, const PackedList &x, int cand0, int r0, int lane)
 {
     lds_int *const tables = x.lens + kLenRound * kLenChunks, *const before = x.align == 1 ? tables : tables + kLenChunks;
-    lds_int *const sums = tables + 2 * kLenChunks + (x.align == 1 ? 0 : kLenWaves);
     constexpr int n = kLenPerLane;
-    int upto = before[n * lane + n - 1]; // lane j: rows of the first n*(j + 1) chunks
-#pragma unroll
-    for (int i = 0; i < kLenWaves - 1; ++i)
-        upto += i < (lane / (64 / kLenWaves)) ? sums[i] : 0;
+    const int upto = rows_upto(x, lane);
     const int g = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= r0)); // (below 64: the row exists)
     const int base = g > 0 ? __builtin_amdgcn_readlane(upto, g > 0 ? g - 1 : 0) : 0;
     const int part = before[n * g + (lane & (n - 1))] + (g % (64 / kLenWaves) ? base - before[g > 0 ? n * g - 1 : 0] : base);
@@ -190,16 +198,28 @@ __device__ inline Walk find_row(const Args &a, const PackedList &x, int cand0, i
     return w;
 }
 
-// One block of 32 packed rows.
-template <bool TWO> struct PackedBlock {
+// One block of 32 packed rows whose window takes up to STEPS steps of 32 positions.
+template <int STEPS> struct PackedBlock {
     int r0, rows;   // its first row, its rows
     int b, first;   // the window's first candidate and that one's first packed row
     int width;      // the window's positions
-    unsigned win;   // lane l (TWO; else lanes l and l + 32): window position l (the last one past the end): (candidate - b) << 6 | position
+    unsigned win;   // lane l (STEPS > 1; else lanes l and l + 32): window position l (the last one past the end): (candidate - b) << 6 | position
+    unsigned win2;  // (STEPS == 3) lanes l and l + 32: position 64 + l
     unsigned o_off; // byte offset of the lane's row from the first candidate's first out row; bit 0: stored as zero
-    unsigned sees;  // the window's keys that the lane's row sees: as bits, or (TWO) their last one and 256 times their first
+    unsigned sees;  // the window's keys that the lane's row sees: as bits, or (STEPS > 1) their last one and 256 times their first
     bool wide;      // its rows end early: the next candidate lies too far away for 32-bit offsets from the first one's rows
 };
+
+// The entry of window position pos.
+template <int STEPS> __device__ inline unsigned window_entry(const PackedBlock<STEPS> &x, int pos)
+{
+    const unsigned e = (unsigned)__shfl((int)x.win, pos & 63, 64);
+    if constexpr (STEPS == 3) {
+        const unsigned e2 = (unsigned)__shfl((int)x.win2, pos & 31, 64);
+        return pos < 64 ? e : e2;
+    }
+    return e;
+}
 
 // One lane's row of a packed block.  A row past its candidate's length (align 32) takes the query row and the keys of
 // the last position that the block sees and is stored as zero; rows past the list's or the candidate's end are the last one once more.
@@ -208,7 +228,7 @@ struct PackedRow {
     unsigned from, own; // entries (as in `win`) of the row it loads and of the row it stores
 };
 
-template <bool TWO> __device__ inline PackedRow packed_row(const Args &a, const PackedBlock<TWO> &x, int row, int align)
+template <int STEPS> __device__ inline PackedRow packed_row(const Args &a, const PackedBlock<STEPS> &x, int row, int align)
 {
     PackedRow y;
     const int most = align > 1 ? a.S * a.G - 1 : x.r0 - x.first + x.rows - 1;
@@ -217,7 +237,7 @@ template <bool TWO> __device__ inline PackedRow packed_row(const Args &a, const 
     const int pos = (int)fdiv(j, a.div_g);
     y.gq = j - pos * a.G;
     y.pos = pos < x.width ? pos : x.width - 1;
-    y.from = (unsigned)__shfl((int)x.win, y.pos, 64);
+    y.from = window_entry(x, y.pos);
     y.own = pos < x.width ? y.from : (unsigned)pos;
     return y;
 }
@@ -228,11 +248,11 @@ __device__ inline unsigned packed_off(unsigned entry, unsigned sb, unsigned ss) 
 // The block of packed rows r0..; w at or before the candidate of row r0, and left at its last row's.  q_off: byte offset of the
 // lane's query row from the first candidate's first one; y: the lane's row.  Where candidates lie too far apart the block ends before
 // the first such one (`wide`).
-template <bool TWO>
-__device__ inline PackedBlock<TWO> packed_block(const Args &a, const PackedArgs &pa, const Ctx &X, Walk &w, int r0, const PackedList &list, unsigned &q_off,
+template <int STEPS>
+__device__ inline PackedBlock<STEPS> packed_block(const Args &a, const PackedArgs &pa, const Ctx &X, Walk &w, int r0, const PackedList &list, unsigned &q_off,
                                                 PackedRow &y)
 {
-    PackedBlock<TWO> x;
+    PackedBlock<STEPS> x;
     x.r0 = r0;
     int last = list.total - r0 < kBlockRows ? list.total - 1 : r0 + kBlockRows - 1;
     int end = w.first + packed_run(a, w.len, list.align);
@@ -245,8 +265,8 @@ __device__ inline PackedBlock<TWO> packed_block(const Args &a, const PackedArgs 
     x.b = w.b;
     x.first = w.first;
     x.wide = false;
-    const int l = TWO ? X.lane : X.c32;
-    unsigned entry = l; // as if all were the first candidate's
+    const int l = STEPS > 1 ? X.lane : X.c32;
+    unsigned entry = l, entry2 = 64 + X.c32; // as if all were the first candidate's
     int at = 0;         // window position of the walk's candidate's first
     while (end <= last) {
         if (w.b + 1 - x.b >= pa.span) {
@@ -260,6 +280,8 @@ __device__ inline PackedBlock<TWO> packed_block(const Args &a, const PackedArgs 
         w.len = packed_len(a, w.b);
         end += packed_run(a, w.len, list.align);
         entry = l >= at ? (unsigned)((w.b - x.b) << 6 | (l - at)) : entry;
+        if (STEPS == 3)
+            entry2 = 64 + X.c32 >= at ? (unsigned)((w.b - x.b) << 6 | (64 + X.c32 - at)) : entry2;
     }
     x.rows = last - r0 + 1;
     const int upto = __builtin_amdgcn_readfirstlane((int)fdiv(last - w.first, a.div_g)) + 1; // the last candidate's positions
@@ -267,20 +289,21 @@ __device__ inline PackedBlock<TWO> packed_block(const Args &a, const PackedArgs 
     x.width = at + more;
     const unsigned end_entry = (unsigned)((w.b - x.b) << 6 | (more - 1));
     x.win = l < x.width ? entry : end_entry;
+    x.win2 = STEPS == 3 && 64 + X.c32 < x.width ? entry2 : end_entry;
     y = packed_row(a, x, X.c32, list.align);
     const unsigned rh = (unsigned)(X.head * a.G + y.gq);
     q_off = packed_off(y.from, pa.q_sb, pa.q_ss) + __umul24(rh, pa.q_sh);
     x.o_off = (packed_off(y.own, pa.o_sb, pa.o_ss) + __umul24(rh, pa.o_sh)) | (y.own == y.from ? 0u : 1u);
     const int lo = y.pos - (int)(y.from & 63); // the window's keys from its candidate's first to its own
-    x.sees = TWO ? (unsigned)(y.pos | lo << 8) : (2u << y.pos) - (1u << lo);
+    x.sees = STEPS > 1 ? (unsigned)(y.pos | lo << 8) : (2u << y.pos) - (1u << lo);
     return x;
 }
 
 // The bits of the keys that the lane's row sees of window positions k0 .. k0 + 31, element e's at 8*(e/4) + e%4.
-template <bool TWO> __device__ inline int sees_bits(const PackedBlock<TWO> &x, int k0, int h)
+template <int STEPS> __device__ inline int sees_bits(const PackedBlock<STEPS> &x, int k0, int h)
 {
     unsigned bits = x.sees;
-    if constexpr (TWO) {
+    if constexpr (STEPS > 1) {
         const int end = (int)(x.sees & 255) + 1 - k0, lo = (int)(x.sees >> 8) - k0; // one past the last key, the first one
         bits = (end >= 32 ? ~0u : end > 0 ? (1u << end) - 1u : 0u) & (lo <= 0 ? ~0u : lo < 32 ? ~0u << lo : 0u);
     }
@@ -298,9 +321,9 @@ __device__ inline void load_q_packed(const Args &a, const PackedArgs &pa, const 
 
 // K fragments and V rows of the window's positions k0..k0+31 (layouts as in load_suffix_k and load_suffix_v; past the
 // window its last position, which no row takes for that one's).
-template <bool TWO> __device__ inline void load_window_k(const PackedArgs &pa, const Ctx &X, const PackedBlock<TWO> &x, int k0, uintx4 (&kf)[8])
+template <int STEPS> __device__ inline void load_window_k(const PackedArgs &pa, const Ctx &X, const PackedBlock<STEPS> &x, int k0, uintx4 (&kf)[8])
 {
-    const unsigned e = TWO ? (unsigned)__shfl((int)x.win, k0 + X.c32, 64) : x.win;
+    const unsigned e = STEPS > 1 ? window_entry(x, k0 + X.c32) : x.win;
     const unsigned char *kp = reinterpret_cast<const unsigned char *>(X.ksg) + (unsigned long long)(unsigned)x.b * pa.k_sb +
                               (packed_off(e, pa.k_sb, pa.k_ss) + 16u * X.h);
 #pragma unroll
@@ -308,12 +331,12 @@ template <bool TWO> __device__ inline void load_window_k(const PackedArgs &pa, c
         kf[ks] = *reinterpret_cast<const uintx4 *>(kp + 32 * ks);
 }
 
-template <bool TWO> __device__ inline void load_window_v(const PackedArgs &pa, const Ctx &X, const PackedBlock<TWO> &x, int k0, uintx4 (&vf)[2][4])
+template <int STEPS> __device__ inline void load_window_v(const PackedArgs &pa, const Ctx &X, const PackedBlock<STEPS> &x, int k0, uintx4 (&vf)[2][4])
 {
     const unsigned char *base = reinterpret_cast<const unsigned char *>(X.vsg) + (unsigned long long)(unsigned)x.b * pa.k_sb;
 #pragma unroll
     for (int j = 0; j < 2; ++j) { // (fragment (dt, u) = (it, h) of load_suffix_v)
-        const unsigned e = (unsigned)__shfl((int)x.win, k0 + 16 * j + 8 * X.h + X.sv_row_lo, 64);
+        const unsigned e = window_entry(x, k0 + 16 * j + 8 * X.h + X.sv_row_lo);
         const unsigned char *vp = base + (packed_off(e, pa.k_sb, pa.k_ss) + (unsigned)X.sv_chunk_lo * 16u);
 #pragma unroll
         for (int it = 0; it < 4; ++it)
@@ -322,8 +345,8 @@ template <bool TWO> __device__ inline void load_window_v(const PackedArgs &pa, c
 }
 
 // Normalise and store the block (as store_block).
-template <bool TWO>
-__device__ inline void store_packed(const Args &a, const PackedArgs &pa, const Ctx &X, const PackedBlock<TWO> &x, int align, float m, float l, const floatx16 (&o)[4])
+template <int STEPS>
+__device__ inline void store_packed(const Args &a, const PackedArgs &pa, const Ctx &X, const PackedBlock<STEPS> &x, int align, float m, float l, const floatx16 (&o)[4])
 {
     const float ltot = sum_of_halves(l);
     const float inv = 1.0f / ltot;
@@ -384,36 +407,44 @@ __device__ inline void store_padding(const Args &a, const Ctx &X, int b, int ali
         }
 }
 
-// The classic online softmax over a packed block whatever its rows and prefix are (prefix images in LDS).
-__device__ __attribute__((always_inline)) void packed_general_block(const Args &a, const PackedArgs &pa, const Ctx &X, int ntiles, const Walk &begin, int r0, const PackedList &list)
-{
-    Walk w = begin;
-    unsigned q_off;
+// The classic online softmax over a packed block whatever its rows and its prefix are: the block's rows and Q, and, after the
+// prefix, its window and the store.
+template <int STEPS> struct GeneralBlock {
+    PackedBlock<STEPS> x;
     PackedRow y;
+    Row row;
+    RowState st;
+    uintx4 q[8];
+};
+
+template <int STEPS>
+__device__ __attribute__((always_inline)) void packed_general_begin(const Args &a, const PackedArgs &pa, const Ctx &X, Walk w, int r0, const PackedList &list,
+                                                                    GeneralBlock<STEPS> &g)
+{
+    unsigned q_off;
     PackedArgs far = pa;
     far.span = 1 << 26; // (the offsets that do not reach are not used here)
-    const PackedBlock<true> x = packed_block<true>(a, far, X, w, r0, list, q_off, y);
-    Row row;
-    row.rb = x.b + (y.from >> 6);
-    row.ri = y.from & 63;
-    row.rh = X.head * a.G + y.gq;
-    uintx4 q[8];
-    load_q(a, X, row, q);
-    RowState st;
-    st.m = -INFINITY;
-    st.l = 0.f;
+    g.x = packed_block<STEPS>(a, far, X, w, r0, list, q_off, g.y);
+    g.row.rb = g.x.b + (g.y.from >> 6);
+    g.row.ri = g.y.from & 63;
+    g.row.rh = X.head * a.G + g.y.gq;
+    load_q(a, X, g.row, g.q);
+    g.st.m = -INFINITY;
+    g.st.l = 0.f;
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
         for (int e = 0; e < 16; ++e)
-            st.o[dt][e] = 0.f;
-    for (int kt = 0; kt < ntiles; ++kt)
-        prefix_tile_classic(X, X.k_lane + kt * kTileBytes, X.v_lane + kt * kTileBytes, X.P - kt * kTileKeys, q, st);
-    for (int k0 = 0; k0 < x.width; k0 += kTileKeys) {
+            g.st.o[dt][e] = 0.f;
+}
+
+template <int STEPS> __device__ __attribute__((always_inline)) void packed_general_end(const Args &a, const Ctx &X, GeneralBlock<STEPS> &g)
+{
+    for (int k0 = 0; k0 < g.x.width; k0 += kTileKeys) {
         uintx4 kf[8], vf[2][4];
         auto row_of = [&](const unsigned short *base, int pos) {
-            const unsigned e = (unsigned)__shfl((int)x.win, pos, 64);
-            return base + (long long)(x.b + (int)(e >> 6)) * a.ks_sb + (long long)(e & 63) * a.ks_ss;
+            const unsigned e = window_entry(g.x, pos);
+            return base + (long long)(g.x.b + (int)(e >> 6)) * a.ks_sb + (long long)(e & 63) * a.ks_ss;
         };
         const unsigned short *kp = row_of(X.ksg, k0 + X.c32) + 8 * X.h;
 #pragma unroll
@@ -426,39 +457,38 @@ __device__ __attribute__((always_inline)) void packed_general_block(const Args &
             for (int it = 0; it < 4; ++it)
                 vf[j][it] = ld_global16(vp + 32 * it);
         }
-        const unsigned bits = (unsigned)sees_bits(x, k0, X.h);
+        const unsigned bits = (unsigned)sees_bits(g.x, k0, X.h);
         floatx16 s;
 #pragma unroll
         for (int e = 0; e < 16; ++e)
             s[e] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks)
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), as_bf16x8(q[ks]), s, 0, 0, 0);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[ks]), as_bf16x8(g.q[ks]), s, 0, 0, 0);
 #pragma unroll
         for (int e = 0; e < 16; ++e)
             s[e] = bits >> (8 * (e >> 2) + (e & 3)) & 1 ? s[e] : -INFINITY;
         bf16x8 pf[2];
-        softmax_tile(s, st, X.c, pf);
-        pv_from_scratch(X, vf[0], pf[0], st.o);
-        pv_from_scratch(X, vf[1], pf[1], st.o);
+        softmax_tile(s, g.st, X.c, pf);
+        pv_from_scratch(X, vf[0], pf[0], g.st.o);
+        pv_from_scratch(X, vf[1], pf[1], g.st.o);
     }
-    const float ltot = sum_of_halves(st.l);
-    const unsigned at = y.own; // (entries and heads of the rows that this lane stores come from the lanes that own them)
+    const float ltot = sum_of_halves(g.st.l);
     unsigned short *dst[4];
     bool dst_ok[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < 4; ++u) { // (entries and heads of the rows that this lane stores come from the lanes that own them)
         const int from = 8 * u + (X.lane >> 3);
-        const unsigned e = (unsigned)__shfl((int)at, from, 64);
-        const int rh = __shfl(row.rh, from, 64);
-        dst[u] = reinterpret_cast<unsigned short *>(a.out) + (long long)(x.b + (int)(e >> 6)) * a.o_sb + (long long)(e & 63) * a.o_ss + (long long)rh * a.o_sh +
+        const unsigned e = (unsigned)__shfl((int)g.y.own, from, 64);
+        const int rh = __shfl(g.row.rh, from, 64);
+        dst[u] = reinterpret_cast<unsigned short *>(a.out) + (long long)(g.x.b + (int)(e >> 6)) * a.o_sb + (long long)(e & 63) * a.o_ss + (long long)rh * a.o_sh +
                  8 * (X.lane & 7);
         dst_ok[u] = true;
     }
-    store_rows(X, dst, dst_ok, y.own == y.from, 1.0f / ltot, st.o);
+    store_rows(X, dst, dst_ok, g.y.own == g.y.from, 1.0f / ltot, g.st.o);
     if (a.lse && X.h == 0)
-        a.lse[((long long)(x.b + (int)(y.own >> 6)) * a.Hq + row.rh) * a.S + (int)(y.own & 63)] =
-            y.own == y.from ? (st.m + __builtin_log2f(ltot)) * kLn2 : -INFINITY;
+        a.lse[((long long)(g.x.b + (int)(g.y.own >> 6)) * a.Hq + g.row.rh) * a.S + (int)(g.y.own & 63)] =
+            g.y.own == g.y.from ? (g.st.m + __builtin_log2f(ltot)) * kLn2 : -INFINITY;
 }
 
 } // namespace

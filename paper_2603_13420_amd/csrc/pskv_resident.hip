@@ -328,7 +328,7 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles, 
 
 // ------------------------------------------------------------------------------------------
 // Pipelined path over packed rows (see pskv_packed.hpp).  Preconditions (checked by the launcher): suffix lengths; S <= 32; a window
-// of at most 32 positions unless TWO; padded prefix of at least three tiles, one head's of less than 2^31 bytes.
+// of at most 32 * STEPS positions; a prefix, one head's of less than 2^31 bytes.
 //
 // Bound by the instructions of a block, as the kernel above, and by memory where the prefix is short; what it gains is blocks: 20480
 // instead of 23700 for 1024 candidates of 16..24 of 24 positions, 32/8 heads, P 256 (129 -> 120 us; the same with eight instructions 118 -> 109).
@@ -338,7 +338,8 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles, 
 // Small calls take a workgroup per block while there are compute units: a wavefront alone on its SIMD gets through a block in
 // little more than half the time (32 candidates of 20 positions, 32/8 heads, P 128: 11.2 us with eight blocks to a workgroup, 8.5 so; 12 before).
 // ------------------------------------------------------------------------------------------
-template <bool TWO>
+// TILES: 1 or 2, the prefix has so many tiles; 3: three and more.  (An instruction whose own prefix has fewer goes the general way.)
+template <int STEPS, int TILES>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
 void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int max_tiles)
 {
@@ -356,13 +357,15 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
 
     for (int vh = blockIdx.x % vh_slots; vh < VH; vh += vh_slots) {
         set_vhead(a, X, vh);
-        const int T = (X.P + kTileKeys - 1) / kTileKeys;
+        const int tiles = (X.P + kTileKeys - 1) / kTileKeys;
+        const bool fits = TILES == 3 ? tiles >= 3 : tiles == TILES;
+        const int T = TILES == 3 ? tiles : TILES; // (of a prefix that fits)
         __syncthreads(); // every wavefront is done with the images and the scratch of the virtual head before
 
         PackedList list;
         int blk = 0, blk_lo = 0, blk_hi = 0;
         Walk w, begin;
-        PackedBlock<TWO> nxt = {0, 1, X.cand0, 0, 1, 0u, 0u, 1u, false};
+        PackedBlock<STEPS> nxt = {0, 1, X.cand0, 0, 1, 0u, 0u, 0u, 1u, false};
         unsigned q_off = (unsigned)(X.head * a.G) * pa.q_sh;
         uintx4 q[8]; // this block's Q fragments until their last use, then the next block's
         bool any_bad = false;
@@ -370,7 +373,7 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
         auto advance = [&](int n) __attribute__((always_inline)) {
             for (; n < blk_hi; ++n) {
                 PackedRow row;
-                nxt = packed_block<TWO>(a, pa, fresh_lane(X), w, n * kBlockRows, list, q_off, row);
+                nxt = packed_block<STEPS>(a, pa, fresh_lane(X), w, n * kBlockRows, list, q_off, row);
                 if (!nxt.wide)
                     break;
                 any_bad = true;
@@ -393,7 +396,7 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
         } else {
             const TileSlot ts = make_tile_slot(fresh - kLenWaves * 64);
             const unsigned row = (unsigned)a.kp_sp * 2u;
-            for (int t = 0; t < T; ++t) {
+            for (int t = 0; t < tiles; ++t) {
                 const int left = X.P - t * kTileKeys - 1; // the last row's place in the tile
                 lds_u8 *const at = smem + t * kTileBytes + (wslot - kLenWaves) * 1024;
                 const unsigned char *const k0 = reinterpret_cast<const unsigned char *>(X.kpg) + (unsigned)t * kTileKeys * row;
@@ -406,7 +409,7 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
             }
         }
         __syncthreads();
-        list = choose_list<TWO>(a, pa, T, waves, per_chunk, lens);
+        list = choose_list<STEPS>(a, pa, tiles, waves, per_chunk, lens);
         {
             // Shares as in the kernel above: contiguous ranges, a quarter of the workgroup's per SIMD, 7/12 of that for the first of its two.
             const int nblocks = (list.total + kBlockRows - 1) / kBlockRows, each = (int)fdiv(nblocks, pa.div_n), over = nblocks - each * per_vh;
@@ -416,16 +419,16 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
             blk_lo = wslot < 4 ? part_lo : split, blk_hi = wslot < 4 ? split : part_hi;
             if (blk_lo < blk_hi)
                 begin = w = find_row(a, list, X.cand0, blk_lo * kBlockRows, fresh & 63);
-            blk = T < 3 ? blk_hi : advance(blk_lo);
+            blk = !fits ? blk_hi : advance(blk_lo);
             load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
         }
         asm volatile("" ::: "memory"); // (Q's eight requests stand before this)
         if (wslot >= kLenWaves) {
             PSKV_WAIT_VM(8);
-            if (T > 0) { // zeros where the last tile has no row
+            if (tiles > 0) { // zeros where the last tile has no row
                 const TileSlot ts = make_tile_slot(fresh - kLenWaves * 64);
-                const int left = X.P - (T - 1) * kTileKeys - 1;
-                lds_u8 *const at = smem + (T - 1) * kTileBytes + (fresh - kLenWaves * 64) * 16;
+                const int left = X.P - (tiles - 1) * kTileKeys - 1;
+                lds_u8 *const at = smem + (tiles - 1) * kTileBytes + (fresh - kLenWaves * 64) * 16;
                 if (ts.k_row > left) {
                     *(lds_u128 *)at = uintx4{0, 0, 0, 0};
                     *(lds_u128 *)(at + kTileBytes / 2) = uintx4{0, 0, 0, 0};
@@ -446,7 +449,7 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
         const int pads = waves * __builtin_amdgcn_readfirstlane((int)((float)shares * __builtin_amdgcn_rcpf((float)(blk_hi > blk ? blk_hi - blk : 1))) + 1);
 
         while (blk < blk_hi) {
-            const PackedBlock<TWO> x = nxt;
+            const PackedBlock<STEPS> x = nxt;
             // Loads are retired in issue order, so what is needed last is requested first.
             uintx4 skf[8], svf[2][4];
             load_window_k(pa, fresh_lane(X), x, 0, skf);
@@ -460,10 +463,23 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
             for (int ks = 0; ks < 8; ++ks)
                 sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*(lds_u128 *)(X.k_lane + ks * 1024)), as_bf16x8(q[ks]),
                                                              sA, 0, 0, 0);
-            Pre pre;
+            auto hide_past_prefix = [&]() __attribute__((always_inline)) { // ragged last prefix tile: keys past the prefix are not visible
+                if (X.P & (kTileKeys - 1)) {
+                    int bits = (1 << (X.P - (T - 1) * kTileKeys)) - 1;
+                    bits >>= 4 * fresh_lane(X).h; // element e holds key 8*(e/4) + e%4 + 4*h of the tile
 #pragma unroll
-            for (int i = 0; i < kDist; ++i)
-                pre.k[i] = *(lds_u128 *)(kimg(1) + i * 1024);
+                    for (int e = 0; e < 16; ++e)
+                        sA[e] = hide_unless_bit(sA[e], bits, 8 * (e >> 2) + (e & 3));
+                }
+            };
+            if (TILES == 1)
+                hide_past_prefix(); // (before the maximum)
+            Pre pre;
+            if constexpr (TILES > 1) {
+#pragma unroll
+                for (int i = 0; i < kDist; ++i)
+                    pre.k[i] = *(lds_u128 *)(kimg(1) + i * 1024);
+            }
             float m = sA[0];
 #pragma unroll
             for (int e = 1; e < 16; ++e)
@@ -478,40 +494,41 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
 
             // ---- pipeline over the prefix tiles: step t = scores of tile t+1, weights of tile t,
             //      value product of tile t-1 ----
-            pipe_tile<true, false, false, false, 0, true, true>(kimg(1), skf, vimg(0), kimg(2), vimg(0), pre, q, sA, sB,
-                                                                X.c, m, 0, l, pA, pA, o);
-            pipe_tile<true, false, true, true, 0, true, true>(kimg(2), skf, vimg(0), added_here(X.k_lane, (3 < T ? 3 : T - 1) * kTileBytes), vimg(1), pre,
-                                                              q, sB, sA, X.c, m, 0, l, pA, pB, o);
-            int t = 2;
-            for (; t + 1 <= T - 2; t += 2) {
-                pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 1), skf, vimg(t - 1), kimg(t + 2), vimg(t), pre,
-                                                                   q, sA, sB, X.c, m, 0, l, pB, pA, o);
-                pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 2), skf, vimg(t), kimg(t + 3 < T ? t + 3 : T - 1),
-                                                                   vimg(t + 1), pre, q, sB, sA, X.c, m, 0, l, pA, pB, o);
-            }
-            if (t <= T - 2) { // one step left over: do it and put scores and weights back in their places
-                pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 1), skf, vimg(t - 1), kimg(T - 1), vimg(t), pre,
-                                                                   q, sA, sB, X.c, m, 0, l, pB, pA, o);
+            if constexpr (TILES == 3) {
+                pipe_tile<true, false, false, false, 0, true, true>(kimg(1), skf, vimg(0), kimg(2), vimg(0), pre, q, sA, sB,
+                                                                    X.c, m, 0, l, pA, pA, o);
+                pipe_tile<true, false, true, true, 0, true, true>(kimg(2), skf, vimg(0), added_here(X.k_lane, (3 < T ? 3 : T - 1) * kTileBytes), vimg(1), pre,
+                                                                  q, sB, sA, X.c, m, 0, l, pA, pB, o);
+                int t = 2;
+                for (; t + 1 <= T - 2; t += 2) {
+                    pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 1), skf, vimg(t - 1), kimg(t + 2), vimg(t), pre,
+                                                                       q, sA, sB, X.c, m, 0, l, pB, pA, o);
+                    pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 2), skf, vimg(t), kimg(t + 3 < T ? t + 3 : T - 1),
+                                                                       vimg(t + 1), pre, q, sB, sA, X.c, m, 0, l, pA, pB, o);
+                }
+                if (t <= T - 2) { // one step left over: do it and put scores and weights back in their places
+                    pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 1), skf, vimg(t - 1), kimg(T - 1), vimg(t), pre,
+                                                                       q, sA, sB, X.c, m, 0, l, pB, pA, o);
+                    sA = sB;
+                    pB[0] = pA[0];
+                    pB[1] = pA[1];
+                }
+            } else if constexpr (TILES == 2) {
+                pipe_tile<true, false, false, false, 0, false, true>(kimg(1), skf, vimg(0), kimg(1), vimg(0), pre, q, sA, sB,
+                                                                     X.c, m, 0, l, pA, pB, o);
                 sA = sB;
-                pB[0] = pA[0];
-                pB[1] = pA[1];
             }
-            if (X.P & (kTileKeys - 1)) { // ragged last prefix tile: keys past the prefix are not visible
-                int bits = (1 << (X.P - (T - 1) * kTileKeys)) - 1;
-                bits >>= 4 * fresh_lane(X).h; // element e holds key 8*(e/4) + e%4 + 4*h of the tile
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    sA[e] = hide_unless_bit(sA[e], bits, 8 * (e >> 2) + (e & 3));
-            }
+            if (TILES > 1)
+                hide_past_prefix();
             load_window_v(pa, fresh_lane(X), x, 0, svf); // one step ahead of its use
             lds_u8 *const v_last = added_here(X.v_lane, (T - 1) * kTileBytes);
             // ---- last prefix tile: the "next scores" are the window's first ones, from the K registers ----
-            pipe_tile<true, true, true, false, 0, false, true>(kimg(0), skf, added_here(X.v_lane, (T - 2) * kTileBytes), kimg(0), v_last, pre, q, sA,
-                                                               sB, X.c, m, 0, l, pB, pA, o);
+            pipe_tile<true, true, (TILES > 1), (TILES == 2), 0, false, true>(kimg(0), skf, TILES == 3 ? added_here(X.v_lane, (T - 2) * kTileBytes) : X.v_lane, kimg(0),
+                                                                             v_last, pre, q, sA, sB, X.c, m, 0, l, pB, pA, o);
 
             // Unless the window goes on, Q has been used for the last time: the next block's rows and Q take its place.
             // (Requested unconditionally, past the end for the last block once more.)
-            const bool more = TWO && x.width > kTileKeys;
+            const bool more = STEPS > 1 && x.width > kTileKeys;
             if (!more) {
                 blk = advance(blk + 1);
                 load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
@@ -519,7 +536,7 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
 
             // ---- first window step: mask and weights under the value product of the last prefix
             //      tile; then its own value product through the scratch tile ----
-            pipe_tile<false, false, true, false, 2, false, false>(kimg(0), skf, v_last, kimg(0), vimg(0), pre, q, sB, sB,
+            pipe_tile<false, false, true, (TILES == 1), 2, false, false>(kimg(0), skf, v_last, kimg(0), vimg(0), pre, q, sB, sB,
                                                                   X.c, m, sees_bits(x, 0, fresh_lane(X).h), l, pA, pB, o);
             const Ctx Y = fresh_lane(X);
             if (more)
@@ -548,9 +565,14 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
         // Rare: some row met scores far above its first tile's maximum, or a block's candidates lie far apart: whatever this
         // wavefront stored is replaced by the general path's result.  The same for an instruction whose prefix is too short for
         // the pipeline.
-        if (any_bad || T < 3)
-            for (int b2 = blk_lo; b2 < blk_hi; ++b2)
-                packed_general_block(a, pa, X, T, begin, b2 * kBlockRows, list);
+        if (any_bad || !fits)
+            for (int b2 = blk_lo; b2 < blk_hi; ++b2) {
+                GeneralBlock<2> g;
+                packed_general_begin(a, pa, X, begin, b2 * kBlockRows, list, g);
+                for (int kt = 0; kt < tiles; ++kt)
+                    prefix_tile_classic(X, X.k_lane + kt * kTileBytes, X.v_lane + kt * kTileBytes, X.P - kt * kTileKeys, g.q, g.st);
+                packed_general_end(a, X, g);
+            }
     } // virtual heads
 }
 
@@ -572,7 +594,8 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
         for (auto kernel : {resident_pipelined_kernel<true>, resident_pipelined_kernel<false>})
             if (s == hipSuccess)
                 s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
-        for (auto kernel : {resident_packed_kernel<true>, resident_packed_kernel<false>})
+        for (auto kernel : {resident_packed_kernel<2, 1>, resident_packed_kernel<1, 1>, resident_packed_kernel<2, 2>, resident_packed_kernel<1, 2>,
+                            resident_packed_kernel<2, 3>, resident_packed_kernel<1, 3>})
             if (s == hipSuccess)
                 s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, max_lds);
         return s;
@@ -604,13 +627,18 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
     }
     // Rows packed by their lengths, where there are lengths: us, before and so: 32/8 heads: 1500 x 20, P 200: 177, 152; 1500 x 8..20: 145, 117; 500 x 28,
     // P 250: 91, 82; 700 x 28, P 128: 95, 94; 500 x 32: 93, 93; 1500 x 32: 237, 242 (nothing to pack); 32/32: 1500 x 14, P 200: 182, 154; 512 x 20, P 128:
-    // 75, 75 (its bytes alone take 66); 700 x 22..32, P 128: 139, 142; 28/4: 200 x 28, P 100: 25.3, 21.8; 8 x 12..24, 32/8, P 100: 11.3, 7.8.
+    // 75, 75 (its bytes alone take 66); 700 x 22..32, P 128: 139, 142; 28/4: 200 x 28, P 100: 25.3, 21.8; 8 x 12..24, 32/8, P 100: 11.3, 7.8; prefixes of one
+    // tile or two (before: the general kernel): 300 x 20, P 40, 32/8: 29.5, 25.1; 600 x 10..20, P 64: 54, 42; 1500 x 32, P 32, 32/32: 313, 328.
     PackedArgs pa;
     const ResidentSplit packed = resident_split(a, own * kNW, kNW, num_cu); // (a workgroup per block while there are compute units)
-    if (a.len && max_tiles >= 3 && a.S <= kTileKeys && own <= 0x7fffffffLL / kBlockRows && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && packed_args(a, (unsigned)packed.per_vh, kNW, pa)) {
+    if (a.len && max_tiles >= 1 && a.S <= kTileKeys && own <= 0x7fffffffLL / kBlockRows && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && packed_args(a, (unsigned)packed.per_vh, kNW, pa)) {
         const long long window = packed_window(a);
         pa.dense = window <= 2 * kTileKeys;
-        return launch_kernel(window <= kTileKeys ? resident_packed_kernel<false> : resident_packed_kernel<true>,
+        const bool two = window > kTileKeys;
+        auto kernel = max_tiles == 1 ? (two ? resident_packed_kernel<2, 1> : resident_packed_kernel<1, 1>)
+                      : max_tiles == 2 ? (two ? resident_packed_kernel<2, 2> : resident_packed_kernel<1, 2>)
+                                       : (two ? resident_packed_kernel<2, 3> : resident_packed_kernel<1, 3>);
+        return launch_kernel(kernel,
                              dim3((unsigned)(packed.per_vh * packed.vh_slots)), dim3(kNW * 64), (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes,
                              stream, a, pa, (int)packed.per_vh, (int)packed.vh_slots, max_tiles);
     }

@@ -72,6 +72,11 @@ def check(pk, inp, q_batch_stride=0, backward=True):
     (11, 100, 19, 3, 7, 1),      # heads that do not divide a block
     (3, 128, 31, 9, 40, 1),      # more heads than rows in a block
     (1, 96, 1, 1, 1, 1),
+    (9, 1, 20, 1, 4, 4),         # one prefix tile: a single row, all but full, full
+    (9, 31, 24, 1, 8, 2),
+    (9, 32, 19, 4, 7, 1),
+    (9, 33, 20, 1, 4, 4),        # two: the second with one row, full
+    (30, 64, 24, 8, 8, 2),
     (1300, 128, 3, 0, 2, 1),     # three candidates per thread of the workgroup that adds the lengths up
     (2200, 96, 2, 0, 1, 1),      # more lengths than it holds at a time
     (7, 40, 40, 33, 8, 2),       # (backward) one prefix tile, windows of up to 48 positions
