@@ -863,12 +863,12 @@ void bwd_dq_packed_kernel(BwdArgs g, PackedArgs pa, int per_vh, int vh_slots, in
                 store_rows(Y, dst, dst_ok, y.own == y.from, a.scale, o);
             }
             if (pad < a.C) {
-                store_padding(a, fresh_lane(X), X.cand0 + pad, list.align, g.dq, pa.q_sb, pa.q_ss, pa.q_sh, nullptr);
+                store_padding(a, fresh_lane(X), X.cand0 + pad, packed_len(a, X.cand0 + pad), list.align, g.dq, pa.q_sb, pa.q_ss, pa.q_sh, nullptr);
                 pad += waves;
             }
         }
         for (; pad < a.C; pad += waves)
-            store_padding(a, fresh_lane(X), X.cand0 + pad, list.align, g.dq, pa.q_sb, pa.q_ss, pa.q_sh, nullptr);
+            store_padding(a, fresh_lane(X), X.cand0 + pad, packed_len(a, X.cand0 + pad), list.align, g.dq, pa.q_sb, pa.q_ss, pa.q_sh, nullptr);
     }
 }
 

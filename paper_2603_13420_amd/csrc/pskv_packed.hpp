@@ -248,9 +248,10 @@ __device__ inline unsigned packed_off(unsigned entry, unsigned sb, unsigned ss) 
 // The block of packed rows r0..; w at or before the candidate of row r0, and left at its last row's.  q_off: byte offset of the
 // lane's query row from the first candidate's first one; y: the lane's row.  Where candidates lie too far apart the block ends before
 // the first such one (`wide`).
-template <int STEPS>
-__device__ inline PackedBlock<STEPS> packed_block(const Args &a, const PackedArgs &pa, const Ctx &X, Walk &w, int r0, const PackedList &list, unsigned &q_off,
-                                                PackedRow &y)
+// len_of(b): length of candidate b.
+template <int STEPS, typename F>
+__device__ __attribute__((always_inline)) PackedBlock<STEPS> packed_block(const Args &a, const PackedArgs &pa, const Ctx &X, Walk &w, int r0, const PackedList &list,
+                                                                          unsigned &q_off, PackedRow &y, F len_of)
 {
     PackedBlock<STEPS> x;
     x.r0 = r0;
@@ -259,7 +260,7 @@ __device__ inline PackedBlock<STEPS> packed_block(const Args &a, const PackedArg
     while (end <= r0) {
         w.first = end;
         ++w.b;
-        w.len = packed_len(a, w.b);
+        w.len = len_of(w.b);
         end += packed_run(a, w.len, list.align);
     }
     x.b = w.b;
@@ -277,7 +278,7 @@ __device__ inline PackedBlock<STEPS> packed_block(const Args &a, const PackedArg
         at += w.len;
         w.first = end;
         ++w.b;
-        w.len = packed_len(a, w.b);
+        w.len = len_of(w.b);
         end += packed_run(a, w.len, list.align);
         entry = l >= at ? (unsigned)((w.b - x.b) << 6 | (l - at)) : entry;
         if (STEPS == 3)
@@ -297,6 +298,13 @@ __device__ inline PackedBlock<STEPS> packed_block(const Args &a, const PackedArg
     const int lo = y.pos - (int)(y.from & 63); // the window's keys from its candidate's first to its own
     x.sees = STEPS > 1 ? (unsigned)(y.pos | lo << 8) : (2u << y.pos) - (1u << lo);
     return x;
+}
+
+template <int STEPS>
+__device__ inline PackedBlock<STEPS> packed_block(const Args &a, const PackedArgs &pa, const Ctx &X, Walk &w, int r0, const PackedList &list, unsigned &q_off,
+                                                PackedRow &y)
+{
+    return packed_block<STEPS>(a, pa, X, w, r0, list, q_off, y, [&](int b) { return packed_len(a, b); });
 }
 
 // The bits of the keys that the lane's row sees of window positions k0 .. k0 + 31, element e's at 8*(e/4) + e%4.
@@ -390,11 +398,11 @@ __device__ inline void window_step_fixed(const Ctx &X, int bits, const floatx16 
     pv_from_scratch(X, svf[1], as_bf16x8(uintx4{pk[4], pk[5], pk[6], pk[7]}), o);
 }
 
-// Zeros for candidate b's rows past those that its blocks store, of this KV head's query heads (whole rows, 16 lanes each), in a
+// Zeros for candidate b's (of the given length) rows past those that its blocks store, of this KV head's query heads (whole rows, 16 lanes each), in a
 // tensor with the given strides (bytes), and minus infinity in lse (null: none).
-__device__ inline void store_padding(const Args &a, const Ctx &X, int b, int align, void *out, unsigned sb, unsigned ss, unsigned sh, float *lse)
+__device__ inline void store_padding(const Args &a, const Ctx &X, int b, int len, int align, void *out, unsigned sb, unsigned ss, unsigned sh, float *lse)
 {
-    const int all = a.S * a.G, from = packed_run(a, packed_len(a, b), align);
+    const int all = a.S * a.G, from = packed_run(a, len, align);
     unsigned char *base = reinterpret_cast<unsigned char *>(out) + (unsigned long long)(unsigned)b * sb + (unsigned)(X.head * a.G) * sh;
     for (int r = from + (X.lane >> 4); r < all; r += 4) {
         const unsigned t = fdiv(r, a.div_g), gq = r - t * a.G;

@@ -487,7 +487,7 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
             m = max_of_halves(m) * X.c; // (the other half-wave holds the other 16 keys)
             // (Stores whose number the compiler does not know stand where the next wait for a load is far: after Q's, before K's.)
             for (const int to = pad + pads < a.C ? pad + pads : a.C; pad < to; pad += waves)
-                store_padding(a, fresh_lane(X), X.cand0 + pad, list.align, a.out, pa.o_sb, pa.o_ss, pa.o_sh, a.lse);
+                store_padding(a, fresh_lane(X), X.cand0 + pad, packed_len(a, X.cand0 + pad), list.align, a.out, pa.o_sb, pa.o_ss, pa.o_sh, a.lse);
             float l = 0.f;
             floatx16 o[4];
             uintx4 pA[2], pB[2]; // packed weights of the current and of the previous tile, roles alternating
@@ -560,7 +560,7 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
             store_packed(a, pa, fresh_lane(X), x, list.align, m, l, o);
         }
         for (; pad < a.C; pad += waves)
-            store_padding(a, fresh_lane(X), X.cand0 + pad, list.align, a.out, pa.o_sb, pa.o_ss, pa.o_sh, a.lse);
+            store_padding(a, fresh_lane(X), X.cand0 + pad, packed_len(a, X.cand0 + pad), list.align, a.out, pa.o_sb, pa.o_ss, pa.o_sh, a.lse);
 
         // Rare: some row met scores far above its first tile's maximum, or a block's candidates lie far apart: whatever this
         // wavefront stored is replaced by the general path's result.  The same for an instruction whose prefix is too short for

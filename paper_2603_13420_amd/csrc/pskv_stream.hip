@@ -22,7 +22,7 @@
 // suffix K/V then goes through the ring like the prefix.  The fourth is the third with passes of half the size, two at
 // a time on a compute unit.
 // Operand layouts and the pieces shared with the resident kernels are in pskv_mfma.hpp.
-#include "pskv_mfma.hpp"
+#include "pskv_packed.hpp"
 
 namespace pskv {
 namespace {
@@ -412,6 +412,396 @@ void stream_pipelined_kernel(Args a, int npasses, int nb, FastDiv div_nb)
             set_vhead(a, X, ps2.vh);
             if (ps2.exists && (wg_bad || (X.P + kTileKeys - 1) / kTileKeys < kMinTiles))
                 general_pass(a, X, smem, tid, ps2.vh, ps2.blk - cand_of(ps2.blk) * nb, ps2.active, cand_of(ps2.blk), WHOLE ? 0 : rows_c);
+        }
+}
+
+// ------------------------------------------------------------------------------------------
+// Pipelined passes over packed rows (pskv_packed.hpp): calls with one prefix and suffix lengths, S <= 64, in place of the
+// pipelined kernel above.  A pass is `waves` blocks of one KV head's list (the same list for every head), eight unless
+// there are fewer passes than compute units; wavefronts without a block only stage.  Windows of up to STEPS steps.
+//
+// Bound as the pipelined kernel, tile steps and, at a pass' ends, waits that all of the workgroup shares; what it gains is passes:
+// 4096 candidates of 32..64 positions, 40/40 heads, P 512: 246 thousand blocks for 328 thousand, 3632 -> 3155 us, although a block's
+// window takes 2.3 steps instead of 1.5.  A pass costs more than there: the search for its first candidate (64 lengths at a time, asked
+// for two steps before), the places of rows and keys, and one length per wavefront of a candidate whose padding it stores.
+// Tried: the next pass's Q asked for in one place before the window's steps, with this pass's kept or fetched again for the later ones:
+// 46 to 69 registers spilled, 0.82 of the pipelined kernel's speed there; asked for after the store it was slower, too.  As it is its
+// loads stand under two branches.
+// ------------------------------------------------------------------------------------------
+struct PackedPass {
+    int head, blk; // KV head, this wavefront's block
+    bool exists;   // the pass id holds an item (the same for the whole workgroup)
+    bool active;   // ... and this wavefront has a block
+};
+
+__device__ inline PackedPass packed_pass(const Args &a, int p, int npasses, int nblocks, int waves, int wave)
+{
+    PackedPass ps;
+    const int ngroups = (nblocks + waves - 1) / waves, items = a.Hkv * ngroups;
+    const int x = p & 7, y = p >> 3; // (ids as in make_pass)
+    const int item = ngroups < kLongHead ? x * ((items + 7) >> 3) + y : ((y / kChunk) * 8 + x) * kChunk + y % kChunk;
+    ps.exists = p < npasses && item < items && (ngroups >= kLongHead || y < (items + 7) >> 3);
+    const int hpos = ps.exists ? item / ngroups : 0, group = ps.exists ? item - hpos * ngroups : 0;
+    const int nfull = a.Hkv >> 3, rem = a.Hkv & 7, cut = rem * (nfull + 1); // (heads in the order 0, 8, ..., 1, 9, ...)
+    const int r = hpos < cut ? hpos / (nfull + 1) : rem + (hpos - cut) / (nfull > 0 ? nfull : 1);
+    ps.head = (hpos < cut ? hpos - r * (nfull + 1) : (hpos - cut) - (r - rem) * nfull) * 8 + r;
+    ps.blk = group * waves + wave;
+    ps.active = ps.exists && wave < waves && ps.blk < nblocks;
+    return ps;
+}
+
+// Where a row of the list is looked for.
+struct RowSearch {
+    int cand, base; // first candidate, the rows before it
+    int len;        // lane j: length of candidate cand + j (0 past the last one)
+};
+
+template <int STEPS>
+__global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
+void stream_packed_kernel(Args a, PackedArgs pa)
+{
+    extern __shared__ __align__(16) unsigned char smem_generic[];
+    lds_u8 *smem = (lds_u8 *)smem_generic;
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    Ctx X = make_stream_ctx(a, smem, tid);
+    auto kimg = [&](int t) { return X.k_lane + (t & (kRing - 1)) * kSlotBytes; };
+    auto vimg = [&](int t) { return X.v_lane + (t & (kRing - 1)) * kSlotBytes; };
+    const int T = (a.P + kTileKeys - 1) / kTileKeys;
+
+    // The list of rows, added up in the ring's place; what the passes need of it stays in a register per lane.
+    const int per_chunk = (a.C + kLenChunks - 1) / kLenChunks;
+    int upto;
+    PackedList list;
+    {
+        lds_int *const lens = (lds_int *)smem;
+        if (wave < kLenWaves) {
+            ChunkRows mine = {0, 0};
+            for (int k0 = 0; k0 < per_chunk; k0 += kLenRound) {
+                int len[kLenRound];
+                const int n = per_chunk - k0 < kLenRound ? per_chunk - k0 : kLenRound;
+                load_lengths(a, 0, per_chunk, k0, n, tid, len);
+                count_lengths(a, per_chunk, k0, n, len, lens, tid, mine);
+            }
+            add_up(mine, lens, tid);
+        }
+        __syncthreads();
+        list = choose_list<STEPS>(a, pa, T, 0, per_chunk, lens);
+        upto = rows_upto(list, tid & 63);
+        __syncthreads();
+    }
+    // Every candidate has all its rows: a row's candidate is a division away, and nothing is padding.
+    const int rows_c = a.S * a.G;
+    const bool full = list.total == a.C * rows_c;
+    const int nblocks = (list.total + kBlockRows - 1) / kBlockRows;
+    int waves = kNW; // blocks of a pass
+    while (waves > 1 && (long long)a.Hkv * ((nblocks + waves / 2 - 1) / (waves / 2)) <= gridDim.x)
+        waves /= 2;
+    const int ngroups = (nblocks + waves - 1) / waves;
+    const int npasses = (int)(8 * pass_ids_per_xcd((long long)a.Hkv * ngroups, ngroups));
+
+    // Padding: every pair of a KV head and a candidate belongs to one wavefront, which stores some at the end of each pass.
+    const int all_waves = gridDim.x * kNW, pairs = a.Hkv * a.C;
+    int pair = list.total == a.C * packed_run(a, a.S, list.align) ? pairs : blockIdx.x * kNW + wave, pair_head = pair / a.C, pair_cand = pair - pair_head * a.C;
+    const int step_head = all_waves / a.C, step_cand = all_waves - step_head * a.C;
+    const int shares = (pairs + all_waves - 1) / all_waves, passes = (npasses + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int each = __builtin_amdgcn_readfirstlane(shares / (passes > 0 ? passes : 1)) + 1;
+    auto pair_len = [&]() { return pair < pairs ? packed_len(a, pair_cand) : 0; };
+    auto store_pair = [&](int len) __attribute__((always_inline)) {
+        Ctx Y = fresh_lane(X);
+        Y.head = pair_head;
+        store_padding(a, Y, pair_cand, len, list.align, a.out, pa.o_sb, pa.o_ss, pa.o_sh, a.lse);
+        pair += all_waves;
+        pair_head += step_head;
+        pair_cand += step_cand;
+        if (pair_cand >= a.C) {
+            pair_cand -= a.C;
+            ++pair_head;
+        }
+    };
+
+    auto lengths_from = [&](int cand) __attribute__((always_inline)) {
+        const int c = cand + fresh_lane(X).lane, len = a.len[c < a.C ? c : a.C - 1];
+        return c < a.C ? len : 0;
+    };
+    auto search_begin = [&](int r0) __attribute__((always_inline)) {
+        RowSearch z = {0, 0, 0};
+        if (full)
+            return z;
+        const int g = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= r0));
+        z.base = g > 0 ? __builtin_amdgcn_readlane(upto, g > 0 ? g - 1 : 0) : 0;
+        z.cand = __builtin_amdgcn_readfirstlane(g * kLenPerLane * per_chunk);
+        z.len = lengths_from(z.cand);
+        return z;
+    };
+    auto search_end = [&](RowSearch &z, int r0) __attribute__((always_inline)) {
+        Walk w;
+        for (;;) {
+            z.len = clamp_len(a, z.len);
+            const int sum = wave_scan(packed_run(a, z.len, list.align)), all = __builtin_amdgcn_readlane(sum, 63);
+            if (z.base + all > r0) {
+                const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(z.base + sum <= r0));
+                w.b = z.cand + c;
+                w.first = z.base + (c > 0 ? __builtin_amdgcn_readlane(sum, c > 0 ? c - 1 : 0) : 0);
+                w.len = __builtin_amdgcn_readlane(z.len, c);
+                return w;
+            }
+            z.base += all; // (64 at a time: 4096 candidates and more)
+            z.cand += 64;
+            z.len = lengths_from(z.cand);
+        }
+    };
+
+    // this thread's two requests for tile kt (kt <= the last tile), straight into slot kt % 8
+    const TileSlot ts = make_tile_slot(tid);
+    const unsigned row_bytes = (unsigned)a.kp_sp * 2u;
+    const unsigned k_off = (unsigned)ts.k_row * row_bytes + ts.k_chunk * 16u, v_off = (unsigned)ts.v_row * row_bytes + ts.v_chunk * 16u;
+    const int past = T * kTileKeys - a.P; // rows that the last tile lacks
+    auto request = [&](int kt) {
+        const unsigned base = (unsigned)kt * kTileKeys * row_bytes;
+        lds_u8 *slot = smem + (kt & (kRing - 1)) * kSlotBytes + wave * 1024;
+        unsigned ko = k_off, vo = v_off;
+        if (kt == T - 1 && past) { // (rows past the prefix: its last one; never visible)
+            int t2 = tid;
+            asm volatile("" : "+v"(t2));
+            const TileSlot t = make_tile_slot(t2);
+            const int lastr = kTileKeys - 1 - past;
+            ko -= (unsigned)(t.k_row > lastr ? t.k_row - lastr : 0) * row_bytes;
+            vo -= (unsigned)(t.v_row > lastr ? t.v_row - lastr : 0) * row_bytes;
+        }
+        request_to_lds(reinterpret_cast<const unsigned char *>(X.kpg) + base, ko, slot);
+        request_to_lds(reinterpret_cast<const unsigned char *>(X.vpg) + base, vo, slot + kTileBytes);
+    };
+    // The ring protocol is that of the kernel above.
+    auto pass_top = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 7; ++u)
+            if (u < T)
+                request(u);
+        if (T >= 7)
+            PSKV_WAIT_VM(6);
+        else
+            PSKV_WAIT_VM(0);
+        __syncthreads();
+    };
+    auto pair_top = [&](int t) __attribute__((always_inline)) {
+        if (t + 4 <= T - 1)
+            PSKV_WAIT_VM(2);
+        else
+            PSKV_WAIT_VM(0);
+        __syncthreads();
+        if (t + 5 <= T - 1)
+            request(t + 5);
+        if (t + 6 <= T - 1)
+            request(t + 6);
+    };
+
+    bool wg_bad = false;
+    int p = blockIdx.x;
+    PackedPass ps = packed_pass(a, p, npasses, nblocks, waves, wave);
+    PackedBlock<STEPS> nxt = {0, 1, 0, 0, 1, 0u, 0u, 0u, 1u, false};
+    unsigned q_off = 0;
+    uintx4 q[8]; // this pass's Q fragments until their last use, then the next pass's
+    // The next pass's block: its place in the list (z: where to look), its rows and Q.
+    auto take_block = [&](RowSearch z) __attribute__((always_inline)) {
+        if (ps.active) {
+            X.head = ps.head;
+            const int r0 = ps.blk * kBlockRows;
+            Walk w;
+            if (full) {
+                w.b = (int)fdiv(fdiv(r0, a.div_g), a.div_s);
+                w.first = w.b * rows_c;
+                w.len = packed_len(a, w.b);
+            } else {
+                w = search_end(z, r0);
+            }
+            PackedRow row;
+            nxt = packed_block<STEPS>(a, pa, fresh_lane(X), w, r0, list, q_off, row, [&](int b) {
+                return !full && b - z.cand < 64 ? __builtin_amdgcn_readlane(z.len, b - z.cand) : packed_len(a, b);
+            });
+        }
+        load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
+    };
+    RowSearch z = search_begin(ps.active ? ps.blk * kBlockRows : 0);
+    take_block(z);
+
+    while (p < npasses) {
+        if (!ps.exists) {
+            p += gridDim.x;
+            ps = packed_pass(a, p, npasses, nblocks, waves, wave);
+            z = search_begin(ps.active ? ps.blk * kBlockRows : 0);
+            take_block(z);
+            continue;
+        }
+        set_vhead(a, X, ps.head);
+        bool bad = false;
+        const bool active = ps.active;
+        const int pad_len = pair_len(); // (asked for here: waited for together with the tiles)
+        pass_top();
+        if (!active) { // only staging
+            for (int t = 2; t + 1 <= T - 2; t += 2)
+                pair_top(t);
+            p += gridDim.x;
+            ps = packed_pass(a, p, npasses, nblocks, waves, wave);
+            z = search_begin(ps.active ? ps.blk * kBlockRows : 0);
+            take_block(z);
+        } else {
+            const PackedBlock<STEPS> x = nxt;
+
+            // ---- first prefix tile: scores, reference maximum ----
+            floatx16 sA, sB; // raw scores of the current and of the next tile, roles alternating
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                sA[e] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks)
+                sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(*(lds_u128 *)(kimg(0) + ks * 1024)), as_bf16x8(q[ks]), sA,
+                                                             0, 0, 0);
+            Pre pre;
+#pragma unroll
+            for (int i = 0; i < kDist; ++i)
+                pre.k[i] = *(lds_u128 *)(kimg(1) + i * 1024);
+            float m = sA[0];
+#pragma unroll
+            for (int e = 1; e < 16; ++e)
+                m = fmaxf(m, sA[e]);
+            m = max_of_halves(m) * X.c; // (the other half-wave holds the other 16 keys)
+            float l = 0.f;
+            floatx16 o[4];
+            uintx4 pA[2], pB[2]; // packed weights of the current and of the previous tile, roles alternating
+            uintx4 skf[8], svf[2][4];
+
+            // ---- pipeline over the prefix tiles (as above) ----
+            pipe_tile<true, false, false, false, 0, true, true>(kimg(1), skf, vimg(0), kimg(2), vimg(0), pre, q, sA, sB,
+                                                                X.c, m, 0, l, pA, pA, o);
+            pipe_tile<true, false, true, true, 0, true, true>(kimg(2), skf, vimg(0), kimg(3), vimg(1), pre, q, sB, sA, X.c,
+                                                              m, 0, l, pA, pB, o);
+#define PSKV_STEP_PAIR(t)                                                                                              \
+    do {                                                                                                               \
+        pipe_tile<true, false, true, false, 0, true, true>(kimg((t) + 1), skf, vimg((t) - 1), kimg((t) + 2),           \
+                                                           vimg(t), pre, q, sA, sB, X.c, m, 0, l, pB, pA, o);          \
+        pipe_tile<true, false, true, false, 0, true, true>(kimg((t) + 2), skf, vimg(t),                                \
+                                                           kimg((t) + 3 < T ? (t) + 3 : T - 1), vimg((t) + 1),         \
+                                                           pre, q, sB, sA, X.c, m, 0, l, pA, pB, o);                   \
+    } while (0)
+            int t = 2;
+            for (; t + 3 <= T - 2; t += 2) {
+                pair_top(t);
+                PSKV_STEP_PAIR(t);
+            }
+            // The last pair requests no further tiles; the window's K fragments and the lengths around the next pass's first row,
+            // needed two or three steps from here, are requested now.
+            const bool last_pair = t + 1 <= T - 2;
+            if (last_pair)
+                pair_top(t);
+            p += gridDim.x;
+            ps = packed_pass(a, p, npasses, nblocks, waves, wave);
+            z = search_begin(ps.active ? ps.blk * kBlockRows : 0);
+            load_window_k(pa, fresh_lane(X), x, 0, skf);
+            if (last_pair) {
+                PSKV_STEP_PAIR(t);
+                t += 2;
+            }
+#undef PSKV_STEP_PAIR
+            if (t <= T - 2) { // one step left over: do it and put scores and weights back in their places
+                pipe_tile<true, false, true, false, 0, true, true>(kimg(t + 1), skf, vimg(t - 1), kimg(T - 1), vimg(t), pre,
+                                                                   q, sA, sB, X.c, m, 0, l, pB, pA, o);
+                sA = sB;
+                pB[0] = pA[0];
+                pB[1] = pA[1];
+            }
+            if (past) { // ragged last prefix tile: keys past the prefix are not visible
+                int bits = (1 << (kTileKeys - past)) - 1;
+                bits >>= 4 * fresh_lane(X).h; // element e holds key 8*(e/4) + e%4 + 4*h of the tile
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    sA[e] = hide_unless_bit(sA[e], bits, 8 * (e >> 2) + (e & 3));
+            }
+            load_window_v(pa, fresh_lane(X), x, 0, svf); // one step ahead of its use
+            lds_u8 *const v_last = added_here(X.v_lane, ((T - 1) & (kRing - 1)) * kSlotBytes);
+            // ---- last prefix tile: the "next scores" are the window's first ones ----
+            pipe_tile<true, true, true, false, 0, false, true>(kimg(0), skf, added_here(X.v_lane, ((T - 2) & (kRing - 1)) * kSlotBytes), kimg(0), v_last, pre, q,
+                                                               sA, sB, X.c, m, 0, l, pB, pA, o);
+
+            // Unless the window goes on, Q has been used for the last time: the next pass's takes its place.
+            const int head = X.head; // (of this pass)
+            const bool more = STEPS > 1 && x.width > kTileKeys;
+            if (!more)
+                take_block(z);
+
+            // ---- first window step: mask and weights under the value product of the last prefix
+            //      tile; then its own value product through the scratch tile ----
+            pipe_tile<false, false, true, false, 2, false, false>(kimg(0), skf, v_last, kimg(0), vimg(0), pre, q, sB, sB,
+                                                                  X.c, m, sees_bits(x, 0, fresh_lane(X).h), l, pA, pB, o);
+            const Ctx Y = fresh_lane(X);
+            if (more)
+                load_window_k(pa, Y, x, kTileKeys, skf);
+            pv_from_scratch(Y, svf[0], as_bf16x8(pB[0]), o);
+            pv_from_scratch(Y, svf[1], as_bf16x8(pB[1]), o);
+            if (more) {
+                for (int k0 = kTileKeys;; k0 += kTileKeys) {
+                    load_window_v(pa, fresh_lane(X), x, k0, svf);
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        sB[e] = 0.f;
+#pragma unroll
+                    for (int ks = 0; ks < 8; ++ks)
+                        sB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(skf[ks]), as_bf16x8(q[ks]), sB, 0, 0, 0);
+                    const bool again = STEPS > 2 && k0 + kTileKeys < x.width;
+                    if (again)
+                        load_window_k(pa, fresh_lane(X), x, k0 + kTileKeys, skf);
+                    window_step_fixed(Y, sees_bits(x, k0, Y.h), sB, m, l, svf, o);
+                    if (!again)
+                        break;
+                }
+                take_block(z);
+            }
+
+            bad = x.wide || __builtin_amdgcn_ballot_w64(!(l < kBig)) != 0;
+            Ctx W = fresh_lane(X);
+            W.head = head;
+            store_packed(a, pa, W, x, list.align, m, l, o);
+        }
+        if (pair < pairs)
+            store_pair(pad_len);
+        for (int n = 1; n < each && pair < pairs; ++n)
+            store_pair(pair_len());
+        // the wavefront's verdict goes into the first word of its own scratch tile
+        if (X.lane == 0)
+            *(lds_int *)X.scr = bad ? 1 : 0;
+        __syncthreads(); // ends the pass: the ring is free, the verdicts are visible
+        wg_bad |= __builtin_amdgcn_ballot_w64(*(lds_int *)(smem + kRing * kSlotBytes + (X.lane & (kNW - 1)) * kScrBytes) !=
+                                              0) != 0;
+    }
+    while (pair < pairs)
+        store_pair(pair_len());
+
+    // Rare: some row met scores far above its first tile's maximum, or a block's candidates lie far apart; whatever this
+    // workgroup stored is then replaced by the general path's result.
+    if (wg_bad)
+        for (int p2 = blockIdx.x; p2 < npasses; p2 += gridDim.x) {
+            ps = packed_pass(a, p2, npasses, nblocks, waves, wave);
+            if (!ps.exists)
+                continue;
+            set_vhead(a, X, ps.head);
+            GeneralBlock<STEPS> g;
+            const int r0 = ps.active ? ps.blk * kBlockRows : 0;
+            z = search_begin(r0);
+            packed_general_begin(a, pa, X, full ? Walk{0, 0, packed_len(a, 0)} : search_end(z, r0), r0, list, g);
+            uintx4 kv, vv;
+            load_tile_chunks(a, X, ts, 0, kv, vv);
+            __syncthreads(); // whatever the ring held has been used by every wavefront
+            write_tile_chunks(X, ts, 0, smem, smem + kTileBytes, tid, kv, vv);
+            __syncthreads();
+            for (int kt = 0; kt < T; ++kt) {
+                load_tile_chunks(a, X, ts, kt + 1 < T ? kt + 1 : kt, kv, vv);
+                prefix_tile_classic(X, X.k_lane + (kt & 1) * kSlotBytes, X.v_lane + (kt & 1) * kSlotBytes, X.P - kt * kTileKeys, g.q, g.st);
+                if (kt + 1 < T)
+                    write_tile_chunks(X, ts, kt + 1, smem + ((kt + 1) & 1) * kSlotBytes, smem + ((kt + 1) & 1) * kSlotBytes + kTileBytes, tid, kv, vv);
+                __syncthreads();
+            }
+            if (ps.active)
+                packed_general_end(a, X, g);
         }
 }
 
@@ -1101,6 +1491,9 @@ int device_cu_count(hipError_t &e)
                             stream_pipelined_kernel<false, false>})
             if (s == hipSuccess)
                 s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+        for (auto kernel : {stream_packed_kernel<1>, stream_packed_kernel<2>, stream_packed_kernel<3>})
+            if (s == hipSuccess)
+                s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
         for (auto kernel : {stream_candidate4_kernel<true>, stream_candidate4_kernel<false>})
             if (s == hipSuccess)
                 s = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kCLdsBytes);
@@ -1238,6 +1631,22 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
                             : (whole ? stream_candidate4_kernel<true> : stream_candidate4_kernel<false>);
         return launch_kernel(kernel, dim3((unsigned)(npasses < places ? npasses : places)), dim3(waves * 64), eight ? kLdsBytes : kCLdsBytes, stream,
                              a, (int)npasses, cs);
+    }
+    // Rows packed by their lengths, where there are lengths.  us, before and so: 300 candidates, P 700: 16 positions, 40/40 heads: 118, 102;
+    // 20..40: 299, 210; 12..24, 28/4: 92, 75; 24: 93, 95; 700, P 300, 40/40: 40: 470, 377; 64: 554, 563; 32..64: 502, 479; 16 x 24: 22.6, 15.2.
+    // Not whole blocks of grouped heads or of one block per candidate: which is faster depends on lengths that the host does not know, and
+    // without padding the pipelined kernel is: 1500 x 32, 32/8, P 400: 423, 442 (16..32: 404, 350); 256 x 32, P 2048: 241, 245 (233, 186);
+    // 300 x 32, 40/40, P 700: 178, 194 (170, 171).  What this costs: 1 to 5 % where nothing is padded (700 x 64 above), and calls of
+    // two rounds of the chip that stay two: 120 x 24, 28/4, P 512: 38, 40; 40 x 32..64, 40/40, P 1000: 68, 74.  Sizes do not tell these
+    // either: 120 x 12..24 is 1.48 times as fast.
+    if (PackedArgs pa; a.len && a.Np == 1 && (!whole || (a.G == 1 && a.S > kTileKeys)) && max_tiles >= kMinTiles && a.S <= 2 * kTileKeys && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL &&
+                       a.C * nb <= 0x7fffffffLL / kBlockRows && (long long)a.C * a.Hkv < 0x7fffffffLL - num_cu * kNW &&
+                       stream_pass_ids(a, a.C * nb) <= 0x7fffffffLL - 8 && packed_args(a, (unsigned)num_cu, kNW, pa)) {
+        const long long window = packed_window(a);
+        pa.dense = window <= 3 * kTileKeys;
+        const long long widest = pa.dense && window > a.S ? window : a.S;
+        auto kernel = widest <= kTileKeys ? stream_packed_kernel<1> : widest <= 2 * kTileKeys ? stream_packed_kernel<2> : stream_packed_kernel<3>;
+        return launch_kernel(kernel, dim3((unsigned)num_cu), dim3(kNW * 64), kLdsBytes, stream, a, pa);
     }
     // Own blocks make more passes, each in 0.7 of the general kernel's time, 0.8 with the second own step: not where
     // that costs a round of the chip.

@@ -88,21 +88,38 @@ def test_packed_rows(pk, B, P, S, lo, Hq, Hkv):
     check(pk, gen.make_inputs(w, pad="nan"))
 
 
+@pytest.mark.parametrize("B,P,S,lo,Hq,Hkv", [
+    (7, 257, 20, 1, 4, 4),       # streamed prefixes: a ragged last tile, two-step windows, one block per pass
+    (40, 288, 9, 0, 2, 2),
+    (12, 512, 64, 32, 4, 4),     # windows of three steps
+    (9, 300, 64, 64, 2, 2),      # ... nothing padded
+    (10, 400, 25, 3, 14, 2),     # one-step windows
+    (300, 320, 21, 1, 10, 10),   # several blocks per pass, some passes with fewer
+    (2200, 260, 2, 0, 1, 1),     # more lengths than are held at a time
+    (4200, 260, 2, 0, 3, 3),     # ... and than a search takes at once; heads that no XCD has alone
+])
+def test_packed_rows_streamed(pk, B, P, S, lo, Hq, Hkv):
+    w = gen.custom_workload(f"packed_stream_{B}_{P}_{S}", B, P, S, lo, S, Hq, Hkv, 128, "bf16", index=3500 + B + P + S)
+    check(pk, gen.make_inputs(w, pad="nan"), backward=False)
+
+
+@pytest.mark.parametrize("P", [120, 300])
 @pytest.mark.parametrize("name", ["none", "first", "last", "middle", "one", "alternate"])
-def test_empty_candidates(pk, name):
+def test_empty_candidates(pk, name, P):
     B, S = 70, 24
     lens = {"none": [0] * B, "first": [0] * 40 + [S] * 30, "last": [9] * 30 + [0] * 40, "middle": [S] * 5 + [0] * 60 + [7] * 5,
             "one": [0] * 33 + [13] + [0] * 36, "alternate": [(i % 2) * (i % S + 1) for i in range(B)]}[name]
-    w = gen.custom_workload(f"packed_empty_{name}", B, 120, S, 0, S, 4, 2, 128, "bf16", index=3200)
+    w = gen.custom_workload(f"packed_empty_{name}_{P}", B, P, S, 0, S, 14, 2, 128, "bf16", index=3200 + P)
     inp = gen.make_inputs(w, pad="nan")
     put_lengths(inp, lens)
     check(pk, inp)
 
 
-def test_candidates_far_apart(pk):
+@pytest.mark.parametrize("P", [100, 300])
+def test_candidates_far_apart(pk, P):
     # 150 empty candidates between two that share a block, query rows of consecutive ones 16 MB apart: beyond 32-bit offsets
     B, S = 300, 8
-    w = gen.custom_workload("packed_far", B, 100, S, 0, S, 2, 1, 128, "bf16", index=3201)
+    w = gen.custom_workload(f"packed_far_{P}", B, P, S, 0, S, 2, 1, 128, "bf16", index=3201)
     inp = gen.make_inputs(w, pad="nan")
     put_lengths(inp, [3] + [0] * 150 + [8] * 20 + [0] * 128 + [5])
     check(pk, inp, q_batch_stride=(1 << 23) - 8)
@@ -119,10 +136,10 @@ def test_several_instructions(pk, Np, C, P, S, lo, Hq, Hkv):
     check(pk, inp)
 
 
-@pytest.mark.parametrize("S,Hq,Hkv", [(20, 4, 4), (24, 8, 2)])
-def test_rows_that_need_rescaling(pk, S, Hq, Hkv):
+@pytest.mark.parametrize("S,Hq,Hkv,P", [(20, 4, 4, 200), (24, 8, 2, 200), (20, 4, 4, 300), (50, 2, 2, 300)])
+def test_rows_that_need_rescaling(pk, S, Hq, Hkv, P):
     # scores some 100 above the first tile's maximum, in a prefix tile for some rows and among the own keys for others
-    w = gen.custom_workload(f"packed_rescale_{S}", 12, 200, S, 5, S, Hq, Hkv, 128, "bf16", index=3400 + S)
+    w = gen.custom_workload(f"packed_rescale_{S}_{P}", 12, P, S, 5, S, Hq, Hkv, 128, "bf16", index=3400 + S)
     inp = gen.make_inputs(w, pad="nan")
     loud = lambda x: gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(x) * 8)
     inp.k_pre[150] = loud(inp.k_pre[150])
