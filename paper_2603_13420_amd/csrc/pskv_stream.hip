@@ -13,14 +13,14 @@
 // read from HBM about once per XCD: pass ids are laid out so that the workgroups of one XCD
 // (workgroup ids go round the XCDs) work on one head at a time, and find it in that XCD's L2.
 //
-// Four kernels.  The pipelined one (every 32-row block inside one candidate) is the software
+// Five kernels.  The pipelined one (every 32-row block inside one candidate) is the software
 // pipeline of the resident-prefix kernel with the tile images taken from the ring, the suffix
 // handled after the prefix, and a fixed per-row reference maximum; when a row turns out to
 // need rescaling, the workgroup repeats its passes on the general path.  The general one
 // (any shape) is the classic online softmax, one tile at a time.  The third (further down) is
 // for suffix-side segments of several tiles: its passes are cut out of one candidate, whose own
 // suffix K/V then goes through the ring like the prefix.  The fourth is the third with passes of half the size, two at
-// a time on a compute unit.
+// a time on a compute unit.  The fifth is the pipelined one with blocks of valid rows only (pskv_packed.hpp).
 // Operand layouts and the pieces shared with the resident kernels are in pskv_mfma.hpp.
 #include "pskv_packed.hpp"
 
