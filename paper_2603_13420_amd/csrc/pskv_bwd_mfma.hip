@@ -1447,9 +1447,8 @@ hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream)
     if (const ResidentSplit packed = resident_split(a, a.C * nb * kNW, kNW, num_cu);
         a.len && !small && a.P <= kDqMaxTiles * kTileKeys && a.S <= 2 * kTileKeys && a.C * nb <= 0x7fffffffLL / kBlockRows &&
         (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && packed_args(a, (unsigned)packed.per_vh, kNW, pa)) {
-        const long long window = packed_window(a);
-        pa.dense = window <= 2 * kTileKeys;
-        return launch_kernel(window <= kTileKeys ? bwd_dq_packed_kernel<1> : bwd_dq_packed_kernel<2>,
+        const bool two = packed_steps(a, 2, pa.dense) > 1;
+        return launch_kernel(two ? bwd_dq_packed_kernel<2> : bwd_dq_packed_kernel<1>,
                              dim3((unsigned)(packed.per_vh * packed.vh_slots)), dim3(kNW * 64), (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes,
                              stream, g, pa, (int)packed.per_vh, (int)packed.vh_slots, max_tiles);
     }

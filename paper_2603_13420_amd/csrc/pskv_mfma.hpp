@@ -60,7 +60,7 @@ __device__ inline lds_u8 *added_here(lds_u8 *p, int n)
     return lds_at(lds_addr(p) + (unsigned)n);
 }
 
-__device__ inline unsigned fdiv(unsigned n, FastDiv d) { return (unsigned)(((unsigned long long)n * d.mul) >> d.shift); }
+__host__ __device__ inline unsigned fdiv(unsigned n, FastDiv d) { return (unsigned)(((unsigned long long)n * d.mul) >> d.shift); }
 
 __device__ inline uintx4 ld_global16(const unsigned short *p) { return *reinterpret_cast<const uintx4 *>(p); }
 

@@ -17,7 +17,7 @@ namespace pskv {
 struct PackedArgs {
     unsigned q_sb, q_ss, q_sh, o_sb, o_ss, o_sh, k_sb, k_ss;
     int span;       // candidates of one block at most, counted from its first one, for which 32-bit offsets from that one's rows reach
-    int dense;      // windows of align 1 fit the kernel's
+    bool dense;     // windows of align 1 fit the kernel's
     FastDiv div_n;  // division by the number of workgroups that share a list
     FastDiv div_w;  // ... of wavefronts
 };
@@ -51,13 +51,62 @@ inline long long packed_window(const Args &a)
     return a.S - 1 + tokens;
 }
 
-namespace {
+// Steps of a window, at most `most`; dense: lists of align 1 have no wider ones.
+inline int packed_steps(const Args &a, int most, bool &dense)
+{
+    const long long window = packed_window(a);
+    dense = window <= most * kTileKeys;
+    return (int)((dense ? window : a.S) + kTileKeys - 1) / kTileKeys;
+}
 
-typedef __attribute__((address_space(3))) int lds_int;
+// Arithmetic of the lists, the same on the device and on the host (where tests run it).
 
 struct Walk {
     int b, first, len; // candidate (global index), its first packed row, its length: wave-uniform
 };
+
+// Rows of a candidate of the given length in the list.
+__host__ __device__ inline int packed_run(const Args &a, int len, int align) { return (len * a.G + align - 1) & -align; }
+
+// Chooses the alignment, from the rows of either list.  Blocks across candidates are fewer, but their
+// windows may go on to a second step: where a candidate's positions and a block's are more than 32, which with lengths of n
+// is one block in n / (n + 32/G - 32).  A block takes the time of its tiles and some 6 more; a second step is counted
+// as 18 - 1.4 for every prefix tile, what it costs and what blocks that memory bounds do not gain by being fewer.  us, across
+// candidates and inside them, 1500 candidates, P 200 (500, P 250; 700, P 128): 32/32 heads: 20 positions: 222, 237 (81, 91; 107, 106);
+// 17..25: 252, 246 (92, 94; 117, 114); 11..28: 246, 242 (87, 92; 119, 115); 22..32: 320, 300 (114, 103; 154, 143); 32/8: 28 positions: 217, 234 (83,
+// 89; 96, 95); 32: 245, 243 (94, 93; 105, 105); 22..32: 217, 225 (84, 85; 93, 91); no second steps: 20: 153, 172 (57, 63; 65, 69).
+// Where every wavefront has at most one block either way, blocks inside candidates: they take the shorter walk (32 candidates of 8..20,
+// 32/8 heads, P 128: 11.6 us across, 11.1 inside).
+template <int STEPS> __host__ __device__ inline int packed_align(const Args &a, bool dense, int tiles, int waves, int total, int total32)
+{
+    long long second = STEPS > 1 ? total - 32LL * (a.G - 1) * a.C : 0; // rows of blocks with a second step
+    second = second > 0 ? second : 0;
+    const int second_cost = tiles < 10 ? 180 - 14 * tiles : 40; // (tenths of a tile's time)
+    const bool one = dense && total32 > 32 * waves && (long long)total * (10 * (tiles + 6)) + second_cost * second < (long long)total32 * (10 * (tiles + 6));
+    return one ? 1 : kBlockRows;
+}
+
+// Whether a row's candidate is a division by S*G away: every candidate has S*G rows in the list.  Across candidates the sum says so, no
+// candidate having more.  Inside them it says so where S*G is a multiple of 32; where it is not, a run may be longer than S*G, and the
+// sum of long and short ones can be the same (runs of 64, 32, 32 and 32 rows, S 40).
+__host__ __device__ inline bool packed_by_division(const Args &a, int total, int align)
+{
+    return total == a.C * a.S * a.G && (align == 1 || a.S * a.G % kBlockRows == 0);
+}
+
+// The candidate (of one instruction's) of row r0, found so; its length is left to be filled in.
+__host__ __device__ inline Walk walk_by_division(const Args &a, int r0)
+{
+    Walk w;
+    w.b = (int)fdiv(fdiv(r0, a.div_g), a.div_s);
+    w.first = w.b * a.S * a.G;
+    w.len = 0;
+    return w;
+}
+
+namespace {
+
+typedef __attribute__((address_space(3))) int lds_int;
 
 // Length of candidate b, b the same for the whole wavefront (as len_uniform; there are lengths).
 __device__ inline int packed_len(const Args &a, int b)
@@ -65,8 +114,6 @@ __device__ inline int packed_len(const Args &a, int b)
     typedef const __attribute__((address_space(4))) int *const_int_ptr;
     return clamp_len(a, ((const_int_ptr)(unsigned long long)a.len)[__builtin_amdgcn_readfirstlane(b)]);
 }
-
-__device__ inline int packed_run(const Args &a, int len, int align) { return (len * a.G + align - 1) & -align; }
 
 // Sum over the lanes up to and with this one.
 __device__ inline int wave_scan(int v)
@@ -135,15 +182,7 @@ __device__ inline void add_up(const ChunkRows &c, lds_int *lens, int tid)
     }
 }
 
-// Chooses the alignment.  Blocks across candidates are fewer, but their
-// windows may go on to a second step: where a candidate's positions and a block's are more than 32, which with lengths of n
-// is one block in n / (n + 32/G - 32).  A block takes the time of its tiles and some 6 more; a second step is counted
-// as 18 - 1.4 for every prefix tile, what it costs and what blocks that memory bounds do not gain by being fewer.  us, across
-// candidates and inside them, 1500 candidates, P 200 (500, P 250; 700, P 128): 32/32 heads: 20 positions: 222, 237 (81, 91; 107, 106);
-// 17..25: 252, 246 (92, 94; 117, 114); 11..28: 246, 242 (87, 92; 119, 115); 22..32: 320, 300 (114, 103; 154, 143); 32/8: 28 positions: 217, 234 (83,
-// 89; 96, 95); 32: 245, 243 (94, 93; 105, 105); 22..32: 217, 225 (84, 85; 93, 91); no second steps: 20: 153, 172 (57, 63; 65, 69).
-// Where every wavefront has at most one block either way, blocks inside candidates: they take the shorter walk (32 candidates of 8..20,
-// 32/8 heads, P 128: 11.6 us across, 11.1 inside).
+// The list of the alignment that is chosen (see packed_align).
 template <int STEPS>
 __device__ inline PackedList choose_list(const Args &a, const PackedArgs &pa, int tiles, int waves, int per_chunk, lds_int *lens)
 {
@@ -156,13 +195,9 @@ __device__ inline PackedList choose_list(const Args &a, const PackedArgs &pa, in
     }
     total = __builtin_amdgcn_readfirstlane(total);
     total32 = __builtin_amdgcn_readfirstlane(total32);
-    long long second = STEPS > 1 ? total - 32LL * (a.G - 1) * a.C : 0; // rows of blocks with a second step
-    second = second > 0 ? second : 0;
-    const int second_cost = tiles < 10 ? 180 - 14 * tiles : 40; // (tenths of a tile's time)
-    const bool one = pa.dense && total32 > 32 * waves && (long long)total * (10 * (tiles + 6)) + second_cost * second < (long long)total32 * (10 * (tiles + 6));
     PackedList x;
-    x.align = one ? 1 : kBlockRows;
-    x.total = one ? total : total32;
+    x.align = packed_align<STEPS>(a, pa.dense, tiles, waves, total, total32);
+    x.total = x.align == 1 ? total : total32;
     x.per_chunk = per_chunk;
     x.lens = lens;
     return x;

@@ -632,9 +632,7 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
     PackedArgs pa;
     const ResidentSplit packed = resident_split(a, own * kNW, kNW, num_cu); // (a workgroup per block while there are compute units)
     if (a.len && max_tiles >= 1 && a.S <= kTileKeys && own <= 0x7fffffffLL / kBlockRows && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && packed_args(a, (unsigned)packed.per_vh, kNW, pa)) {
-        const long long window = packed_window(a);
-        pa.dense = window <= 2 * kTileKeys;
-        const bool two = window > kTileKeys;
+        const bool two = packed_steps(a, 2, pa.dense) > 1;
         auto kernel = max_tiles == 1 ? (two ? resident_packed_kernel<2, 1> : resident_packed_kernel<1, 1>)
                       : max_tiles == 2 ? (two ? resident_packed_kernel<2, 2> : resident_packed_kernel<1, 2>)
                                        : (two ? resident_packed_kernel<2, 3> : resident_packed_kernel<1, 3>);

@@ -490,9 +490,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
         upto = rows_upto(list, tid & 63);
         __syncthreads();
     }
-    // Every candidate has all its rows: a row's candidate is a division away, and nothing is padding.
-    const int rows_c = a.S * a.G;
-    const bool full = list.total == a.C * rows_c;
+    const bool full = packed_by_division(a, list.total, list.align);
     const int nblocks = (list.total + kBlockRows - 1) / kBlockRows;
     int waves = kNW; // blocks of a pass
     while (waves > 1 && (long long)a.Hkv * ((nblocks + waves / 2 - 1) / (waves / 2)) <= gridDim.x)
@@ -609,8 +607,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
             const int r0 = ps.blk * kBlockRows;
             Walk w;
             if (full) {
-                w.b = (int)fdiv(fdiv(r0, a.div_g), a.div_s);
-                w.first = w.b * rows_c;
+                w = walk_by_division(a, r0);
                 w.len = packed_len(a, w.b);
             } else {
                 w = search_end(z, r0);
@@ -1642,10 +1639,8 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
     if (PackedArgs pa; a.len && a.Np == 1 && (!whole || (a.G == 1 && a.S > kTileKeys)) && max_tiles >= kMinTiles && a.S <= 2 * kTileKeys && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL &&
                        a.C * nb <= 0x7fffffffLL / kBlockRows && (long long)a.C * a.Hkv < 0x7fffffffLL - num_cu * kNW &&
                        stream_pass_ids(a, a.C * nb) <= 0x7fffffffLL - 8 && packed_args(a, (unsigned)num_cu, kNW, pa)) {
-        const long long window = packed_window(a);
-        pa.dense = window <= 3 * kTileKeys;
-        const long long widest = pa.dense && window > a.S ? window : a.S;
-        auto kernel = widest <= kTileKeys ? stream_packed_kernel<1> : widest <= 2 * kTileKeys ? stream_packed_kernel<2> : stream_packed_kernel<3>;
+        const int steps = packed_steps(a, 3, pa.dense);
+        auto kernel = steps == 1 ? stream_packed_kernel<1> : steps == 2 ? stream_packed_kernel<2> : stream_packed_kernel<3>;
         return launch_kernel(kernel, dim3((unsigned)num_cu), dim3(kNW * 64), kLdsBytes, stream, a, pa);
     }
     // Own blocks make more passes, each in 0.7 of the general kernel's time, 0.8 with the second own step: not where

@@ -6,6 +6,7 @@ import pytest
 
 from paper_2603_13420_amd import inputs as gen
 import parity_util as pu
+from test_parity_own_blocks_gpu import check as check_guarded
 
 pytestmark = pytest.mark.gpu
 
@@ -151,3 +152,19 @@ def test_rows_that_need_rescaling(pk, S, Hq, Hkv, P):
     for x in (inp.v_pre, inp.v_suf):
         x[...] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(x) * np.float32(0.25))
     check(pk, inp, backward=False)
+
+
+@pytest.mark.parametrize("lens,S,Hq,Hkv,P", [
+    ([38, 30, 30, 30], 40, 4, 4, 257),       # lengths whose rows, each filled up to whole blocks, are as many as B*S*G: not a full batch
+    ([40, 32, 32, 32], 40, 4, 4, 300),
+    ([32, 32, 48, 48] * 3, 48, 2, 2, 260),
+    ([40, 32], 40, 4, 2, 320),
+    ([59, 59, 41, 59, 55, 57, 60, 48], 60, 4, 2, 300),
+    ([40] * 9, 40, 4, 4, 300),               # full ones
+    ([64] * 5 + [33, 40], 64, 4, 4, 300),
+])
+def test_lengths_that_add_up_like_full_ones(pk, lens, S, Hq, Hkv, P):
+    w = gen.custom_workload(f"packed_sum_{S}_{P}", len(lens), P, S, 0, S, Hq, Hkv, 128, "bf16", index=3600 + S + P)
+    inp = gen.make_inputs(w, pad="nan")
+    put_lengths(inp, lens)
+    check_guarded(pk, inp)
