@@ -104,6 +104,67 @@ __host__ __device__ inline Walk walk_by_division(const Args &a, int r0)
     return w;
 }
 
+__host__ __device__ inline int same_in_all_lanes(int x)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return __builtin_amdgcn_readfirstlane(x);
+#else
+    return x;
+#endif
+}
+
+// The candidates of a block's rows.
+struct BlockSpan {
+    int b, first; // the first one, its first row in the list
+    int last;     // the block's last row
+    int width;    // positions of the window, one or more
+    bool wide;    // it ends early: the next candidate is `span` or more away from the first one
+};
+
+// What window position l holds after the walk has entered the n-th candidate: (candidate - the first one) << 6 | position.
+__host__ __device__ inline unsigned enter_window(unsigned entry, int l, int n, int at) { return l >= at ? (unsigned)(n << 6 | (l - at)) : entry; }
+
+// Walks over the block of rows r0.. of a list of `total` rows: w, at or before the candidate of row r0, is left at the last row's or
+// (wide) at the last one before the next, which may be empty.  len_of(b): length of candidate b; enter(n, at): the walk enters the
+// n-th candidate after the first one, whose first position is the window's at-th.  It ends at the last candidate (cand_end is one
+// past it), whatever the lengths say.
+template <typename L, typename E>
+__host__ __device__ __attribute__((always_inline)) inline BlockSpan walk_block(const Args &a, Walk &w, int r0, int total, int align, int span, int cand_end, L len_of,
+                                                                               E enter)
+{
+    BlockSpan x;
+    x.last = total - r0 < kBlockRows ? total - 1 : r0 + kBlockRows - 1;
+    int end = w.first + packed_run(a, w.len, align);
+    while (end <= r0 && w.b + 1 < cand_end) {
+        w.first = end;
+        ++w.b;
+        w.len = len_of(w.b);
+        end += packed_run(a, w.len, align);
+    }
+    x.b = w.b;
+    x.first = w.first;
+    x.wide = false;
+    int at = 0; // window position of the walk's candidate's first
+    while (end <= x.last && w.b + 1 < cand_end) {
+        if (w.b + 1 - x.b >= span) {
+            x.last = end - 1;
+            x.wide = true;
+            break;
+        }
+        at += w.len;
+        w.first = end;
+        ++w.b;
+        w.len = len_of(w.b);
+        end += packed_run(a, w.len, align);
+        enter(w.b - x.b, at);
+    }
+    // The walk's candidate's positions: up to the last row's, none of an empty one.
+    const int upto = x.last < w.first ? 0 : same_in_all_lanes((int)fdiv(x.last - w.first, a.div_g)) + 1;
+    x.width = at + (upto < w.len ? upto : w.len);
+    x.width = x.width > 1 ? x.width : 1;
+    return x;
+}
+
 namespace {
 
 typedef __attribute__((address_space(3))) int lds_int;
@@ -273,7 +334,7 @@ template <int STEPS> __device__ inline PackedRow packed_row(const Args &a, const
     y.gq = j - pos * a.G;
     y.pos = pos < x.width ? pos : x.width - 1;
     y.from = window_entry(x, y.pos);
-    y.own = pos < x.width ? y.from : (unsigned)pos;
+    y.own = pos < x.width ? y.from : (unsigned)(pos < a.S ? pos : a.S - 1);
     return y;
 }
 
@@ -289,41 +350,21 @@ __device__ __attribute__((always_inline)) PackedBlock<STEPS> packed_block(const 
                                                                           unsigned &q_off, PackedRow &y, F len_of)
 {
     PackedBlock<STEPS> x;
-    x.r0 = r0;
-    int last = list.total - r0 < kBlockRows ? list.total - 1 : r0 + kBlockRows - 1;
-    int end = w.first + packed_run(a, w.len, list.align);
-    while (end <= r0) {
-        w.first = end;
-        ++w.b;
-        w.len = len_of(w.b);
-        end += packed_run(a, w.len, list.align);
-    }
-    x.b = w.b;
-    x.first = w.first;
-    x.wide = false;
     const int l = STEPS > 1 ? X.lane : X.c32;
     unsigned entry = l, entry2 = 64 + X.c32; // as if all were the first candidate's
-    int at = 0;         // window position of the walk's candidate's first
-    while (end <= last) {
-        if (w.b + 1 - x.b >= pa.span) {
-            last = end - 1;
-            x.wide = true;
-            break;
-        }
-        at += w.len;
-        w.first = end;
-        ++w.b;
-        w.len = len_of(w.b);
-        end += packed_run(a, w.len, list.align);
-        entry = l >= at ? (unsigned)((w.b - x.b) << 6 | (l - at)) : entry;
+    const BlockSpan sp = walk_block(a, w, r0, list.total, list.align, pa.span, X.cand0 + a.C, len_of, [&](int n, int at) __attribute__((always_inline)) {
+        entry = enter_window(entry, l, n, at);
         if (STEPS == 3)
-            entry2 = 64 + X.c32 >= at ? (unsigned)((w.b - x.b) << 6 | (64 + X.c32 - at)) : entry2;
-    }
-    x.rows = last - r0 + 1;
-    const int upto = __builtin_amdgcn_readfirstlane((int)fdiv(last - w.first, a.div_g)) + 1; // the last candidate's positions
-    const int more = upto < w.len ? upto : w.len;
-    x.width = at + more;
-    const unsigned end_entry = (unsigned)((w.b - x.b) << 6 | (more - 1));
+            entry2 = enter_window(entry2, 64 + X.c32, n, at);
+    });
+    x.r0 = r0;
+    x.rows = sp.last - r0 + 1;
+    x.b = sp.b;
+    x.first = sp.first;
+    x.width = sp.width;
+    x.wide = sp.wide;
+    const unsigned end1 = (unsigned)__builtin_amdgcn_readlane((int)entry, (sp.width - 1) & 63); // the last position's, whatever the walk ended at
+    const unsigned end_entry = STEPS == 3 && sp.width > 64 ? (unsigned)__builtin_amdgcn_readlane((int)entry2, (sp.width - 65) & 63) : end1;
     x.win = l < x.width ? entry : end_entry;
     x.win2 = STEPS == 3 && 64 + X.c32 < x.width ? entry2 : end_entry;
     y = packed_row(a, x, X.c32, list.align);

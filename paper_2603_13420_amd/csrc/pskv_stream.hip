@@ -537,8 +537,10 @@ void stream_packed_kernel(Args a, PackedArgs pa)
         for (;;) {
             z.len = clamp_len(a, z.len);
             const int sum = wave_scan(packed_run(a, z.len, list.align)), all = __builtin_amdgcn_readlane(sum, 63);
-            if (z.base + all > r0) {
-                const int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(z.base + sum <= r0));
+            const int left = a.C - 1 - z.cand < 63 ? a.C - 1 - z.cand : 63; // (the last candidate ends it, whatever the lengths say)
+            if (z.base + all > r0 || left < 63) {
+                int c = __builtin_popcountll(__builtin_amdgcn_ballot_w64(z.base + sum <= r0));
+                c = c < left ? c : left;
                 w.b = z.cand + c;
                 w.first = z.base + (c > 0 ? __builtin_amdgcn_readlane(sum, c > 0 ? c - 1 : 0) : 0);
                 w.len = __builtin_amdgcn_readlane(z.len, c);

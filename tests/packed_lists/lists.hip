@@ -37,3 +37,21 @@ extern "C" void packed_place(int C, int S, int Hq, int Hkv, int r0, int *b, int 
     const Walk w = walk_by_division(problem(C, S, Hq, Hkv), r0);
     *b = w.b, *first = w.first;
 }
+
+// One block: its first candidate, that one's first row, last row, window width and `wide`; the window's first 96 entries; and what the
+// walk is left at (in: what it begins at).
+extern "C" void packed_walk(int C, int S, int Hq, int Hkv, const int *len, int r0, int total, int align, int span, int (&walk)[3], int (&out)[5], unsigned (&window)[96])
+{
+    const Args a = problem(C, S, Hq, Hkv);
+    Walk w = {walk[0], walk[1], walk[2]};
+    for (int l = 0; l < 96; ++l)
+        window[l] = l;
+    const BlockSpan x = walk_block(a, w, r0, total, align, span, C, [&](int b) { return b < C ? len[b] : (__builtin_trap(), 0); }, [&](int n, int at) {
+        for (int l = 0; l < 96; ++l)
+            window[l] = enter_window(window[l], l, n, at);
+    });
+    for (int l = x.width; x.width > 0 && l < 96; ++l)
+        window[l] = window[(x.width - 1) % 96];
+    walk[0] = w.b, walk[1] = w.first, walk[2] = w.len;
+    out[0] = x.b, out[1] = x.first, out[2] = x.last, out[3] = x.width, out[4] = x.wide;
+}

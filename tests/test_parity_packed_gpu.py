@@ -6,6 +6,7 @@ import pytest
 
 from paper_2603_13420_amd import inputs as gen
 import parity_util as pu
+from test_packed_lists import lib as lists, packed  # noqa: F401 (lists is a fixture)
 from test_parity_own_blocks_gpu import check as check_guarded
 
 pytestmark = pytest.mark.gpu
@@ -123,6 +124,28 @@ def test_candidates_far_apart(pk, P):
     w = gen.custom_workload(f"packed_far_{P}", B, P, S, 0, S, 2, 1, 128, "bf16", index=3201)
     inp = gen.make_inputs(w, pad="nan")
     put_lengths(inp, [3] + [0] * 150 + [8] * 20 + [0] * 128 + [5])
+    check(pk, inp, q_batch_stride=(1 << 23) - 8)
+
+
+def alignment(lists, w, lens, streamed=False):
+    """(window steps, alignment) of the list that the kernel makes of these lengths on this card."""
+    import torch
+    cus, heads, G = torch.cuda.get_device_properties(0).multi_processor_count, getattr(w, "Np", 1) * w.Hkv, w.Hq // w.Hkv
+    C = w.B // getattr(w, "Np", 1)
+    wavefronts = 0 if streamed else 8 * min(cus // min(heads, cus), C * ((w.S * G + 31) // 32))
+    steps, _, align, _ = packed(lists, [int(x) for x in lens], w.S, w.Hq, w.Hkv, 3 if streamed else 2, w.P, wavefronts)
+    return steps, align
+
+
+@pytest.mark.parametrize("Hq,Hkv,P", [(32, 32, 100), (64, 32, 100), (96, 32, 50), (32, 32, 20)])
+def test_candidates_far_apart_in_one_block(pk, lists, Hq, Hkv, P):
+    # the same where blocks go across candidates in the resident kernels, dq among them: they end early, at an empty candidate
+    B, S = 330, 8
+    lens = [3] + [0] * 140 + [8] * 90 + [0] * 98 + [5]
+    w = gen.custom_workload(f"packed_far_{P}_{Hq}", B, P, S, 0, S, Hq, Hkv, 128, "bf16", index=3202 + Hq)
+    assert alignment(lists, w, lens)[1] == 1
+    inp = gen.make_inputs(w, pad="nan")
+    put_lengths(inp, lens)
     check(pk, inp, q_batch_stride=(1 << 23) - 8)
 
 
