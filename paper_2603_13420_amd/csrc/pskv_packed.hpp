@@ -491,8 +491,8 @@ __device__ inline void store_padding(const Args &a, const Ctx &X, int b, int len
         }
 }
 
-// The classic online softmax over a packed block whatever its rows and its prefix are: the block's rows and Q, and, after the
-// prefix, its window and the store.
+// The classic online softmax over a packed block whatever its rows and its prefix are: the block's rows and Q (w as in walk_block, and left
+// for the next block), and, after the prefix, its window and the store.
 template <int STEPS> struct GeneralBlock {
     PackedBlock<STEPS> x;
     PackedRow y;
@@ -502,7 +502,7 @@ template <int STEPS> struct GeneralBlock {
 };
 
 template <int STEPS>
-__device__ __attribute__((always_inline)) void packed_general_begin(const Args &a, const PackedArgs &pa, const Ctx &X, Walk w, int r0, const PackedList &list,
+__device__ __attribute__((always_inline)) void packed_general_begin(const Args &a, const PackedArgs &pa, const Ctx &X, Walk &w, int r0, const PackedList &list,
                                                                     GeneralBlock<STEPS> &g)
 {
     unsigned q_off;

@@ -565,14 +565,16 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
         // Rare: some row met scores far above its first tile's maximum, or a block's candidates lie far apart: whatever this
         // wavefront stored is replaced by the general path's result.  The same for an instruction whose prefix is too short for
         // the pipeline.
-        if (any_bad || !fits)
+        if (any_bad || !fits) {
+            w = begin;
             for (int b2 = blk_lo; b2 < blk_hi; ++b2) {
                 GeneralBlock<2> g;
-                packed_general_begin(a, pa, X, begin, b2 * kBlockRows, list, g);
+                packed_general_begin(a, pa, X, w, b2 * kBlockRows, list, g);
                 for (int kt = 0; kt < tiles; ++kt)
                     prefix_tile_classic(X, X.k_lane + kt * kTileBytes, X.v_lane + kt * kTileBytes, X.P - kt * kTileKeys, g.q, g.st);
                 packed_general_end(a, X, g);
             }
+        }
     } // virtual heads
 }
 

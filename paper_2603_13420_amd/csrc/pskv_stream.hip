@@ -552,6 +552,14 @@ void stream_packed_kernel(Args a, PackedArgs pa)
         }
     };
 
+    auto find = [&](RowSearch &z, int r0) __attribute__((always_inline)) {
+        if (!full)
+            return search_end(z, r0);
+        Walk w = walk_by_division(a, r0);
+        w.len = packed_len(a, w.b);
+        return w;
+    };
+
     // this thread's two requests for tile kt (kt <= the last tile), straight into slot kt % 8
     const TileSlot ts = make_tile_slot(tid);
     const unsigned row_bytes = (unsigned)a.kp_sp * 2u;
@@ -607,13 +615,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
         if (ps.active) {
             X.head = ps.head;
             const int r0 = ps.blk * kBlockRows;
-            Walk w;
-            if (full) {
-                w = walk_by_division(a, r0);
-                w.len = packed_len(a, w.b);
-            } else {
-                w = search_end(z, r0);
-            }
+            Walk w = find(z, r0);
             PackedRow row;
             nxt = packed_block<STEPS>(a, pa, fresh_lane(X), w, r0, list, q_off, row, [&](int b) {
                 return !full && b - z.cand < 64 ? __builtin_amdgcn_readlane(z.len, b - z.cand) : packed_len(a, b);
@@ -786,7 +788,8 @@ void stream_packed_kernel(Args a, PackedArgs pa)
             GeneralBlock<STEPS> g;
             const int r0 = ps.active ? ps.blk * kBlockRows : 0;
             z = search_begin(r0);
-            packed_general_begin(a, pa, X, full ? Walk{0, 0, packed_len(a, 0)} : search_end(z, r0), r0, list, g);
+            Walk w = find(z, r0);
+            packed_general_begin(a, pa, X, w, r0, list, g);
             uintx4 kv, vv;
             load_tile_chunks(a, X, ts, 0, kv, vv);
             __syncthreads(); // whatever the ring held has been used by every wavefront
