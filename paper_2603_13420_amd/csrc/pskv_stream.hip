@@ -604,7 +604,8 @@ void stream_packed_kernel(Args a, PackedArgs pa)
             request(t + 6);
     };
 
-    bool wg_bad = false;
+    unsigned long long bad_passes = 0; // bit n & 63: the workgroup's n-th pass has to be repeated
+    int turn = 0;                      // number of the pass that comes next
     int p = blockIdx.x;
     PackedPass ps = packed_pass(a, p, npasses, nblocks, waves, wave);
     PackedBlock<STEPS> nxt = {0, 1, 0, 0, 1, 0u, 0u, 0u, 1u, false};
@@ -628,6 +629,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
 
     while (p < npasses) {
         if (!ps.exists) {
+            ++turn;
             p += gridDim.x;
             ps = packed_pass(a, p, npasses, nblocks, waves, wave);
             z = search_begin(ps.active ? ps.blk * kBlockRows : 0);
@@ -771,18 +773,20 @@ void stream_packed_kernel(Args a, PackedArgs pa)
         if (X.lane == 0)
             *(lds_int *)X.scr = bad ? 1 : 0;
         __syncthreads(); // ends the pass: the ring is free, the verdicts are visible
-        wg_bad |= __builtin_amdgcn_ballot_w64(*(lds_int *)(smem + kRing * kSlotBytes + (X.lane & (kNW - 1)) * kScrBytes) !=
-                                              0) != 0;
+        if (__builtin_amdgcn_ballot_w64(*(lds_int *)(smem + kRing * kSlotBytes + (X.lane & (kNW - 1)) * kScrBytes) != 0))
+            bad_passes |= 1ull << (turn & 63);
+        ++turn;
     }
     while (pair < pairs)
         store_pair(pair_len());
 
-    // Rare: some row met scores far above its first tile's maximum, or a block's candidates lie far apart; whatever this
-    // workgroup stored is then replaced by the general path's result.
-    if (wg_bad)
-        for (int p2 = blockIdx.x; p2 < npasses; p2 += gridDim.x) {
+    // Rare: some row met scores far above its first tile's maximum, or a block's candidates lie far apart; what such a pass
+    // stored is then replaced by the general path's result.  (Only such passes: one candidate in need of it among 300 x 40
+    // positions, 40/40 heads, P 700: 320 us, all of a workgroup's passes 536, the general kernel 317.)
+    if (bad_passes)
+        for (int p2 = blockIdx.x, n = 0; p2 < npasses; p2 += gridDim.x, ++n) {
             ps = packed_pass(a, p2, npasses, nblocks, waves, wave);
-            if (!ps.exists)
+            if (!ps.exists || !(bad_passes >> (n & 63) & 1))
                 continue;
             set_vhead(a, X, ps.head);
             GeneralBlock<STEPS> g;

@@ -177,6 +177,19 @@ def test_rows_that_need_rescaling(pk, S, Hq, Hkv, P):
     check(pk, inp, backward=False)
 
 
+@pytest.mark.parametrize("S,lo", [(20, 20), (20, 3), (40, 30)])
+def test_some_passes_need_rescaling(pk, S, lo):
+    # several passes for a workgroup, of which few are repeated (values as above)
+    w = gen.custom_workload(f"packed_repeat_{S}_{lo}", 300, 300, S, lo, S, 24, 24, 128, "bf16", index=3450 + S + lo)
+    inp = gen.make_inputs(w, pad="nan")
+    inp.k_pre[290] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(inp.k_pre[290]) * 8)
+    for b in (0, 131, 299):
+        inp.q[b, :, ::5] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(inp.q[b, :, ::5]) * 8)
+    for x in (inp.v_pre, inp.v_suf):
+        x[...] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(x) * np.float32(0.25))
+    check(pk, inp, backward=False)
+
+
 @pytest.mark.parametrize("lens,S,Hq,Hkv,P", [
     ([38, 30, 30, 30], 40, 4, 4, 257),       # lengths whose rows, each filled up to whole blocks, are as many as B*S*G: not a full batch
     ([40, 32, 32, 32], 40, 4, 4, 300),
