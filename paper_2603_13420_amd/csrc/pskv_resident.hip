@@ -338,25 +338,47 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles, 
 // Small calls take a workgroup per block while there are compute units: a wavefront alone on its SIMD gets through a block in
 // little more than half the time (32 candidates of 20 positions, 32/8 heads, P 128: 11.2 us with eight blocks to a workgroup, 8.5 so; 12 before).
 // ------------------------------------------------------------------------------------------
+struct PackedLaunch {
+    Args a;
+    PackedArgs pa;
+    int per_vh, vh_slots, max_tiles;
+};
+
 // TILES: 1 or 2, the prefix has so many tiles; 3: three and more.  (An instruction whose own prefix has fewer goes the general way.)
+
 template <int STEPS, int TILES>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
-void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int max_tiles)
+void resident_packed_kernel(PackedLaunch launch)
 {
     extern __shared__ __align__(16) unsigned char smem_generic[];
     lds_u8 *smem = (lds_u8 *)smem_generic;
-    const int tid = threadIdx.x;
-    Ctx X = make_ctx(a, smem, max_tiles, tid);
-    const int VH = a.Np * a.Hkv;
-    auto kimg = [&](int t) { return X.k_lane + t * kTileBytes; };
-    auto vimg = [&](int t) { return X.v_lane + t * kTileBytes; };
-    const int wslot = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int slice = blockIdx.x / vh_slots;
-    const int per_chunk = (a.C + kLenChunks - 1) / kLenChunks, waves = per_vh * kNW, me = slice * kNW + wslot;
-    lds_int *const lens = (lds_int *)(smem + 2 * max_tiles * kTileBytes); // (in the scratch)
+    // The arguments and all that is made of them are taken anew for every virtual head, and for the general path once more: kept over the
+    // loops, 104 to 149 of them were spilled to lanes of vector registers, whose every use is a v_readlane (now 16 to 22, and 236 vector registers for 255;
+    // us, before and so: 1024 x 24, 32/8 heads, P 256: 138.2, 137.6; 512 x 20, 32/32, P 128: 74.5, 72.7; 512 x 16..32: 97.8, 94.6).
+    auto context = [&](const PackedLaunch &g, int vh) __attribute__((always_inline)) {
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));
+        Ctx Y = make_ctx(g.a, smem, g.max_tiles, t);
+        set_vhead(g.a, Y, vh);
+        return Y;
+    };
 
-    for (int vh = blockIdx.x % vh_slots; vh < VH; vh += vh_slots) {
+    const int VH = launch.a.Np * launch.a.Hkv, slots = launch.vh_slots;
+    for (int vh = __builtin_amdgcn_readfirstlane(blockIdx.x % slots); vh < VH; vh += slots) {
+        const PackedLaunch &launch = first_parameter<PackedLaunch>();
+        const Args &a = launch.a;
+        const PackedArgs &pa = launch.pa;
+        const int per_vh = launch.per_vh, max_tiles = launch.max_tiles;
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        Ctx X = make_ctx(a, smem, max_tiles, tid);
         set_vhead(a, X, vh);
+        auto kimg = [&](int t) { return X.k_lane + t * kTileBytes; };
+        auto vimg = [&](int t) { return X.v_lane + t * kTileBytes; };
+        const int wslot = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int slice = __builtin_amdgcn_readfirstlane(blockIdx.x / launch.vh_slots);
+        const int per_chunk = (a.C + kLenChunks - 1) / kLenChunks, waves = per_vh * kNW, me = slice * kNW + wslot;
+        lds_int *const lens = (lds_int *)(smem + 2 * max_tiles * kTileBytes); // (in the scratch)
         const int tiles = (X.P + kTileKeys - 1) / kTileKeys;
         const bool fits = TILES == 3 ? tiles >= 3 : tiles == TILES;
         const int T = TILES == 3 ? tiles : TILES; // (of a prefix that fits)
@@ -410,9 +432,10 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
         }
         __syncthreads();
         list = choose_list<STEPS>(a, pa, tiles, waves, per_chunk, lens);
+        const int nblocks = (list.total + kBlockRows - 1) / kBlockRows;
         {
             // Shares as in the kernel above: contiguous ranges, a quarter of the workgroup's per SIMD, 7/12 of that for the first of its two.
-            const int nblocks = (list.total + kBlockRows - 1) / kBlockRows, each = (int)fdiv(nblocks, pa.div_n), over = nblocks - each * per_vh;
+            const int each = (int)fdiv(nblocks, pa.div_n), over = nblocks - each * per_vh;
             const int wg_lo = slice * each + (slice < over ? slice : over), wg_n = each + (slice < over ? 1 : 0), simd = wslot & 3;
             const int part_lo = wg_lo + (wg_n * simd >> 2), part_hi = wg_lo + (wg_n * (simd + 1) >> 2);
             const int split = part_lo + ((part_hi - part_lo) * 7 + 6) / 12;
@@ -566,13 +589,15 @@ void resident_packed_kernel(Args a, PackedArgs pa, int per_vh, int vh_slots, int
         // wavefront stored is replaced by the general path's result.  The same for an instruction whose prefix is too short for
         // the pipeline.
         if (any_bad || !fits) {
+            const PackedLaunch &again = first_parameter<PackedLaunch>();
+            const Ctx Y = context(again, vh);
             w = begin;
             for (int b2 = blk_lo; b2 < blk_hi; ++b2) {
                 GeneralBlock<2> g;
-                packed_general_begin(a, pa, X, w, b2 * kBlockRows, list, g);
+                packed_general_begin(again.a, again.pa, Y, w, b2 * kBlockRows, list, g);
                 for (int kt = 0; kt < tiles; ++kt)
-                    prefix_tile_classic(X, X.k_lane + kt * kTileBytes, X.v_lane + kt * kTileBytes, X.P - kt * kTileKeys, g.q, g.st);
-                packed_general_end(a, X, g);
+                    prefix_tile_classic(Y, Y.k_lane + kt * kTileBytes, Y.v_lane + kt * kTileBytes, Y.P - kt * kTileKeys, g.q, g.st);
+                packed_general_end(again.a, Y, g);
             }
         }
     } // virtual heads
@@ -640,7 +665,7 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
                                        : (two ? resident_packed_kernel<2, 3> : resident_packed_kernel<1, 3>);
         return launch_kernel(kernel,
                              dim3((unsigned)(packed.per_vh * packed.vh_slots)), dim3(kNW * 64), (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes,
-                             stream, a, pa, (int)packed.per_vh, (int)packed.vh_slots, max_tiles);
+                             stream, PackedLaunch{a, pa, (int)packed.per_vh, (int)packed.vh_slots, max_tiles});
     }
     // One workgroup per compute unit.
     const ResidentSplit split = resident_split(a, pipelined ? own : stacked, kNW, num_cu);
