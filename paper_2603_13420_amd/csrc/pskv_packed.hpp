@@ -20,6 +20,7 @@ struct PackedArgs {
     bool dense;     // windows of align 1 fit the kernel's
     FastDiv div_n;  // division by the number of workgroups that share a list
     FastDiv div_w;  // ... of wavefronts
+    FastDiv div_run; // by the rows of a full candidate, filled up to whole blocks
 };
 
 // False: a stride is too long for the 24-bit multiplications of the offsets (16 MB), or a candidate for 32-bit ones.
@@ -40,6 +41,7 @@ inline bool packed_args(const Args &a, unsigned sharers, int waves, PackedArgs &
     const long long one = 0x7fffffffLL / 2, span = one / sb; // what block_offsets_fit grants one candidate, elements
     x.span = (int)(span < 1 << 20 ? span : 1 << 20); // (a window entry has 26 bits for it)
     x.div_n = make_fastdiv(sharers);
+    x.div_run = make_fastdiv((unsigned)((a.S * a.G + 31) & -32));
     x.div_w = make_fastdiv(sharers * (unsigned)waves);
     return true;
 }
@@ -86,24 +88,6 @@ template <int STEPS> __host__ __device__ inline int packed_align(const Args &a, 
     return one ? 1 : kBlockRows;
 }
 
-// Whether a row's candidate is a division by S*G away: every candidate has S*G rows in the list.  Across candidates the sum says so, no
-// candidate having more.  Inside them it says so where S*G is a multiple of 32; where it is not, a run may be longer than S*G, and the
-// sum of long and short ones can be the same (runs of 64, 32, 32 and 32 rows, S 40).
-__host__ __device__ inline bool packed_by_division(const Args &a, int total, int align)
-{
-    return total == a.C * a.S * a.G && (align == 1 || a.S * a.G % kBlockRows == 0);
-}
-
-// The candidate (of one instruction's) of row r0, found so; its length is left to be filled in.
-__host__ __device__ inline Walk walk_by_division(const Args &a, int r0)
-{
-    Walk w;
-    w.b = (int)fdiv(fdiv(r0, a.div_g), a.div_s);
-    w.first = w.b * a.S * a.G;
-    w.len = 0;
-    return w;
-}
-
 __host__ __device__ inline int same_in_all_lanes(int x)
 {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -111,6 +95,20 @@ __host__ __device__ inline int same_in_all_lanes(int x)
 #else
     return x;
 #endif
+}
+
+// Whether every run of the list is a full candidate's, so that a row's candidate is a division away.  No run is longer, so the sum says so.
+// (Rows in all are not enough: with each candidate on blocks of its own, runs of 64, 32, 32 and 32 rows are as many as four candidates' 40.)
+__host__ __device__ inline bool packed_even(const Args &a, int total, int align) { return total == a.C * packed_run(a, a.S, align); }
+
+// The candidate (of one instruction's) of row r0 of such a list; its length is left to be filled in.  div_run: by a full candidate's run of whole blocks.
+__host__ __device__ inline Walk walk_even(const Args &a, FastDiv div_run, int align, int r0)
+{
+    Walk w;
+    w.b = same_in_all_lanes((int)(align == 1 ? fdiv(fdiv(r0, a.div_g), a.div_s) : fdiv(r0, div_run)));
+    w.first = w.b * packed_run(a, a.S, align);
+    w.len = 0;
+    return w;
 }
 
 // The candidates of a block's rows.
@@ -197,6 +195,7 @@ static_assert(kListInts * 4 <= kNW * kScrBytes, "the list's tables stand in the 
 
 struct PackedList {
     int total, align; // rows
+    bool even, full;  // every run is a full candidate's; nothing is padded
     int per_chunk;
     lds_int *lens;    // first, second, ... lengths of the chunks (of the last round), then rows of a wavefront's chunks up to and with each, for align 1 and for 32, and the wavefronts' rows
 };
@@ -259,6 +258,8 @@ __device__ inline PackedList choose_list(const Args &a, const PackedArgs &pa, in
     PackedList x;
     x.align = packed_align<STEPS>(a, pa.dense, tiles, waves, total, total32);
     x.total = x.align == 1 ? total : total32;
+    x.even = packed_even(a, x.total, x.align);
+    x.full = total == a.C * a.S * a.G;
     x.per_chunk = per_chunk;
     x.lens = lens;
     return x;

@@ -385,17 +385,26 @@ void resident_packed_kernel(PackedLaunch launch)
         __syncthreads(); // every wavefront is done with the images and the scratch of the virtual head before
 
         PackedList list;
-        int blk = 0, blk_lo = 0, blk_hi = 0;
+        int blk = 0, blk_lo = 0, blk_hi = 0, step = 1; // this wavefront's blocks: from blk_lo, every step-th
         Walk w, begin;
         PackedBlock<STEPS> nxt = {0, 1, X.cand0, 0, 1, 0u, 0u, 0u, 1u, false};
         unsigned q_off = (unsigned)(X.head * a.G) * pa.q_sh;
         uintx4 q[8]; // this block's Q fragments until their last use, then the next block's
         bool any_bad = false;
+        // A block's place in an even list.
+        auto place = [&](int n) __attribute__((always_inline)) {
+            Walk y = walk_even(a, pa.div_run, list.align, n * kBlockRows);
+            y.b += X.cand0;
+            y.len = list.full ? a.S : packed_len(a, y.b);
+            return y;
+        };
         // Moves on to the next block whose candidates lie close enough together; w and nxt stay where they are past the last one.
         auto advance = [&](int n) __attribute__((always_inline)) {
-            for (; n < blk_hi; ++n) {
+            for (; n < blk_hi; n += step) {
+                if (step > 1)
+                    w = place(n);
                 PackedRow row;
-                nxt = packed_block<STEPS>(a, pa, fresh_lane(X), w, n * kBlockRows, list, q_off, row);
+                nxt = packed_block<STEPS>(a, pa, X, w, n * kBlockRows, list, q_off, row);
                 if (!nxt.wide)
                     break;
                 any_bad = true;
@@ -434,14 +443,24 @@ void resident_packed_kernel(PackedLaunch launch)
         list = choose_list<STEPS>(a, pa, tiles, waves, per_chunk, lens);
         const int nblocks = (list.total + kBlockRows - 1) / kBlockRows;
         {
-            // Shares as in the kernel above: contiguous ranges, a quarter of the workgroup's per SIMD, 7/12 of that for the first of its two.
+            // Contiguous ranges, a quarter of the workgroup's per SIMD, 7/12 of that for the first of its two as in the kernel above, or half where
+            // rounding makes that 5 of 8 or 4 of 6 and grouped heads share a candidate's keys (us, 7/12 and half, nothing padded, P 128, 32/8: 256 x 32: 46.9,
+            // 42.9; 256 x 24: 37.9, 35.5; 512 x 20: 51.2, 49.5; 32/32: 256 x 24: 48.3, 50.8; 1500 x 24: 254, 263).
             const int each = (int)fdiv(nblocks, pa.div_n), over = nblocks - each * per_vh;
             const int wg_lo = slice * each + (slice < over ? slice : over), wg_n = each + (slice < over ? 1 : 0), simd = wslot & 3;
-            const int part_lo = wg_lo + (wg_n * simd >> 2), part_hi = wg_lo + (wg_n * (simd + 1) >> 2);
-            const int split = part_lo + ((part_hi - part_lo) * 7 + 6) / 12;
+            const int part_lo = wg_lo + (wg_n * simd >> 2), part_hi = wg_lo + (wg_n * (simd + 1) >> 2), part = part_hi - part_lo;
+            const int split = part_lo + (a.G > 1 && part <= 16 ? (part + 1) >> 1 : (part * 7 + 6) / 12);
             blk_lo = wslot < 4 ? part_lo : split, blk_hi = wslot < 4 ? split : part_hi;
+            // In turn, neighbouring blocks to neighbouring wavefronts, where places are a division away and bytes bound the call: one block per
+            // candidate and key head, or full windows, or a short prefix (us, ranges and in turn: 32/32: 512 x 20, P 128: 72.8, 69.7; 1500 x 24, P 32: 249, 239; 1500 x
+            // 32, P 32: 326, 311; 1500 x 22..32: 291, 277; 32/8: 1500 x 28, P 32: 179, 166; 1500 x 24, P 200, not so: 181, 185).
+            if (list.even && list.align > 1 && (a.G == 1 || a.S == kTileKeys || TILES < 3)) {
+                step = waves;
+                blk_lo = me;
+                blk_hi = nblocks;
+            }
             if (blk_lo < blk_hi)
-                begin = w = find_row(a, list, X.cand0, blk_lo * kBlockRows, fresh & 63);
+                begin = w = list.even ? place(blk_lo) : find_row(a, list, X.cand0, blk_lo * kBlockRows, fresh & 63);
             blk = !fits ? blk_hi : advance(blk_lo);
             load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
         }
@@ -466,16 +485,16 @@ void resident_packed_kernel(PackedLaunch launch)
 
         // Padding: the instruction's candidates are dealt out over the wavefronts, and their rows past their lengths stored a
         // few candidates per block.
-        int pad = me;
+        int pad = list.full ? a.C : me;
         int shares = (int)fdiv(a.C + waves - 1, pa.div_w);
         asm volatile("" : "+s"(shares));
-        const int pads = waves * __builtin_amdgcn_readfirstlane((int)((float)shares * __builtin_amdgcn_rcpf((float)(blk_hi > blk ? blk_hi - blk : 1))) + 1);
+        const int pads = waves * __builtin_amdgcn_readfirstlane((int)((float)(shares * step) * __builtin_amdgcn_rcpf((float)(blk_hi > blk ? blk_hi - blk : 1))) + 1);
 
         while (blk < blk_hi) {
             const PackedBlock<STEPS> x = nxt;
             // Loads are retired in issue order, so what is needed last is requested first.
             uintx4 skf[8], svf[2][4];
-            load_window_k(pa, fresh_lane(X), x, 0, skf);
+            load_window_k(pa, X, x, 0, skf);
 
             // ---- first prefix tile: scores, reference maximum ----
             floatx16 sA, sB; // raw scores of the current and of the next tile, roles alternating
@@ -543,7 +562,7 @@ void resident_packed_kernel(PackedLaunch launch)
             }
             if (TILES > 1)
                 hide_past_prefix();
-            load_window_v(pa, fresh_lane(X), x, 0, svf); // one step ahead of its use
+            load_window_v(pa, X, x, 0, svf); // one step ahead of its use
             lds_u8 *const v_last = added_here(X.v_lane, (T - 1) * kTileBytes);
             // ---- last prefix tile: the "next scores" are the window's first ones, from the K registers ----
             pipe_tile<true, true, (TILES > 1), (TILES == 2), 0, false, true>(kimg(0), skf, TILES == 3 ? added_here(X.v_lane, (T - 2) * kTileBytes) : X.v_lane, kimg(0),
@@ -553,34 +572,34 @@ void resident_packed_kernel(PackedLaunch launch)
             // (Requested unconditionally, past the end for the last block once more.)
             const bool more = STEPS > 1 && x.width > kTileKeys;
             if (!more) {
-                blk = advance(blk + 1);
-                load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
+                blk = advance(blk + step);
+                load_q_packed(a, pa, X, nxt.b, q_off, q);
             }
 
             // ---- first window step: mask and weights under the value product of the last prefix
             //      tile; then its own value product through the scratch tile ----
             pipe_tile<false, false, true, (TILES == 1), 2, false, false>(kimg(0), skf, v_last, kimg(0), vimg(0), pre, q, sB, sB,
-                                                                  X.c, m, sees_bits(x, 0, fresh_lane(X).h), l, pA, pB, o);
-            const Ctx Y = fresh_lane(X);
+                                                                  X.c, m, sees_bits(x, 0, X.h), l, pA, pB, o);
+            const Ctx Y = X;
             if (more)
                 load_window_k(pa, Y, x, kTileKeys, skf);
             pv_from_scratch(Y, svf[0], as_bf16x8(pB[0]), o);
             pv_from_scratch(Y, svf[1], as_bf16x8(pB[1]), o);
             if (more) {
-                load_window_v(pa, fresh_lane(X), x, kTileKeys, svf);
+                load_window_v(pa, X, x, kTileKeys, svf);
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
                     sB[e] = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < 8; ++ks)
                     sB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(skf[ks]), as_bf16x8(q[ks]), sB, 0, 0, 0);
-                blk = advance(blk + 1);
-                load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
+                blk = advance(blk + step);
+                load_q_packed(a, pa, X, nxt.b, q_off, q);
                 window_step_fixed(Y, sees_bits(x, kTileKeys, Y.h), sB, m, l, svf, o);
             }
 
             any_bad |= __builtin_amdgcn_ballot_w64(!(l < kBig)) != 0;
-            store_packed(a, pa, fresh_lane(X), x, list.align, m, l, o);
+            store_packed(a, pa, STEPS == 1 || TILES == 1 ? X : fresh_lane(X), x, list.align, m, l, o);
         }
         for (; pad < a.C; pad += waves)
             store_padding(a, fresh_lane(X), X.cand0 + pad, packed_len(a, X.cand0 + pad), list.align, a.out, pa.o_sb, pa.o_ss, pa.o_sh, a.lse);
@@ -592,7 +611,7 @@ void resident_packed_kernel(PackedLaunch launch)
             const PackedLaunch &again = first_parameter<PackedLaunch>();
             const Ctx Y = context(again, vh);
             w = begin;
-            for (int b2 = blk_lo; b2 < blk_hi; ++b2) {
+            for (int b2 = blk_lo; b2 < blk_hi; b2 += step) {
                 GeneralBlock<2> g;
                 packed_general_begin(again.a, again.pa, Y, w, b2 * kBlockRows, list, g);
                 for (int kt = 0; kt < tiles; ++kt)

@@ -490,7 +490,6 @@ void stream_packed_kernel(Args a, PackedArgs pa)
         upto = rows_upto(list, tid & 63);
         __syncthreads();
     }
-    const bool full = packed_by_division(a, list.total, list.align);
     const int nblocks = (list.total + kBlockRows - 1) / kBlockRows;
     int waves = kNW; // blocks of a pass
     while (waves > 1 && (long long)a.Hkv * ((nblocks + waves / 2 - 1) / (waves / 2)) <= gridDim.x)
@@ -500,7 +499,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
 
     // Padding: every pair of a KV head and a candidate belongs to one wavefront, which stores some at the end of each pass.
     const int all_waves = gridDim.x * kNW, pairs = a.Hkv * a.C;
-    int pair = list.total == a.C * packed_run(a, a.S, list.align) ? pairs : blockIdx.x * kNW + wave, pair_head = pair / a.C, pair_cand = pair - pair_head * a.C;
+    int pair = list.even ? pairs : blockIdx.x * kNW + wave, pair_head = pair / a.C, pair_cand = pair - pair_head * a.C;
     const int step_head = all_waves / a.C, step_cand = all_waves - step_head * a.C;
     const int shares = (pairs + all_waves - 1) / all_waves, passes = (npasses + (int)gridDim.x - 1) / (int)gridDim.x;
     const int each = __builtin_amdgcn_readfirstlane(shares / (passes > 0 ? passes : 1)) + 1;
@@ -524,7 +523,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
     };
     auto search_begin = [&](int r0) __attribute__((always_inline)) {
         RowSearch z = {0, 0, 0};
-        if (full)
+        if (list.even)
             return z;
         const int g = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= r0));
         z.base = g > 0 ? __builtin_amdgcn_readlane(upto, g > 0 ? g - 1 : 0) : 0;
@@ -553,9 +552,9 @@ void stream_packed_kernel(Args a, PackedArgs pa)
     };
 
     auto find = [&](RowSearch &z, int r0) __attribute__((always_inline)) {
-        if (!full)
+        if (!list.even)
             return search_end(z, r0);
-        Walk w = walk_by_division(a, r0);
+        Walk w = walk_even(a, pa.div_run, list.align, r0);
         w.len = packed_len(a, w.b);
         return w;
     };
@@ -619,7 +618,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
             Walk w = find(z, r0);
             PackedRow row;
             nxt = packed_block<STEPS>(a, pa, fresh_lane(X), w, r0, list, q_off, row, [&](int b) {
-                return !full && b - z.cand < 64 ? __builtin_amdgcn_readlane(z.len, b - z.cand) : packed_len(a, b);
+                return !list.even && b - z.cand < 64 ? __builtin_amdgcn_readlane(z.len, b - z.cand) : packed_len(a, b);
             });
         }
         load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);

@@ -12,7 +12,7 @@ static Args problem(int C, int S, int Hq, int Hkv)
 }
 
 // The list's rows and alignment, as a kernel with room for `most` window steps and `waves` wavefronts to a list chooses it
-// (choose_list), and whether candidates are found by division; returns the window steps.
+// (choose_list), and whether every run is a full candidate's; returns the window steps.
 extern "C" int packed_list(int C, int S, int Hq, int Hkv, const int *len, int most, int tiles, int waves, int *total_out, int *align_out, int *division)
 {
     const Args a = problem(C, S, Hq, Hkv);
@@ -28,13 +28,15 @@ extern "C" int packed_list(int C, int S, int Hq, int Hkv, const int *len, int mo
                                    : packed_align<3>(a, dense, tiles, waves, total, total32);
     *total_out = align == 1 ? total : total32;
     *align_out = align;
-    *division = packed_by_division(a, *total_out, align);
+    *division = packed_even(a, *total_out, align);
     return steps;
 }
 
-extern "C" void packed_place(int C, int S, int Hq, int Hkv, int r0, int *b, int *first)
+// The candidate of row r0 of a list whose runs are all full candidates', and that one's first row.
+extern "C" void packed_place(int C, int S, int Hq, int Hkv, int align, int r0, int *b, int *first)
 {
-    const Walk w = walk_by_division(problem(C, S, Hq, Hkv), r0);
+    const Args a = problem(C, S, Hq, Hkv);
+    const Walk w = walk_even(a, make_fastdiv((unsigned)packed_run(a, S, kBlockRows)), align, r0);
     *b = w.b, *first = w.first;
 }
 

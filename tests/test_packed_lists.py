@@ -23,7 +23,7 @@ def lib(tmp_path_factory):
 
 
 def packed(lib, lens, S, Hq, Hkv, most, P, waves):
-    """(window steps, rows, alignment, whether candidates are found by division) of the list of these lengths."""
+    """(window steps, rows, alignment, whether every run is a full candidate's) of the list of these lengths."""
     out = [ctypes.c_int() for _ in range(3)]
     arr = (ctypes.c_int * len(lens))(*lens)
     steps = lib.packed_list(len(lens), S, Hq, Hkv, arr, most, (P + 31) // 32, waves, *map(ctypes.byref, out))
@@ -58,11 +58,10 @@ def lengths(rng, kind, B, S):
     ([59, 59, 41, 59, 55, 57, 60, 48], 60, 4, 2, 300),
 ])
 def test_mixed_lengths_that_add_up_like_full_ones(lib, lens, S, Hq, Hkv, P):
-    G, most = Hq // Hkv, 3
-    _, total, align, division = packed(lib, lens, S, Hq, Hkv, most, P, 0)
-    rows = rows_of(lens, G, align)
-    assert total == len(rows)
-    assert not division or all(rows[r] == (r // (S * G), r // (S * G) * S * G) for r in range(total))
+    G = Hq // Hkv
+    _, total, align, even = packed(lib, lens, S, Hq, Hkv, 3, P, 0)
+    assert (total, align, even) == (len(lens) * S * G, BLOCK, 0)
+    assert total == len(rows_of(lens, G, align))
 
 
 @pytest.mark.parametrize("kind", ["uniform", "two", "full", "holes"])
@@ -74,13 +73,13 @@ def test_candidates_found_by_division(lib, kind, Hq, Hkv):
         B, S, P = int(rng.integers(1, 40)), int(rng.integers(1, 65)), int(rng.integers(65, 1100))
         lens = [int(x) for x in lengths(rng, kind, B, S)]
         for most, waves in ((3, 0), (2, 8)):
-            _, total, align, division = packed(lib, lens, S, Hq, Hkv, most, P, waves)
+            _, total, align, even = packed(lib, lens, S, Hq, Hkv, most, P, waves)
             rows = rows_of(lens, G, align)
             assert total == len(rows)
-            if division:
+            if even:
                 found += 1
                 for r0 in range(0, total, BLOCK):
-                    lib.packed_place(B, S, Hq, Hkv, r0, ctypes.byref(b), ctypes.byref(first))
+                    lib.packed_place(B, S, Hq, Hkv, align, r0, ctypes.byref(b), ctypes.byref(first))
                     assert (b.value, first.value) == rows[r0], (lens, S, G, P, align, r0)
     assert found or kind != "full"
 
