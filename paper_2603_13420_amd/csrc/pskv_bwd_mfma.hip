@@ -680,26 +680,38 @@ void bwd_dq_resident_kernel(BwdArgs g, int nb, FastDiv div_nb, int per_vh, int v
 // ranges of blocks that differ by one at most, and its prefix straight into LDS.  Ranges next to each other belong to different
 // workgroups: handing a workgroup eight neighbouring ones cost 2 % over 74 calls, 7 % where a wavefront has a few blocks.
 // ------------------------------------------------------------------------------------------
+struct DqPacked {
+    BwdArgs g;
+    PackedArgs pa;
+    int per_vh, vh_slots, max_tiles;
+};
+
 template <int STEPS>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
-void bwd_dq_packed_kernel(BwdArgs g, PackedArgs pa, int per_vh, int vh_slots, int max_tiles)
+void bwd_dq_packed_kernel(DqPacked call)
 {
-    const Args &a = g.f;
     extern __shared__ __align__(256) unsigned char smem_generic[];
     lds_u8 *smem = (lds_u8 *)smem_generic;
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    Ctx X;
-    X.lane = tid & 63;
-    X.h = X.lane >> 5;
-    X.c32 = X.lane & 31;
-    X.c = a.scale * kLog2e;
-    X.scr = smem + 2 * max_tiles * kTileBytes + wave * kScrBytes;
-    const HalfPlaces hp = half_places(X.lane);
-    const int VH = a.Np * a.Hkv, slice = blockIdx.x / vh_slots, per_chunk = (a.C + kLenChunks - 1) / kLenChunks;
-    const int waves = per_vh * kNW, me = wave * per_vh + slice;
-    lds_int *const lens = (lds_int *)(smem + 2 * max_tiles * kTileBytes); // (in the scratch)
-    for (int vh = blockIdx.x % vh_slots; vh < VH; vh += vh_slots) {
+    const int VH = call.g.f.Np * call.g.f.Hkv, slots = call.vh_slots;
+    for (int vh = __builtin_amdgcn_readfirstlane(blockIdx.x % slots); vh < VH; vh += slots) {
+        const DqPacked &call = first_parameter<DqPacked>(); // (read again, as in the forward kernel)
+        const BwdArgs &g = call.g;
+        const Args &a = g.f;
+        const PackedArgs &pa = call.pa;
+        const int per_vh = call.per_vh, max_tiles = call.max_tiles;
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        Ctx X;
+        X.lane = tid & 63;
+        X.h = X.lane >> 5;
+        X.c32 = X.lane & 31;
+        X.c = a.scale * kLog2e;
+        X.scr = smem + 2 * max_tiles * kTileBytes + wave * kScrBytes;
+        const HalfPlaces hp = half_places(X.lane);
+        const int slice = __builtin_amdgcn_readfirstlane(blockIdx.x / call.vh_slots), per_chunk = (a.C + kLenChunks - 1) / kLenChunks;
+        const int waves = per_vh * kNW, me = wave * per_vh + slice;
+        lds_int *const lens = (lds_int *)(smem + 2 * max_tiles * kTileBytes); // (in the scratch)
         set_vhead(a, X, vh);
         const int T = (X.P + kTileKeys - 1) / kTileKeys;
         __syncthreads(); // every wavefront is done with the images and the scratch of the virtual head before
@@ -1450,7 +1462,7 @@ hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream)
         const bool two = packed_steps(a, 2, pa.dense) > 1;
         return launch_kernel(two ? bwd_dq_packed_kernel<2> : bwd_dq_packed_kernel<1>,
                              dim3((unsigned)(packed.per_vh * packed.vh_slots)), dim3(kNW * 64), (size_t)2 * max_tiles * kTileBytes + kNW * kScrBytes,
-                             stream, g, pa, (int)packed.per_vh, (int)packed.vh_slots, max_tiles);
+                             stream, DqPacked{g, pa, (int)packed.per_vh, (int)packed.vh_slots, max_tiles});
     }
     // Passes of four blocks of one candidate, where they come out full: at less than four blocks in five the
     // wavefronts without one cost more than sharing the tiles saves (five blocks in two passes, 40 positions x

@@ -456,10 +456,17 @@ struct RowSearch {
     int len;        // lane j: length of candidate cand + j (0 past the last one)
 };
 
+struct StreamPacked {
+    Args a;
+    PackedArgs pa;
+};
+
 template <int STEPS>
 __global__ __attribute__((amdgpu_flat_work_group_size(512, 512), amdgpu_waves_per_eu(2, 2)))
-void stream_packed_kernel(Args a, PackedArgs pa)
+void stream_packed_kernel(StreamPacked call)
 {
+    const Args &a = call.a;
+    const PackedArgs &pa = call.pa;
     extern __shared__ __align__(16) unsigned char smem_generic[];
     lds_u8 *smem = (lds_u8 *)smem_generic;
     const int tid = threadIdx.x;
@@ -503,8 +510,8 @@ void stream_packed_kernel(Args a, PackedArgs pa)
     const int step_head = all_waves / a.C, step_cand = all_waves - step_head * a.C;
     const int shares = (pairs + all_waves - 1) / all_waves, passes = (npasses + (int)gridDim.x - 1) / (int)gridDim.x;
     const int each = __builtin_amdgcn_readfirstlane(shares / (passes > 0 ? passes : 1)) + 1;
-    auto pair_len = [&]() { return pair < pairs ? packed_len(a, pair_cand) : 0; };
-    auto store_pair = [&](int len) __attribute__((always_inline)) {
+    auto pair_len = [&](const Args &a) { return pair < pairs ? packed_len(a, pair_cand) : 0; };
+    auto store_pair = [&](const Args &a, const PackedArgs &pa, int len) __attribute__((always_inline)) {
         Ctx Y = fresh_lane(X);
         Y.head = pair_head;
         store_padding(a, Y, pair_cand, len, list.align, a.out, pa.o_sb, pa.o_ss, pa.o_sh, a.lse);
@@ -517,21 +524,21 @@ void stream_packed_kernel(Args a, PackedArgs pa)
         }
     };
 
-    auto lengths_from = [&](int cand) __attribute__((always_inline)) {
+    auto lengths_from = [&](const Args &a, int cand) __attribute__((always_inline)) {
         const int c = cand + fresh_lane(X).lane, len = a.len[c < a.C ? c : a.C - 1];
         return c < a.C ? len : 0;
     };
-    auto search_begin = [&](int r0) __attribute__((always_inline)) {
+    auto search_begin = [&](const Args &a, int r0) __attribute__((always_inline)) {
         RowSearch z = {0, 0, 0};
         if (list.even)
             return z;
         const int g = __builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= r0));
         z.base = g > 0 ? __builtin_amdgcn_readlane(upto, g > 0 ? g - 1 : 0) : 0;
         z.cand = __builtin_amdgcn_readfirstlane(g * kLenPerLane * per_chunk);
-        z.len = lengths_from(z.cand);
+        z.len = lengths_from(a, z.cand);
         return z;
     };
-    auto search_end = [&](RowSearch &z, int r0) __attribute__((always_inline)) {
+    auto search_end = [&](const Args &a, RowSearch &z, int r0) __attribute__((always_inline)) {
         Walk w;
         for (;;) {
             z.len = clamp_len(a, z.len);
@@ -547,13 +554,13 @@ void stream_packed_kernel(Args a, PackedArgs pa)
             }
             z.base += all; // (64 at a time: 4096 candidates and more)
             z.cand += 64;
-            z.len = lengths_from(z.cand);
+            z.len = lengths_from(a, z.cand);
         }
     };
 
-    auto find = [&](RowSearch &z, int r0) __attribute__((always_inline)) {
+    auto find = [&](const Args &a, const PackedArgs &pa, RowSearch &z, int r0) __attribute__((always_inline)) {
         if (!list.even)
-            return search_end(z, r0);
+            return search_end(a, z, r0);
         Walk w = walk_even(a, pa.div_run, list.align, r0);
         w.len = packed_len(a, w.b);
         return w;
@@ -611,11 +618,11 @@ void stream_packed_kernel(Args a, PackedArgs pa)
     unsigned q_off = 0;
     uintx4 q[8]; // this pass's Q fragments until their last use, then the next pass's
     // The next pass's block: its place in the list (z: where to look), its rows and Q.
-    auto take_block = [&](RowSearch z) __attribute__((always_inline)) {
+    auto take_block = [&](const Args &a, const PackedArgs &pa, RowSearch z) __attribute__((always_inline)) {
         if (ps.active) {
             X.head = ps.head;
             const int r0 = ps.blk * kBlockRows;
-            Walk w = find(z, r0);
+            Walk w = find(a, pa, z, r0);
             PackedRow row;
             nxt = packed_block<STEPS>(a, pa, fresh_lane(X), w, r0, list, q_off, row, [&](int b) {
                 return !list.even && b - z.cand < 64 ? __builtin_amdgcn_readlane(z.len, b - z.cand) : packed_len(a, b);
@@ -623,30 +630,34 @@ void stream_packed_kernel(Args a, PackedArgs pa)
         }
         load_q_packed(a, pa, fresh_lane(X), nxt.b, q_off, q);
     };
-    RowSearch z = search_begin(ps.active ? ps.blk * kBlockRows : 0);
-    take_block(z);
+    RowSearch z = search_begin(a, ps.active ? ps.blk * kBlockRows : 0);
+    take_block(a, pa, z);
 
     while (p < npasses) {
+        // (the arguments are read again for every pass: kept over the passes, hundreds of scalars would be spilled to vector registers' lanes)
+        const StreamPacked &call = first_parameter<StreamPacked>();
+        const Args &a = call.a;
+        const PackedArgs &pa = call.pa;
         if (!ps.exists) {
             ++turn;
             p += gridDim.x;
             ps = packed_pass(a, p, npasses, nblocks, waves, wave);
-            z = search_begin(ps.active ? ps.blk * kBlockRows : 0);
-            take_block(z);
+            z = search_begin(a, ps.active ? ps.blk * kBlockRows : 0);
+            take_block(a, pa, z);
             continue;
         }
         set_vhead(a, X, ps.head);
         bool bad = false;
         const bool active = ps.active;
-        const int pad_len = pair_len(); // (asked for here: waited for together with the tiles)
+        const int pad_len = pair_len(a); // (asked for here: waited for together with the tiles)
         pass_top();
         if (!active) { // only staging
             for (int t = 2; t + 1 <= T - 2; t += 2)
                 pair_top(t);
             p += gridDim.x;
             ps = packed_pass(a, p, npasses, nblocks, waves, wave);
-            z = search_begin(ps.active ? ps.blk * kBlockRows : 0);
-            take_block(z);
+            z = search_begin(a, ps.active ? ps.blk * kBlockRows : 0);
+            take_block(a, pa, z);
         } else {
             const PackedBlock<STEPS> x = nxt;
 
@@ -698,7 +709,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
                 pair_top(t);
             p += gridDim.x;
             ps = packed_pass(a, p, npasses, nblocks, waves, wave);
-            z = search_begin(ps.active ? ps.blk * kBlockRows : 0);
+            z = search_begin(a, ps.active ? ps.blk * kBlockRows : 0);
             load_window_k(pa, fresh_lane(X), x, 0, skf);
             if (last_pair) {
                 PSKV_STEP_PAIR(t);
@@ -729,7 +740,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
             const int head = X.head; // (of this pass)
             const bool more = STEPS > 1 && x.width > kTileKeys;
             if (!more)
-                take_block(z);
+                take_block(a, pa, z);
 
             // ---- first window step: mask and weights under the value product of the last prefix
             //      tile; then its own value product through the scratch tile ----
@@ -756,7 +767,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
                     if (!again)
                         break;
                 }
-                take_block(z);
+                take_block(a, pa, z);
             }
 
             bad = x.wide || __builtin_amdgcn_ballot_w64(!(l < kBig)) != 0;
@@ -765,9 +776,9 @@ void stream_packed_kernel(Args a, PackedArgs pa)
             store_packed(a, pa, W, x, list.align, m, l, o);
         }
         if (pair < pairs)
-            store_pair(pad_len);
+            store_pair(a, pa, pad_len);
         for (int n = 1; n < each && pair < pairs; ++n)
-            store_pair(pair_len());
+            store_pair(a, pa, pair_len(a));
         // the wavefront's verdict goes into the first word of its own scratch tile
         if (X.lane == 0)
             *(lds_int *)X.scr = bad ? 1 : 0;
@@ -777,12 +788,15 @@ void stream_packed_kernel(Args a, PackedArgs pa)
         ++turn;
     }
     while (pair < pairs)
-        store_pair(pair_len());
+        store_pair(a, pa, pair_len(a));
 
     // Rare: some row met scores far above its first tile's maximum, or a block's candidates lie far apart; what such a pass
     // stored is then replaced by the general path's result.  (Only such passes: one candidate in need of it among 300 x 40
     // positions, 40/40 heads, P 700: 320 us, all of a workgroup's passes 536, the general kernel 317.)
-    if (bad_passes)
+    if (bad_passes) {
+        const StreamPacked &call = first_parameter<StreamPacked>();
+        const Args &a = call.a;
+        const PackedArgs &pa = call.pa;
         for (int p2 = blockIdx.x, n = 0; p2 < npasses; p2 += gridDim.x, ++n) {
             ps = packed_pass(a, p2, npasses, nblocks, waves, wave);
             if (!ps.exists || !(bad_passes >> (n & 63) & 1))
@@ -790,8 +804,8 @@ void stream_packed_kernel(Args a, PackedArgs pa)
             set_vhead(a, X, ps.head);
             GeneralBlock<STEPS> g;
             const int r0 = ps.active ? ps.blk * kBlockRows : 0;
-            z = search_begin(r0);
-            Walk w = find(z, r0);
+            z = search_begin(a, r0);
+            Walk w = find(a, pa, z, r0);
             packed_general_begin(a, pa, X, w, r0, list, g);
             uintx4 kv, vv;
             load_tile_chunks(a, X, ts, 0, kv, vv);
@@ -808,6 +822,7 @@ void stream_packed_kernel(Args a, PackedArgs pa)
             if (ps.active)
                 packed_general_end(a, X, g);
         }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1649,7 +1664,7 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
                        stream_pass_ids(a, a.C * nb) <= 0x7fffffffLL - 8 && packed_args(a, (unsigned)num_cu, kNW, pa)) {
         const int steps = packed_steps(a, 3, pa.dense);
         auto kernel = steps == 1 ? stream_packed_kernel<1> : steps == 2 ? stream_packed_kernel<2> : stream_packed_kernel<3>;
-        return launch_kernel(kernel, dim3((unsigned)num_cu), dim3(kNW * 64), kLdsBytes, stream, a, pa);
+        return launch_kernel(kernel, dim3((unsigned)num_cu), dim3(kNW * 64), kLdsBytes, stream, StreamPacked{a, pa});
     }
     // Own blocks make more passes, each in 0.7 of the general kernel's time, 0.8 with the second own step: not where
     // that costs a round of the chip.
