@@ -744,7 +744,14 @@ void bwd_dq_packed_kernel(DqPacked call)
         const PackedList list = choose_list<STEPS>(a, pa, T, waves, per_chunk, lens);
         const int nblocks = (list.total + kBlockRows - 1) / kBlockRows;
         const int each = (int)fdiv(nblocks, pa.div_w), over = nblocks - each * waves;
-        const int blk_lo = me * each + (me < over ? me : over), blk_hi = blk_lo + each + (me < over ? 1 : 0);
+        int blk_lo = me * each + (me < over ? me : over), blk_hi = blk_lo + each + (me < over ? 1 : 0), step = 1; // from blk_lo, every step-th
+        // Blocks in turn where places are a division away and each key head has one query head, as in the forward kernel (us for the whole backward pass,
+        // ranges and in turn, 32/32 heads, P 128: 64 x 28: 45.3, 42.5; 256 x 16..32: 136, 132; 700 x 32: 437, 432; before this kernel 43.9, 132, 432).
+        if (list.even && list.align > 1 && a.G == 1) {
+            step = waves;
+            blk_lo = slice * kNW + wave;
+            blk_hi = nblocks;
+        }
         Walk w = {X.cand0, 0, 0};
         if (blk_lo < blk_hi)
             w = find_row(a, list, X.cand0, blk_lo * kBlockRows, fresh & 63);
@@ -757,8 +764,13 @@ void bwd_dq_packed_kernel(DqPacked call)
         for (int r0 = blk_lo * kBlockRows; r0 < row_hi;) {
             unsigned q_off;
             PackedRow row;
+            if (step > 1) {
+                w = walk_even(a, pa.div_run, kBlockRows, r0);
+                w.b += X.cand0;
+                w.len = packed_len(a, w.b);
+            }
             const PackedBlock<STEPS> x = packed_block<STEPS>(a, pa, fresh_lane(X), w, r0, list, q_off, row);
-            r0 += x.rows; // (a block of 32 rows, or of fewer where the next candidate is far away)
+            r0 += step > 1 ? step * kBlockRows : x.rows; // (a block of 32 rows, or of fewer where the next candidate is far away)
             const int rh = X.head * a.G + row.gq, b = x.b + (int)(row.from >> 6), ri = (int)(row.from & 63);
 
             // requested first, so that it is there with the rows below and costs no round trip of its own
