@@ -51,7 +51,7 @@ vp = ctypes.c_void_p
 t = [vp((1 + i) << 42) for i in range(14)]          # addresses 4 TB apart
 for c in json.load(sys.stdin):
     p = pk.make_multi_params(pk.make_params(c["B"], c["S"], c["P"], c["Hq"], c["Hkv"], c["D"], c["dtype"]), c["Np"])
-    lens = (t[13] if c["Np"] > 1 else None, None)
+    lens = (t[13] if c["Np"] > 1 else None, t[12] if c["lens"] else None)
     if c["call"] == "fwd":
         rc = lib.pskv_attn_fwd_multi(ctypes.byref(p), *t[:5], *lens, t[5], None, None, 0, None)
     else:
@@ -63,15 +63,16 @@ for c in json.load(sys.stdin):
 
 
 def named(mangled, kernel):
-    """Whether a mangled name is that of `kernel`_kernel, with its first template arguments if "<true,false>" or the like is behind it."""
+    """Whether a mangled name is that of `kernel`_kernel, with its first template arguments if "<true,false>", "<2,1>" or the like is behind it."""
     name, _, args = kernel.partition("<")
     name += "_kernel"
-    args = "I" + args.rstrip(">").replace("true", "Lb1E").replace("false", "Lb0E").replace(",", "") if args else ""
+    args = "I" + "".join({"true": "Lb1E", "false": "Lb0E"}.get(x, f"Li{x}E") for x in args.rstrip(">").split(",")) if args else ""
     return f"{len(name)}{name}{args}" in mangled
 
 
-def case(call, dtype, D, B, P, S, Hq, Hkv, Np=1):
-    return dict(call=call, dtype=dtype, D=D, B=B, P=P, S=S, Hq=Hq, Hkv=Hkv, Np=Np)
+def case(call, dtype, D, B, P, S, Hq, Hkv, Np=1, lens=False):
+    """lens: the call brings suffix lengths."""
+    return dict(call=call, dtype=dtype, D=D, B=B, P=P, S=S, Hq=Hq, Hkv=Hkv, Np=Np, lens=lens)
 
 
 def launches(tmp_path, cases):

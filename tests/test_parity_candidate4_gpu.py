@@ -19,7 +19,7 @@ def pk():
 
 
 def takes_four(tmp_path, w, Np=1):
-    (rc, got), = notes.launches(tmp_path, [notes.case("fwd", "bf16", 128, w.B, w.P, w.S, w.Hq, w.Hkv, Np)])
+    (rc, got), = notes.launches(tmp_path, [notes.case("fwd", "bf16", 128, w.B, w.P, w.S, w.Hq, w.Hkv, Np, lens=True)])
     assert rc == 0 and "stream_candidate4" in got[0][2], got
 
 

@@ -1,5 +1,5 @@
-"""The pipelined forward kernels on candidates whose rows fill no whole number of 32-row blocks (each has
-blocks of its own, the last one partly empty), against the oracle."""
+"""Forward calls of candidates whose rows fill no whole number of 32-row blocks, against the oracle.  They bring
+lengths; test_parity_without_lengths_gpu.py has calls without."""
 import numpy as np
 import pytest
 

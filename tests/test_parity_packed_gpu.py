@@ -1,6 +1,7 @@
-"""GPU parity of the kernels over packed rows, where they can go wrong: blocks across candidates and inside them, windows of one
-step and of two, more candidates than threads, empty candidates, candidates far apart in memory, prefixes too short for the
-pipeline, rows that need rescaling.  Padded rows hold NaN; results start as NaN."""
+"""GPU parity of the kernels over packed rows, where they can go wrong: blocks across candidates and inside them, in ranges and in
+turn, windows of one step and of two, more candidates than threads, empty candidates, candidates far apart in memory, prefixes too
+short for the pipeline, rows that need rescaling.  Padded rows hold NaN; results start as NaN.  Which list a problem makes is asked of
+the kernels' own function (test_packed_lists.py) where a test is about that."""
 import numpy as np
 import pytest
 
@@ -79,7 +80,7 @@ def check(pk, inp, q_batch_stride=0, backward=True):
     (9, 32, 19, 4, 7, 1),
     (9, 33, 20, 1, 4, 4),        # two: the second with one row, full
     (30, 64, 24, 8, 8, 2),
-    (1300, 128, 3, 0, 2, 1),     # three candidates per thread of the workgroup that adds the lengths up
+    (1300, 128, 3, 0, 2, 1),     # six candidates per thread of those that add the lengths up
     (2200, 96, 2, 0, 1, 1),      # more lengths than it holds at a time
     (7, 40, 40, 33, 8, 2),       # (backward) one prefix tile, windows of up to 48 positions
     (6, 0, 64, 1, 4, 4),         # ... no prefix, the longest suffix
@@ -127,13 +128,13 @@ def test_candidates_far_apart(pk, P):
     check(pk, inp, q_batch_stride=(1 << 23) - 8)
 
 
-def alignment(lists, w, lens, streamed=False):
+def alignment(lists, w, lens, streamed=False, P=None):
     """(window steps, alignment) of the list that the kernel makes of these lengths on this card."""
     import torch
     cus, heads, G = torch.cuda.get_device_properties(0).multi_processor_count, getattr(w, "Np", 1) * w.Hkv, w.Hq // w.Hkv
     C = w.B // getattr(w, "Np", 1)
     wavefronts = 0 if streamed else 8 * min(cus // min(heads, cus), C * ((w.S * G + 31) // 32))
-    steps, _, align, _ = packed(lists, [int(x) for x in lens], w.S, w.Hq, w.Hkv, 3 if streamed else 2, w.P, wavefronts)
+    steps, _, align, _ = packed(lists, [int(x) for x in lens], w.S, w.Hq, w.Hkv, 3 if streamed else 2, w.P if P is None else P, wavefronts)
     return steps, align
 
 
@@ -147,6 +148,59 @@ def test_candidates_far_apart_in_one_block(pk, lists, Hq, Hkv, P):
     inp = gen.make_inputs(w, pad="nan")
     put_lengths(inp, lens)
     check(pk, inp, q_batch_stride=(1 << 23) - 8)
+
+
+# More blocks than wavefronts: 32 key heads have eight workgroups, 64 wavefronts, each.
+@pytest.mark.parametrize("B,P,S,lo,Hq,Hkv,steps,align", [
+    (140, 20, 10, 1, 32, 32, 2, 1),      # across candidates: one prefix tile, two, and more; two window steps
+    (140, 50, 12, 1, 32, 32, 2, 1),
+    (140, 200, 20, 1, 32, 32, 2, 1),
+    (300, 130, 9, 0, 32, 32, 2, 1),      # ... empty candidates in blocks
+    (60, 130, 20, 5, 128, 32, 1, 1),     # ... one step
+    (60, 40, 24, 9, 128, 32, 1, 1),
+    (40, 100, 19, 3, 224, 32, 1, 1),     # ... groups of seven
+    (150, 128, 20, 20, 32, 32, 2, 32),   # a block for each candidate, in turn
+    (150, 128, 20, 12, 32, 32, 2, 32),   # ... lengths differ, blocks do not
+    (200, 31, 32, 2, 32, 32, 2, 32),
+    (130, 64, 32, 32, 32, 32, 2, 32),
+    (150, 40, 32, 30, 32, 32, 2, 32),    # ... some blocks of two rows less
+    (70, 150, 32, 32, 64, 32, 2, 32),    # ... two blocks for each
+    (40, 33, 28, 28, 128, 32, 2, 32),    # ... four, the last one half full
+    (130, 100, 32, 0, 32, 32, 2, 32),    # candidates without rows: blocks in ranges again
+])
+def test_lists_of_more_blocks_than_wavefronts(pk, lists, B, P, S, lo, Hq, Hkv, steps, align):
+    w = gen.custom_workload(f"packed_many_{B}_{P}_{S}_{lo}", B, P, S, lo, S, Hq, Hkv, 128, "bf16", index=3650 + B + P + S + lo)
+    inp = gen.make_inputs(w, pad="nan")
+    assert alignment(lists, w, inp.suf_len) == (steps, align)
+    check(pk, inp)
+
+
+@pytest.mark.parametrize("Np,C,P,S,lo,Hq,Hkv,align", [
+    (4, 80, 200, 20, 2, 8, 8, 1), (4, 80, 100, 20, 20, 8, 8, 32), (2, 60, 64, 20, 4, 64, 16, 1),
+])
+def test_such_lists_of_several_instructions(pk, lists, Np, C, P, S, lo, Hq, Hkv, align):
+    w = gen.custom_multi_workload(f"packed_many_multi_{P}_{lo}", Np, C, P, P, P, S, lo, S, Hq, Hkv, 128, "bf16", index=3850 + P + lo)
+    inp = gen.make_multi_inputs(w, pad="nan")
+    inp.pre_len[:2] = P, P // 3         # (the second one goes the general way, or has fewer tiles)
+    inp.k_pre[1, :P - P // 3] = inp.v_pre[1, :P - P // 3] = 0x7FC0
+    for n in range(Np):
+        assert alignment(lists, w, inp.suf_len[n * C:(n + 1) * C], P=int(inp.pre_len[n]))[1] == align
+    check(pk, inp)
+
+
+@pytest.mark.parametrize("B,P,S,lo,Hq,Hkv,align", [
+    (140, 200, 20, 1, 32, 32, 1), (60, 130, 20, 5, 128, 32, 1), (150, 128, 20, 12, 32, 32, 32), (70, 150, 32, 32, 64, 32, 32), (140, 60, 10, 1, 32, 32, 1),
+])
+def test_such_lists_with_rows_that_need_rescaling(pk, lists, B, P, S, lo, Hq, Hkv, align):
+    w = gen.custom_workload(f"packed_many_rescale_{P}_{S}_{lo}", B, P, S, lo, S, Hq, Hkv, 128, "bf16", index=3900 + P + S + lo)
+    inp = gen.make_inputs(w, pad="nan")
+    assert alignment(lists, w, inp.suf_len)[1] == align
+    inp.k_pre[P - 5] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(inp.k_pre[P - 5]) * 8)
+    for b in (0, B // 2, B - 1):
+        inp.q[b] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(inp.q[b]) * 8)
+    for x in (inp.v_pre, inp.v_suf):    # (values as in test_rows_that_need_rescaling)
+        x[...] = gen.f32_to_bf16_bits(gen.bf16_bits_to_f32(x) * np.float32(0.25))
+    check(pk, inp, backward=False)
 
 
 @pytest.mark.parametrize("Np,C,P,S,lo,Hq,Hkv", [(6, 9, 128, 20, 1, 4, 4), (5, 30, 200, 24, 12, 8, 2), (40, 3, 100, 11, 0, 14, 2)])

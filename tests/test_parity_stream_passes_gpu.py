@@ -1,5 +1,5 @@
-"""Forward candidate passes of eight blocks and pipelined passes with two and more own steps against the oracle, at the
-edges of their rings, blocks and passes; that a problem takes the kernel is checked as well."""
+"""Forward candidate passes of eight blocks, pipelined passes with three own steps and passes over packed rows with two and three
+window steps against the oracle, at the edges of their rings, blocks and passes; that a problem takes the kernel is checked as well."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 def takes(tmp_path, kernel, w, Np=1):
-    (rc, got), = notes.launches(tmp_path, [notes.case("fwd", "bf16", 128, w.B, w.P, w.S, w.Hq, w.Hkv, Np)])
+    (rc, got), = notes.launches(tmp_path, [notes.case("fwd", "bf16", 128, w.B, w.P, w.S, w.Hq, w.Hkv, Np, lens=True)])
     assert rc == 0 and notes.named(got[0][2], kernel), got
 
 
@@ -26,10 +26,11 @@ def takes(tmp_path, kernel, w, Np=1):
     ("stream_candidate<false>", 12, 200, 90, 5, 90, 32, 8),    # passes of eight and of four blocks, three own tiles
     ("stream_candidate<false>", 9, 130, 150, 0, 150, 32, 8),   # passes of eight, eight and three, five own tiles
     ("stream_candidate<false>", 17, 300, 60, 33, 60, 32, 8),   # a long prefix
-    ("stream_pipelined<false,true>", 65, 200, 64, 0, 64, 8, 8),  # two own steps
-    ("stream_pipelined<false,true>", 65, 257, 64, 33, 64, 8, 8),
-    ("stream_pipelined<false,false>", 65, 257, 54, 0, 54, 8, 8),   # ... the second block not full
-    ("stream_pipelined<false,false>", 65, 300, 60, 30, 60, 8, 8),
+    ("stream_packed<3>", 65, 200, 64, 0, 64, 8, 8),
+    ("stream_packed<3>", 65, 257, 64, 33, 64, 8, 8),
+    ("stream_packed<3>", 65, 257, 54, 0, 54, 8, 8),
+    ("stream_packed<3>", 65, 300, 60, 30, 60, 8, 8),
+    ("stream_pipelined<false,true>", 33, 288, 40, 0, 40, 32, 8),    # two own steps, whole blocks of grouped heads
     ("stream_pipelined<false,false>", 33, 288, 92, 0, 92, 16, 16),  # three own steps
 ])
 def test_stream_passes(pk, tmp_path, kernel, B, P, S, lo, hi, Hq, Hkv):  # noqa: F811
@@ -40,7 +41,7 @@ def test_stream_passes(pk, tmp_path, kernel, B, P, S, lo, hi, Hq, Hkv):  # noqa:
 
 @pytest.mark.parametrize("kernel,B,P,S,Hq,Hkv", [
     ("stream_candidate<true>", 17, 100, 64, 32, 8), ("stream_candidate<false>", 17, 130, 44, 32, 8),
-    ("stream_pipelined<false,true>", 65, 200, 64, 8, 8), ("stream_pipelined<false,false>", 65, 260, 60, 8, 8),
+    ("stream_packed<3>", 65, 200, 64, 8, 8), ("stream_packed<3>", 65, 260, 60, 8, 8),
 ])
 def test_scores_far_above_the_first_tile(pk, tmp_path, kernel, B, P, S, Hq, Hkv):  # noqa: F811
     """A late key of 130 and more above everything before it: the workgroup's passes once more on the general path."""

@@ -6,9 +6,9 @@ from paper_2603_13420_amd import binding as pk
 import launch_notes as notes
 
 
-def check(tmp_path, call, problems):
-    """The kernel's whole name, and with "<true>" or "<false>" its first template argument."""
-    cases = [notes.case(call, "bf16", 128, *p[:-1]) for p in problems]
+def check(tmp_path, call, problems, lens=False):
+    """The kernel's whole name, and with "<true>", "<2,1>" or the like its first template arguments.  lens: the call brings lengths."""
+    cases = [notes.case(call, "bf16", 128, *p[:-1], lens=lens) for p in problems]
     for (*_, kernel), c, (rc, got) in zip(problems, cases, notes.launches(tmp_path, cases)):
         assert rc == pk.PSKV_OK and notes.named(got[0][2], kernel), (c, kernel, got)
 
@@ -61,3 +61,25 @@ def test_forward_candidate_passes(tmp_path):
         (34, 1114, 111, 28, 4, 1, "stream_pipelined<false>"), (245, 676, 34, 32, 8, 1, "stream_pipelined<false>"),
         (43, 603, 113, 40, 40, 1, "stream_general"), (300, 700, 13, 32, 8, 1, "stream_general"), (512, 512, 29, 32, 32, 1, "stream_pipelined<true>"),
     ])
+
+
+def test_calls_with_lengths(tmp_path):
+    # packed<window steps, prefix tiles (resident; 3: three and more)>, and what is left to the kernels of calls without lengths
+    check(tmp_path, "fwd", [
+        (8, 1, 20, 4, 4, 1, "resident_packed<2,1>"), (8, 32, 20, 4, 4, 1, "resident_packed<2,1>"), (8, 33, 20, 4, 4, 1, "resident_packed<2,2>"),
+        (8, 64, 24, 8, 2, 1, "resident_packed<1,2>"), (8, 65, 20, 4, 4, 1, "resident_packed<2,3>"), (40, 100, 20, 4, 4, 2, "resident_packed<2,3>"),
+        (1024, 256, 25, 32, 8, 1, "resident_packed<1,3>"), (1024, 256, 26, 32, 8, 1, "resident_packed<2,3>"), (64, 256, 32, 32, 32, 1, "resident_packed<2,3>"),
+        (64, 0, 20, 4, 4, 1, "resident_general"), (64, 256, 33, 32, 32, 1, "resident_general"),
+        (300, 512, 20, 32, 8, 1, "stream_packed<1>"), (64, 257, 20, 32, 32, 1, "stream_packed<2>"), (700, 300, 33, 40, 40, 1, "stream_packed<2>"),
+        (700, 300, 64, 40, 40, 1, "stream_packed<3>"), (65, 200, 64, 8, 8, 1, "stream_packed<3>"),
+        # whole blocks of grouped heads, or one per candidate; longer suffixes; several prefixes
+        (1500, 400, 32, 32, 8, 1, "stream_pipelined<true,true>"), (300, 700, 32, 40, 40, 1, "stream_pipelined<true,true>"),
+        (300, 512, 40, 32, 8, 1, "stream_pipelined<false,true>"), (40, 300, 65, 40, 40, 1, "stream_general"), (40, 300, 20, 4, 4, 2, "stream_general"),
+        (16, 128, 90, 32, 8, 1, "stream_candidate<false>"),
+    ], lens=True)
+    check(tmp_path, "bwd", [
+        (1024, 256, 24, 32, 8, 1, "bwd_dq_packed<1>"), (500, 128, 20, 32, 32, 1, "bwd_dq_packed<2>"), (100, 0, 20, 4, 4, 1, "bwd_dq_packed<2>"),
+        (500, 128, 64, 32, 32, 1, "bwd_dq_packed<2>"), (500, 128, 65, 32, 32, 1, "bwd_dq_resident"), (64, 257, 24, 32, 8, 1, "bwd_dq_mfma"),
+        (512, 256, 32, 32, 8, 8, "bwd_dq_packed<2>"),
+        (32, 128, 28, 32, 8, 1, "bwd_dq_unit"), (64, 256, 32, 32, 8, 1, "bwd_dq_unit"),     # few blocks, in full passes
+    ], lens=True)
