@@ -17,7 +17,12 @@
  * the rows that see it and no others, except on the matrix-core path of bf16 tensors with D == 128:
  * there hidden keys of a 32-key step take part with a weight of zero, and a non-finite one among them can
  * turn rows that do not see it (earlier positions of the same candidate, neighbours in a 32-row
- * block) into NaN.  PSKV_IMPL_SIMPLE keeps such rows apart for every shape it covers.
+ * block) into NaN.  With suf_len a block may hold rows of several candidates, also where S times the
+ * group's heads is a multiple of 32, and its steps hold all positions of those candidates from their first ones on,
+ * so that a non-finite key or value can reach any candidate that shares a block with its own.  Where the blocks
+ * begin depends on all lengths of the call (of the instruction): a candidate's results may
+ * differ in their last bits from call to call of other neighbours, within the path's rounding.
+ * PSKV_IMPL_SIMPLE keeps such rows apart for every shape it covers.
  *
  * All pointers except the params struct and the returned strings are DEVICE pointers owned
  * by the caller.  The library allocates, frees and retains no device memory and keeps no

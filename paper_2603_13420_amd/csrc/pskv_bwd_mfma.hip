@@ -676,8 +676,8 @@ void bwd_dq_resident_kernel(BwdArgs g, int nb, FastDiv div_nb, int per_vh, int v
 
 // ------------------------------------------------------------------------------------------
 // The same over packed rows (pskv_packed.hpp): calls with suffix lengths, S <= 64.  A block's own keys are its window's.
-// Bound as the kernel above; it has fewer blocks (20480 for 23700 at the size named there: the whole backward pass 293 -> 278 us),
-// ranges of blocks that differ by one at most, and its prefix straight into LDS.  Ranges next to each other belong to different
+// Bound as the kernel above; it has fewer blocks (20480 for 23700 at the size named there: the whole backward pass 299 -> 281 us),
+// ranges of blocks that differ by one at most (or blocks in turn), and its prefix straight into LDS.  Ranges next to each other belong to different
 // workgroups: handing a workgroup eight neighbouring ones cost 2 % over 74 calls, 7 % where a wavefront has a few blocks.
 // ------------------------------------------------------------------------------------------
 struct DqPacked {
@@ -1463,8 +1463,9 @@ hipError_t launch_bwd_dq_mfma(const BwdArgs &g, hipStream_t stream)
     const ResidentSplit split = resident_split(a, a.C * nb, kNW, num_cu);
     // Rows packed by their lengths, where there are lengths: all of the resident kernel's calls and those of the streaming one up to 256 prefix
     // rows; calls of fewer than three blocks per wavefront that fill passes of four (below) stay with those.  us for the whole
-    // backward pass, before and so: 1024 x 16..24, 32/8 heads, P 256: 293, 277; 500 x 20, P 250: 151, 142; 500 x 14..28: 171, 151; 700 x 14..28, P 128:
-    // 203, 189; 700 x 32..64: 487, 460; 700 x 10, 32/32: 223, 180; 700 x 32: 431, 441 (nothing to pack); 32 x 10, 32/8: 18.7, 15.7; 32 x 28: 19.7, 20.9 (passes).
+    // backward pass, in those and so: 1024 x 16..24, 32/8 heads, P 256: 299, 281; 500 x 20, P 250: 152, 140; 500 x 14..28: 172, 151; 700 x 14..28, P 128:
+    // 203, 188; 700 x 32..64: 480, 466; 700 x 10, 32/32: 223, 180; 32 x 10, 32/8: 19.0, 16.2; 32 x 28: 19.7, 20.9 (passes); nothing to pack: 700 x 32, 32/32: 430,
+    // 431; 500 x 48, 28/4, P 250: 300, 307.
     const int max_tiles = (a.P + kTileKeys - 1) / kTileKeys;
     PackedArgs pa;
     const bool small = split.each < 3 && nb * 5 >= (nb + kUnitWaves - 1) / kUnitWaves * kUnitWaves * 4;

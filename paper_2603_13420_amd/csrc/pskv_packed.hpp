@@ -6,6 +6,8 @@
 // The keys that a block's rows see besides the prefix lie in one WINDOW, the positions of the block's candidates
 // from the first one's first to the last row's own, and a row sees those from its candidate's first one to itself.
 //
+// A list whose runs are all a full candidate's is `even`: places in it are a division away, and its blocks can go to the wavefronts in turn.
+//
 // The lengths are in device memory.  Every workgroup adds them up (`PackedList`), finds the candidate of the row it begins
 // with and goes on from candidate to candidate (`Walk`).
 #pragma once

@@ -17,8 +17,8 @@
 // suffix fits one 32-key step: it overlaps, inside each wavefront, the score product of the
 // next tile (matrix cores) with the exponentials of the current one (vector ALU), requests
 // everything it needs from global memory a full block ahead, and never branches on data.
-// The third takes calls that bring suffix lengths (and the same suffix and prefix sizes as the pipelined one): the same pipeline over
-// packed rows, valid ones only (pskv_packed.hpp).
+// The third takes calls that bring suffix lengths, S <= 32 and 1 <= P, whatever their candidates' rows fill, where 32-bit and 24-bit
+// offsets reach (packed_args): the same pipeline over packed rows, valid ones only (pskv_packed.hpp).
 // Operand layouts and the pieces shared with the streaming kernels are in pskv_mfma.hpp.
 #include "pskv_packed.hpp"
 
@@ -331,12 +331,13 @@ void resident_pipelined_kernel(Args a, int per_vh, int vh_slots, int max_tiles, 
 // of at most 32 * STEPS positions; a prefix, one head's of less than 2^31 bytes.
 //
 // Bound by the instructions of a block, as the kernel above, and by memory where the prefix is short; what it gains is blocks: 20480
-// instead of 23700 for 1024 candidates of 16..24 of 24 positions, 32/8 heads, P 256 (129 -> 120 us; the same with eight instructions 118 -> 109).
-// A block costs some 15 % more vector instructions than there (places of rows and keys, masks with two ends).  Two things cost
-// more than they look: a spilled register's reload in the block loop waits for every request in flight (six of them took back all of the
-// gain), and a store under a branch makes the wait for the next block's Q one for the stores.
+// instead of 23700 for 1024 candidates of 16..24 of 24 positions, 32/8 heads, P 256 (127.5 -> 118 us; the same with eight instructions 117 -> 110).
+// For the same blocks it takes 2 % more vector instructions than that one (512 x 32, P 128: 11.48 million for 11.23; places of rows and keys, masks with two ends).
+// Three things cost more than they look: a spilled register's reload in the block loop waits for every request in flight (six of them took back all of the
+// gain), a store under a branch makes the wait for the next block's Q one for the stores, and scalars that are kept over everything end up in
+// lanes of vector registers (12.87 million vector instructions then).
 // Small calls take a workgroup per block while there are compute units: a wavefront alone on its SIMD gets through a block in
-// little more than half the time (32 candidates of 20 positions, 32/8 heads, P 128: 11.2 us with eight blocks to a workgroup, 8.5 so; 12 before).
+// little more than half the time (32 candidates of 20 positions, 32/8 heads, P 128: 11.2 us with eight blocks to a workgroup, 8.5 so; 8.1 by now, 12.4 in the kernels before).
 // ------------------------------------------------------------------------------------------
 struct PackedLaunch {
     Args a;
@@ -679,10 +680,11 @@ hipError_t launch_resident(const Args &a, hipStream_t stream)
         const long long each_own = resident_split(a, own, kNW, num_cu).each, each_stacked = resident_split(a, stacked, kNW, num_cu).each;
         pipelined = each_own * (max_tiles + 1) + 4 <= 1.7 * each_stacked * (max_tiles + 1 + straddled);
     }
-    // Rows packed by their lengths, where there are lengths: us, before and so: 32/8 heads: 1500 x 20, P 200: 177, 152; 1500 x 8..20: 145, 117; 500 x 28,
-    // P 250: 91, 82; 700 x 28, P 128: 95, 94; 500 x 32: 93, 93; 1500 x 32: 237, 242 (nothing to pack); 32/32: 1500 x 14, P 200: 182, 154; 512 x 20, P 128:
-    // 75, 75 (its bytes alone take 66); 700 x 22..32, P 128: 139, 142; 28/4: 200 x 28, P 100: 25.3, 21.8; 8 x 12..24, 32/8, P 100: 11.3, 7.8; prefixes of one
-    // tile or two (before: the general kernel): 300 x 20, P 40, 32/8: 29.5, 25.1; 600 x 10..20, P 64: 54, 42; 1500 x 32, P 32, 32/32: 313, 328.
+    // Rows packed by their lengths, where there are lengths: us, in the kernels above and so: 32/8 heads: 1500 x 20, P 200: 179, 152; 1500 x 8..20: 146, 116; 500 x 28,
+    // P 250: 93, 85; 700 x 28, P 128: 94.9, 93.7; 32/32: 1500 x 14, P 200: 187, 158; 512 x 20, P 128: 76.5, 73.9 (its bytes alone take 66); 700 x 22..32, P 128: 147,
+    // 143; 28/4: 200 x 28, P 100: 32.3, 27.9; 8 x 12..24, 32/8, P 100: 11.5, 7.2; prefixes of one tile or two: 300 x 20, P 40, 32/8: 33.3, 30.4; 600 x 10..20, P 64:
+    // 54.6, 48.0.  Nothing to pack: 500 x 32, 32/8, P 250: 93.3, 93.9; 1500 x 32, P 200: 240, 244; 1500 x 24: 183, 182; 1500 x 32, 32/32, P 32: 313, 310; what is left
+    // below is 1500 x 24, 32/32, P 128: 247, 259 (512 x 24: 87.0, 87.5) and 28/4 heads of 32 positions: 256 x 32, P 192: 44.6, 45.7.
     PackedArgs pa;
     const ResidentSplit packed = resident_split(a, own * kNW, kNW, num_cu); // (a workgroup per block while there are compute units)
     if (a.len && max_tiles >= 1 && a.S <= kTileKeys && own <= 0x7fffffffLL / kBlockRows && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL && packed_args(a, (unsigned)packed.per_vh, kNW, pa)) {

@@ -421,7 +421,7 @@ void stream_pipelined_kernel(Args a, int npasses, int nb, FastDiv div_nb)
 // there are fewer passes than compute units; wavefronts without a block only stage.  Windows of up to STEPS steps.
 //
 // Bound as the pipelined kernel, tile steps and, at a pass' ends, waits that all of the workgroup shares; what it gains is passes:
-// 4096 candidates of 32..64 positions, 40/40 heads, P 512: 246 thousand blocks for 328 thousand, 3632 -> 3155 us, although a block's
+// 4096 candidates of 32..64 positions, 40/40 heads, P 512: 246 thousand blocks for 328 thousand, 3742 -> 3254 us, although a block's
 // window takes 2.3 steps instead of 1.5.  A pass costs more than there: the search for its first candidate (64 lengths at a time, asked
 // for two steps before), the places of rows and keys, and one length per wavefront of a candidate whose padding it stores.
 // Tried: the next pass's Q asked for in one place before the window's steps, with this pass's kept or fetched again for the later ones:
@@ -1652,13 +1652,13 @@ hipError_t launch_stream(const Args &a, hipStream_t stream)
         return launch_kernel(kernel, dim3((unsigned)(npasses < places ? npasses : places)), dim3(waves * 64), eight ? kLdsBytes : kCLdsBytes, stream,
                              a, (int)npasses, cs);
     }
-    // Rows packed by their lengths, where there are lengths.  us, before and so: 300 candidates, P 700: 16 positions, 40/40 heads: 118, 102;
-    // 20..40: 299, 210; 12..24, 28/4: 92, 75; 24: 93, 95; 700, P 300, 40/40: 40: 470, 377; 64: 554, 563; 32..64: 502, 479; 16 x 24: 22.6, 15.2.
+    // Rows packed by their lengths, where there are lengths.  us, in the kernels below and so: 300 candidates, P 700: 16 positions, 40/40 heads: 118, 100;
+    // 20..40: 298, 201; 12..24, 28/4: 96, 80; 700, P 300, 40/40: 40: 469, 366; 64: 555, 555; 32..64: 498, 463; 16 x 24, P 700: 35.0, 19.9.
     // Not whole blocks of grouped heads or of one block per candidate: which is faster depends on lengths that the host does not know, and
     // without padding the pipelined kernel is: 1500 x 32, 32/8, P 400: 423, 442 (16..32: 404, 350); 256 x 32, P 2048: 241, 245 (233, 186);
-    // 300 x 32, 40/40, P 700: 178, 194 (170, 171).  What this costs: 1 to 5 % where nothing is padded (700 x 64 above), and calls of
-    // two rounds of the chip that stay two: 120 x 24, 28/4, P 512: 38, 40; 40 x 32..64, 40/40, P 1000: 68, 74.  Sizes do not tell these
-    // either: 120 x 12..24 is 1.48 times as fast.
+    // 300 x 32, 40/40, P 700: 178, 194 (170, 171).  What this costs: 2 to 5 % where nothing is padded and own blocks are nearly full (300 x 24, 28/4, P 700: 97,
+    // 101; 300 x 28, 40/40: 173, 182; 120 x 24, 28/4, P 512: 37.8, 38.6, but at 12..24 of them 36.9, 25.3), and calls of two rounds of the chip that stay two: 40 x
+    // 32..64, 40/40, P 1000: 76, 83.  Choosing whole candidates' blocks there by counting rounds on the device gave 77.5, and cost every call half a us.
     if (PackedArgs pa; a.len && a.Np == 1 && (!whole || (a.G == 1 && a.S > kTileKeys)) && max_tiles >= kMinTiles && a.S <= 2 * kTileKeys && (long long)a.P * a.kp_sp * 2 < 0x7fffffffLL &&
                        a.C * nb <= 0x7fffffffLL / kBlockRows && (long long)a.C * a.Hkv < 0x7fffffffLL - num_cu * kNW &&
                        stream_pass_ids(a, a.C * nb) <= 0x7fffffffLL - 8 && packed_args(a, (unsigned)num_cu, kNW, pa)) {
