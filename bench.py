@@ -26,7 +26,7 @@ PRERAMP_LAUNCHES = 300        # untimed launches right before the counted warm-u
                               # climbs from idle over roughly the first hundred launches of a run
 
 
-FORWARD_SOURCES = ("pskv_internal.h", "pskv_mfma.hpp", "pskv_resident.hip", "pskv_stream.hip", "pskv_simple.hip")
+FORWARD_SOURCES = ("pskv_internal.h", "pskv_mfma.hpp", "pskv_packed.hpp", "pskv_resident.hip", "pskv_stream.hip", "pskv_simple.hip")
 BACKWARD_SOURCES = FORWARD_SOURCES + ("pskv_bwd_mfma.hip", "pskv_bwd_simple.hip")
 
 
@@ -82,15 +82,15 @@ def alg_counts(w, suf_len, pre_len=None):
 # kernel sources they were taken on (kernel_source_rev()).  When the sources have changed since, the
 # bench line reports no traffic and says why, instead of a figure that no longer holds.
 HBM_TRAFFIC = {
-    "gqa8b_bf16": {"file": "resident_pipelined_kernel_gqa8b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 111887253504.0, "fetch_kib": 142277.4, "fetch_scale": 2.0, "write_kib": 197632.3, "write_scale": 1.0},
-    "ldec_gqa8b_bf16": {"file": "stream_candidate4_kernel_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 134809124864.0, "fetch_kib": 224628.3, "fetch_scale": 2.0, "write_kib": 327680.0, "write_scale": 1.0},
-    "ldec_qwen7b_bf16": {"file": "stream_candidate4_kernel_ldec_qwen7b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 116735868928.0, "fetch_kib": 169132.7, "fetch_scale": 2.0, "write_kib": 286720.0, "write_scale": 1.0},
-    "longprefix_bf16": {"file": "stream_pipelined_kernel_longprefix_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 279172874240.0, "fetch_kib": 63734.2, "fetch_scale": 2.0, "write_kib": 66563.0, "write_scale": 1.0},
-    "mha13b_bf16": {"file": "stream_pipelined_kernel_mha13b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 3004086353920.0, "fetch_kib": 3171534.3, "fetch_scale": 2.0, "write_kib": 2625024.0, "write_scale": 1.0},
-    "mha7b_bf16": {"file": "resident_general_kernel_mha7b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 34359738368.0, "fetch_kib": 127414.3, "fetch_scale": 2.0, "write_kib": 81921.1, "write_scale": 1.0},
-    "multi32_gqa8b_bf16": {"file": "resident_pipelined_kernel_multi32_gqa8b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 85198897152.0, "fetch_kib": 151799.7, "fetch_scale": 2.0, "write_kib": 197632.0, "write_scale": 1.0},
-    "multi4_long_bf16": {"file": "stream_pipelined_kernel_multi4_long_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 73014444032.0, "fetch_kib": 53989.3, "fetch_scale": 2.0, "write_kib": 66579.1, "write_scale": 1.0},
-    "multi8_gqa8b_bf16": {"file": "resident_pipelined_kernel_multi8_gqa8b_bf16_hbm_traffic.txt", "rev": "e94594f07e4a", "mfma_flops": 93021274112.0, "fetch_kib": 142678.2, "fetch_scale": 2.0, "write_kib": 197632.0, "write_scale": 1.0},
+    "gqa8b_bf16": {"file": "resident_packed_kernel_gqa8b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 96901005312.0, "fetch_kib": 159213.9, "fetch_scale": 2.0, "write_kib": 196608.2, "write_scale": 1.0},
+    "ldec_gqa8b_bf16": {"file": "stream_candidate4_kernel_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 134809124864.0, "fetch_kib": 224541.6, "fetch_scale": 2.0, "write_kib": 327680.0, "write_scale": 1.0},
+    "ldec_qwen7b_bf16": {"file": "stream_candidate4_kernel_ldec_qwen7b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 116735868928.0, "fetch_kib": 168983.0, "fetch_scale": 2.0, "write_kib": 286720.0, "write_scale": 1.0},
+    "longprefix_bf16": {"file": "stream_pipelined_kernel_longprefix_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 279172874240.0, "fetch_kib": 63972.8, "fetch_scale": 2.0, "write_kib": 66564.9, "write_scale": 1.0},
+    "mha13b_bf16": {"file": "stream_packed_kernel_mha13b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 2351263907840.0, "fetch_kib": 3069023.0, "fetch_scale": 2.0, "write_kib": 2621441.4, "write_scale": 1.0},
+    "mha7b_bf16": {"file": "resident_packed_kernel_mha7b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 42949672960.0, "fetch_kib": 124736.7, "fetch_scale": 2.0, "write_kib": 82078.0, "write_scale": 1.0},
+    "multi32_gqa8b_bf16": {"file": "resident_packed_kernel_multi32_gqa8b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 74151100416.0, "fetch_kib": 167849.9, "fetch_scale": 2.0, "write_kib": 196611.8, "write_scale": 1.0},
+    "multi4_long_bf16": {"file": "stream_pipelined_kernel_multi4_long_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 73014444032.0, "fetch_kib": 53987.5, "fetch_scale": 2.0, "write_kib": 66582.2, "write_scale": 1.0},
+    "multi8_gqa8b_bf16": {"file": "resident_packed_kernel_multi8_gqa8b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 80480305152.0, "fetch_kib": 159056.2, "fetch_scale": 2.0, "write_kib": 196608.8, "write_scale": 1.0},
 }
 
 
@@ -138,10 +138,10 @@ def cpu_baseline_multi(inp, budget_s=12.0):
 
 # The same for one backward call (its two kernels together).
 HBM_TRAFFIC_BWD = {
-    "gqa8b_bf16": {"file": "bwd_kernels_gqa8b_bf16_hbm_traffic.txt", "rev": "ec609a1c48e7", "mfma_flops": 192694714368.0, "fetch_kib": 515239.8, "fetch_scale": 2.0, "write_kib": 300628.8, "write_scale": 1.0},
-    "ldec_gqa8b_bf16": {"file": "bwd_kernels_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "ec609a1c48e7", "mfma_flops": 313824116736.0, "fetch_kib": 904500.7, "fetch_scale": 2.0, "write_kib": 496137.0, "write_scale": 1.0},
-    "longprefix_bf16": {"file": "bwd_kernels_longprefix_bf16_hbm_traffic.txt", "rev": "ec609a1c48e7", "mfma_flops": 427349245952.0, "fetch_kib": 216854.5, "fetch_scale": 2.0, "write_kib": 99374.5, "write_scale": 1.0},
-    "mha7b_bf16": {"file": "bwd_kernels_mha7b_bf16_hbm_traffic.txt", "rev": "ec609a1c48e7", "mfma_flops": 81604378624.0, "fetch_kib": 374523.8, "fetch_scale": 2.0, "write_kib": 250368.6, "write_scale": 1.0},
+    "gqa8b_bf16": {"file": "bwd_kernels_gqa8b_bf16_hbm_traffic.txt", "rev": "f54128cfe9f7", "mfma_flops": 170215342080.0, "fetch_kib": 548756.8, "fetch_scale": 2.0, "write_kib": 297874.4, "write_scale": 1.0},
+    "ldec_gqa8b_bf16": {"file": "bwd_kernels_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "f54128cfe9f7", "mfma_flops": 313824116736.0, "fetch_kib": 905083.3, "fetch_scale": 2.0, "write_kib": 496137.1, "write_scale": 1.0},
+    "longprefix_bf16": {"file": "bwd_kernels_longprefix_bf16_hbm_traffic.txt", "rev": "f54128cfe9f7", "mfma_flops": 427349245952.0, "fetch_kib": 219124.8, "fetch_scale": 2.0, "write_kib": 99371.8, "write_scale": 1.0},
+    "mha7b_bf16": {"file": "bwd_kernels_mha7b_bf16_hbm_traffic.txt", "rev": "f54128cfe9f7", "mfma_flops": 81604378624.0, "fetch_kib": 374564.2, "fetch_scale": 2.0, "write_kib": 247297.8, "write_scale": 1.0},
 }
 
 
