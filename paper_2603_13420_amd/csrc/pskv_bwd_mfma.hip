@@ -770,7 +770,8 @@ void bwd_dq_packed_kernel(DqPacked call)
                 w.len = packed_len(a, w.b);
             }
             const PackedBlock<STEPS> x = packed_block<STEPS>(a, pa, fresh_lane(X), w, r0, list, q_off, row);
-            r0 += step > 1 ? step * kBlockRows : x.rows; // (a block of 32 rows, or of fewer where the next candidate is far away)
+            const int next = step > 1 ? step * kBlockRows : x.rows; // (a block of 32 rows, or of fewer where the next candidate is far away)
+            r0 = row_hi - r0 > next ? r0 + next : row_hi;           // (the sum may need more than 32 bits)
             const int rh = X.head * a.G + row.gq, b = x.b + (int)(row.from >> 6), ri = (int)(row.from & 63);
 
             // requested first, so that it is there with the rows below and costs no round trip of its own

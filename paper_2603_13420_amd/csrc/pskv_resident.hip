@@ -495,7 +495,7 @@ void resident_packed_kernel(PackedLaunch launch)
         // the same times, and in calls of a few blocks they do not drift apart.  Longer calls do by themselves, prefixes of seven tiles and more hide it, and with
         // one block the wait would only be added.  us, together and so, on a card where this shows most (they differ), P 128: 32/32: 512 x 20: 78.0, 74.0; 256 x 14..20:
         // 43.9, 37.8; 512 x 24: 95.1, 87.5; 32/8: 256 x 32: 46.4, 42.4; 512 x 8: 27.0, 23.8; beyond: 1500 x 32: 206, 211; P 256: 512 x 32: 94.7, 97.1.
-        if (TILES == 3 && T <= 6 && wslot >= kNW / 2 && nblocks >= 2 * waves && nblocks <= 8 * waves)
+        if (TILES == 3 && fits && T <= 6 && wslot >= kNW / 2 && nblocks >= 2 * waves && nblocks <= 8 * waves)
             for (int i = 0; i < T + 3; ++i)
                 __builtin_amdgcn_s_sleep(11);
 
