@@ -82,15 +82,15 @@ def alg_counts(w, suf_len, pre_len=None):
 # kernel sources they were taken on (kernel_source_rev()).  When the sources have changed since, the
 # bench line reports no traffic and says why, instead of a figure that no longer holds.
 HBM_TRAFFIC = {
-    "gqa8b_bf16": {"file": "resident_packed_kernel_gqa8b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 96901005312.0, "fetch_kib": 159213.9, "fetch_scale": 2.0, "write_kib": 196608.2, "write_scale": 1.0},
-    "ldec_gqa8b_bf16": {"file": "stream_candidate4_kernel_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 134809124864.0, "fetch_kib": 224541.6, "fetch_scale": 2.0, "write_kib": 327680.0, "write_scale": 1.0},
-    "ldec_qwen7b_bf16": {"file": "stream_candidate4_kernel_ldec_qwen7b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 116735868928.0, "fetch_kib": 168983.0, "fetch_scale": 2.0, "write_kib": 286720.0, "write_scale": 1.0},
-    "longprefix_bf16": {"file": "stream_pipelined_kernel_longprefix_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 279172874240.0, "fetch_kib": 63972.8, "fetch_scale": 2.0, "write_kib": 66564.9, "write_scale": 1.0},
-    "mha13b_bf16": {"file": "stream_packed_kernel_mha13b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 2351263907840.0, "fetch_kib": 3069023.0, "fetch_scale": 2.0, "write_kib": 2621441.4, "write_scale": 1.0},
-    "mha7b_bf16": {"file": "resident_packed_kernel_mha7b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 42949672960.0, "fetch_kib": 124736.7, "fetch_scale": 2.0, "write_kib": 82078.0, "write_scale": 1.0},
-    "multi32_gqa8b_bf16": {"file": "resident_packed_kernel_multi32_gqa8b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 74151100416.0, "fetch_kib": 167849.9, "fetch_scale": 2.0, "write_kib": 196611.8, "write_scale": 1.0},
-    "multi4_long_bf16": {"file": "stream_pipelined_kernel_multi4_long_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 73014444032.0, "fetch_kib": 53987.5, "fetch_scale": 2.0, "write_kib": 66582.2, "write_scale": 1.0},
-    "multi8_gqa8b_bf16": {"file": "resident_packed_kernel_multi8_gqa8b_bf16_hbm_traffic.txt", "rev": "1618234fbd02", "mfma_flops": 80480305152.0, "fetch_kib": 159056.2, "fetch_scale": 2.0, "write_kib": 196608.8, "write_scale": 1.0},
+    "gqa8b_bf16": {"file": "resident_packed_kernel_gqa8b_bf16_hbm_traffic.txt", "rev": "f5f190b7a8cd", "mfma_flops": 96901005312.0, "fetch_kib": 159093.8, "fetch_scale": 2.0, "write_kib": 196608.6, "write_scale": 1.0},
+    "ldec_gqa8b_bf16": {"file": "stream_candidate4_kernel_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "f5f190b7a8cd", "mfma_flops": 134809124864.0, "fetch_kib": 224501.7, "fetch_scale": 2.0, "write_kib": 327680.0, "write_scale": 1.0},
+    "ldec_qwen7b_bf16": {"file": "stream_candidate4_kernel_ldec_qwen7b_bf16_hbm_traffic.txt", "rev": "f5f190b7a8cd", "mfma_flops": 116735868928.0, "fetch_kib": 168966.7, "fetch_scale": 2.0, "write_kib": 286720.0, "write_scale": 1.0},
+    "longprefix_bf16": {"file": "stream_pipelined_kernel_longprefix_bf16_hbm_traffic.txt", "rev": "f5f190b7a8cd", "mfma_flops": 279172874240.0, "fetch_kib": 63775.3, "fetch_scale": 2.0, "write_kib": 66570.0, "write_scale": 1.0},
+    "mha13b_bf16": {"file": "stream_packed_kernel_mha13b_bf16_hbm_traffic.txt", "rev": "f5f190b7a8cd", "mfma_flops": 2351263907840.0, "fetch_kib": 3070860.5, "fetch_scale": 2.0, "write_kib": 2621441.3, "write_scale": 1.0},
+    "mha7b_bf16": {"file": "resident_packed_kernel_mha7b_bf16_hbm_traffic.txt", "rev": "f5f190b7a8cd", "mfma_flops": 42949672960.0, "fetch_kib": 124703.9, "fetch_scale": 2.0, "write_kib": 82075.1, "write_scale": 1.0},
+    "multi32_gqa8b_bf16": {"file": "resident_packed_kernel_multi32_gqa8b_bf16_hbm_traffic.txt", "rev": "f5f190b7a8cd", "mfma_flops": 74151100416.0, "fetch_kib": 167936.0, "fetch_scale": 2.0, "write_kib": 196611.6, "write_scale": 1.0},
+    "multi4_long_bf16": {"file": "stream_pipelined_kernel_multi4_long_bf16_hbm_traffic.txt", "rev": "f5f190b7a8cd", "mfma_flops": 73014444032.0, "fetch_kib": 53987.6, "fetch_scale": 2.0, "write_kib": 66593.5, "write_scale": 1.0},
+    "multi8_gqa8b_bf16": {"file": "resident_packed_kernel_multi8_gqa8b_bf16_hbm_traffic.txt", "rev": "f5f190b7a8cd", "mfma_flops": 80480305152.0, "fetch_kib": 159080.0, "fetch_scale": 2.0, "write_kib": 196608.9, "write_scale": 1.0},
 }
 
 
@@ -138,10 +138,10 @@ def cpu_baseline_multi(inp, budget_s=12.0):
 
 # The same for one backward call (its two kernels together).
 HBM_TRAFFIC_BWD = {
-    "gqa8b_bf16": {"file": "bwd_kernels_gqa8b_bf16_hbm_traffic.txt", "rev": "f54128cfe9f7", "mfma_flops": 170215342080.0, "fetch_kib": 548756.8, "fetch_scale": 2.0, "write_kib": 297874.4, "write_scale": 1.0},
-    "ldec_gqa8b_bf16": {"file": "bwd_kernels_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "f54128cfe9f7", "mfma_flops": 313824116736.0, "fetch_kib": 905083.3, "fetch_scale": 2.0, "write_kib": 496137.1, "write_scale": 1.0},
-    "longprefix_bf16": {"file": "bwd_kernels_longprefix_bf16_hbm_traffic.txt", "rev": "f54128cfe9f7", "mfma_flops": 427349245952.0, "fetch_kib": 219124.8, "fetch_scale": 2.0, "write_kib": 99371.8, "write_scale": 1.0},
-    "mha7b_bf16": {"file": "bwd_kernels_mha7b_bf16_hbm_traffic.txt", "rev": "f54128cfe9f7", "mfma_flops": 81604378624.0, "fetch_kib": 374564.2, "fetch_scale": 2.0, "write_kib": 247297.8, "write_scale": 1.0},
+    "gqa8b_bf16": {"file": "bwd_kernels_gqa8b_bf16_hbm_traffic.txt", "rev": "479d58512a69", "mfma_flops": 170215342080.0, "fetch_kib": 548682.5, "fetch_scale": 2.0, "write_kib": 297876.7, "write_scale": 1.0},
+    "ldec_gqa8b_bf16": {"file": "bwd_kernels_ldec_gqa8b_bf16_hbm_traffic.txt", "rev": "479d58512a69", "mfma_flops": 313824116736.0, "fetch_kib": 904869.2, "fetch_scale": 2.0, "write_kib": 496137.1, "write_scale": 1.0},
+    "longprefix_bf16": {"file": "bwd_kernels_longprefix_bf16_hbm_traffic.txt", "rev": "479d58512a69", "mfma_flops": 427349245952.0, "fetch_kib": 216717.6, "fetch_scale": 2.0, "write_kib": 99366.9, "write_scale": 1.0},
+    "mha7b_bf16": {"file": "bwd_kernels_mha7b_bf16_hbm_traffic.txt", "rev": "479d58512a69", "mfma_flops": 81604378624.0, "fetch_kib": 374563.8, "fetch_scale": 2.0, "write_kib": 247297.4, "write_scale": 1.0},
 }
 
 
